@@ -21,8 +21,8 @@
 //     logits around 20): scores leave the matrix core raw, and one fused multiply-add per score,
 //     s * z - m * z with z = softmax_scale * log2(e), makes them base-2 logits relative to the running
 //     maximum m.
-//   - m is raised lazily (only when a score exceeds it by more than 2^8, so probabilities may exceed 1
-//     until then) behind one uniform branch per iteration.  When it is raised after iteration j, the
+//   - m is raised lazily (only when a score exceeds it by more than 2^32, see kLazyGrowth: probabilities may
+//     exceed 1 until then) behind one uniform branch per iteration.  When it is raised after iteration j, the
 //     row sums are rescaled at once; the output accumulators, which still have to take P(j) V(j) at the
 //     old scale during iteration j+1, are rescaled one iteration later.
 //   - The loop is unrolled over one turn of the rings (eight steps), so every LDS address is a register
@@ -41,7 +41,6 @@ constexpr int kDenseRing = 4;        // K tiles, and V tiles, resident in LDS
 constexpr int kDenseWaves = 4;       // waves per workgroup
 constexpr int kDenseQB = 2;          // 32-query blocks per wave
 constexpr int kDenseRows = kDenseWaves * kDenseQB * 32;   // query rows per workgroup
-constexpr float kLazyStep = 8.0f;    // log2 of the growth that forces a rescale
 
 typedef __attribute__((ext_vector_type(16))) int i32x16;
 
@@ -118,7 +117,7 @@ struct DenseState<128> {
                      "={v[192:207]}"(kop[0]), "={v[208:223]}"(kop[1]), DLLM_LS_OUT_128, "={v74}"(mx[0]),
                      "={v75}"(mx[1]), [grow] "=s"(grow)
                    : DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[96:111]}"(st_a[0]),
-                     "{v[112:127]}"(st_a[1]), "{v[176:191]}"(pb_b), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyStep),
+                     "{v[112:127]}"(st_a[1]), "{v[176:191]}"(pb_b), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth),
                      [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1), [kt] "s"(tl.k), [vt] "s"(tl.v),
                      [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]), [lo2] "v"(tl.off[2]), [lo3] "v"(tl.off[3]),
                      [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
@@ -129,7 +128,7 @@ struct DenseState<128> {
                      "={v[192:207]}"(kop[0]), "={v[208:223]}"(kop[1]), DLLM_LS_OUT_128, "={v74}"(mx[0]),
                      "={v75}"(mx[1]), [grow] "=s"(grow)
                    : DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[128:143]}"(st_b[0]),
-                     "{v[144:159]}"(st_b[1]), "{v[160:175]}"(pb_a), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyStep),
+                     "{v[144:159]}"(st_b[1]), "{v[160:175]}"(pb_a), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth),
                      [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
                    : "memory", DLLM_DENSE_SCRATCH);
   }
@@ -207,7 +206,7 @@ struct DenseState<64> {
                      "={v[192:207]}"(kop[0]), DLLM_LS_OUT_64, "={v74}"(mx[0]),
                      "={v75}"(mx[1]), [grow] "=s"(grow)
                    : DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[96:111]}"(st_a[0]), "{v[112:127]}"(st_a[1]),
-                     "{v[176:191]}"(pb_b), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyStep), [koff] "n"(KOFF), [voff0] "n"(VOFF0),
+                     "{v[176:191]}"(pb_b), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0),
                      [voff1] "n"(VOFF1), [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),
                      [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
                    : "memory", "m0", "scc", DLLM_DENSE_SCRATCH);
@@ -217,7 +216,7 @@ struct DenseState<64> {
                      "={v[192:207]}"(kop[0]), DLLM_LS_OUT_64, "={v74}"(mx[0]),
                      "={v75}"(mx[1]), [grow] "=s"(grow)
                    : DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[128:143]}"(st_b[0]), "{v[144:159]}"(st_b[1]),
-                     "{v[160:175]}"(pb_a), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyStep), [koff] "n"(KOFF), [voff0] "n"(VOFF0),
+                     "{v[160:175]}"(pb_a), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0),
                      [voff1] "n"(VOFF1)
                    : "memory", DLLM_DENSE_SCRATCH);
   }

@@ -28,7 +28,6 @@ constexpr int kTile = 32;        // kept rows per wave tile
 constexpr int kWaves = 4;
 constexpr int kWavesMulti = 8;        // waves of a workgroup that walks several lists, one after the other
 constexpr int kMultiTilesPerWave = 8; // chunk_rows <= kMultiTilesPerWave * kWavesMulti * kTile there
-constexpr float kLazyStepS = 8.0f;
 constexpr int kMaxTilesPerWave = 16;  // chunk_rows <= kMaxTilesPerWave * kWaves * kTile
 #ifndef DLLM_SPARSE_DEPTH
 #define DLLM_SPARSE_DEPTH 1
@@ -168,7 +167,7 @@ __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* 
 #pragma unroll
   for (int i = 0; i < 16; i += 2) tmax = fmaxf(fmaxf(tmax, st[i]), st[i + 1]);
   tmax = max_across_halves(tmax) * zscale;   // zscale >= 0
-  if (__builtin_amdgcn_ballot_w64(tmax > m_used + kLazyStepS) != 0) {
+  if (__builtin_amdgcn_ballot_w64(tmax > m_used + kLazyGrowth) != 0) {
     const float m_new = fmaxf(m_used, tmax);
     const float alpha = __builtin_amdgcn_exp2f(m_used - m_new);   // first tile: exp2(-inf) = 0
     m_used = m_new;

@@ -801,3 +801,23 @@ def test_random_shapes_through_every_entry_point(seed):
     if len(rows):
         got = dw.o.float().cpu().numpy()[rows]
         assert np.abs(got - oracle_attend(w, ref)[rows]).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("growth", [20.0, 31.0, 33.0, 70.0])
+@pytest.mark.parametrize("D", [128, 64])
+def test_attend_scores_that_grow_around_the_lazy_rescale_step(D, growth):
+    """The running maximum is raised only when a base-2 logit exceeds it by more than 2^32: one key in the middle and
+    one near the end stand `growth` above all others (which stay near zero), so the probabilities before a raise reach
+    2^growth and the output is a mean of those keys' V rows (weights exact in bf16: same bound as everywhere)."""
+    lens = [400, 330]
+    w = custom(16, torch.bfloat16, 4, 2, D, lens, [32, 330], [300, 0], mode=np.array([0, 1], np.uint8))
+    scale = w.softmax_scale * math.log2(math.e)
+    w.q.fill_(1.0)
+    k = 0.01 * w.k.float()
+    for b in range(2):
+        lo, hi = int(w.cu_kv[b]), int(w.cu_kv[b + 1])
+        for pos in (lo + 150, hi - 20):
+            k[pos] = growth / (scale * D)
+    w.k.copy_(k.to(torch.bfloat16))
+    err = check_attend(w, oracle_select(w), name=f"growth 2^{growth:g}")
+    say(f"max abs error {err:.3e}")
