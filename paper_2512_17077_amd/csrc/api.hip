@@ -291,12 +291,10 @@ dllm_status dllm_hcsa_attend(const dllm_batch* batch, const int32_t* idx, const 
     e = dllm::launch_zero_sparse_outputs(s, batch->dtype, batch->cu_q, seq_mode, o, stream);
   if (e != hipSuccess) return device_result(e, "dllm_hcsa_attend");
   if (batch->dtype == DLLM_F32) {
-    if (cu_k != nullptr)
+    // one launch: every sequence as its flag says; without cu_k only those flagged dense are left
+    if (cu_k != nullptr || seq_mode != nullptr)
       e = dllm::launch_attend_f32(s, batch->q, batch->k, batch->v, batch->cu_q, batch->cu_kv, idx, cu_k, total_k,
-                                  seq_mode, 0, o, stream);
-    if (e == hipSuccess && seq_mode != nullptr)
-      e = dllm::launch_attend_f32(s, batch->q, batch->k, batch->v, batch->cu_q, batch->cu_kv, idx, cu_k, total_k,
-                                  seq_mode, 1, o, stream);
+                                  seq_mode, cu_k != nullptr ? 0 : 1, o, stream);
   } else {
     // dense sequences first: they are the long-running part of a mixed batch
     if (seq_mode != nullptr)

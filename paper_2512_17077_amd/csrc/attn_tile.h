@@ -33,7 +33,8 @@ constexpr float kLog2e = 1.4426950408889634f;
 // same factor and are floating-point, so nothing is lost to rounding (keys more than 2^126 below m vanish
 // either way), and 2^32 times the longest sequence times |V| up to 2^80 stays finite.  Raising m costs a pass
 // over all accumulators: with a step of 2^8, heads with salient keys (5 % of the K rows four times as long)
-// raised it in so many 32-key steps that the dense part of a mixed burst (32 heads, 8 sequences of 2048) took 623 us instead of 520.
+// raised it in so many 32-key steps that the dense part of a mixed burst (32 heads, 8 sequences of 2048) took
+// 623 us instead of 520.
 constexpr float kLazyGrowth = 32.0f;
 
 // XOR applied to the chunk index of `row`; depends on row & 15 only

@@ -52,8 +52,8 @@ struct AttendPlan {
 };
 AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k);
 
-// `which` selects the sequences a launch works on: 0 = those not flagged dense (all, if seq_mode
-// is NULL), attended over their kept rows; 1 = those flagged dense; 2 = every sequence, as dense.
+// `which` selects the sequences a launch works on: 0 = all, each as its flag in seq_mode says (fp32 only);
+// 1 = those flagged dense; 2 = every sequence, as dense.
 hipError_t launch_attend_f32(const Shape& s, const void* q, const void* k, const void* v, const int32_t* cu_q,
                              const int32_t* cu_kv, const int32_t* idx, const int32_t* cu_k, int32_t total_k,
                              const uint8_t* seq_mode, int which, void* o, hipStream_t st);

@@ -821,3 +821,19 @@ def test_attend_scores_that_grow_around_the_lazy_rescale_step(D, growth):
     w.k.copy_(k.to(torch.bfloat16))
     err = check_attend(w, oracle_select(w), name=f"growth 2^{growth:g}")
     say(f"max abs error {err:.3e}")
+
+
+@pytest.mark.parametrize("D,hq,hkv", [(64, 4, 4), (64, 8, 2), (128, 2, 1)])
+@pytest.mark.parametrize("wide", [False, True])
+def test_f32_attend_tile_edges(D, hq, hkv, wide):
+    """Kept rows and sequence lengths around the 16-key tiles and the eight waves that share them, query counts around
+    the 16- and 32-query tiles; few queries take the one-block form, `wide` batches the two-block one."""
+    keep = [1, 15, 16, 17, 127, 128, 129, 130, 0, 300, 0, 5]
+    qlens = [1, 15, 16, 17, 31, 32, 33, 32, 7, 32, 65, 200 if wide else 8]
+    lens = [1, 15, 16, 40, 127, 300, 129, 200, 9, 300, 65, 200]
+    mode = np.array([0, 1, 0, 0, 1, 0, 0, 0, 0, 0, 1, 1], np.uint8)
+    if wide:
+        qlens[10] = 4096 // hq
+    w = custom(17, torch.float32, hq, hkv, D, lens, qlens, [0 if m else k for k, m in zip(keep, mode)], mode=mode, salient=0.1)
+    err = check_attend(w, oracle_select(w), name=f"f32 tile edges wide={wide}")
+    say(f"max abs error {err:.3e}")
