@@ -137,14 +137,17 @@ def _raise(status: int):
         raise DllmError(status, last_error())
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+# Addresses and streams go through ctypes as plain integers (the prototypes say c_void_p), and the current stream
+# is asked for by device number: torch.cuda.current_stream() builds a Stream object, 2.5 of the 10 us a call of
+# two launches took on the host; small calls are bound by exactly that time.
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    return None if t is None else t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
+def _stream(stream) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def make_batch(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, cu_q: torch.Tensor, cu_kv: torch.Tensor,
