@@ -1,5 +1,6 @@
 // C ABI of libdllm_hcsa: host-side argument checks, workspace plans and kernel dispatch.
 // Every check happens before the first HIP call, so a rejected call launches nothing.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -162,23 +163,38 @@ dllm_status scratch_of_current_device(void** out) {
 
 namespace dllm {
 
-AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k) {
+// How many chunks the kept lists of a call are cut into.  One workgroup takes its rows at no more than about
+// 42 GB/s however many of its gathers are in flight (a compute unit's own limit: 11.3 ns per 512-byte pair of K
+// and V rows, four or eight waves alike), so with fewer lists than compute units long lists are cut until
+// every compute unit has a chunk; what that cannot beat is the card's own rate (7 TB/s in this sum), and it
+// costs a merge launch.  Of the numbers of chunks that fit, the one with the least
+//     max(rows per chunk x 11.3 ns, bytes / 7 TB/s) + (merge: 2.6 us + 0.1 us per chunk)
+// is taken.  Measured with 32 heads x 128, attend calls back to back: one list of 256 rows per head 8.1 us whole,
+// 9.0 in two; 512 rows 11.4 whole, 10.0 in four; 2048 rows 28.2 whole, 15.0 in eight; four sequences of 512 rows
+// 12.2 whole, 14.3 in two, of 276 to 994 rows 17.5 whole, 15.3 in two, of 2048 rows 32.2 whole, 29.2 in two.
+// total_k: rows kept per head over the batch, or -1 for the workspace query, which does not know it and plans for the
+// most chunks any total can ask for.
+AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k) {
   AttendPlan p{};
   p.chunk_rows = max_k > 0 ? max_k : 1;
   p.n_chunks = 1;
   p.max_k = max_k;
   if (dt == DLLM_BF16 && max_k > 0) {
-    // Two workgroups of four waves fit a compute unit (512 slots on the chip).  With at least that many
-    // (sequence, head) pairs, chunks are as long as a wave's tile list allows (2048 rows: sixteen tiles);
-    // with fewer pairs, kept lists are cut finer so the chip still fills.  Chunks are multiples of the
-    // 128 rows four waves take per step.
-    const int64_t units = int64_t(s.batch) * s.hq;
-    int64_t want = 512 / units;
-    if (want < 1) want = 1;
-    int64_t rows = ((max_k + want - 1) / want + 127) / 128 * 128;
-    if (rows > 2048) rows = 2048;
-    p.chunk_rows = int32_t(rows);
-    p.n_chunks = int32_t((max_k + rows - 1) / rows);
+    constexpr int64_t kUnits = 256;   // compute units
+    const int64_t lists = int64_t(s.batch) * s.hq;
+    const double row_ns = 11.3 * s.d / 128, all_ns = total_k < 0 ? 0.0 : double(total_k) * s.hq * 4 * s.d / 7000.0;
+    double best = 0.0;
+    for (int64_t n = 1; n == 1 || n * lists <= kUnits; ++n) {
+      const int64_t rows = ((max_k + n - 1) / n + 127) / 128 * 128;   // multiples of what four waves take per step
+      const double t = std::max(double(rows) * row_ns, all_ns) + (n > 1 ? 2600.0 + 100.0 * double(n) : 0.0);
+      if (n == 1 || t < best) {
+        best = t;
+        p.chunk_rows = int32_t(rows);
+      }
+      if (rows == 128) break;
+    }
+    p.chunk_rows = std::min(p.chunk_rows, 2048);   // as long as a wave's list of tiles allows
+    p.n_chunks = int32_t((int64_t(max_k) + p.chunk_rows - 1) / p.chunk_rows);
   }
   if (p.n_chunks > 1) {
     const size_t slots = size_t(p.n_chunks) * size_t(s.total_q) * size_t(s.hq);
@@ -263,7 +279,7 @@ dllm_status dllm_hcsa_select(const dllm_batch* batch, const int32_t* cu_k, int32
 size_t dllm_hcsa_attend_workspace(const dllm_batch* batch, int32_t max_k) {
   dllm::Shape s;
   if (check_batch(batch, &s) != DLLM_OK || max_k < 0) return 0;
-  return dllm::plan_attend(s, batch->dtype, max_k).bytes;
+  return dllm::plan_attend(s, batch->dtype, max_k, -1).bytes;
 }
 
 dllm_status dllm_hcsa_attend(const dllm_batch* batch, const int32_t* idx, const int32_t* cu_k, int32_t total_k,
@@ -281,8 +297,9 @@ dllm_status dllm_hcsa_attend(const dllm_batch* batch, const int32_t* idx, const 
     return fail(DLLM_ERR_INVALID_ARG, "cu_k may be NULL only when total_k is 0 (got total_k=%d)", total_k);
   if (seq_mode != nullptr && (st = check_dense_strides(batch)) != DLLM_OK) return st;
   if (total_k > 0 && (st = check_sparse_strides(batch)) != DLLM_OK) return st;
-  const dllm::AttendPlan plan = dllm::plan_attend(s, batch->dtype, max_k);
-  if ((st = check_workspace(workspace, workspace_bytes, plan.bytes)) != DLLM_OK) return st;
+  const size_t need = dllm::plan_attend(s, batch->dtype, max_k, -1).bytes;   // what the query says, whatever this call takes
+  if ((st = check_workspace(workspace, workspace_bytes, need)) != DLLM_OK) return st;
+  const dllm::AttendPlan plan = dllm::plan_attend(s, batch->dtype, max_k, total_k);
   g_err[0] = 0;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   hipError_t e = dllm::validate_inputs(s, batch->cu_q, batch->cu_kv, cu_k, idx, seq_mode, total_k, max_k, 0, stream);

@@ -26,13 +26,9 @@ namespace dllm {
 
 constexpr int kTile = 32;        // kept rows per wave tile
 constexpr int kWaves = 4;
+constexpr int kMaxChunkRows = 2048;   // kept rows one workgroup walks at most
 constexpr int kWavesMulti = 8;        // waves of a workgroup that walks several lists, one after the other
 constexpr int kMultiTilesPerWave = 8; // chunk_rows <= kMultiTilesPerWave * kWavesMulti * kTile there
-constexpr int kMaxTilesPerWave = 16;  // chunk_rows <= kMaxTilesPerWave * kWaves * kTile
-#ifndef DLLM_SPARSE_DEPTH
-#define DLLM_SPARSE_DEPTH 1
-#endif
-constexpr int kDepth = DLLM_SPARSE_DEPTH;   // tiles of gathered rows a wave keeps in flight in registers
 // The k-th tile wave `wave` takes of a pass after its first (tile w is wave w's first).  Two waves share
 // a SIMD and the older one (waves 0-3) wins the arbitration for memory instructions, so with equal
 // shares four waves finish early and wait at the merge.  The later tiles are therefore dealt in periods
@@ -221,13 +217,15 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   constexpr int TILEB = kTile * ROWB;
   constexpr int NLD = kTile * CH / 64;  // 16-byte loads per lane per tile and tensor
   constexpr int NDB = D / 32;           // 32-wide blocks of head_dim in the output
+  constexpr int W = kWaves;
+  constexpr int MAXT = kMaxChunkRows / (W * kTile);   // tiles per wave at most
 
   // per wave: K tile then V tile; reused as fp32 merge space afterwards
-  __shared__ __attribute__((aligned(16))) char lds[kWaves][2 * TILEB];
+  __shared__ __attribute__((aligned(16))) char lds[W][2 * TILEB];
   // the 32 queries of the current query tile (same swizzled layout as a K tile)
   __shared__ __attribute__((aligned(16))) char qtile[TILEB];
   // kept-row ids of each wave's tiles; after the loop each wave leaves its (m, l) pairs in its own part
-  __shared__ int sm_rows[kWaves][kMaxTilesPerWave * kTile];
+  __shared__ int sm_rows[W][MAXT * kTile];
 
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 31, hf = lane >> 5;
@@ -255,7 +253,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   const int g = h / s.group;
 
   if (kb == 0) {  // nothing kept: defined as zeros
-    for (int e = threadIdx.x; e < nq * D; e += kWaves * 64)
+    for (int e = threadIdx.x; e < nq * D; e += W * 64)
       o[(int64_t(q0 + e / D) * s.hq + h) * D + e % D] = 0;
     return;
   }
@@ -283,19 +281,6 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   };
 
   for (int qt = 0; qt * 32 < nq; ++qt) {
-    // Q tile -> LDS: thread f takes chunk f % CH of query row f / CH (zeros past the last query)
-    {
-      constexpr int NQL = kTile * CH / (kWaves * 64);
-#pragma unroll
-      for (int i = 0; i < NQL; ++i) {
-        const int f = i * kWaves * 64 + threadIdx.x, r = f / CH, c = f % CH;
-        const int qi = qt * 32 + r;
-        v4u x = v4u{0u, 0u, 0u, 0u};
-        if (qi < nq)
-          x = *reinterpret_cast<const v4u*>(q + int64_t(q0 + qi) * s.q_tok + int64_t(h) * s.q_head + c * 8);
-        *reinterpret_cast<v4u*>(qtile + tile_off<D>(r, c)) = x;
-      }
-    }
     float m_used = -INFINITY, lsum = 0.0f;
     f32x16 acc[NDB];
 #pragma unroll
@@ -303,16 +288,34 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[db][i] = 0.0f;
 
-    // Kept-row ids of every tile this wave will walk go to LDS once (positions past the end repeat
-    // the last kept row; such rows are masked out of the softmax below).
+    // Kept-row ids of this wave's tiles (positions past the end repeat the last kept row; such rows are
+    // masked out of the softmax below).  They are asked for before the queries, and a wave's first gather
+    // leaves as soon as its own are here: the workgroup meets only once the first rows are on their way.
     int* my_rows = sm_rows[wave];
+    auto row_id = [&](int jj) -> int {
+      const int slot = jj * 64 + lane;   // tile slot / 32, row slot % 32 of this wave
+      const int t = min(c0 + (wave + (slot >> 5) * W) * kTile + (slot & 31), c1 - 1);
+      return idx != nullptr ? rows[t] : t;   // NULL idx: identity lists (a packed cache)
+    };
+    int ids[MAXT / 2];
 #pragma unroll
-    for (int j = 0; j < kMaxTilesPerWave / 2; ++j) {
-      const int slot = j * 64 + lane;   // tile slot / 32, row slot % 32 of this wave
-      const int t = min(c0 + (wave + (slot >> 5) * kWaves) * kTile + (slot & 31), c1 - 1);
-      my_rows[slot] = idx != nullptr ? rows[t] : t;   // NULL idx: identity lists (a packed cache)
+    for (int jj = 0; jj < MAXT / 2; ++jj) ids[jj] = row_id(jj);
+    // Q tile: thread f takes chunk f % CH of query row f / CH (zeros past the last query)
+    constexpr int NQL = (kTile * CH + W * 64 - 1) / (W * 64);
+    v4u qx[NQL];
+#pragma unroll
+    for (int i = 0; i < NQL; ++i) {
+      const int f = i * W * 64 + threadIdx.x, r = f / CH, c = f % CH;
+      const int qi = qt * 32 + r;
+      qx[i] = v4u{0u, 0u, 0u, 0u};
+      if (r < kTile && qi < nq)
+        qx[i] = *reinterpret_cast<const v4u*>(q + int64_t(q0 + qi) * s.q_tok + int64_t(h) * s.q_head + c * 8);
     }
-    __syncthreads();   // Q tile and row ids are in place
+#pragma unroll
+    for (int jj = 0; jj < MAXT / 2; ++jj) my_rows[jj * 64 + lane] = ids[jj];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // gather the wave's j-th tile into a register buffer
     auto fetch = [&](v4u (&kr)[NLD], v4u (&vr)[NLD], int j) {
 #pragma unroll
@@ -336,7 +339,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
         *reinterpret_cast<v4u*>(ktile + woff) = kr[i];
         *reinterpret_cast<v4u*>(vtile + woff) = vr[i];
       }
-      if (tile + kDepth * kWaves < ntiles) fetch(kr, vr, j + kDepth);
+      if (tile + W < ntiles) fetch(kr, vr, j + 1);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -345,34 +348,24 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
       __builtin_amdgcn_wave_barrier();
     };
 
-    if constexpr (kDepth == 2) {
-      v4u kra[NLD], vra[NLD], krb[NLD], vrb[NLD];
-      int tile = wave, j = 0;
-      if (tile < ntiles) fetch(kra, vra, 0);
-      if (tile + kWaves < ntiles) fetch(krb, vrb, 1);
-      while (tile < ntiles) {
-        round(kra, vra, j, tile);
-        tile += kWaves;
-        ++j;
-        if (tile >= ntiles) break;
-        round(krb, vrb, j, tile);
-        tile += kWaves;
-        ++j;
-      }
-    } else {
-      v4u kra[NLD], vra[NLD];
-      int tile = wave;
-      if (tile < ntiles) fetch(kra, vra, 0);
-      for (int j = 0; tile < ntiles; ++j, tile += kWaves) round(kra, vra, j, tile);
+    v4u kra[NLD], vra[NLD];
+    int tile = wave;
+    if (tile < ntiles) fetch(kra, vra, 0);
+#pragma unroll
+    for (int i = 0; i < NQL; ++i) {
+      const int f = i * W * 64 + threadIdx.x, r = f / CH, c = f % CH;
+      if (r < kTile) *reinterpret_cast<v4u*>(qtile + tile_off<D>(r, c)) = qx[i];
     }
+    __syncthreads();   // the queries are in place
+    for (int j = 0; tile < ntiles; ++j, tile += W) round(kra, vra, j, tile);
 
-    // ---- merge the four waves' (m, l, O^T) through LDS.  Every wave leaves its own running maximum,
+    // ---- merge the waves' (m, l, O^T) through LDS.  Every wave leaves its own running maximum,
     // row sum and unscaled accumulators in LDS that only it has used (its kept-row ids and its tile
     // buffers), so one barrier is enough; the wave that reduces a head_dim block applies the factors
     // exp2(m_w - m) while it adds.
     const float l = sum_across_halves(lsum);
     float* sm_ml = reinterpret_cast<float*>(&sm_rows[0][0]);   // [wave][m: 32 | l: 32], row stride = a wave's id area
-    constexpr int kMlStride = kMaxTilesPerWave * kTile;
+    constexpr int kMlStride = MAXT * kTile;
     if (hf == 0) {
       sm_ml[wave * kMlStride + col] = m_used;
       sm_ml[wave * kMlStride + 32 + col] = l;
@@ -385,28 +378,31 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
         mrg[((wave * NDB + db) * 4 + i4) * 64 + lane] =
             make_float4(acc[db][4 * i4 + 0], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]);
     __syncthreads();
-    if (wave < NDB) {
-      const int db = wave;
+    {
+      // every wave reduces its share of the tile: head_dim block db, register quads i4_0 ...
+      constexpr int PARTS = W / NDB, NQ4 = 4 / PARTS;
+      static_assert(W % NDB == 0 && 4 % PARTS == 0, "the waves split the output evenly");
+      const int db = wave % NDB, i4_0 = (wave / NDB) * NQ4;
       float m_all = -INFINITY;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) m_all = fmaxf(m_all, sm_ml[w * kMlStride + col]);
-      float f[kWaves];
+      for (int w = 0; w < W; ++w) m_all = fmaxf(m_all, sm_ml[w * kMlStride + col]);
+      float f[W];
       float l_all = 0.0f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
+      for (int w = 0; w < W; ++w) {
         f[w] = __builtin_amdgcn_exp2f(sm_ml[w * kMlStride + col] - m_all);   // 0 for a wave that saw no tile
         l_all += sm_ml[w * kMlStride + 32 + col] * f[w];
       }
-      float outv[16];
+      float outv[4 * NQ4];
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
+      for (int n = 0; n < NQ4; ++n) {
         float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) {
-          const float4 x = mrg[((w * NDB + db) * 4 + i4) * 64 + lane];
+        for (int w = 0; w < W; ++w) {
+          const float4 x = mrg[((w * NDB + db) * 4 + i4_0 + n) * 64 + lane];
           a.x += x.x * f[w]; a.y += x.y * f[w]; a.z += x.z * f[w]; a.w += x.w * f[w];
         }
-        outv[4 * i4 + 0] = a.x; outv[4 * i4 + 1] = a.y; outv[4 * i4 + 2] = a.z; outv[4 * i4 + 3] = a.w;
+        outv[4 * n + 0] = a.x; outv[4 * n + 1] = a.y; outv[4 * n + 2] = a.z; outv[4 * n + 3] = a.w;
       }
       const int qi = qt * 32 + col;
       if (qi < nq) {
@@ -414,20 +410,20 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
           const float inv = 1.0f / l_all;
           uint16_t* op = o + (int64_t(q0 + qi) * s.hq + h) * D + db * 32 + 4 * hf;
 #pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4) {
+          for (int n = 0; n < NQ4; ++n) {
             v2u w2;
-            w2.x = cvt_pk_bf16(outv[4 * i4 + 0] * inv, outv[4 * i4 + 1] * inv);
-            w2.y = cvt_pk_bf16(outv[4 * i4 + 2] * inv, outv[4 * i4 + 3] * inv);
-            *reinterpret_cast<v2u*>(op + 8 * i4) = w2;
+            w2.x = cvt_pk_bf16(outv[4 * n + 0] * inv, outv[4 * n + 1] * inv);
+            w2.y = cvt_pk_bf16(outv[4 * n + 2] * inv, outv[4 * n + 3] * inv);
+            *reinterpret_cast<v2u*>(op + 8 * (i4_0 + n)) = w2;
           }
         } else {
           const int64_t slot = (int64_t(chunk) * s.total_q + (q0 + qi)) * s.hq + h;
           float* pp = po + slot * D + db * 32 + 4 * hf;
 #pragma unroll
-          for (int i4 = 0; i4 < 4; ++i4)
-            *reinterpret_cast<float4*>(pp + 8 * i4) =
-                make_float4(outv[4 * i4 + 0], outv[4 * i4 + 1], outv[4 * i4 + 2], outv[4 * i4 + 3]);
-          if (db == 0 && hf == 0) { pm[slot] = m_all; pl[slot] = l_all; }
+          for (int n = 0; n < NQ4; ++n)
+            *reinterpret_cast<float4*>(pp + 8 * (i4_0 + n)) =
+                make_float4(outv[4 * n + 0], outv[4 * n + 1], outv[4 * n + 2], outv[4 * n + 3]);
+          if (wave == 0 && hf == 0) { pm[slot] = m_all; pl[slot] = l_all; }
         }
       }
     }
@@ -710,46 +706,54 @@ __global__ __launch_bounds__(kWavesMulti * 64, 1) void attend_sparse_multi_bf16_
   }
 }
 
-// Merge the chunk partials of every (sequence, head) that needed more than one chunk.
-// One workgroup per (head, sequence): 8 threads per query row, each owning D/8 output elements,
-// so all loads of a row are independent and issued together.
+// Merge the chunk partials of every (sequence, head) that needed more than one chunk.  The launch is a few
+// hundred kilobytes and nothing but latency, so it is spread thin (eight query rows per workgroup, one thread
+// per four output elements) and the partials of four chunks are asked for at once.
 template <int D>
 __global__ __launch_bounds__(256) void attend_sparse_combine_kernel(
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const uint8_t* __restrict__ seq_mode,
     const float* __restrict__ po, const float* __restrict__ pm, const float* __restrict__ pl,
     uint16_t* __restrict__ o, int32_t chunk_rows, Shape s DLLM_CHECK_PARAM) {
   DLLM_CHECK_EXIT();
-  const int h = blockIdx.x, b = blockIdx.y;
+  constexpr int TPR = D / 4, ROWS = 256 / TPR;   // threads per row, rows per workgroup
+  const int h = blockIdx.y, b = blockIdx.z;
+  const int k0 = cu_k[b], k1 = cu_k[b + 1], q0 = cu_q[b], nq = cu_q[b + 1] - q0;
   if (seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE) return;
-  const int kb = cu_k[b + 1] - cu_k[b];
-  const int nch = chunk_geom(kb, chunk_rows).n;
-  if (nch <= 1) return;
-  const int q0 = cu_q[b], nq = cu_q[b + 1] - q0;
-  constexpr int EPT = D / 8;   // elements per thread
-  const int sub = threadIdx.x & 7;
-  for (int i = threadIdx.x >> 3; i < nq; i += 32) {
-    float m_all = -INFINITY;
-    for (int c = 0; c < nch; ++c) m_all = fmaxf(m_all, pm[(int64_t(c) * s.total_q + (q0 + i)) * s.hq + h]);
-    float l_all = 0.0f, a[EPT];
+  const int nch = chunk_geom(k1 - k0, chunk_rows).n;
+  const int i = blockIdx.x * ROWS + threadIdx.x / TPR, sub = threadIdx.x % TPR;
+  if (nch <= 1 || i >= nq) return;
+  const int64_t row = int64_t(q0 + i) * s.hq + h, pitch = int64_t(s.total_q) * s.hq;   // slot of chunk c: row + c * pitch
+  float m_all = -INFINITY, l_all = 0.0f;
+  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  for (int c0 = 0; c0 < nch; c0 += 4) {
+    float m[4], l[4];
+    float4 x[4];
 #pragma unroll
-    for (int e = 0; e < EPT; ++e) a[e] = 0.0f;
-    for (int c = 0; c < nch; ++c) {
-      const int64_t slot = (int64_t(c) * s.total_q + (q0 + i)) * s.hq + h;
-      const float w = __builtin_amdgcn_exp2f(pm[slot] - m_all);
-      l_all += pl[slot] * w;
-      const float4* src = reinterpret_cast<const float4*>(po + slot * D + sub * EPT);
-#pragma unroll
-      for (int e = 0; e < EPT / 4; ++e) {
-        const float4 x = src[e];
-        a[4 * e + 0] += x.x * w; a[4 * e + 1] += x.y * w; a[4 * e + 2] += x.z * w; a[4 * e + 3] += x.w * w;
-      }
+    for (int u = 0; u < 4; ++u) {   // past the last chunk: that chunk again, with no weight
+      const int64_t slot = row + min(c0 + u, nch - 1) * pitch;
+      m[u] = pm[slot];
+      l[u] = pl[slot];
+      x[u] = *reinterpret_cast<const float4*>(po + slot * D + sub * 4);
     }
-    const float inv = 1.0f / l_all;
-    uint16_t* op = o + (int64_t(q0 + i) * s.hq + h) * D + sub * EPT;
+    float m_new = m_all;
 #pragma unroll
-    for (int e = 0; e < EPT; e += 2)
-      *reinterpret_cast<uint32_t*>(op + e) = cvt_pk_bf16(a[e] * inv, a[e + 1] * inv);
+    for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, m[u]);
+    const float old = __builtin_amdgcn_exp2f(m_all - m_new);   // first round: exp2(-inf) = 0
+    l_all *= old;
+    a.x *= old; a.y *= old; a.z *= old; a.w *= old;
+    m_all = m_new;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float w = c0 + u < nch ? __builtin_amdgcn_exp2f(m[u] - m_all) : 0.0f;
+      l_all += l[u] * w;
+      a.x += x[u].x * w; a.y += x[u].y * w; a.z += x[u].z * w; a.w += x[u].w * w;
+    }
   }
+  const float inv = 1.0f / l_all;
+  v2u w2;
+  w2.x = cvt_pk_bf16(a.x * inv, a.y * inv);
+  w2.y = cvt_pk_bf16(a.z * inv, a.w * inv);
+  *reinterpret_cast<v2u*>(o + row * D + sub * 4) = w2;
 }
 
 hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const void* q, const void* k,
@@ -791,20 +795,22 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
     dim3 grid(p.n_chunks, s.hq, s.batch);
     // the start order only matters when the workgroups cannot all be resident at once (two per compute unit)
     const int ranked = n_items > 512 ? 1 : 0;
-    if (s.d == 128)
-      attend_sparse_bf16_kernel<128><<<grid, kWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, idx, cu_k, total_k,
-                                                                  seq_mode, oh, po, pm, pl, p.chunk_rows, ranked, s DLLM_CHECK_PASS);
-    else
-      attend_sparse_bf16_kernel<64><<<grid, kWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, idx, cu_k, total_k,
-                                                                 seq_mode, oh, po, pm, pl, p.chunk_rows, ranked, s DLLM_CHECK_PASS);
+    auto launch = [&](auto kernel) {
+      kernel<<<grid, kWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, idx, cu_k, total_k, seq_mode, oh, po, pm, pl,
+                                           p.chunk_rows, ranked, s DLLM_CHECK_PASS);
+    };
+    if (s.d == 128) launch(attend_sparse_bf16_kernel<128>);
+    else launch(attend_sparse_bf16_kernel<64>);
   }
   e = hipGetLastError();
   if (e != hipSuccess || p.n_chunks <= 1) return e;
-  dim3 cgrid(s.hq, s.batch);
-  if (s.d == 128)
-    attend_sparse_combine_kernel<128><<<cgrid, 256, 0, st>>>(cu_q, cu_k, seq_mode, po, pm, pl, oh, p.chunk_rows, s DLLM_CHECK_PASS);
-  else
-    attend_sparse_combine_kernel<64><<<cgrid, 256, 0, st>>>(cu_q, cu_k, seq_mode, po, pm, pl, oh, p.chunk_rows, s DLLM_CHECK_PASS);
+  auto combine = [&](auto kernel) {
+    const int rows = 256 / (s.d / 4);
+    kernel<<<dim3((s.max_q + rows - 1) / rows, s.hq, s.batch), 256, 0, st>>>(cu_q, cu_k, seq_mode, po, pm, pl, oh,
+                                                                             p.chunk_rows, s DLLM_CHECK_PASS);
+  };
+  if (s.d == 128) combine(attend_sparse_combine_kernel<128>);
+  else combine(attend_sparse_combine_kernel<64>);
   return hipGetLastError();
 }
 

@@ -50,7 +50,7 @@ struct AttendPlan {
   int32_t max_k;       // the caller's bound on kept rows per (sequence, head)
   size_t off_po, off_pm, off_pl, bytes;
 };
-AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k);
+AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k);
 
 // `which` selects the sequences a launch works on: 0 = all, each as its flag in seq_mode says (fp32 only);
 // 1 = those flagged dense; 2 = every sequence, as dense.

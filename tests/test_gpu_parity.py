@@ -837,3 +837,14 @@ def test_f32_attend_tile_edges(D, hq, hkv, wide):
     w = custom(17, torch.float32, hq, hkv, D, lens, qlens, [0 if m else k for k, m in zip(keep, mode)], mode=mode, salient=0.1)
     err = check_attend(w, oracle_select(w), name=f"f32 tile edges wide={wide}")
     say(f"max abs error {err:.3e}")
+
+
+@pytest.mark.parametrize("hq,hkv,D,keep", [(32, 32, 128, [500]), (16, 4, 128, [1000, 130]), (8, 2, 64, [1023, 3, 640]),
+                                            (4, 4, 128, [129, 410]), (2, 1, 64, [2047]), (32, 8, 128, [2000, 400, 0])])
+def test_attend_kept_lists_cut_over_workgroups(hq, hkv, D, keep):
+    """Fewer lists than compute units: lists are cut into up to as many chunks as fill the chip and merged four
+    chunks at a time; chunk counts that do and do not divide by four, a second query tile, short lists in between."""
+    w = custom(18, torch.bfloat16, hq, hkv, D, [max(k, 1) + 50 for k in keep], [32, 45, 7][:len(keep)], keep, salient=0.05)
+    dw = workload.DeviceWorkload(w)
+    assert hcsa.dllm_hcsa_attend_workspace(dw.batch, dw.max_k) > 0
+    check_attend(w, oracle_select(w), dw=dw)
