@@ -132,20 +132,13 @@ struct DenseState<128> {
                      [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
                    : "memory", DLLM_DENSE_SCRATCH);
   }
-  // the closing P V product, with the probabilities of pb_a (A) or pb_b; `ad`: addr with the V row
+  // the closing P V product, with the probabilities of pb_a; `ad`: addr with the V row
   // offset added to the V^T operand addresses (it is not a compile-time constant here)
-  template <bool A>
   __device__ __forceinline__ void tail(i32x16 ad) {
-    if constexpr (A)
-      asm volatile(DLLM_DENSE_TAIL_128_A
-                   : DLLM_ACC_OUT, DLLM_LS_OUT_128
-                   : DLLM_ACC_TIED, DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v[160:175]}"(pb_a), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 256)
-                   : "memory", DLLM_DENSE_SCRATCH);
-    else
-      asm volatile(DLLM_DENSE_TAIL_128_B
-                   : DLLM_ACC_OUT, DLLM_LS_OUT_128
-                   : DLLM_ACC_TIED, DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v[176:191]}"(pb_b), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 256)
-                   : "memory", DLLM_DENSE_SCRATCH);
+    asm volatile(DLLM_DENSE_TAIL_128
+                 : DLLM_ACC_OUT, DLLM_LS_OUT_128
+                 : DLLM_ACC_TIED, DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v[160:175]}"(pb_a), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 256)
+                 : "memory", DLLM_DENSE_SCRATCH);
   }
   // S^T(0) into st_a from the K operands in kop
   __device__ __forceinline__ void score0() {
@@ -220,18 +213,11 @@ struct DenseState<64> {
                      [voff1] "n"(VOFF1)
                    : "memory", DLLM_DENSE_SCRATCH);
   }
-  template <bool A>
   __device__ __forceinline__ void tail(i32x16 ad) {
-    if constexpr (A)
-      asm volatile(DLLM_DENSE_TAIL_64_A
-                   : DLLM_ACC_OUT, DLLM_LS_OUT_64
-                   : DLLM_ACC_TIED, DLLM_LS_TIED("4", "5"), [ones] "v"(ones), "{v[160:175]}"(pb_a), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 128)
-                   : "memory", DLLM_DENSE_SCRATCH);
-    else
-      asm volatile(DLLM_DENSE_TAIL_64_B
-                   : DLLM_ACC_OUT, DLLM_LS_OUT_64
-                   : DLLM_ACC_TIED, DLLM_LS_TIED("4", "5"), [ones] "v"(ones), "{v[176:191]}"(pb_b), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 128)
-                   : "memory", DLLM_DENSE_SCRATCH);
+    asm volatile(DLLM_DENSE_TAIL_64
+                 : DLLM_ACC_OUT, DLLM_LS_OUT_64
+                 : DLLM_ACC_TIED, DLLM_LS_TIED("4", "5"), [ones] "v"(ones), "{v[160:175]}"(pb_a), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 128)
+                 : "memory", DLLM_DENSE_SCRATCH);
   }
   __device__ __forceinline__ void score0() {
     asm volatile(DLLM_DENSE_SCORE0_64
@@ -674,8 +660,11 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     i32x16 ad = w.addr;
 #pragma unroll
     for (int i = 8; i < 16; ++i) ad[i] += voff;
-    if (nsteps & 1) w.template tail<true>(ad);
-    else w.template tail<false>(ad);
+    // (One tail for both cases, after moving sixteen registers: with a tail in either arm of a branch the
+    // compiler carries all accumulators through vector registers and back where the arms meet, 2500 of the
+    // 2900 cycles from the last step to the stores.)
+    if (!(nsteps & 1)) w.pb_a = w.pb_b;
+    w.tail(ad);
   }
 #ifdef DLLM_DENSE_STAMPS
   const uint64_t t_loop1 = __builtin_readcyclecounter();

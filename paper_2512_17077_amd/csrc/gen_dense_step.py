@@ -295,8 +295,7 @@ def main():
     for D in (128, 64):
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_AB", gen_step(D, ST_A, ST_B, PB_A, PB_B, with_loads=True)))
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_BA", gen_step(D, ST_B, ST_A, PB_B, PB_A)))
-        out.append(as_macro(f"DLLM_DENSE_TAIL_{D}_A", gen_step(D, 0, 0, 0, PB_A, False, False)))
-        out.append(as_macro(f"DLLM_DENSE_TAIL_{D}_B", gen_step(D, 0, 0, 0, PB_B, False, False)))
+        out.append(as_macro(f"DLLM_DENSE_TAIL_{D}", gen_step(D, 0, 0, 0, PB_A, False, False)))
         out.append(as_macro(f"DLLM_DENSE_SCORE0_{D}", gen_score0(D)))
         out.append(as_macro(f"DLLM_DENSE_ACC_INIT_{D}", gen_acc_init(D)))
         out.append(as_macro(f"DLLM_DENSE_ACC_SCALE_{D}", gen_acc_scale(D)))
