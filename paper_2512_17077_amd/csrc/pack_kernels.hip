@@ -5,8 +5,10 @@
 // Pure data movement, bound by HBM: per kept (head, row) pair one K row and one V row are gathered
 // (16-byte non-temporal loads, a row's chunks in neighbouring lanes) and written out contiguously.
 // A workgroup takes a run of consecutive list positions of one (sequence, head), so its stores cover
-// one contiguous span (written with non-temporal stores: the packed rows are not read again soon);
-// several rows per lane group are in flight before the first store.
+// one contiguous span; several rows per lane group are in flight before the first store.  The stores are
+// plain ones: the attention that follows reads the packed rows, and finds up to 256 MB of them in the
+// memory-side cache (16 sequences of 32 heads, 135 MB packed, then attended over: 81.9 us with non-temporal
+// stores, 73.7 us with plain ones).
 #include "common.h"
 
 namespace dllm {
@@ -53,8 +55,8 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(
   for (int p = 0; p < kPackInFlight; ++p) {
     const int t = t0 + p * ROWS + sub;
     if (t < kb) {
-      __builtin_nontemporal_store(kr[p], reinterpret_cast<v4u*>(kout + t * out_row));
-      __builtin_nontemporal_store(vr[p], reinterpret_cast<v4u*>(vout + t * out_row));
+      *reinterpret_cast<v4u*>(kout + t * out_row) = kr[p];
+      *reinterpret_cast<v4u*>(vout + t * out_row) = vr[p];
     }
   }
 }
