@@ -204,7 +204,8 @@ __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* 
   }
 }
 
-template <int D>
+// Once: K and V rows are read with the non-temporal hint (gathers_once)
+template <int D, bool Once>
 __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ idx,
@@ -321,8 +322,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
         const uint32_t off = __umul24(uint32_t(my_rows[j * kTile + (i * 64 + lane) / CH]), pitch) + coff;
-        kr[i] = load_once(kbase + off);
-        vr[i] = load_once(vbase + off);
+        kr[i] = load_once<Once>(kbase + off);
+        vr[i] = load_once<Once>(vbase + off);
       }
     };
     // one tile: registers -> LDS, refill the registers with the tile after next, then the math
@@ -799,8 +800,13 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
       kernel<<<grid, kWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, idx, cu_k, total_k, seq_mode, oh, po, pm, pl,
                                            p.chunk_rows, ranked, s DLLM_CHECK_PASS);
     };
-    if (s.d == 128) launch(attend_sparse_bf16_kernel<128>);
-    else launch(attend_sparse_bf16_kernel<64>);
+    if (gathers_once(s, 2)) {
+      if (s.d == 128) launch(attend_sparse_bf16_kernel<128, true>);
+      else launch(attend_sparse_bf16_kernel<64, true>);
+    } else {
+      if (s.d == 128) launch(attend_sparse_bf16_kernel<128, false>);
+      else launch(attend_sparse_bf16_kernel<64, false>);
+    }
   }
   e = hipGetLastError();
   if (e != hipSuccess || p.n_chunks <= 1) return e;

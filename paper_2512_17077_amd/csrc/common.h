@@ -22,6 +22,17 @@ struct Shape {
   float scale;
 };
 
+// Whether K rows are better read with the non-temporal hint (load_once).  A Reuse step streams K for the scores
+// and then gathers rows of the same K: while K is small, lines left in the caches by the first are found by the
+// second.  Measured per selection / per step of selection and attention, hint against no hint in both: K of 10 MB
+// 9.66 / 19.0 against 9.23 / 18.65 us, 21 MB 12.6 / 22.3 against 12.2 / 21.2, 42 MB 16.3 / 26.7 against 16.2 / 25.8, 34 MB
+// under grouped queries 16.9 / 29.4 against 16.7 / 28.0; but the stream itself loses from 100 MB on (34.1 against 35.1 us;
+// at 168 MB 38.4 against 41.8), the gather from 260 MB on (33.1 against 36.2 us on the kept rows of 264 MB of K, while 101 MB
+// gains 55.4 -> 53.5 us a step, 168 MB 59.0 -> 57.4).
+inline int64_t k_bytes(const Shape& s, int es) { return int64_t(s.total_kv) * s.hkv * s.d * es; }
+inline bool streams_once(const Shape& s, int es) { return k_bytes(s, es) > (int64_t(64) << 20); }
+inline bool gathers_once(const Shape& s, int es) { return k_bytes(s, es) > (int64_t(128) << 20); }
+
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // ---- selection (select_kernels.hip)
@@ -88,18 +99,14 @@ hipError_t validate_inputs(const Shape& s, const int32_t* cu_q, const int32_t* c
                            int32_t forced_tail, hipStream_t st);
 
 // ---- device helpers
-// 16-byte load of data that is read once per launch (K/V rows streamed or gathered from HBM): the
-// non-temporal hint keeps such lines from displacing reusable data in the caches, which measurably
-// raises the HBM read rate on MI355X.
-#ifndef DLLM_STREAM_NT
-#define DLLM_STREAM_NT 1
-#endif
+// 16-byte load of data that is read once per launch (K/V rows streamed or gathered from HBM).  With Once set it
+// carries the non-temporal hint, which keeps such lines from displacing reusable data in the caches and
+// measurably raises the HBM read rate on MI355X (selection over 264 MB of K: 52.0 against 57.7 us); without it the
+// lines may stay, for a call whose K is small enough to be found again (streams_once, gathers_once).
+template <bool Once = true>
 __device__ __forceinline__ v4u load_once(const void* p) {
-#if DLLM_STREAM_NT
-  return __builtin_nontemporal_load(static_cast<const v4u*>(p));
-#else
-  return *static_cast<const v4u*>(p);
-#endif
+  if constexpr (Once) return __builtin_nontemporal_load(static_cast<const v4u*>(p));
+  else return *static_cast<const v4u*>(p);
 }
 // Inclusive prefix sum over the 64 lanes of a wave (all lanes active) through the data-parallel
 // primitives: shifts by 1, 2, 4, 8 within each row of 16 lanes, then the last lane of row 0 (2) is

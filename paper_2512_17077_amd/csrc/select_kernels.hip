@@ -33,7 +33,8 @@ __device__ __forceinline__ int swz(int row) {
   return (row / rows_per_line) & (CH - 1);
 }
 
-// ES: element bytes (2 = bf16, 4 = fp32); D: head_dim; GT: query heads scored per pass over the tile.
+// ES: element bytes (2 = bf16, 4 = fp32); D: head_dim; GT: query heads scored per pass over the tile;
+// Once: K is read with the non-temporal hint (streams_once).
 // Each wave walks `tiles_per_wave` consecutive 64-row tiles; while it scores one tile out of LDS the
 // next tile's rows are already in flight into registers.
 // acc += q[J + e] * kv[e] for e = 0 .. N-1 in this order, one fused multiply-add each, where q[j] is
@@ -77,7 +78,7 @@ __device__ __forceinline__ void for_each_index(F& f, std::integer_sequence<int, 
   (f(std::integral_constant<int, C>{}), ...);
 }
 
-template <int ES, int D, int GT>
+template <int ES, int D, int GT, bool Once>
 __global__ __launch_bounds__(kScoreWaves * 64, (ES * D <= 256 ? 2 : 1)) void score_kernel(
     const char* __restrict__ k, const char* __restrict__ q, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ cu_k, float* __restrict__ scores,
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(kScoreWaves * 64, (ES * D <= 256 ? 2 : 1)) void sco
 #pragma unroll
     for (int i = 0; i < CH; ++i) {
       const int row = min(r0 + (i * 64 + lane) / CH, L - 1);
-      regs[i] = load_once(base + row * row_pitch);
+      regs[i] = load_once<Once>(base + row * row_pitch);
     }
   };
   if (ntiles > 0) fetch(first);
@@ -1074,9 +1075,14 @@ static hipError_t launch_score(const Shape& s, const void* k, const void* q, con
     kernel<<<grid, block, sums_bytes, st>>>(kp, qp, cu_q, cu_kv, cu_k, scores, tpw, s DLLM_CHECK_PASS);
     return hipGetLastError();
   };
-  if (s.group % 4 == 0) return launch(score_kernel<ES, D, 4>);
-  if (s.group % 2 == 0) return launch(score_kernel<ES, D, 2>);
-  return launch(score_kernel<ES, D, 1>);
+  if (streams_once(s, ES)) {
+    if (s.group % 4 == 0) return launch(score_kernel<ES, D, 4, true>);
+    if (s.group % 2 == 0) return launch(score_kernel<ES, D, 2, true>);
+    return launch(score_kernel<ES, D, 1, true>);
+  }
+  if (s.group % 4 == 0) return launch(score_kernel<ES, D, 4, false>);
+  if (s.group % 2 == 0) return launch(score_kernel<ES, D, 2, false>);
+  return launch(score_kernel<ES, D, 1, false>);
 }
 
 static std::atomic<int32_t> g_select_form{DLLM_SELECT_FORM_AUTO};
