@@ -7,6 +7,15 @@
 //     owns 64 of them as two blocks of 32.  Every K operand (ds_read_b128) and every V^T operand
 //     (ds_read_b64_tr_b16) fetched from LDS feeds two MFMAs, one per block, which halves the LDS
 //     operand traffic per flop, and the two blocks give the wave independent work to interleave.
+//   - Calls with too few query rows for the compute units take the split form (KS = 2): a workgroup owns 128 query
+//     rows, wave pair 0 takes the first 32 keys of every tile and wave pair 1 the other 32, and the pairs merge
+//     their (m, l, O) through LDS at the end.  Every step is then a tile's first: K rows are requested four tiles
+//     ahead and V rows two (the rings hold four of each; scores run two steps ahead of the P V product), and the
+//     step waits for all but the previous step's requests.  One layer of one request (32 heads x 128, 1024 keys):
+//     29.7 -> 24.6 us.
+//   - Queries come in and outputs go out through LDS in whole rows: lanes of an operand or accumulator register lie
+//     in 32 different rows, and its 16- or 8-byte pieces cost the load and store paths one line each (the same
+//     layer 31.0 -> 27.8 us unsplit, 25.2 -> 23.4 us split).
 //   - K/V tiles of 64 keys go from global memory straight into LDS (global_load_lds, 16 bytes per
 //     lane), two tiles ahead of their use, into rings of four tiles each (128 KB at D = 128); one
 //     workgroup barrier per tile.  LDS tiles are XOR-swizzled by row; since the LDS side of such a load
@@ -28,6 +37,7 @@
 //   - The loop is unrolled over one turn of the rings (eight steps), so every LDS address is a register
 //     fixed before the loop plus an immediate offset.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -40,7 +50,8 @@ constexpr int kDenseK = 64;          // keys per LDS tile
 constexpr int kDenseRing = 4;        // K tiles, and V tiles, resident in LDS
 constexpr int kDenseWaves = 4;       // waves per workgroup
 constexpr int kDenseQB = 2;          // 32-query blocks per wave
-constexpr int kDenseRows = kDenseWaves * kDenseQB * 32;   // query rows per workgroup
+// query rows per workgroup; with KS = 2 two wave pairs take the same rows and half of every tile's keys each
+constexpr int dense_rows(int ks) { return kDenseWaves * kDenseQB * 32 / ks; }
 
 typedef __attribute__((ext_vector_type(16))) int i32x16;
 
@@ -69,6 +80,7 @@ template <int NLD>
 struct DenseTileLoad {
   const char *k, *v;
   uint32_t off[NLD];
+  uint32_t off_v[NLD];   // split form only: there K and V rows of different tiles are requested
   uint32_t wave_lds;
 };
 
@@ -93,6 +105,36 @@ struct DenseTileLoad {
 #define DLLM_LS_OUT_64 "={a[96:111]}"(ls[0]), "={a[112:127]}"(ls[1])
 #define DLLM_LS_TIED(a, b) a(ls[0]), b(ls[1])
 
+// One step: AB reads the scores st_a and the probabilities pb_b and leaves the next scores in st_b and its own
+// probabilities in pb_a, BA the other way round.  Split: the texts in which every step requests a tile.
+#define DLLM_STEP_FUNCTION(D, NLD)                                                                                  \
+  template <bool AB, bool Split, int KOFF, int VOFF0, int VOFF1, int LK, int LV>                                    \
+  __device__ __forceinline__ void step(float zs, const DenseTileLoad<NLD>& tl, uint64_t& grow) {                    \
+    if constexpr (AB && Split)                                                                                      \
+      asm volatile(DLLM_DENSE_STEP_##D##_AB_SPLIT                                                                   \
+                   : DLLM_STEP_OUT("={v[128:143]}"(st_b[0]), "={v[144:159]}"(st_b[1]), "={v[160:175]}"(pb_a))        \
+                   : DLLM_STEP_IN("{v[96:111]}"(st_a[0]), "{v[112:127]}"(st_a[1]), "{v[176:191]}"(pb_b)),            \
+                     DLLM_STEP_LOADS_SPLIT                                                                          \
+                   : "memory", "m0", "scc", DLLM_DENSE_SCRATCH);                                                    \
+    else if constexpr (Split)                                                                                       \
+      asm volatile(DLLM_DENSE_STEP_##D##_BA_SPLIT                                                                   \
+                   : DLLM_STEP_OUT("={v[96:111]}"(st_a[0]), "={v[112:127]}"(st_a[1]), "={v[176:191]}"(pb_b))         \
+                   : DLLM_STEP_IN("{v[128:143]}"(st_b[0]), "{v[144:159]}"(st_b[1]), "{v[160:175]}"(pb_a)),           \
+                     DLLM_STEP_LOADS_SPLIT                                                                          \
+                   : "memory", "m0", "scc", DLLM_DENSE_SCRATCH);                                                    \
+    else if constexpr (AB)                                                                                          \
+      asm volatile(DLLM_DENSE_STEP_##D##_AB                                                                         \
+                   : DLLM_STEP_OUT("={v[128:143]}"(st_b[0]), "={v[144:159]}"(st_b[1]), "={v[160:175]}"(pb_a))        \
+                   : DLLM_STEP_IN("{v[96:111]}"(st_a[0]), "{v[112:127]}"(st_a[1]), "{v[176:191]}"(pb_b)),            \
+                     DLLM_STEP_LOADS                                                                                \
+                   : "memory", "m0", "scc", DLLM_DENSE_SCRATCH);                                                    \
+    else                                                                                                            \
+      asm volatile(DLLM_DENSE_STEP_##D##_BA                                                                         \
+                   : DLLM_STEP_OUT("={v[96:111]}"(st_a[0]), "={v[112:127]}"(st_a[1]), "={v[176:191]}"(pb_b))         \
+                   : DLLM_STEP_IN("{v[128:143]}"(st_b[0]), "{v[144:159]}"(st_b[1]), "{v[160:175]}"(pb_a))            \
+                   : "memory", DLLM_DENSE_SCRATCH);                                                                 \
+  }
+
 template <>
 struct DenseState<128> {
   static constexpr int kAcc = 128;   // accumulator registers
@@ -109,29 +151,20 @@ struct DenseState<128> {
   "{a[0:15]}"(acc[0]), "{a[16:31]}"(acc[1]), "{a[32:47]}"(acc[2]), "{a[48:63]}"(acc[3]), "{a[64:79]}"(acc[4]), \
       "{a[80:95]}"(acc[5]), "{a[96:111]}"(acc[6]), "{a[112:127]}"(acc[7])
 #define DLLM_Q_IN "{a[128:143]}"(q[0]), "{a[144:159]}"(q[1]), "{a[160:175]}"(q[2]), "{a[176:191]}"(q[3])
-  template <bool AB, int KOFF, int VOFF0, int VOFF1, int LK, int LV>
-  __device__ __forceinline__ void step(float zs, const DenseTileLoad<4>& tl, uint64_t& grow) {
-    if constexpr (AB)
-      asm volatile(DLLM_DENSE_STEP_128_AB
-                   : DLLM_ACC_OUT, "={v[128:143]}"(st_b[0]), "={v[144:159]}"(st_b[1]), "={v[160:175]}"(pb_a),
-                     "={v[192:207]}"(kop[0]), "={v[208:223]}"(kop[1]), DLLM_LS_OUT_128, "={v74}"(mx[0]),
-                     "={v75}"(mx[1]), [grow] "=s"(grow)
-                   : DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[96:111]}"(st_a[0]),
-                     "{v[112:127]}"(st_a[1]), "{v[176:191]}"(pb_b), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth),
-                     [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1), [kt] "s"(tl.k), [vt] "s"(tl.v),
-                     [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]), [lo2] "v"(tl.off[2]), [lo3] "v"(tl.off[3]),
-                     [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
-                   : "memory", "m0", "scc", DLLM_DENSE_SCRATCH);
-    else
-      asm volatile(DLLM_DENSE_STEP_128_BA
-                   : DLLM_ACC_OUT, "={v[96:111]}"(st_a[0]), "={v[112:127]}"(st_a[1]), "={v[176:191]}"(pb_b),
-                     "={v[192:207]}"(kop[0]), "={v[208:223]}"(kop[1]), DLLM_LS_OUT_128, "={v74}"(mx[0]),
-                     "={v75}"(mx[1]), [grow] "=s"(grow)
-                   : DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[128:143]}"(st_b[0]),
-                     "{v[144:159]}"(st_b[1]), "{v[160:175]}"(pb_a), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth),
-                     [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
-                   : "memory", DLLM_DENSE_SCRATCH);
-  }
+#define DLLM_STEP_OUT(st0, st1, pb) DLLM_ACC_OUT, st0, st1, pb, "={v[192:207]}"(kop[0]), "={v[208:223]}"(kop[1]), \
+      DLLM_LS_OUT_128, "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
+#define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"),          \
+      [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr),             \
+      [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
+#define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
+      [lo2] "v"(tl.off[2]), [lo3] "v"(tl.off[3]), [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
+#define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1]),                     \
+      [vo2] "v"(tl.off_v[2]), [vo3] "v"(tl.off_v[3])
+  DLLM_STEP_FUNCTION(128, 4)
+#undef DLLM_STEP_OUT
+#undef DLLM_STEP_IN
+#undef DLLM_STEP_LOADS
+#undef DLLM_STEP_LOADS_SPLIT
   // the closing P V product, with the probabilities of pb_a; `ad`: addr with the V row
   // offset added to the V^T operand addresses (it is not a compile-time constant here)
   __device__ __forceinline__ void tail(i32x16 ad) {
@@ -191,28 +224,19 @@ struct DenseState<64> {
 #define DLLM_ACC_TIED "0"(acc[0]), "1"(acc[1]), "2"(acc[2]), "3"(acc[3])
 #define DLLM_ACC_IN "{a[0:15]}"(acc[0]), "{a[16:31]}"(acc[1]), "{a[32:47]}"(acc[2]), "{a[48:63]}"(acc[3])
 #define DLLM_Q_IN "{a[64:79]}"(q[0]), "{a[80:95]}"(q[1])
-  template <bool AB, int KOFF, int VOFF0, int VOFF1, int LK, int LV>
-  __device__ __forceinline__ void step(float zs, const DenseTileLoad<2>& tl, uint64_t& grow) {
-    if constexpr (AB)
-      asm volatile(DLLM_DENSE_STEP_64_AB
-                   : DLLM_ACC_OUT, "={v[128:143]}"(st_b[0]), "={v[144:159]}"(st_b[1]), "={v[160:175]}"(pb_a),
-                     "={v[192:207]}"(kop[0]), DLLM_LS_OUT_64, "={v74}"(mx[0]),
-                     "={v75}"(mx[1]), [grow] "=s"(grow)
-                   : DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[96:111]}"(st_a[0]), "{v[112:127]}"(st_a[1]),
-                     "{v[176:191]}"(pb_b), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0),
-                     [voff1] "n"(VOFF1), [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),
-                     [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
-                   : "memory", "m0", "scc", DLLM_DENSE_SCRATCH);
-    else
-      asm volatile(DLLM_DENSE_STEP_64_BA
-                   : DLLM_ACC_OUT, "={v[96:111]}"(st_a[0]), "={v[112:127]}"(st_a[1]), "={v[176:191]}"(pb_b),
-                     "={v[192:207]}"(kop[0]), DLLM_LS_OUT_64, "={v74}"(mx[0]),
-                     "={v75}"(mx[1]), [grow] "=s"(grow)
-                   : DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, "{v[128:143]}"(st_b[0]), "{v[144:159]}"(st_b[1]),
-                     "{v[160:175]}"(pb_a), "{v[80:95]}"(addr), [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0),
-                     [voff1] "n"(VOFF1)
-                   : "memory", DLLM_DENSE_SCRATCH);
-  }
+#define DLLM_STEP_OUT(st0, st1, pb) DLLM_ACC_OUT, st0, st1, pb, "={v[192:207]}"(kop[0]), DLLM_LS_OUT_64,             \
+      "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
+#define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones),            \
+      "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr), [zs] "s"(zs),                  \
+      [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
+#define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
+      [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
+#define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1])
+  DLLM_STEP_FUNCTION(64, 2)
+#undef DLLM_STEP_OUT
+#undef DLLM_STEP_IN
+#undef DLLM_STEP_LOADS
+#undef DLLM_STEP_LOADS_SPLIT
   __device__ __forceinline__ void tail(i32x16 ad) {
     asm volatile(DLLM_DENSE_TAIL_64
                  : DLLM_ACC_OUT, DLLM_LS_OUT_64
@@ -256,7 +280,8 @@ __device__ __forceinline__ void for_each_round(F& f, std::integer_sequence<int, 
 }
 
 // which: 1 = only sequences flagged dense in seq_mode; 2 = every sequence
-template <int D>
+// KS: wave groups that share the keys (1 or 2; see launch_attend_dense_bf16 for which calls take which)
+template <int D, int KS>
 __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv, const uint8_t* __restrict__ seq_mode,
@@ -271,11 +296,18 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   constexpr int NLD = kDenseK * CH / NTHREADS;   // 16-byte loads per lane, tile and tensor
   constexpr int NT = D / 16;
   constexpr int NDB = D / 32;
-  constexpr int ROUND = 2 * kDenseRing;          // steps in one turn of the rings
+  constexpr int SPT = 2 / KS;                    // steps a wave takes per tile
+  constexpr int ROUND = SPT * kDenseRing;        // steps in one turn of the rings
+  constexpr int AHEAD_K = KS == 1 ? 2 : 4;       // a tile's first step requests the K rows of the tile this far ahead,
+  constexpr int AHEAD_V = 2;                     // and the V rows of this one
+  // a ring turn that starts with fewer steps than this left (or the step after it) reaches the last tile
+  constexpr int NEAR_END = KS == 1 ? 2 * ROUND : 2 * ROUND + 2;
+  constexpr int kDenseRows = dense_rows(KS);
   static_assert(NLD >= 1 && kDenseK * CH % NTHREADS == 0, "tile does not split evenly over the threads");
   static_assert(kDenseRing * TILEB <= 65536, "ring offsets must fit the 16-bit LDS offset field");
 
-  __shared__ __attribute__((aligned(16))) char smem[2 * kDenseRing * TILEB];   // K ring, V ring
+  // K ring, V ring, and 64 rows more: the queries pass through LDS too (see below), one slot per wave that has its own
+  __shared__ __attribute__((aligned(16))) char smem[(2 * kDenseRing + 1) * TILEB];
 
   // Which query tile of which (sequence, head) this workgroup takes.
   //
@@ -375,6 +407,9 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   const int g = h / s.group;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int col = lane & 31, hf = lane >> 5;
+  // the query blocks this wave takes, and which half of every tile's keys (0 when all waves take both)
+  const int qwave = KS == 1 ? wave : wave & 1;
+  const int part = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave >> 1);
 #ifdef DLLM_DENSE_STAMPS
   // timing experiments only: every workgroup leaves shader-clock counts in its own first output row
   // (and stores no outputs): [0] entry, [1] loop start, [2] loop end, [3] end, [4..11] cycles spent in
@@ -429,11 +464,11 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #pragma unroll
     for (int i = 0; i < 16; ++i) w.addr[i] = 0;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) w.addr[t] = kaddr.off(t);
+    for (int t = 0; t < NT; ++t) w.addr[t] = kaddr.off(t) + part * 32 * ROWB;
 #pragma unroll
     for (int rd = 0; rd < 2; ++rd)
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) w.addr[8 + NDB * rd + db] = VBASE + vaddr.off(rd, db);
+      for (int db = 0; db < NDB; ++db) w.addr[8 + NDB * rd + db] = VBASE + vaddr.off(rd, db) + part * 32 * ROWB;
   }
   // Global side of the tile loads: this lane's chunk f = i * NTHREADS + tid of a tile lands at LDS
   // byte 16 * f, i.e. row f / CH, chunk slot f % CH, and must hold chunk (slot ^ swizzle(row)) of
@@ -478,13 +513,41 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #define DLLM_IC(x) std::integral_constant<int, (x)> {}
 
   // the first tiles are requested before anything else, so their latency overlaps the Q loads
-  const int rem = L % 32;
-  const int nsteps = L / 32 + (rem ? 1 : 0);
+  const int nsteps = KS == 1 ? (L + 31) / 32 : ntiles;
+  // valid keys of this wave's last step: 32, or fewer when the sequence ends inside it (none at all is possible for
+  // the second half of a tile)
+  const int last_valid = KS == 1 ? L - 32 * (nsteps - 1) : max(0, min(32, L - kDenseK * (ntiles - 1) - 32 * part));
+  // ... K rows of the first scores, then the queries, then the rest
   load_tile(kbase, 0, DLLM_IC(0));
-  load_tile(vbase, 0, DLLM_IC(VBASE));
-  if (ntiles > 1) {
-    load_tile(kbase, 1, DLLM_IC(TILEB));
-    load_tile(vbase, 1, DLLM_IC(VBASE + TILEB));
+  if constexpr (KS == 2)
+    if (ntiles > 1) load_tile(kbase, 1, DLLM_IC(TILEB));
+  // The wave's 64 query rows go through LDS, into ring slots that no tile needs yet and the slot behind the rings:
+  // read straight into the operand layout, an instruction touches 32 rows of 32 bytes each, and the sixteen of them took
+  // 3200 to 5200 cycles to issue.  Rows past the last query repeat it (their columns are never stored).
+  const int qslot = KS == 1 ? (wave < 2 ? 2 + wave : wave == 2 ? kDenseRing + 2 : 2 * kDenseRing)
+                            : (qwave == 0 ? kDenseRing + 2 : 2 * kDenseRing);
+  static_assert(kDenseQB * 32 == kDenseK, "a wave's queries fill one slot");
+  constexpr int NQLD = CH / KS;   // loads of 1 KB: with KS = 2 each wave of a pair that shares the queries brings half
+  {
+    const uint32_t stage = __builtin_amdgcn_readfirstlane(lds_addr(smem) + qslot * TILEB + part * NQLD * 1024);
+    const uint16_t* qh = q + int64_t(q0) * s.q_tok + int64_t(h) * s.q_head;
+    auto round = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      const int f = (part * NQLD + i) * 64 + lane, r = f / CH;
+      const int qi = min(qbase + qwave * 64 + r, nq - 1);
+      load16_to_lds<i * 1024>(qh + int64_t(qi) * s.q_tok + (((f % CH) ^ tile_swz<D>(r)) << 3), stage);
+    };
+    for_each_round(round, std::make_integer_sequence<int, NQLD>{});
+  }
+  if constexpr (KS == 1) {
+    load_tile(vbase, 0, DLLM_IC(VBASE));
+    if (ntiles > 1) {
+      load_tile(kbase, 1, DLLM_IC(TILEB));
+      load_tile(vbase, 1, DLLM_IC(VBASE + TILEB));
+    }
+  } else {
+    if (ntiles > 2) load_tile(kbase, 2, DLLM_IC(2 * TILEB));
+    load_tile(vbase, 0, DLLM_IC(VBASE));
   }
 #ifdef DLLM_DENSE_FILL_RING   // timing experiments only: all four ring slots filled once (tiles 0..3)
   if (ntiles > 3) {
@@ -494,30 +557,16 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     load_tile(vbase, 3, DLLM_IC(VBASE + 3 * TILEB));
   }
 #endif
-  // Iteration 0 multiplies an all-zero P with the second half of ring slot 3 of V (the step "before
-  // the first"): clear it, so that no stale NaN pattern meets the zeros.  Tile 3 lands there later.
+  // Iteration 0 multiplies an all-zero P with the rows of ring slot 3 of V that the step "before the first" would
+  // have used (the second half of the slot, or both halves when the keys are split): clear them, so that no stale
+  // NaN pattern meets the zeros.  Tile 3 lands there later.
   {
-    constexpr int kHalf = 32 * ROWB;
-    for (int e = tid * 16; e < kHalf; e += NTHREADS * 16)
-      *reinterpret_cast<v4u*>(smem + VBASE + 3 * TILEB + kHalf + e) = v4u{0u, 0u, 0u, 0u};
+    constexpr int kFrom = KS == 1 ? 32 * ROWB : 0;
+    for (int e = kFrom + tid * 16; e < TILEB; e += NTHREADS * 16)
+      *reinterpret_cast<v4u*>(smem + VBASE + 3 * TILEB + e) = v4u{0u, 0u, 0u, 0u};
   }
 
-  // Q^T operands: lane (col = query, hf) holds Q[query][16t + 8hf .. +8) for every step t, as given
   const float zscale = s.scale * kLog2e;   // > 0; scores * zscale are base-2 logits
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    const int qi = qbase + (wave * NQB + qb) * 32 + col;
-    const uint16_t* qp = q + int64_t(q0 + qi) * s.q_tok + int64_t(h) * s.q_head;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      v4u x = v4u{0u, 0u, 0u, 0u};
-      if (qi < nq) x = *reinterpret_cast<const v4u*>(qp + 16 * t + 8 * hf);
-      w.q_set(qb, t, 0, __uint_as_float(x.x));
-      w.q_set(qb, t, 1, __uint_as_float(x.y));
-      w.q_set(qb, t, 2, __uint_as_float(x.z));
-      w.q_set(qb, t, 3, __uint_as_float(x.w));
-    }
-  }
   // per query (lane pair l, l ^ 32): -m * z for the running maximum m of the raw scores (w.nmz), the factor
   // the accumulators (outputs and row sums) still have to take, and the accumulators
   float palpha[NQB];
@@ -565,28 +614,60 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   // the last tile the last one is requested again, into a ring slot nobody reads any more.
   const int64_t tile_bytes = int64_t(kDenseK) * pitch;
   const bool last_whole = ntiles * kDenseK == L;
-  const int load_idx = min(2, ntiles - 1);   // tile the first tile boundary requests
   DenseTileLoad<NLD> tl;
-  tl.k = kbase + load_idx * tile_bytes;
-  tl.v = vbase + load_idx * tile_bytes;
   tl.wave_lds = wave_lds;
+  int64_t advance_k, advance_v;   // what the pointers move by after a tile's first step; 0 once they reached the last tile
+  auto aim_loads = [&](int tile) __attribute__((always_inline)) {   // for the requests of `tile`'s first step
+    const int tk = min(tile + AHEAD_K, ntiles - 1), tv = min(tile + AHEAD_V, ntiles - 1);
+    advance_k = tk < ntiles - 1 ? tile_bytes : 0;
+    advance_v = tv < ntiles - 1 ? tile_bytes : 0;
+    tl.k = kbase + tk * tile_bytes;
+    tl.v = vbase + tv * tile_bytes;
 #pragma unroll
-  for (int i = 0; i < NLD; ++i) tl.off[i] = (load_idx == ntiles - 1 && !last_whole) ? ld_off_last[i] : ld_off[i];
+    for (int i = 0; i < NLD; ++i) {
+      tl.off[i] = (tk == ntiles - 1 && !last_whole) ? ld_off_last[i] : ld_off[i];
+      if constexpr (KS == 2) tl.off_v[i] = (tv == ntiles - 1 && !last_whole) ? ld_off_last[i] : ld_off[i];
+    }
+  };
+  aim_loads(0);
 
-  wait_tile_loads();
+  // the first scores need the queries and the K rows requested before them; the loads after those stay in flight (the
+  // first step waits for them, see its text), unless the sequence is so short that some were left out
+  if (ntiles > (KS == 1 ? 1 : 3)) wait_tile_loads_but<(KS == 1 ? 3 : 2) * NLD>();
+  else wait_tile_loads();
   __syncthreads();
+  // Q^T operands: lane (col = query, hf) holds Q[query][16t + 8hf .. +8) for every step t, as given
+  {
+    KAddr<D> qaddr;
+    qaddr.init(lane);
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const v4u x = *reinterpret_cast<const v4u*>(smem + qslot * TILEB + qb * 32 * ROWB + qaddr.off(t));
+        w.q_set(qb, t, 0, __uint_as_float(x.x));
+        w.q_set(qb, t, 1, __uint_as_float(x.y));
+        w.q_set(qb, t, 2, __uint_as_float(x.z));
+        w.q_set(qb, t, 3, __uint_as_float(x.w));
+      }
+  }
 
   // scores of step 0, its maxima outright (they may be negative)
   k_operands(0);
   w.score0();
-  if (nsteps == 1 && rem) mask_tail(w.st_a, rem);
+  if (nsteps == 1 && last_valid < 32) mask_tail(w.st_a, last_valid);
+  const bool no_keys = KS == 2 && nsteps == 1 && last_valid == 0;   // this wave pair's half of the only tile is empty
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) w.nmz[qb] = -(max_across_halves(lane_max(w.st_a[qb])) * zscale);
+  for (int qb = 0; qb < NQB; ++qb) w.nmz[qb] = no_keys ? 0.0f : -(max_across_halves(lane_max(w.st_a[qb])) * zscale);
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
     for (int i = 0; i < 16; ++i) w.st_b[qb][i] = 0.0f;
-  k_operands(32 * ROWB);   // step 1 (stale LDS if there is none; then unused)
+  if constexpr (KS == 2) {   // what a step before the first would have requested, so that every step finds the same in flight
+    if (ntiles > 3) load_tile(kbase, 3, DLLM_IC(3 * TILEB));
+    if (ntiles > 1) load_tile(vbase, 1, DLLM_IC(VBASE + TILEB));
+  }
+  k_operands(KS == 1 ? 32 * ROWB : TILEB);   // step 1 (stale LDS if there is none; then unused)
 
   // Iteration j at position R = j % ROUND of the ring turn, which fixes every LDS offset.  Between two
   // steps the common path is a handful of scalar instructions and one branch; everything else (the end
@@ -600,14 +681,14 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   int j = 0;        // steps done
   int jb = 0;       // steps done at the start of the current ring turn
   uint32_t special = 0;   // (kept wave-uniform in a scalar register)
-  int64_t advance = load_idx < ntiles - 1 ? tile_bytes : 0;   // what the tile pointers move by after a tile's first step; 0 once they reached the last tile
   DLLM_STAMP_LOOP_START();
+  // ring offset of the rows of the step at ring position r
+  constexpr auto step_off = [](int r) constexpr { return (r / SPT) * TILEB + (r % SPT) * 32 * ROWB; };
   // one step at ring position R (the text, with every offset it needs)
 #define DLLM_RUN_STEP(R, grow)                                                                                  \
-  w.template step<(R) % 2 == 0, ((((R) + 2) % ROUND) / 2) * TILEB + (((R) + 2) % 2) * 32 * ROWB,                 \
-                  ((((R) + ROUND - 1) % ROUND) / 2) * TILEB + (((R) + ROUND - 1) % 2) * 32 * ROWB,               \
-                  ((((R) + ROUND - 1) % ROUND) / 2) * TILEB + (((R) + ROUND - 1) % 2) * 32 * ROWB + 16 * ROWB,   \
-                  (((R) / 2 + 2) % kDenseRing) * TILEB, VBASE + (((R) / 2 + 2) % kDenseRing) * TILEB>(zscale, tl, grow)
+  w.template step<(R) % 2 == 0, KS == 2, step_off(((R) + 2) % ROUND), step_off(((R) + ROUND - 1) % ROUND),        \
+                  step_off(((R) + ROUND - 1) % ROUND) + 16 * ROWB, (((R) / SPT + AHEAD_K) % kDenseRing) * TILEB,  \
+                  VBASE + (((R) / SPT + AHEAD_V) % kDenseRing) * TILEB>(zscale, tl, grow)
   // what may need doing after step number j - 1 (at ring position R); true when the sequence is finished
   auto careful = [&](auto rc, uint64_t grow) __attribute__((always_inline)) -> bool {
     constexpr int R = decltype(rc)::value;
@@ -618,20 +699,15 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     }
     if (j >= nsteps) return true;
     // tile requests near the end: the pointers stop at the last tile, whose rows may end early
-    const int next_load = min((j + 1) / 2 + 2, ntiles - 1);   // tile the next boundary requests
-    advance = next_load < ntiles - 1 ? tile_bytes : 0;
-    tl.k = kbase + next_load * tile_bytes;
-    tl.v = vbase + next_load * tile_bytes;
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) tl.off[i] = (next_load == ntiles - 1 && !last_whole) ? ld_off_last[i] : ld_off[i];
-    const bool ragged = rem != 0 && j + 1 == nsteps;
+    aim_loads((j + SPT - 1) / SPT);   // the next boundary is the first step of this tile
+    const bool ragged = last_valid < 32 && j + 1 == nsteps;
     if (ragged || grow != 0) {
       // Mask the ragged last step and raise the running maxima for the scores of step j.  Keys past the
       // end were scored from copies of the last row (the tile loads clamp the row), so they carry that
       // row's score and the lane maxima need no second look after masking.
       if (ragged) {
-        if constexpr (R % 2 == 0) mask_tail(w.st_b, rem);
-        else mask_tail(w.st_a, rem);
+        if constexpr (R % 2 == 0) mask_tail(w.st_b, last_valid);
+        else mask_tail(w.st_a, last_valid);
       }
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
@@ -643,7 +719,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
       }
       pending = true;
     }
-    special = __builtin_amdgcn_readfirstlane((pending || j + 2 * ROUND > nsteps) ? 1u : 0u);
+    special = __builtin_amdgcn_readfirstlane((pending || j + NEAR_END > nsteps) ? 1u : 0u);
     return false;
   };
 #define DLLM_STEP(R)                                         \
@@ -651,9 +727,9 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     uint64_t grow;                                           \
     DLLM_RUN_STEP(R, grow);                                  \
     DLLM_STAMP_STEP(R);                                      \
-    if ((R) % 2 == 0) {                                      \
-      tl.k += advance;                                       \
-      tl.v += advance;                                       \
+    if ((R) % SPT == 0) {                                    \
+      tl.k += advance_k;                                     \
+      tl.v += advance_v;                                     \
     }                                                        \
     if (__builtin_expect((uint32_t(grow) | uint32_t(grow >> 32) | special) != 0, 0)) { \
       j = jb + (R) + 1;                                      \
@@ -661,21 +737,23 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     }                                                        \
   }
   for (;;) {
-    special = __builtin_amdgcn_readfirstlane((pending || jb + 2 * ROUND > nsteps) ? 1u : 0u);
+    special = __builtin_amdgcn_readfirstlane((pending || jb + NEAR_END > nsteps) ? 1u : 0u);
     DLLM_STEP(0)
     DLLM_STEP(1)
     DLLM_STEP(2)
     DLLM_STEP(3)
-    DLLM_STEP(4)
-    DLLM_STEP(5)
-    DLLM_STEP(6)
-    DLLM_STEP(7)
+    if constexpr (ROUND == 8) {
+      DLLM_STEP(4)
+      DLLM_STEP(5)
+      DLLM_STEP(6)
+      DLLM_STEP(7)
+    }
     jb += ROUND;
   }
   // the last step's P V product: its probabilities are in pb_a after an odd number of steps, else in pb_b
   {
     const int last = nsteps - 1;
-    const int voff = ((last >> 1) % kDenseRing) * TILEB + (last & 1) * 32 * ROWB;
+    const int voff = (last / SPT % kDenseRing) * TILEB + (last % SPT) * 32 * ROWB;
     i32x16 ad = w.addr;
 #pragma unroll
     for (int i = 8; i < 16; ++i) ad[i] += voff;
@@ -704,48 +782,137 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #endif
   float lrow[NQB];
   w.row_sums(lrow[0], lrow[1]);   // lanes 0..31: the query's sum; lanes 32..63: row 4 of the block, zero
+  // Writes query block qb: accumulators `a` ([db][16]) over the row sum l.  A lane holds four elements of one row at a
+  // time, so the block goes through LDS (`stage`, the wave's own 32 rows) and out in whole rows.
+  auto store_block = [&](int qb, const float* a, float l, char* stage) __attribute__((always_inline)) {
+    const float inv = 1.0f / l;
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    const int qi = qbase + (wave * NQB + qb) * 32 + col;
-    const float l = sum_across_halves(lrow[qb]);
-    if (qi < nq) {
-      const float inv = 1.0f / l;
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
-      for (int db = 0; db < NDB; ++db) {
-        uint16_t* op = o + (int64_t(q0 + qi) * s.hq + h) * D + db * 32 + 4 * hf;
-#pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          v2u w2;
-          const float* a = accv + 16 * (NDB * qb + db) + 4 * i4;
-          w2.x = cvt_pk_bf16(a[0] * inv, a[1] * inv);
-          w2.y = cvt_pk_bf16(a[2] * inv, a[3] * inv);
-          *reinterpret_cast<v2u*>(op + 8 * i4) = w2;
-        }
+      for (int i4 = 0; i4 < 4; ++i4) {
+        v2u w2;
+        const float* x = a + 16 * db + 4 * i4;
+        w2.x = cvt_pk_bf16(x[0] * inv, x[1] * inv);
+        w2.y = cvt_pk_bf16(x[2] * inv, x[3] * inv);
+        *reinterpret_cast<v2u*>(stage + tile_off<D>(col, 4 * db + i4) + 8 * hf) = w2;
       }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int i = 0; i < 32 * CH / 64; ++i) {
+      const int f = i * 64 + lane, r = f / CH, c = f % CH;
+      const int qi = qbase + (qwave * NQB + qb) * 32 + r;
+      if (qi < nq)
+        *reinterpret_cast<v4u*>(o + (int64_t(q0 + qi) * s.hq + h) * D + c * 8) =
+            *reinterpret_cast<const v4u*>(stage + tile_off<D>(r, c));
     }
+  };
+  wait_tile_loads();   // the requests past the last tile still write to the rings, which are now space for the outputs
+  __syncthreads();
+  if constexpr (KS == 1) {
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) store_block(qb, accv + 16 * NDB * qb, sum_across_halves(lrow[qb]), smem + (NQB * wave + qb) * 32 * ROWB);
+  } else {
+    // Two waves hold (m, l, O) of the same queries over different keys: each finishes the block with its own number
+    // (`part`) and hands the other one over through LDS.
+    static_assert(NQB == 2 && kDenseWaves == 4, "two wave pairs, two blocks each");
+    constexpr int kBlock = NDB * 4 * 64;   // float4s of one block
+    float4* mrg = reinterpret_cast<float4*>(smem);                              // [wave][db][i4][lane]
+    float* ml = reinterpret_cast<float*>(smem + kDenseWaves * kBlock * 16);     // [wave][m: 32 | l: 32]
+    static_assert(kDenseWaves * kBlock * 16 + kDenseWaves * 64 * 4 <= 2 * kDenseRing * TILEB, "merge space");
+    auto hand_over = [&](auto qc) __attribute__((always_inline)) {
+      constexpr int QB = decltype(qc)::value;
+#pragma unroll
+      for (int n = 0; n < NDB * 4; ++n) {
+        const float* x = accv + 16 * NDB * QB + 4 * n;
+        mrg[wave * kBlock + n * 64 + lane] = make_float4(x[0], x[1], x[2], x[3]);
+      }
+      const float l = sum_across_halves(lrow[QB]);
+      if (hf == 0) {
+        ml[wave * 64 + col] = no_keys ? -INFINITY : -w.nmz[QB];
+        ml[wave * 64 + 32 + col] = l;
+      }
+    };
+    auto finish = [&](auto qc) __attribute__((always_inline)) {
+      constexpr int QB = decltype(qc)::value;
+      const int other = wave ^ 2;
+      const float m_mine = no_keys ? -INFINITY : -w.nmz[QB], m_other = ml[other * 64 + col];
+      const float m = fmaxf(m_mine, m_other);   // one of the two has seen a key
+      const float f_mine = __builtin_amdgcn_exp2f(m_mine - m), f_other = __builtin_amdgcn_exp2f(m_other - m);
+      float x[16 * NDB];
+#pragma unroll
+      for (int n = 0; n < NDB * 4; ++n) {
+        const float4 y = mrg[other * kBlock + n * 64 + lane];
+        const float* a = accv + 16 * NDB * QB + 4 * n;
+        x[4 * n + 0] = a[0] * f_mine + y.x * f_other;
+        x[4 * n + 1] = a[1] * f_mine + y.y * f_other;
+        x[4 * n + 2] = a[2] * f_mine + y.z * f_other;
+        x[4 * n + 3] = a[3] * f_mine + y.w * f_other;
+      }
+      // (the space the other wave's block came through is this wave's alone now)
+      store_block(QB, x, sum_across_halves(lrow[QB]) * f_mine + ml[other * 64 + 32 + col] * f_other,
+                  smem + other * kBlock * 16);
+    };
+    if (part == 0) hand_over(DLLM_IC(1)); else hand_over(DLLM_IC(0));
+    __syncthreads();
+    if (part == 0) finish(DLLM_IC(0)); else finish(DLLM_IC(1));
   }
+}
+
+// Whether a call splits every tile's keys between two wave pairs (2) or not (1).  The split form makes twice the
+// workgroups, each half as long, for a call that would leave compute units idle; it costs a sixth more per score (every
+// step requests a tile) and the same start and end per workgroup.  In shader cycles, from the clock at the marks of
+// both forms: 1440 per step and 13000 besides at head_dim 128 (split: 1660), 1070 and 7000 at head_dim 64 (split: 1290); one
+// workgroup runs per compute unit at a time.  Measured (us, whole / split): 32 heads x 128, one sequence of 256 14.6 / 11.3,
+// 512 19.6 / 15.0, 1024 29.7 / 24.6 (half the compute units); 2048 65.6 / 75.4 (all of them); three of 768 53.7 / 57.9 (two
+// rounds against three); five of 300 35.4 / 27.1; 16 heads x 64, one of 1024 20.1 / 14.3, three of 1024 21.8 / 28.7, three of
+// 2048 72.9 / 69.6.
+static int key_splits(const Shape& s, int which) {
+  constexpr double kUnits = 256;   // compute units
+  // the densely attended sequences of a mixed call are not known here: as many as total_q can have of the longest
+  const double n = which == 2 ? s.batch : std::max<int64_t>(1, (int64_t(s.total_q) + s.max_q - 1) / s.max_q);
+  const double longest = which == 2 ? s.max_kv : std::min(s.max_kv, s.max_q);
+  const double mean = which == 2 ? double(s.total_kv) / s.batch : longest;
+  const bool even = mean * 8 >= longest * 7 && double(s.total_q) * 8 >= n * s.max_q * 7;
+  auto cost = [&](int ks) -> double {
+    const double rows = dense_rows(ks), nx = std::ceil(s.max_q / rows);
+    const double step = s.d == 128 ? (ks == 1 ? 1440 : 1660) : (ks == 1 ? 1070 : 1290), fixed = s.d == 128 ? 13000 : 7000;
+    const double per_key = step / (32 * ks), one = longest * per_key + fixed;
+    const double units = s.hq * std::min(nx * n, s.total_q / rows + (even ? n : n / 2)) / kUnits;   // rounds of workgroups
+    if (units <= 1) return one;
+    if (even) return std::ceil(units) * one;   // equal workgroups: whole rounds
+    const double avg = mean * per_key + fixed;
+    return std::max(one, units * avg) + avg / 4;
+  };
+  return cost(2) < cost(1) ? 2 : 1;
 }
 
 hipError_t launch_attend_dense_bf16(const Shape& s, const void* q, const void* k, const void* v,
                                     const int32_t* cu_q, const int32_t* cu_kv, const uint8_t* seq_mode, int which,
                                     void* o, hipStream_t st) {
   if (s.max_q == 0) return hipSuccess;   // no sequence has a query: nothing to write
-  const int64_t nx = (s.max_q + kDenseRows - 1) / kDenseRows;
+#ifdef X_KS
+  const int ks = X_KS;
+#else
+  const int ks = key_splits(s, which);
+#endif
+  const int rows = dense_rows(ks);
+  const int64_t nx = (s.max_q + rows - 1) / rows;
   dim3 grid(unsigned(nx), s.hq, s.batch);
   if (s.batch <= 64) {
     // the workgroups place themselves (see the kernel): as many as the batch can have query tiles, times the heads
-    const int64_t tiles = std::min<int64_t>(int64_t(s.total_q) / kDenseRows + s.batch, nx * s.batch);
+    const int64_t tiles = std::min<int64_t>(int64_t(s.total_q) / rows + s.batch, nx * s.batch);
     if (tiles * s.hq < (int64_t(1) << 31)) grid = dim3(unsigned(tiles * s.hq), 1, 1);
   }
-  const uint16_t *qh = static_cast<const uint16_t*>(q), *kh = static_cast<const uint16_t*>(k),
-                 *vh = static_cast<const uint16_t*>(v);
-  if (s.d == 128)
-    attend_dense_bf16_kernel<128><<<grid, kDenseWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, seq_mode, which,
-                                                                     static_cast<uint16_t*>(o), s DLLM_CHECK_PASS);
-  else
-    attend_dense_bf16_kernel<64><<<grid, kDenseWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, seq_mode, which,
-                                                                    static_cast<uint16_t*>(o), s DLLM_CHECK_PASS);
-  return hipGetLastError();
+  auto launch = [&](auto kernel) -> hipError_t {
+    kernel<<<grid, kDenseWaves * 64, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),
+                                              static_cast<const uint16_t*>(v), cu_q, cu_kv, seq_mode, which,
+                                              static_cast<uint16_t*>(o), s DLLM_CHECK_PASS);
+    return hipGetLastError();
+  };
+  if (ks == 2) return s.d == 128 ? launch(attend_dense_bf16_kernel<128, 2>) : launch(attend_dense_bf16_kernel<64, 2>);
+  return s.d == 128 ? launch(attend_dense_bf16_kernel<128, 1>) : launch(attend_dense_bf16_kernel<64, 1>);
 }
 
 }  // namespace dllm

@@ -151,6 +151,9 @@ __device__ __forceinline__ void load4_to_lds(const void* src, uint32_t lds_wave_
 }
 // Waits until every load16_to_lds / load4_to_lds this wave has issued has written its LDS bytes.
 __device__ __forceinline__ void wait_tile_loads() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// ... all but the last N of this wave's vector memory operations.
+template <int N>
+__device__ __forceinline__ void wait_tile_loads_but() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
 // LDS byte address of a pointer into a __shared__ array
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {

@@ -56,8 +56,10 @@ def ar(base, n=1):
     return f"a{base}" if n == 1 else f"a[{base}:{base + n - 1}]"
 
 
-def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_loads=False):
-    """Instruction list of one step.  with_scores/with_softmax False: the closing P V product only."""
+def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_loads=False, split=False):
+    """Instruction list of one step.  with_scores/with_softmax False: the closing P V product only.  split: the form
+    in which two wave pairs share a tile's keys, so every step is a tile's first and requests K and V rows of
+    different tiles, each from offsets of its own."""
     NT, NDB = D // 16, D // 32
     QR = 16 * 2 * NDB                      # a: q[qb][t][4] after the accumulators
     ROWB = 2 * D
@@ -163,10 +165,11 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
     loads = [[] for _ in range(nslots)]
     if with_loads:
         nld = 64 * (D // 8) // 256
-        seq = [("%[kt]", "%[lk]", i) for i in range(nld)] + [("%[vt]", "%[lv]", i) for i in range(nld)]
-        for n, (base, lds, i) in enumerate(seq):
+        vo = "vo" if split else "lo"
+        seq = [("%[kt]", "%[lk]", "lo", i) for i in range(nld)] + [("%[vt]", "%[lv]", vo, i) for i in range(nld)]
+        for n, (base, lds, off, i) in enumerate(seq):
             loads[2 + 2 * n] = [f"s_add_u32 m0, %[wl], {lds}+{i * 256 * 16}",
-                                f"global_load_lds_dwordx4 %[lo{i}], {base}"]
+                                f"global_load_lds_dwordx4 %[{off}{i}], {base}"]
 
     # ---- emit, with the waits for LDS data: reads return in order, so a consumer waits until no more
     # reads are outstanding than were issued after the one it needs (steady state: the previous step's
@@ -213,8 +216,9 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
         if with_loads and s == 1:
             # Tile boundary: the loads issued a tile ago (the next tile) have landed in every wave, and every
             # wave is done with the tile before last, whose ring slots the loads below refill.  Two MFMAs
-            # are in the pipe while the waves meet.
-            lines += ["s_waitcnt vmcnt(0)", "s_barrier"]
+            # are in the pipe while the waves meet.  (split: a tile lasts one step, so the previous step's loads
+            # stay in flight and those before them have landed.)
+            lines += [f"s_waitcnt vmcnt({len(seq) if split else 0})", "s_barrier"]
         if loads[s] and not NO_LOADS:
             lines.append(loads[s][0])
         for dtext, tag in ds[s]:
@@ -290,11 +294,15 @@ def main():
            "// %[grow] (out, scalar pair: lanes whose newest scores outgrew the running maximum by more than %[lazy]);",
            "// in the _AB text (the first step of a tile) also %[kt], %[vt] (scalar pairs: first K / V row of the tile",
            "// to load), %[lo0..] (per-lane byte offsets of the 16-byte chunks), %[wl] (LDS address of the wave's",
-           "// slice of a load round), %[lk], %[lv] (byte offsets of the K / V ring slots to fill).",
+           "// slice of a load round), %[lk], %[lv] (byte offsets of the K / V ring slots to fill).  The _SPLIT texts are",
+           "// the steps of the form that splits a tile's keys between two wave pairs: both request tiles, the V rows at",
+           "// offsets %[vo0..] of their own.",
            ""]
     for D in (128, 64):
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_AB", gen_step(D, ST_A, ST_B, PB_A, PB_B, with_loads=True)))
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_BA", gen_step(D, ST_B, ST_A, PB_B, PB_A)))
+        out.append(as_macro(f"DLLM_DENSE_STEP_{D}_AB_SPLIT", gen_step(D, ST_A, ST_B, PB_A, PB_B, with_loads=True, split=True)))
+        out.append(as_macro(f"DLLM_DENSE_STEP_{D}_BA_SPLIT", gen_step(D, ST_B, ST_A, PB_B, PB_A, with_loads=True, split=True)))
         out.append(as_macro(f"DLLM_DENSE_TAIL_{D}", gen_step(D, 0, 0, 0, PB_A, False, False)))
         out.append(as_macro(f"DLLM_DENSE_SCORE0_{D}", gen_score0(D)))
         out.append(as_macro(f"DLLM_DENSE_ACC_INIT_{D}", gen_acc_init(D)))

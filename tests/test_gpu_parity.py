@@ -366,6 +366,29 @@ def test_dense_small_and_ragged():
         check_attend(w, np.zeros((4, 0), np.int32), name=f"dense {dtype} D={D}")
 
 
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 2), (32, 8)])
+def test_dense_keys_and_queries_around_tile_edges(Hq, Hkv, D):
+    """Key counts around the 32-key steps and 64-key tiles from one key up to past one turn of the tile rings, query
+    counts around the 128 and 256 rows of a workgroup.  With few heads the call splits each tile's keys between
+    wave pairs (the second half of a tile may then hold no key at all), with many it does not."""
+    edges = [1, 31, 32, 33, 64, 65, 95, 97, 128, 161, 192, 257, 289, 320, 353, 513]
+    for part in range(2):
+        lens = edges[8 * part:8 * part + 8]
+        qlens = [256, 129, 1, 255, 128, 256, 127, 250]
+        w = custom(60 + part, torch.bfloat16, Hq, Hkv, D, lens, qlens, [0] * 8, mode=np.ones(8, np.uint8), salient=0.05)
+        dw = workload.DeviceWorkload(w)
+        dw.o.fill_(float("nan"))
+        dw.dense_refresh()
+        ref = oracle_attend(w, np.zeros((Hq, 0), np.int32))
+        assert np.abs(dw.o.float().cpu().numpy() - ref).max() <= 2e-2
+        check_attend(w, np.zeros((Hq, 0), np.int32), name=f"dense edges Hq={Hq} D={D}")
+    # one sequence alone, each length: the shortest key loops by themselves
+    for L in (1, 32, 33, 64, 65, 129, 193):
+        w = custom(70 + L, torch.bfloat16, Hq, Hkv, D, [L], [5], [0], mode=np.ones(1, np.uint8))
+        check_attend(w, np.zeros((Hq, 0), np.int32), name=f"dense L={L}")
+
+
 def test_dense_large_logits():
     """Half of the K rows scaled by 4: base-2 logits reach +-25 and a few keys carry each query.  The
     dense kernel keeps Q as given and scales the fp32 scores (scaling Q and rounding it to bf16 again
