@@ -163,38 +163,59 @@ dllm_status scratch_of_current_device(void** out) {
 
 namespace dllm {
 
-// How many chunks the kept lists of a call are cut into.  One workgroup takes its rows at no more than about
-// 42 GB/s however many of its gathers are in flight (a compute unit's own limit: 11.3 ns per 512-byte pair of K
-// and V rows, four or eight waves alike), so with fewer lists than compute units long lists are cut until
-// every compute unit has a chunk; what that cannot beat is the card's own rate (7 TB/s in this sum), and it
-// costs a merge launch.  Of the numbers of chunks that fit, the one with the least
-//     max(rows per chunk x 11.3 ns, bytes / 7 TB/s) + (merge: 2.6 us + 0.1 us per chunk)
-// is taken.  Measured with 32 heads x 128, attend calls back to back: one list of 256 rows per head 8.1 us whole,
-// 9.0 in two; 512 rows 11.4 whole, 10.0 in four; 2048 rows 28.2 whole, 15.0 in eight; four sequences of 512 rows
-// 12.2 whole, 14.3 in two, of 276 to 994 rows 17.5 whole, 15.3 in two, of 2048 rows 32.2 whole, 29.2 in two.
+// How the kept lists of a call are shared out over the compute units.  One workgroup takes its rows at no more than
+// about 42 GB/s however many of its gathers are in flight (a compute unit's own limit: 11.3 ns per 512-byte pair of K
+// and V rows, four or eight waves alike), so with fewer lists than compute units a list goes to several workgroups,
+// in one of two ways:
+//   - v_split workgroups each take all K rows and 1 / v_split of head_dim of the V rows and of the output.  K is read
+//     again (within one XCD, whose L2 has it), nothing needs merging: 9.8 ns per kept row in two, 8.3 in four, and
+//     where more than one workgroup shares a compute unit, 0.81 of their sum;
+//   - n chunks of consecutive rows, which a second launch merges: 2.6 us, 0.1 us per chunk and 0.55 us per MB of partial
+//     results, and the card's memory is that much busier (0.4 of the time it would take the rows alone).
+// What neither can beat is the card's own rate (7 TB/s in this sum).  The least of these sums is taken.  Measured with
+// 32 heads x 128, attend calls back to back, us whole or in the best chunks / two parts / four parts: one sequence of
+// 256 kept rows 7.3 / 6.4 / 5.8, 512 9.5 / 9.2 / 8.1, 1024 11.4 / 14.2 / 12.3, 2048 14.4 / 23.8 / 20.8; two of 1024 14.2 / 14.3 /
+// 12.5; four of 256 8.6 / 7.5 / 7.9, of 1024 17.3 / 15.1 / 17.9, of 276 to 994 14.8 / 14.6 / 13.6; eight of 1024 28.7 / 31.8 / 43.0.
 // total_k: rows kept per head over the batch, or -1 for the workspace query, which does not know it and plans for the
-// most chunks any total can ask for.
+// most chunks any total can ask for (a larger total only ever makes fewer chunks the better choice).
 AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k) {
   AttendPlan p{};
   p.chunk_rows = max_k > 0 ? max_k : 1;
   p.n_chunks = 1;
   p.max_k = max_k;
+  p.v_split = 1;
   if (dt == DLLM_BF16 && max_k > 0) {
     constexpr int64_t kUnits = 256;   // compute units
+    constexpr int32_t kMostRows = 2048;   // as long as a wave's list of tiles allows
     const int64_t lists = int64_t(s.batch) * s.hq;
-    const double row_ns = 11.3 * s.d / 128, all_ns = total_k < 0 ? 0.0 : double(total_k) * s.hq * 4 * s.d / 7000.0;
+    const double wide = s.d / 128.0, all_ns = total_k < 0 ? 0.0 : double(total_k) * s.hq * 4 * s.d / 7000.0;
+    const double partial_ns = 0.55e-3 * double(s.total_q) * s.hq * s.d * 4;   // per chunk
     double best = 0.0;
     for (int64_t n = 1; n == 1 || n * lists <= kUnits; ++n) {
       const int64_t rows = ((max_k + n - 1) / n + 127) / 128 * 128;   // multiples of what four waves take per step
-      const double t = std::max(double(rows) * row_ns, all_ns) + (n > 1 ? 2600.0 + 100.0 * double(n) : 0.0);
+      double t = std::max(double(rows) * 11.3 * wide, all_ns);
+      if (n > 1) t += 2600.0 + (100.0 + partial_ns) * double(n) + 0.4 * all_ns;
       if (n == 1 || t < best) {
         best = t;
         p.chunk_rows = int32_t(rows);
       }
       if (rows == 128) break;
     }
-    p.chunk_rows = std::min(p.chunk_rows, 2048);   // as long as a wave's list of tiles allows
+    p.chunk_rows = std::min(p.chunk_rows, kMostRows);
     p.n_chunks = int32_t((int64_t(max_k) + p.chunk_rows - 1) / p.chunk_rows);
+    if (total_k >= 0 && max_k <= kMostRows) {
+      for (int vs = 2; vs * 32 <= s.d && vs * lists <= 2 * kUnits; vs *= 2) {
+        const double row_ns = (vs == 2 ? 9.8 : 8.3) * wide, per_unit = double(vs * lists) / kUnits;
+        double t = std::max(double(max_k) * row_ns, all_ns);
+        if (per_unit > 1.0) t = std::max(t, double(total_k) / s.batch * per_unit * 0.81 * row_ns);
+        if (t < best) {
+          best = t;
+          p.v_split = vs;
+          p.n_chunks = 1;
+          p.chunk_rows = (max_k + 127) / 128 * 128;
+        }
+      }
+    }
   }
   if (p.n_chunks > 1) {
     const size_t slots = size_t(p.n_chunks) * size_t(s.total_q) * size_t(s.hq);

@@ -20,6 +20,8 @@
 // a workgroup of its own; attend_sparse_multi_bf16_kernel, for batches with more lists than compute
 // units and lists of unequal length, runs one eight-wave workgroup per compute unit that walks a
 // length-balanced share of the lists back to back.
+#include <type_traits>
+
 #include "attn_tile.h"
 
 namespace dllm {
@@ -128,14 +130,14 @@ __device__ __forceinline__ SeqInfo sequence_of_slot(const int32_t* __restrict__ 
 }
 
 // One 32-key tile that lies in LDS (K rows in ktile, V rows in vtile, the 32 queries in qtile, all in the
-// swizzled tile layout): S^T = K Q^T, online softmax over the first nvalid keys, O^T += V^T P^T.
-template <int D>
+// swizzled tile layout): S^T = K Q^T, online softmax over the first nvalid keys, O^T += V^T P^T for the NDB blocks
+// of 32 head_dim elements that `vt` starts at.
+template <int D, int NDB = D / 32>
 __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* vtile, const char* qtile,
                                                  const KAddr<D>& ka, const VtAddr<D>& vt, int hf, int nvalid,
-                                                 float zscale, float& m_used, float& lsum, f32x16 (&acc)[D / 32]) {
+                                                 float zscale, float& m_used, float& lsum, f32x16 (&acc)[NDB]) {
   constexpr int ROWB = 2 * D;
   constexpr int NT = D / 16;    // MFMA steps along head_dim
-  constexpr int NDB = D / 32;   // 32-wide blocks of head_dim in the output
   // S^T tile: rows = keys, columns = queries
   f32x16 st;
 #pragma unroll
@@ -205,7 +207,9 @@ __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* 
 }
 
 // Once: K and V rows are read with the non-temporal hint (gathers_once)
-template <int D, bool Once>
+// VS: workgroups per list, each of which takes all of the K rows and 1 / VS of head_dim of the V rows and of the
+// output (see plan_attend); they are VS consecutive values of blockIdx.z, so that they share an XCD's L2.
+template <int D, bool Once, int VS>
 __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ idx,
@@ -217,7 +221,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   constexpr int ROWB = 2 * D;
   constexpr int TILEB = kTile * ROWB;
   constexpr int NLD = kTile * CH / 64;  // 16-byte loads per lane per tile and tensor
-  constexpr int NDB = D / 32;           // 32-wide blocks of head_dim in the output
+  constexpr int NDB = D / 32 / VS;      // 32-wide blocks of head_dim in this workgroup's part of the output
+  constexpr int VCH = CH / VS;          // 16-byte chunks of a V row it takes
+  constexpr int NLV = kTile * VCH / 64;
   constexpr int W = kWaves;
   constexpr int MAXT = kMaxChunkRows / (W * kTile);   // tiles per wave at most
 
@@ -240,7 +246,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     fetch_now(s.kv_tok); fetch_now(s.kv_head); fetch_now(s.total_q); fetch_now(s.scale);
   }
   const int chunk = blockIdx.x, h = blockIdx.y;
-  const SeqInfo si = sequence_of_slot(cu_q, cu_kv, cu_k, s.batch, blockIdx.z, lane, ranked != 0);
+  const int vpart = VS == 1 ? 0 : int(blockIdx.z) % VS;
+  const SeqInfo si = sequence_of_slot(cu_q, cu_kv, cu_k, s.batch, int(blockIdx.z) / VS, lane, ranked != 0);
   const int b = si.b;
   if (seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE) return;
   const int ko0 = si.ko0, kb = si.kb;
@@ -254,8 +261,9 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   const int g = h / s.group;
 
   if (kb == 0) {  // nothing kept: defined as zeros
-    for (int e = threadIdx.x; e < nq * D; e += W * 64)
-      o[(int64_t(q0 + e / D) * s.hq + h) * D + e % D] = 0;
+    if (vpart == 0)
+      for (int e = threadIdx.x; e < nq * D; e += W * 64)
+        o[(int64_t(q0 + e / D) * s.hq + h) * D + e % D] = 0;
     return;
   }
 
@@ -272,7 +280,10 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   ka.init(lane);
   VtAddr<D> vt;
   vt.init(lane);
+#pragma unroll
+  for (int rd = 0; rd < 2; ++rd) vt.base[rd] ^= (vpart * NDB) << 6;   // from this part's first block on
   const uint32_t coff = (lane % CH) * 16;   // this lane's byte offset inside a gathered row
+  const uint32_t voff = (vpart * VCH + lane % VCH) * 16;   // ... and inside a gathered V row
   // Registers are what bounds the number of gathered rows in flight, so per-lane LDS offsets are not
   // kept in registers across the loop: each round derives them again (one XOR each) from three values
   // it first passes through opaque(), which keeps the compiler from hoisting the derived ones.
@@ -318,16 +329,23 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // gather the wave's j-th tile into a register buffer
-    auto fetch = [&](v4u (&kr)[NLD], v4u (&vr)[NLD], int j) {
+    auto fetch = [&](v4u (&kr)[NLD], v4u (&vr)[NLV], int j) {
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
         const uint32_t off = __umul24(uint32_t(my_rows[j * kTile + (i * 64 + lane) / CH]), pitch) + coff;
         kr[i] = load_once<Once>(kbase + off);
-        vr[i] = load_once<Once>(vbase + off);
+        if constexpr (VS == 1) vr[i] = load_once<Once>(vbase + off);
+      }
+      if constexpr (VS > 1) {
+#pragma unroll
+        for (int i = 0; i < NLV; ++i) {
+          const uint32_t off = __umul24(uint32_t(my_rows[j * kTile + (i * 64 + lane) / VCH]), pitch) + voff;
+          vr[i] = load_once<Once>(vbase + off);
+        }
       }
     };
     // one tile: registers -> LDS, refill the registers with the tile after next, then the math
-    auto round = [&](v4u (&kr)[NLD], v4u (&vr)[NLD], int j, int tile) {
+    auto round = [&](v4u (&kr)[NLD], v4u (&vr)[NLV], int j, int tile) {
       KAddr<D> kar;
       kar.base = opaque(ka.base);
       VtAddr<D> vtr;
@@ -338,18 +356,25 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
       for (int i = 0; i < NLD; ++i) {
         const int f = i * 64 + lane_o, woff = tile_off<D>(f / CH, f % CH);
         *reinterpret_cast<v4u*>(ktile + woff) = kr[i];
-        *reinterpret_cast<v4u*>(vtile + woff) = vr[i];
+        if constexpr (VS == 1) *reinterpret_cast<v4u*>(vtile + woff) = vr[i];
+      }
+      if constexpr (VS > 1) {
+#pragma unroll
+        for (int i = 0; i < NLV; ++i) {
+          const int f = i * 64 + lane_o;
+          *reinterpret_cast<v4u*>(vtile + tile_off<D>(f / VCH, vpart * VCH + f % VCH)) = vr[i];
+        }
       }
       if (tile + W < ntiles) fetch(kr, vr, j + 1);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 
-      sparse_tile_math<D>(ktile, vtile, qtile, kar, vtr, hf, c1 - (c0 + tile * kTile), zscale, m_used, lsum, acc);
+      sparse_tile_math<D, NDB>(ktile, vtile, qtile, kar, vtr, hf, c1 - (c0 + tile * kTile), zscale, m_used, lsum, acc);
       __builtin_amdgcn_wave_barrier();
     };
 
-    v4u kra[NLD], vra[NLD];
+    v4u kra[NLD], vra[NLV];
     int tile = wave;
     if (tile < ntiles) fetch(kra, vra, 0);
 #pragma unroll
@@ -371,12 +396,14 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
       sm_ml[wave * kMlStride + col] = m_used;
       sm_ml[wave * kMlStride + 32 + col] = l;
     }
-    float4* mrg = reinterpret_cast<float4*>(&lds[0][0]);         // [wave][db][quad][lane], 16 bytes per lane
+    float4* mrg = reinterpret_cast<float4*>(&lds[0][0]);         // [wave: its own tile buffers][db][quad][lane], 16 bytes per lane
+    constexpr int kMrgWave = 2 * TILEB / 16;
+    static_assert(NDB * 4 * 64 <= kMrgWave, "a wave's accumulators fit its tile buffers");
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
 #pragma unroll
       for (int i4 = 0; i4 < 4; ++i4)
-        mrg[((wave * NDB + db) * 4 + i4) * 64 + lane] =
+        mrg[wave * kMrgWave + (db * 4 + i4) * 64 + lane] =
             make_float4(acc[db][4 * i4 + 0], acc[db][4 * i4 + 1], acc[db][4 * i4 + 2], acc[db][4 * i4 + 3]);
     __syncthreads();
     {
@@ -400,7 +427,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
         float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
         for (int w = 0; w < W; ++w) {
-          const float4 x = mrg[((w * NDB + db) * 4 + i4_0 + n) * 64 + lane];
+          const float4 x = mrg[w * kMrgWave + (db * 4 + i4_0 + n) * 64 + lane];
           a.x += x.x * f[w]; a.y += x.y * f[w]; a.z += x.z * f[w]; a.w += x.w * f[w];
         }
         outv[4 * n + 0] = a.x; outv[4 * n + 1] = a.y; outv[4 * n + 2] = a.z; outv[4 * n + 3] = a.w;
@@ -409,7 +436,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
       if (qi < nq) {
         if (nch_b == 1) {
           const float inv = 1.0f / l_all;
-          uint16_t* op = o + (int64_t(q0 + qi) * s.hq + h) * D + db * 32 + 4 * hf;
+          uint16_t* op = o + (int64_t(q0 + qi) * s.hq + h) * D + (vpart * NDB + db) * 32 + 4 * hf;
 #pragma unroll
           for (int n = 0; n < NQ4; ++n) {
             v2u w2;
@@ -419,7 +446,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
           }
         } else {
           const int64_t slot = (int64_t(chunk) * s.total_q + (q0 + qi)) * s.hq + h;
-          float* pp = po + slot * D + db * 32 + 4 * hf;
+          float* pp = po + slot * D + (vpart * NDB + db) * 32 + 4 * hf;   // (VS is 1 here)
 #pragma unroll
           for (int n = 0; n < NQ4; ++n)
             *reinterpret_cast<float4*>(pp + 8 * (i4_0 + n)) =
@@ -793,20 +820,24 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
       else launch(attend_sparse_multi_bf16_kernel<64, false>);
     }
   } else {
-    dim3 grid(p.n_chunks, s.hq, s.batch);
-    // the start order only matters when the workgroups cannot all be resident at once (two per compute unit)
-    const int ranked = n_items > 512 ? 1 : 0;
+    dim3 grid(p.n_chunks, s.hq, s.batch * p.v_split);
+    // the start order only matters when the workgroups cannot all be resident at once (two per compute unit), or
+    // when the parts of lists of unequal length share compute units: long ones then get short ones beside them
+    const int ranked = n_items > 512 || (p.v_split > 1 && n_items * p.v_split > n_cu) ? 1 : 0;
     auto launch = [&](auto kernel) {
       kernel<<<grid, kWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, idx, cu_k, total_k, seq_mode, oh, po, pm, pl,
                                            p.chunk_rows, ranked, s DLLM_CHECK_PASS);
     };
-    if (gathers_once(s, 2)) {
-      if (s.d == 128) launch(attend_sparse_bf16_kernel<128, true>);
-      else launch(attend_sparse_bf16_kernel<64, true>);
-    } else {
-      if (s.d == 128) launch(attend_sparse_bf16_kernel<128, false>);
-      else launch(attend_sparse_bf16_kernel<64, false>);
-    }
+    auto launch_split = [&](auto vs) {
+      constexpr int VS = decltype(vs)::value;
+      if (s.d == 128) launch(attend_sparse_bf16_kernel<128, false, VS>);
+      else if constexpr (VS <= 2) launch(attend_sparse_bf16_kernel<64, false, VS>);
+    };
+    if (p.v_split == 4) launch_split(std::integral_constant<int, 4>{});
+    else if (p.v_split == 2) launch_split(std::integral_constant<int, 2>{});
+    else if (!gathers_once(s, 2)) launch_split(std::integral_constant<int, 1>{});
+    else if (s.d == 128) launch(attend_sparse_bf16_kernel<128, true, 1>);
+    else launch(attend_sparse_bf16_kernel<64, true, 1>);
   }
   e = hipGetLastError();
   if (e != hipSuccess || p.n_chunks <= 1) return e;

@@ -59,6 +59,7 @@ struct AttendPlan {
   int32_t chunk_rows;  // kept rows one workgroup walks
   int32_t n_chunks;    // upper bound on chunks per (sequence, head)
   int32_t max_k;       // the caller's bound on kept rows per (sequence, head)
+  int32_t v_split;     // workgroups per list that share out head_dim of V and O (1, 2 or 4; n_chunks is 1 if more than one)
   size_t off_po, off_pm, off_pl, bytes;
 };
 AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k);

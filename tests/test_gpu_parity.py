@@ -871,3 +871,17 @@ def test_attend_kept_lists_cut_over_workgroups(hq, hkv, D, keep):
     dw = workload.DeviceWorkload(w)
     assert hcsa.dllm_hcsa_attend_workspace(dw.batch, dw.max_k) > 0
     check_attend(w, oracle_select(w), dw=dw)
+
+
+@pytest.mark.parametrize("hq,hkv,D,keep", [(32, 32, 128, [256]), (32, 8, 128, [1, 300, 0]), (32, 32, 128, [256, 33, 200, 31]),
+                                            (6, 2, 128, [65, 64, 0, 1]), (8, 4, 64, [500, 127]), (32, 32, 128, [994, 276, 600, 700])])
+def test_attend_lists_shared_out_by_head_dim(hq, hkv, D, keep):
+    """Short lists and few of them: several workgroups per list, each with all K rows and its part of head_dim of V and
+    of the output (two or four at head_dim 128, two at 64, one or two per compute unit); lists around the 32-row
+    tiles, empty ones, a second query tile, a densely attended sequence in the batch, packed and gathered."""
+    n = len(keep)
+    lens, qlens = [max(k, 1) + 40 for k in keep] + [70], [32, 45, 7, 32][:n] + [70]
+    mode = np.array([0] * n + [1], np.uint8)
+    w = custom(19, torch.bfloat16, hq, hkv, D, lens, qlens, keep + [0], mode=mode, salient=0.05)
+    check_attend(w, oracle_select(w))
+    check_pack_and_packed_attend(custom(19, torch.bfloat16, hq, hkv, D, lens[:n], qlens[:n], keep, salient=0.05), f"parts {keep}")
