@@ -208,7 +208,8 @@ __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* 
 
 // Once: K and V rows are read with the non-temporal hint (gathers_once)
 // VS: workgroups per list, each of which takes all of the K rows and 1 / VS of head_dim of the V rows and of the
-// output (see plan_attend); they are VS consecutive values of blockIdx.z, so that they share an XCD's L2.
+// output (see plan_attend); they are VS consecutive values of blockIdx.z, so with a multiple of eight heads
+// they run on one XCD and share its L2.
 template <int D, bool Once, int VS>
 __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
