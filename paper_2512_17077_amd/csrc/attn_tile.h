@@ -29,13 +29,14 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // The running maximum m of an online softmax is raised lazily: only when a base-2 logit exceeds it by more
-// than this, so probabilities may reach 2^32 instead of 1 in between.  Numerator and denominator carry the
-// same factor and are floating-point, so nothing is lost to rounding (keys more than 2^126 below m vanish
-// either way), and 2^32 times the longest sequence times |V| up to 2^80 stays finite.  Raising m costs a pass
-// over all accumulators: with a step of 2^8, heads with salient keys (5 % of the K rows four times as long)
-// raised it in so many 32-key steps that the dense part of a mixed burst (32 heads, 8 sequences of 2048) took
-// 623 us instead of 520.
-constexpr float kLazyGrowth = 32.0f;
+// than this, so probabilities may reach 2^8 instead of 1 in between.  Numerator and denominator carry the
+// same factor and are floating-point, so nothing is lost to rounding; what it takes is range: sums of |V| times 2^8
+// must stay finite.
+constexpr float kLazyGrowth = 8.0f;
+// The same for dense sequences, which have many steps per wave and pay for a raise with a pass over all
+// accumulators: heads with salient keys (5 % of the K rows four times as long) raise m in so many 32-key steps with a
+// step of 2^8 that the dense part of a mixed burst (32 heads, 8 sequences of 2048) takes 623 us instead of 520.
+constexpr float kLazyGrowthDense = 32.0f;
 
 // XOR applied to the chunk index of `row`; depends on row & 15 only
 template <int D>

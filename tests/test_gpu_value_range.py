@@ -1,0 +1,56 @@
+"""Values near the ends of the number range, where the online softmax keeps a running maximum that lags behind: outputs
+are means of V rows, so V scaled by a power of two must give outputs scaled by it, and keys whose score overflows to
+minus infinity must simply carry no weight."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2512_17077_amd import hcsa, synth, workload
+
+pytestmark = pytest.mark.gpu
+
+TOL = {torch.float32: 1e-5, torch.bfloat16: 2e-2}
+
+
+def growing_workload(dtype, hq, hkv, D, lens, qlens, keep, dense, growth=31.0):
+    """One key near the middle and one near the end of every sequence stand 2^growth above all others, whose base-2 logits
+    stay near zero: a maximum raised late leaves probabilities of 2^growth in the sums."""
+    w = synth.make_workload("range", synth.SEED_BASE + 2000, dtype, hq, hkv, D, lens, qlens, keep,
+                            seq_mode=np.full(len(lens), 1 if dense else 0, np.uint8))
+    w.q.fill_(1.0)
+    k = 0.01 * w.k.float()
+    for b in range(len(lens)):
+        lo, hi = int(w.cu_kv[b]), int(w.cu_kv[b + 1])
+        for pos in (lo + (hi - lo) // 2, hi - 1 - (hi - lo) // 20):
+            k[pos] = growth / (w.softmax_scale * math.log2(math.e) * D)
+    w.k.copy_(k.to(dtype))
+    return w
+
+
+def attend_both_ways(w, log2_scale):
+    """Outputs of the library on V * 2^log2_scale, scaled back, and the oracle's on V (the scaling is exact in both types)."""
+    idx = oracle.select(synth.to_bits(w.q), synth.to_bits(w.k), w.cu_q, w.cu_kv, w.cu_k)
+    ref = oracle.attend(synth.to_bits(w.q), synth.to_bits(w.k), synth.to_bits(w.v), w.cu_q, w.cu_kv, idx, w.cu_k, w.seq_mode,
+                        w.softmax_scale)
+    w.v.copy_((w.v.double() * 2.0 ** log2_scale).to(w.v.dtype))
+    dw = workload.DeviceWorkload(w)
+    dw.attend(torch.from_numpy(np.ascontiguousarray(idx)).to(dw.device))
+    return dw.o.double().cpu().numpy() * 2.0 ** -log2_scale, ref
+
+
+def check_large_values(w, log2_scale):
+    got, ref = attend_both_ways(w, log2_scale)
+    assert np.isfinite(got).all(), "an accumulator overflowed"
+    assert np.abs(got - ref).max() <= TOL[w.dtype]
+
+
+# bf16 inputs: probabilities reach 2^8, so sums over 2^9 keys of |V| up to 2^2 * 2^100 stay below 2^120
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("hq,hkv,lens,keep", [(4, 2, [400], [300]), (32, 8, [2900], [2600]),
+                                              (32, 8, [40 + 30 * b for b in range(16)], [30 + 25 * b for b in range(16)])])
+def test_large_values_in_kept_lists(hq, hkv, lens, keep, D):
+    """One workgroup per list, lists cut into chunks, and many lists per workgroup."""
+    check_large_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, [32] * len(lens), keep, dense=False), 100)
