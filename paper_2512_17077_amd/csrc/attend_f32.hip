@@ -194,12 +194,14 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void attend_f32_kernel(
           for (int i = 0; i < 4; ++i)
             if (4 * j + i >= nvalid) st[nb][i] = -INFINITY;
       }
+      // The maximum is exact, so probabilities never exceed 1 and sums stay below the number of keys times the largest
+      // |V|.  Raising it only past 2^32 overflows from |V| of about 2^80 on and gains 0.6 us on the batch above.
       float tmax[NQ];
       bool grown = false;
 #pragma unroll
       for (int nb = 0; nb < NQ; ++nb) {
         tmax[nb] = quad_max(fmaxf(fmaxf(st[nb][0], st[nb][1]), fmaxf(st[nb][2], st[nb][3])));
-        grown = grown || (tmax[nb] - m_used[nb]) * zscale > kLazyGrowth;
+        grown = grown || tmax[nb] > m_used[nb];
       }
       if (__builtin_amdgcn_ballot_w64(grown) != 0) {
 #pragma unroll

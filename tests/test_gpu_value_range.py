@@ -54,3 +54,13 @@ def check_large_values(w, log2_scale):
 def test_large_values_in_kept_lists(hq, hkv, lens, keep, D):
     """One workgroup per list, lists cut into chunks, and many lists per workgroup."""
     check_large_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, [32] * len(lens), keep, dense=False), 100)
+
+
+# fp32 inputs: the maximum is exact, probabilities stay at or below 1
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("hq,hkv,lens,keep", [(4, 2, [400], [300]), (8, 4, [900, 500, 700], [800, 300, 650])])
+@pytest.mark.parametrize("dense", [False, True])
+def test_large_values_in_fp32(hq, hkv, lens, keep, D, dense):
+    keep = [0] * len(lens) if dense else keep
+    qlens = lens if dense else [32] * len(lens)
+    check_large_values(growing_workload(torch.float32, hq, hkv, D, lens, qlens, keep, dense), 112)
