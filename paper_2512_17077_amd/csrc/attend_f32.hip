@@ -19,6 +19,7 @@
 // in one launch, where one wave per query row with vector arithmetic took 630 us in two; 5.5 us instead of 14.6 on
 // one sequence with 4 heads and 64 kept rows.
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -124,11 +125,13 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void attend_f32_kernel(
   };
   const int ntiles = (n + 15) >> 4;
   const float zscale = s.scale * kLog2e;   // > 0: (score - maximum) * zscale is a base-2 logit
+  // The running maximum starts at the lowest finite number, not at minus infinity: a wave may meet a whole tile of keys
+  // whose scores overflowed to minus infinity, and those weigh nothing instead of (-inf) - (-inf).
   float m_used[NQ], lsum[NQ];
   f32x4 acc[NQ][4 * NH];
 #pragma unroll
   for (int nb = 0; nb < NQ; ++nb) {
-    m_used[nb] = -INFINITY;
+    m_used[nb] = -FLT_MAX;
     lsum[nb] = 0.0f;
 #pragma unroll
     for (int db = 0; db < 4 * NH; ++db) acc[nb][db] = f32x4{0, 0, 0, 0};
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void attend_f32_kernel(
 #pragma unroll
         for (int nb = 0; nb < NQ; ++nb) {
           const float m_new = fmaxf(m_used[nb], tmax[nb]);
-          const float alpha = __builtin_amdgcn_exp2f((m_used[nb] - m_new) * zscale);   // first tile: exp2(-inf) = 0
+          const float alpha = __builtin_amdgcn_exp2f((m_used[nb] - m_new) * zscale);   // first tile: 0, or times sums that are 0
           m_used[nb] = m_new;
           lsum[nb] *= alpha;
 #pragma unroll

@@ -64,3 +64,27 @@ def test_large_values_in_fp32(hq, hkv, lens, keep, D, dense):
     keep = [0] * len(lens) if dense else keep
     qlens = lens if dense else [32] * len(lens)
     check_large_values(growing_workload(torch.float32, hq, hkv, D, lens, qlens, keep, dense), 112)
+
+
+def masked_outputs(dtype, hq, hkv, D, L, first, last):
+    """Dense attention of one sequence whose keys first .. last-1 score minus infinity (their products with the queries
+    overflow, all inputs are finite), and the same over the other keys in fp64."""
+    w = synth.make_workload("masked", synth.SEED_BASE + 2100, dtype, hq, hkv, D, [L], [40], [0], seq_mode=np.ones(1, np.uint8))
+    w.q.copy_((2.0 ** 64 * (1.0 + w.q.float().abs())).to(dtype))
+    w.k.copy_((2.0 ** -64 * w.k.float()).to(dtype))
+    w.k[first:last] = -2.0 ** 70
+    rest = [i for i in range(L) if not first <= i < last]
+    q = w.q.double().transpose(0, 1)
+    k, v = (x.double()[rest].repeat_interleave(hq // hkv, 1).transpose(0, 1) for x in (w.k, w.v))
+    ref = torch.matmul(torch.softmax(torch.matmul(q, k.transpose(1, 2).contiguous()) * w.softmax_scale, -1), v)
+    dw = workload.DeviceWorkload(w)
+    dw.dense_refresh()
+    return dw.o.double().cpu(), ref.transpose(0, 1)
+
+
+@pytest.mark.parametrize("first,last", [(0, 16), (16, 32), (0, 32), (32, 64), (64, 96), (0, 64), (96, 200)])
+@pytest.mark.parametrize("dtype,hq,hkv,D", [(torch.float32, 4, 2, 64), (torch.float32, 4, 2, 128)])
+def test_keys_whose_score_overflows_to_minus_infinity(dtype, hq, hkv, D, first, last):
+    got, ref = masked_outputs(dtype, hq, hkv, D, 200, first, last)
+    assert torch.isfinite(got).all()
+    assert (got - ref).abs().max() <= TOL[dtype]
