@@ -30,8 +30,8 @@
 //     logits around 20): scores leave the matrix core raw, and one fused multiply-add per score,
 //     s * z - m * z with z = softmax_scale * log2(e), makes them base-2 logits relative to the running
 //     maximum m.
-//   - m is raised lazily (only when a score exceeds it by more than 2^32, see kLazyGrowthDense: probabilities may
-//     exceed 1 until then) behind one uniform branch per iteration.  When it is raised after iteration j, the
+//   - m is set 2^24 above the maximum and raised lazily (only when a score exceeds it by more than 2^8, see
+//     kDenseHeadroom) behind one uniform branch per iteration.  When it is raised after iteration j, the
 //     row sums are rescaled at once; the output accumulators, which still have to take P(j) V(j) at the
 //     old scale during iteration j+1, are rescaled one iteration later.
 //   - The loop is unrolled over one turn of the rings (eight steps), so every LDS address is a register
@@ -155,7 +155,7 @@ struct DenseState<128> {
       DLLM_LS_OUT_128, "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
 #define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"),          \
       [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr),             \
-      [zs] "s"(zs), [lazy] "s"(kLazyGrowthDense), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
+      [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
 #define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
       [lo2] "v"(tl.off[2]), [lo3] "v"(tl.off[3]), [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
 #define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1]),                     \
@@ -228,7 +228,7 @@ struct DenseState<64> {
       "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
 #define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones),            \
       "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr), [zs] "s"(zs),                  \
-      [lazy] "s"(kLazyGrowthDense), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
+      [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
 #define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
       [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
 #define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1])
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   if (nsteps == 1 && last_valid < 32) mask_tail(w.st_a, last_valid);
   const bool no_keys = KS == 2 && nsteps == 1 && last_valid == 0;   // this wave pair's half of the only tile is empty
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) w.nmz[qb] = no_keys ? 0.0f : -(max_across_halves(lane_max(w.st_a[qb])) * zscale);
+  for (int qb = 0; qb < NQB; ++qb) w.nmz[qb] = no_keys ? 0.0f : -(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom);
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #pragma unroll
       for (int qb = 0; qb < NQB; ++qb) {
         const float mz_old = -w.nmz[qb];
-        const float mz_new = fmaxf(mz_old, max_across_halves(w.mx[qb]) * zscale);
+        const float mz_new = fmaxf(mz_old, max_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
         const float alpha = __builtin_amdgcn_exp2f(mz_old - mz_new);
         palpha[qb] = alpha;
         w.nmz[qb] = -mz_new;

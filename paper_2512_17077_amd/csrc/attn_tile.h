@@ -33,10 +33,12 @@ constexpr float kLog2e = 1.4426950408889634f;
 // same factor and are floating-point, so nothing is lost to rounding; what it takes is range: sums of |V| times 2^8
 // must stay finite.
 constexpr float kLazyGrowth = 8.0f;
-// The same for dense sequences, which have many steps per wave and pay for a raise with a pass over all
-// accumulators: heads with salient keys (5 % of the K rows four times as long) raise m in so many 32-key steps with a
-// step of 2^8 that the dense part of a mixed burst (32 heads, 8 sequences of 2048) takes 623 us instead of 520.
-constexpr float kLazyGrowthDense = 32.0f;
+// Dense sequences have many steps per wave and pay for a raise with a pass over all accumulators: heads with salient
+// keys (5 % of the K rows four times as long) raise m in so many 32-key steps with a step of 2^8 that the dense part of
+// a mixed burst (32 heads, 8 sequences of 2048) takes 623 us instead of the 520 of a step of 2^32.  So that the larger
+// step does not cost range at the top, m is set this far above the maximum there: probabilities start at 2^-24 and
+// still end at 2^kLazyGrowth.  (At the bottom 2^-24 |V| has to be representable: the matrix cores keep denormals.)
+constexpr float kDenseHeadroom = 24.0f;
 
 // XOR applied to the chunk index of `row`; depends on row & 15 only
 template <int D>

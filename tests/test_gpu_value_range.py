@@ -41,7 +41,7 @@ def attend_both_ways(w, log2_scale):
     return dw.o.double().cpu().numpy() * 2.0 ** -log2_scale, ref
 
 
-def check_large_values(w, log2_scale):
+def check_values(w, log2_scale):
     got, ref = attend_both_ways(w, log2_scale)
     assert np.isfinite(got).all(), "an accumulator overflowed"
     assert np.abs(got - ref).max() <= TOL[w.dtype]
@@ -53,7 +53,7 @@ def check_large_values(w, log2_scale):
                                               (32, 8, [40 + 30 * b for b in range(16)], [30 + 25 * b for b in range(16)])])
 def test_large_values_in_kept_lists(hq, hkv, lens, keep, D):
     """One workgroup per list, lists cut into chunks, and many lists per workgroup."""
-    check_large_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, [32] * len(lens), keep, dense=False), 100)
+    check_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, [32] * len(lens), keep, dense=False), 100)
 
 
 # fp32 inputs: the maximum is exact, probabilities stay at or below 1
@@ -63,7 +63,17 @@ def test_large_values_in_kept_lists(hq, hkv, lens, keep, D):
 def test_large_values_in_fp32(hq, hkv, lens, keep, D, dense):
     keep = [0] * len(lens) if dense else keep
     qlens = lens if dense else [32] * len(lens)
-    check_large_values(growing_workload(torch.float32, hq, hkv, D, lens, qlens, keep, dense), 112)
+    check_values(growing_workload(torch.float32, hq, hkv, D, lens, qlens, keep, dense), 112)
+
+
+# bf16 dense sequences: split over wave pairs with few heads, whole with many
+@pytest.mark.parametrize("D", [128, 64])
+@pytest.mark.parametrize("hq,hkv,lens", [(4, 2, [400]), (4, 2, [33]), (32, 8, [330] * 8), (32, 8, [700, 450, 290, 530, 801, 333])])
+@pytest.mark.parametrize("growth", [6.0, 31.0])
+@pytest.mark.parametrize("log2_scale", [100, -110])
+def test_large_and_small_values_in_dense_sequences(hq, hkv, lens, D, growth, log2_scale):
+    """(Small: products with probabilities of 2^-24 are below the smallest normal number.)"""
+    check_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, lens, [0] * len(lens), True, growth), log2_scale)
 
 
 def masked_outputs(dtype, hq, hkv, D, L, first, last):
