@@ -37,6 +37,7 @@
 //   - The loop is unrolled over one turn of the rings (eight steps), so every LDS address is a register
 //     fixed before the loop plus an immediate offset.
 #include <algorithm>
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 #include <utility>
@@ -657,8 +658,11 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   w.score0();
   if (nsteps == 1 && last_valid < 32) mask_tail(w.st_a, last_valid);
   const bool no_keys = KS == 2 && nsteps == 1 && last_valid == 0;   // this wave pair's half of the only tile is empty
+  // (no lower than the lowest finite number: keys whose scores overflowed to minus infinity weigh nothing instead of
+  // (-inf) - (-inf), also when they fill the first step)
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) w.nmz[qb] = no_keys ? 0.0f : -(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom);
+  for (int qb = 0; qb < NQB; ++qb)
+    w.nmz[qb] = no_keys ? 0.0f : -fmaxf(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
 #pragma unroll
   for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll

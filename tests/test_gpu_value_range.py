@@ -93,7 +93,8 @@ def masked_outputs(dtype, hq, hkv, D, L, first, last):
 
 
 @pytest.mark.parametrize("first,last", [(0, 16), (16, 32), (0, 32), (32, 64), (64, 96), (0, 64), (96, 200)])
-@pytest.mark.parametrize("dtype,hq,hkv,D", [(torch.float32, 4, 2, 64), (torch.float32, 4, 2, 128)])
+@pytest.mark.parametrize("dtype,hq,hkv,D", [(torch.bfloat16, 4, 2, 128), (torch.bfloat16, 4, 2, 64), (torch.float32, 4, 2, 64),
+                                            (torch.float32, 4, 2, 128)])
 def test_keys_whose_score_overflows_to_minus_infinity(dtype, hq, hkv, D, first, last):
     got, ref = masked_outputs(dtype, hq, hkv, D, 200, first, last)
     assert torch.isfinite(got).all()
