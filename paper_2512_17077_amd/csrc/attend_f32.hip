@@ -119,9 +119,9 @@ __global__ __launch_bounds__(kF32Waves * 64, 2) void attend_f32_kernel(
   const int32_t* __restrict__ rows = (dense || idx == nullptr) ? nullptr : idx + int64_t(h) * total_k + ko0;
   const char* kbase = reinterpret_cast<const char*>(k + int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head + 4 * j);
   const char* vbase = reinterpret_cast<const char*>(v + int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head + 4 * c16);
-  const uint32_t pitch16 = uint32_t(s.kv_tok >> 2);   // token stride in units of 16 bytes (strides are multiples of them)
+  const uint64_t pitch = uint64_t(s.kv_tok) * 4;   // bytes from one token to the next (any number: 64 bits throughout)
   auto row_at = [&](const char* base, int row) -> const f32x4* {
-    return reinterpret_cast<const f32x4*>(base + ((uint64_t(uint32_t(row)) * pitch16) << 4));
+    return reinterpret_cast<const f32x4*>(base + uint64_t(uint32_t(row)) * pitch);
   };
   const int ntiles = (n + 15) >> 4;
   const float zscale = s.scale * kLog2e;   // > 0: (score - maximum) * zscale is a base-2 logit

@@ -862,6 +862,28 @@ def test_f32_attend_tile_edges(D, hq, hkv, wide):
     say(f"max abs error {err:.3e}")
 
 
+def test_f32_token_stride_beyond_32_bits():
+    """Two tokens 2^34 elements (64 GiB) apart: row offsets need more than 32 bits of 16-byte units."""
+    step, D = 1 << 34, 64
+    if torch.cuda.mem_get_info()[0] < 70 << 30:
+        pytest.skip("needs 64 GiB of free device memory")
+    try:
+        space = torch.empty(step + 4 * D, dtype=torch.float32, device="cuda")
+        k, v = (torch.as_strided(space, (2, 1, D), (step, 2 * D, 1), offset) for offset in (0, D))
+        gen = torch.Generator(device="cuda").manual_seed(5)
+        for x in (k, v):
+            x.copy_(torch.randn((2, 1, D), generator=gen, device="cuda"))
+        q = torch.randn((3, 1, D), generator=gen, device="cuda")
+        cu_q, cu_kv = (torch.tensor([0, n], dtype=torch.int32, device="cuda") for n in (3, 2))
+        o = torch.empty_like(q)
+        hcsa.dllm_dense_refresh_attend(hcsa.make_batch(q, k, v, cu_q, cu_kv, 3, 2, D ** -0.5), o)
+        p = torch.softmax(q[:, 0].double() @ k[:, 0].double().T.contiguous() * D ** -0.5, -1)
+        assert (o[:, 0].double() - p @ v[:, 0].double()).abs().max() <= TOL[torch.float32]
+    finally:
+        space = k = v = None
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("hq,hkv,D,keep", [(32, 32, 128, [500]), (16, 4, 128, [1000, 130]), (8, 2, 64, [1023, 3, 640]),
                                             (4, 4, 128, [129, 410]), (2, 1, 64, [2047]), (32, 8, 128, [2000, 400, 0])])
 def test_attend_kept_lists_cut_over_workgroups(hq, hkv, D, keep):
