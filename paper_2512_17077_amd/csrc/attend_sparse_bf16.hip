@@ -20,6 +20,7 @@
 // a workgroup of its own; attend_sparse_multi_bf16_kernel, for batches with more lists than compute
 // units and lists of unequal length, runs one eight-wave workgroup per compute unit that walks a
 // length-balanced share of the lists back to back.
+#include <algorithm>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -738,51 +739,57 @@ __global__ __launch_bounds__(kWavesMulti * 64, 1) void attend_sparse_multi_bf16_
 // Merge the chunk partials of every (sequence, head) that needed more than one chunk.  The launch is a few
 // hundred kilobytes and nothing but latency, so it is spread thin (eight query rows per workgroup, one thread
 // per four output elements) and the partials of four chunks are asked for at once.
-template <int D>
+// Turns: the grid has fewer workgroups than max_q asks for, which take the rows in turns (a loop costs 0.3 us of 2.7).
+template <int D, bool Turns>
 __global__ __launch_bounds__(256) void attend_sparse_combine_kernel(
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_k, const uint8_t* __restrict__ seq_mode,
     const float* __restrict__ po, const float* __restrict__ pm, const float* __restrict__ pl,
     uint16_t* __restrict__ o, int32_t chunk_rows, Shape s DLLM_CHECK_PARAM) {
   DLLM_CHECK_EXIT();
-  constexpr int TPR = D / 4, ROWS = 256 / TPR;   // threads per row, rows per workgroup
+  constexpr int TPR = D / 4, ROWS = 256 / TPR;   // threads per row, rows per workgroup and turn
   const int h = blockIdx.y, b = blockIdx.z;
   const int k0 = cu_k[b], k1 = cu_k[b + 1], q0 = cu_q[b], nq = cu_q[b + 1] - q0;
   if (seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE) return;
   const int nch = chunk_geom(k1 - k0, chunk_rows).n;
-  const int i = blockIdx.x * ROWS + threadIdx.x / TPR, sub = threadIdx.x % TPR;
+  int i = blockIdx.x * ROWS + threadIdx.x / TPR;
+  const int sub = threadIdx.x % TPR;
   if (nch <= 1 || i >= nq) return;
-  const int64_t row = int64_t(q0 + i) * s.hq + h, pitch = int64_t(s.total_q) * s.hq;   // slot of chunk c: row + c * pitch
-  float m_all = -INFINITY, l_all = 0.0f;
-  float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-  for (int c0 = 0; c0 < nch; c0 += 4) {
-    float m[4], l[4];
-    float4 x[4];
+  const int64_t pitch = int64_t(s.total_q) * s.hq;   // slot of chunk c: row + c * pitch
+  do {
+    const int64_t row = int64_t(q0 + i) * s.hq + h;
+    float m_all = -INFINITY, l_all = 0.0f;
+    float4 a = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int c0 = 0; c0 < nch; c0 += 4) {
+      float m[4], l[4];
+      float4 x[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {   // past the last chunk: that chunk again, with no weight
-      const int64_t slot = row + min(c0 + u, nch - 1) * pitch;
-      m[u] = pm[slot];
-      l[u] = pl[slot];
-      x[u] = *reinterpret_cast<const float4*>(po + slot * D + sub * 4);
+      for (int u = 0; u < 4; ++u) {   // past the last chunk: that chunk again, with no weight
+        const int64_t slot = row + min(c0 + u, nch - 1) * pitch;
+        m[u] = pm[slot];
+        l[u] = pl[slot];
+        x[u] = *reinterpret_cast<const float4*>(po + slot * D + sub * 4);
+      }
+      float m_new = m_all;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, m[u]);
+      const float old = __builtin_amdgcn_exp2f(m_all - m_new);   // first round: exp2(-inf) = 0
+      l_all *= old;
+      a.x *= old; a.y *= old; a.z *= old; a.w *= old;
+      m_all = m_new;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const float w = c0 + u < nch ? __builtin_amdgcn_exp2f(m[u] - m_all) : 0.0f;
+        l_all += l[u] * w;
+        a.x += x[u].x * w; a.y += x[u].y * w; a.z += x[u].z * w; a.w += x[u].w * w;
+      }
     }
-    float m_new = m_all;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) m_new = fmaxf(m_new, m[u]);
-    const float old = __builtin_amdgcn_exp2f(m_all - m_new);   // first round: exp2(-inf) = 0
-    l_all *= old;
-    a.x *= old; a.y *= old; a.z *= old; a.w *= old;
-    m_all = m_new;
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const float w = c0 + u < nch ? __builtin_amdgcn_exp2f(m[u] - m_all) : 0.0f;
-      l_all += l[u] * w;
-      a.x += x[u].x * w; a.y += x[u].y * w; a.z += x[u].z * w; a.w += x[u].w * w;
-    }
-  }
-  const float inv = 1.0f / l_all;
-  v2u w2;
-  w2.x = cvt_pk_bf16(a.x * inv, a.y * inv);
-  w2.y = cvt_pk_bf16(a.z * inv, a.w * inv);
-  *reinterpret_cast<v2u*>(o + row * D + sub * 4) = w2;
+    const float inv = 1.0f / l_all;
+    v2u w2;
+    w2.x = cvt_pk_bf16(a.x * inv, a.y * inv);
+    w2.y = cvt_pk_bf16(a.z * inv, a.w * inv);
+    *reinterpret_cast<v2u*>(o + row * D + sub * 4) = w2;
+    i += gridDim.x * ROWS;
+  } while (Turns && i < nq);
 }
 
 hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const void* q, const void* k,
@@ -842,13 +849,23 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
   }
   e = hipGetLastError();
   if (e != hipSuccess || p.n_chunks <= 1) return e;
+  // The longest sequence may be one that is attended densely, with thousands of queries and nothing to merge: no more
+  // than about 2048 workgroups are started beyond the four per list that a block of 32 queries takes, and they loop
+  // (8 x 32 lists of 3200 kept rows, two sequences dense with 2048 queries: 25 us with a workgroup per eight rows of
+  // max_q, 5 us like this).
+  const int rows = 256 / (s.d / 4);
+  const int64_t lists = int64_t(s.hq) * s.batch, most = std::max<int64_t>(4, 2048 / lists), all = (s.max_q + rows - 1) / rows;
   auto combine = [&](auto kernel) {
-    const int rows = 256 / (s.d / 4);
-    kernel<<<dim3((s.max_q + rows - 1) / rows, s.hq, s.batch), 256, 0, st>>>(cu_q, cu_k, seq_mode, po, pm, pl, oh,
-                                                                             p.chunk_rows, s DLLM_CHECK_PASS);
+    kernel<<<dim3(unsigned(std::min(all, most)), s.hq, s.batch), 256, 0, st>>>(cu_q, cu_k, seq_mode, po, pm, pl, oh,
+                                                                               p.chunk_rows, s DLLM_CHECK_PASS);
   };
-  if (s.d == 128) combine(attend_sparse_combine_kernel<128>);
-  else combine(attend_sparse_combine_kernel<64>);
+  if (s.d == 128) {
+    if (all <= most) combine(attend_sparse_combine_kernel<128, false>);
+    else combine(attend_sparse_combine_kernel<128, true>);
+  } else {
+    if (all <= most) combine(attend_sparse_combine_kernel<64, false>);
+    else combine(attend_sparse_combine_kernel<64, true>);
+  }
   return hipGetLastError();
 }
 

@@ -895,6 +895,15 @@ def test_attend_kept_lists_cut_over_workgroups(hq, hkv, D, keep):
     check_attend(w, oracle_select(w), dw=dw)
 
 
+@pytest.mark.parametrize("D", [128, 64])
+def test_attend_merges_chunks_of_more_queries_than_one_turn(D):
+    """The merge launch is bounded, so with many queries its workgroups take several turns (at 64 lists 32 workgroups of
+    eight or sixteen rows), beside a sequence in one chunk and one that is attended densely."""
+    w = custom(21, torch.bfloat16, 32, 8, D, [2300, 80, 600], [300 if D == 128 else 550, 33, 600], [2100, 40, 0],
+               mode=np.array([0, 0, 1], np.uint8), salient=0.05)
+    check_attend(w, oracle_select(w))
+
+
 @pytest.mark.parametrize("hq,hkv,D,keep", [(32, 32, 128, [256]), (32, 8, 128, [1, 300, 0]), (32, 32, 128, [256, 33, 200, 31]),
                                             (6, 2, 128, [65, 64, 0, 1]), (8, 4, 64, [500, 127]), (32, 32, 128, [994, 276, 600, 700])])
 def test_attend_lists_shared_out_by_head_dim(hq, hkv, D, keep):
