@@ -156,7 +156,7 @@ struct DenseState<128> {
       DLLM_LS_OUT_128, "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
 #define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"),          \
       [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr),             \
-      [zs] "s"(zs), [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
+      [zs] "s"(zs), [lazy] "s"(kLazyGrowthDense), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
 #define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
       [lo2] "v"(tl.off[2]), [lo3] "v"(tl.off[3]), [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
 #define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1]),                     \
@@ -229,7 +229,7 @@ struct DenseState<64> {
       "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
 #define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones),            \
       "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr), [zs] "s"(zs),                  \
-      [lazy] "s"(kLazyGrowth), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
+      [lazy] "s"(kLazyGrowthDense), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
 #define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
       [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
 #define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1])

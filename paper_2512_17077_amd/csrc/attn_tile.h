@@ -28,16 +28,20 @@ typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-// The running maximum m of an online softmax is raised lazily: only when a base-2 logit exceeds it by more
-// than this, so probabilities may reach 2^8 instead of 1 in between.  Numerator and denominator carry the
-// same factor and are floating-point, so nothing is lost to rounding; what it takes is range: sums of |V| times 2^8
-// must stay finite.
-constexpr float kLazyGrowth = 8.0f;
-// Dense sequences have many steps per wave and pay for a raise with a pass over all accumulators: heads with salient
-// keys (5 % of the K rows four times as long) raise m in so many 32-key steps with a step of 2^8 that the dense part of
-// a mixed burst (32 heads, 8 sequences of 2048) takes 623 us instead of the 520 of a step of 2^32.  So that the larger
-// step does not cost range at the top, m is set this far above the maximum there: probabilities start at 2^-24 and
-// still end at 2^kLazyGrowth.  (At the bottom 2^-24 |V| has to be representable: the matrix cores keep denormals.)
+// The running maximum m of an online softmax (bf16 kernels) is raised lazily: a raise costs a pass over all accumulators.
+// Between raises a key that stands above m has a probability that is rounded to bf16, where a key that has set m has
+// exactly 1, and keys with large probabilities are those whose rounding shows.  Error against 64 bits (5 % of the K rows
+// four times as long; the rounding of the outputs to bf16 alone is 1.65e-3) by how far m may lag, 2^2 / 2^8 / 2^32: kept
+// lists of one layer 1.666 / 1.679 / 1.729e-3, of a small batch 1.668 / 1.694 / 1.765e-3, dense sequences of 1024 keys
+// - / 1.757 / 1.815e-3.
+// Kept lists have few steps per wave, and raise m past 2^2: 0.2 us more than 2^32 on the small batch's 31.4.
+constexpr float kLazyGrowth = 2.0f;
+// Dense sequences have many, and heads with salient keys raise m often with a small lag: the mixed burst (8 sequences of
+// 2048 in its dense part, 32 heads) takes 628 us with a lag of 2^8 and 508 with 2^32, for 3 % of the error.  So that the
+// larger lag does not cost range at the top, m is set kDenseHeadroom above the maximum: probabilities run from 2^-24 to
+// 2^8, and sums overflow only where they would with a lag of 2^8 (|V| of about 2^104).  At the bottom 2^-24 |V| has to
+// be representable: the matrix cores keep denormals.
+constexpr float kLazyGrowthDense = 8.0f;
 constexpr float kDenseHeadroom = 24.0f;
 
 // XOR applied to the chunk index of `row`; depends on row & 15 only

@@ -51,9 +51,10 @@ def check_values(w, log2_scale):
 @pytest.mark.parametrize("D", [128, 64])
 @pytest.mark.parametrize("hq,hkv,lens,keep", [(4, 2, [400], [300]), (32, 8, [2900], [2600]),
                                               (32, 8, [40 + 30 * b for b in range(16)], [30 + 25 * b for b in range(16)])])
-def test_large_values_in_kept_lists(hq, hkv, lens, keep, D):
+@pytest.mark.parametrize("log2_scale", [100, -110])
+def test_large_and_small_values_in_kept_lists(hq, hkv, lens, keep, D, log2_scale):
     """One workgroup per list, lists cut into chunks, and many lists per workgroup."""
-    check_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, [32] * len(lens), keep, dense=False), 100)
+    check_values(growing_workload(torch.bfloat16, hq, hkv, D, lens, [32] * len(lens), keep, dense=False), log2_scale)
 
 
 # fp32 inputs: the maximum is exact, probabilities stay at or below 1
