@@ -896,11 +896,7 @@ hipError_t launch_attend_dense_bf16(const Shape& s, const void* q, const void* k
                                     const int32_t* cu_q, const int32_t* cu_kv, const uint8_t* seq_mode, int which,
                                     void* o, hipStream_t st) {
   if (s.max_q == 0) return hipSuccess;   // no sequence has a query: nothing to write
-#ifdef X_KS
-  const int ks = X_KS;
-#else
   const int ks = key_splits(s, which);
-#endif
   const int rows = dense_rows(ks);
   const int64_t nx = (s.max_q + rows - 1) / rows;
   dim3 grid(unsigned(nx), s.hq, s.batch);
