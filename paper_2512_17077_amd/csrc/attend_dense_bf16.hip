@@ -550,14 +550,6 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     if (ntiles > 2) load_tile(kbase, 2, DLLM_IC(2 * TILEB));
     load_tile(vbase, 0, DLLM_IC(VBASE));
   }
-#ifdef DLLM_DENSE_FILL_RING   // timing experiments only: all four ring slots filled once (tiles 0..3)
-  if (ntiles > 3) {
-    load_tile(kbase, 2, DLLM_IC(2 * TILEB));
-    load_tile(vbase, 2, DLLM_IC(VBASE + 2 * TILEB));
-    load_tile(kbase, 3, DLLM_IC(3 * TILEB));
-    load_tile(vbase, 3, DLLM_IC(VBASE + 3 * TILEB));
-  }
-#endif
   // Iteration 0 multiplies an all-zero P with the rows of ring slot 3 of V that the step "before the first" would
   // have used (the second half of the slot, or both halves when the keys are split): clear them, so that no stale
   // NaN pattern meets the zeros.  Tile 3 lands there later.
