@@ -209,6 +209,16 @@ dllm_status dllm_hcsa_attend(const dllm_batch *batch,
                              const uint8_t *seq_mode, /* device, [batch] or NULL */
                              void *o,             /* device, [total_q, n_q_heads, head_dim] */
                              void *workspace, size_t workspace_bytes, void *hip_stream);
+/*
+ * How an attend call with these arguments shares out its work (bf16; all 1 for fp32), for tests and measurement:
+ *   form_out[0]  chunks that a kept list is cut into at most (with more than 1 a second launch merges them)
+ *   form_out[1]  workgroups per kept list that share out head_dim of V and of the output (1, 2 or 4)
+ *   form_out[2]  wave groups that share the keys of a densely attended sequence (1 or 2): of the sequences flagged
+ *                dense if all_dense is 0, of dllm_dense_refresh_attend if it is not
+ * Host only: reads the descriptor, no device memory, launches nothing.
+ */
+dllm_status dllm_hcsa_attend_form_of(const dllm_batch *batch, int32_t max_k, int32_t total_k, int32_t all_dense,
+                                     int32_t form_out[3] /* host */);
 
 /*
  * Pack (Section 4.5, "Decoupling Logical Sparsity from Physical Layout"): copies every head's kept

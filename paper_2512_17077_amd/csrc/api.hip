@@ -227,6 +227,15 @@ AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t tot
   return p;
 }
 
+// What a call takes, within the workspace that the query asked for.  The query plans without total_k; that no total asks
+// for more chunks than it does is a property of the sums above, which is not relied on: where it failed, the query's own
+// plan would be taken.
+AttendPlan plan_attend_call(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k, size_t* need) {
+  const AttendPlan asked = plan_attend(s, dt, max_k, -1), best = plan_attend(s, dt, max_k, total_k);
+  *need = asked.bytes;
+  return best.bytes <= asked.bytes ? best : asked;
+}
+
 }  // namespace dllm
 
 extern "C" {
@@ -303,6 +312,23 @@ size_t dllm_hcsa_attend_workspace(const dllm_batch* batch, int32_t max_k) {
   return dllm::plan_attend(s, batch->dtype, max_k, -1).bytes;
 }
 
+dllm_status dllm_hcsa_attend_form_of(const dllm_batch* batch, int32_t max_k, int32_t total_k, int32_t all_dense,
+                                     int32_t* form_out) {
+  dllm::Shape s;
+  dllm_status st = check_batch(batch, &s);
+  if (st != DLLM_OK) return st;
+  if (form_out == nullptr) return fail(DLLM_ERR_INVALID_ARG, "form_out must be non-NULL");
+  if (total_k < 0 || max_k < 0 || max_k > total_k || max_k > batch->max_kv)
+    return fail(DLLM_ERR_INVALID_ARG, "need 0 <= max_k <= min(total_k, max_kv) (got max_k=%d, total_k=%d, max_kv=%d)",
+                max_k, total_k, batch->max_kv);
+  size_t need = 0;
+  const dllm::AttendPlan plan = dllm::plan_attend_call(s, batch->dtype, max_k, total_k, &need);
+  form_out[0] = plan.n_chunks;
+  form_out[1] = plan.v_split;
+  form_out[2] = batch->dtype == DLLM_BF16 && s.max_q > 0 ? dllm::dense_key_splits(s, all_dense ? 2 : 1) : 1;
+  return DLLM_OK;
+}
+
 dllm_status dllm_hcsa_attend(const dllm_batch* batch, const int32_t* idx, const int32_t* cu_k, int32_t total_k,
                              int32_t max_k, const uint8_t* seq_mode, void* o, void* workspace,
                              size_t workspace_bytes, void* hip_stream) {
@@ -318,9 +344,9 @@ dllm_status dllm_hcsa_attend(const dllm_batch* batch, const int32_t* idx, const 
     return fail(DLLM_ERR_INVALID_ARG, "cu_k may be NULL only when total_k is 0 (got total_k=%d)", total_k);
   if (seq_mode != nullptr && (st = check_dense_strides(batch)) != DLLM_OK) return st;
   if (total_k > 0 && (st = check_sparse_strides(batch)) != DLLM_OK) return st;
-  const size_t need = dllm::plan_attend(s, batch->dtype, max_k, -1).bytes;   // what the query says, whatever this call takes
+  size_t need = 0;   // what the query says, whatever this call takes
+  const dllm::AttendPlan plan = dllm::plan_attend_call(s, batch->dtype, max_k, total_k, &need);
   if ((st = check_workspace(workspace, workspace_bytes, need)) != DLLM_OK) return st;
-  const dllm::AttendPlan plan = dllm::plan_attend(s, batch->dtype, max_k, total_k);
   g_err[0] = 0;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   hipError_t e = dllm::validate_inputs(s, batch->cu_q, batch->cu_kv, cu_k, idx, seq_mode, total_k, max_k, 0, stream);

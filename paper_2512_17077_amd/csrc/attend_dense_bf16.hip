@@ -864,7 +864,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 // 512 19.6 / 15.0, 1024 29.7 / 24.6 (half the compute units); 2048 65.6 / 75.4 (all of them); three of 768 53.7 / 57.9 (two
 // rounds against three); five of 300 35.4 / 27.1; 16 heads x 64, one of 1024 20.1 / 14.3, three of 1024 21.8 / 28.7, three of
 // 2048 72.9 / 69.6.
-static int key_splits(const Shape& s, int which) {
+int dense_key_splits(const Shape& s, int which) {
   constexpr double kUnits = 256;   // compute units
   // the densely attended sequences of a mixed call are not known here: as many as total_q can have of the longest
   const double n = which == 2 ? s.batch : std::max<int64_t>(1, (int64_t(s.total_q) + s.max_q - 1) / s.max_q);
@@ -888,7 +888,7 @@ hipError_t launch_attend_dense_bf16(const Shape& s, const void* q, const void* k
                                     const int32_t* cu_q, const int32_t* cu_kv, const uint8_t* seq_mode, int which,
                                     void* o, hipStream_t st) {
   if (s.max_q == 0) return hipSuccess;   // no sequence has a query: nothing to write
-  const int ks = key_splits(s, which);
+  const int ks = dense_key_splits(s, which);
   const int rows = dense_rows(ks);
   const int64_t nx = (s.max_q + rows - 1) / rows;
   dim3 grid(unsigned(nx), s.hq, s.batch);

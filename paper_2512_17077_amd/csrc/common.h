@@ -63,6 +63,8 @@ struct AttendPlan {
   size_t off_po, off_pm, off_pl, bytes;
 };
 AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k);
+// Wave groups that share the keys of a densely attended sequence in the bf16 kernel (1 or 2); `which` as below.
+int dense_key_splits(const Shape& s, int which);
 
 // `which` selects the sequences a launch works on: 0 = all, each as its flag in seq_mode says (fp32 only);
 // 1 = those flagged dense; 2 = every sequence, as dense.

@@ -29,7 +29,7 @@ DLLM_SELECT_FORM_AUTO, DLLM_SELECT_FORM_TWO_LAUNCHES, DLLM_SELECT_FORM_ONE_LAUNC
 EXPORTS = [
     "dllm_hcsa_select_workspace", "dllm_hcsa_select", "dllm_hcsa_select_ex", "dllm_hcsa_select_static",
     "dllm_hcsa_set_select_form", "dllm_hcsa_select_form_of",
-    "dllm_hcsa_attend_workspace", "dllm_hcsa_attend",
+    "dllm_hcsa_attend_workspace", "dllm_hcsa_attend", "dllm_hcsa_attend_form_of",
     "dllm_dense_refresh_attend_workspace", "dllm_dense_refresh_attend",
     "dllm_hcsa_pack", "dllm_hcsa_precondition_errors",
     "dllm_last_error", "dllm_hcsa_version",
@@ -97,6 +97,8 @@ def lib() -> ctypes.CDLL:
         L.dllm_hcsa_attend_workspace.argtypes = [P, i32]
         L.dllm_hcsa_attend.restype = ctypes.c_int
         L.dllm_hcsa_attend.argtypes = [P, vp, vp, i32, i32, vp, vp, vp, sz, vp]
+        L.dllm_hcsa_attend_form_of.restype = ctypes.c_int
+        L.dllm_hcsa_attend_form_of.argtypes = [P, i32, i32, i32, ctypes.POINTER(i32)]
         L.dllm_dense_refresh_attend_workspace.restype = sz
         L.dllm_dense_refresh_attend_workspace.argtypes = [P]
         L.dllm_dense_refresh_attend.restype = ctypes.c_int
@@ -235,6 +237,13 @@ def dllm_hcsa_select_static(batch: DllmBatch, cu_k: torch.Tensor, total_k: int, 
 
 def dllm_hcsa_attend_workspace(batch: DllmBatch, max_k: int) -> int:
     return int(lib().dllm_hcsa_attend_workspace(ctypes.byref(batch), int(max_k)))
+
+
+def dllm_hcsa_attend_form_of(batch: DllmBatch, max_k: int = 0, total_k: int = 0, all_dense: bool = False):
+    """(chunks per kept list, workgroups per list over head_dim, wave groups over a dense sequence's keys) of a call."""
+    form = (ctypes.c_int32 * 3)()
+    _raise(lib().dllm_hcsa_attend_form_of(ctypes.byref(batch), int(max_k), int(total_k), int(bool(all_dense)), form))
+    return tuple(form)
 
 
 def dllm_hcsa_attend(batch: DllmBatch, idx: Optional[torch.Tensor], cu_k: Optional[torch.Tensor], total_k: int,

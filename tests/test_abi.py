@@ -2,6 +2,7 @@
 arguments on the host before touching the GPU (so these run without one)."""
 import ctypes
 import os
+import random
 import re
 
 import pytest
@@ -104,6 +105,47 @@ def test_which_form_selection_takes_follows_the_documented_rule():
         hcsa.dllm_hcsa_set_select_form(hcsa.DLLM_SELECT_FORM_AUTO)
 
 
+
+
+def attend_shape(rng):
+    d = rng.choice((64, 128))
+    hq = rng.choice((1, 2, 4, 6, 8, 16, 32, 40, 64))
+    batch = int(2 ** rng.uniform(0, 8))
+    max_kv = int(2 ** rng.uniform(0, 15))
+    b = shaped_batch(batch, hq, 1, d, max_kv * batch, max_kv)
+    b.max_q = int(2 ** rng.uniform(0, 11))
+    b.total_q = b.max_q + int((batch - 1) * b.max_q * rng.random())
+    return b, rng.randint(0, max_kv)
+
+
+def test_an_attend_call_never_takes_more_workspace_than_the_query_asks_for():
+    """The query does not know total_k, the call does and may plan otherwise: partial results of every chunk of the call's
+    plan have to fit what the query said (D + 2 floats per chunk, query row and head)."""
+    rng = random.Random(1)
+    cut = split = 0
+    for _ in range(20000):
+        b, max_k = attend_shape(rng)
+        ws = hcsa.dllm_hcsa_attend_workspace(b, max_k)
+        for total_k in {max_k, max_k + rng.randint(0, (b.batch - 1) * max_k), b.batch * max_k}:
+            chunks, parts, _ = hcsa.dllm_hcsa_attend_form_of(b, max_k, total_k)
+            assert chunks == 1 or ws >= chunks * b.total_q * b.n_q_heads * (b.head_dim + 2) * 4
+            assert parts in (1, 2, 4) and parts * 32 <= b.head_dim and (parts == 1 or chunks == 1)
+            cut, split = cut + (chunks > 1), split + (parts > 1)
+    assert cut > 1000 and split > 1000   # both forms are in the sweep
+
+
+def test_attend_form_of_checks_its_arguments():
+    b = good_batch()
+    form = (ctypes.c_int32 * 3)()
+    call = lambda *a: hcsa.lib().dllm_hcsa_attend_form_of(ctypes.byref(b), *a)
+    assert call(100, 200, 0, form) == 0
+    assert call(100, 99, 0, form) == -1 and call(-1, 99, 0, form) == -1 and call(301, 400, 0, form) == -1
+    assert call(100, 200, 0, None) == -1 and "form_out" in hcsa.last_error()
+    b.dtype = hcsa.DLLM_F32
+    assert hcsa.dllm_hcsa_attend_form_of(b, 300, 300) == (1, 1, 1)
+    b.head_dim = 96
+    with pytest.raises(hcsa.DllmError):
+        hcsa.dllm_hcsa_attend_form_of(b, 300, 300)
 
 
 def select_status(b, cu_k=FAKE, total_k=100, max_k=50, pool_w=1, idx=FAKE, ws=FAKE, ws_bytes=1 << 40):
