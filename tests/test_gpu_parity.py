@@ -378,6 +378,7 @@ def test_dense_keys_and_queries_around_tile_edges(Hq, Hkv, D):
         qlens = [256, 129, 1, 255, 128, 256, 127, 250]
         w = custom(60 + part, torch.bfloat16, Hq, Hkv, D, lens, qlens, [0] * 8, mode=np.ones(8, np.uint8), salient=0.05)
         dw = workload.DeviceWorkload(w)
+        assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == (2 if Hq == 4 else 1)
         dw.o.fill_(float("nan"))
         dw.dense_refresh()
         ref = oracle_attend(w, np.zeros((Hq, 0), np.int32))
@@ -884,14 +885,16 @@ def test_f32_token_stride_beyond_32_bits():
         torch.cuda.empty_cache()
 
 
-@pytest.mark.parametrize("hq,hkv,D,keep", [(32, 32, 128, [500]), (16, 4, 128, [1000, 130]), (8, 2, 64, [1023, 3, 640]),
-                                            (4, 4, 128, [129, 410]), (2, 1, 64, [2047]), (32, 8, 128, [2000, 400, 0])])
-def test_attend_kept_lists_cut_over_workgroups(hq, hkv, D, keep):
+@pytest.mark.parametrize("hq,hkv,D,keep,chunks", [(16, 4, 128, [1000, 130], 4), (2, 1, 64, [2047], 8), (32, 8, 64, [5000, 1666, 40], 3),
+                                                  (32, 8, 128, [1200], 5), (32, 32, 128, [2047], 6), (8, 2, 64, [2600, 866, 40], 7),
+                                                  (4, 2, 128, [1100], 9), (8, 8, 64, [1200], 10), (4, 1, 128, [2600, 1300], 11)])
+def test_attend_kept_lists_cut_over_workgroups(hq, hkv, D, keep, chunks):
     """Fewer lists than compute units: lists are cut into up to as many chunks as fill the chip and merged four
-    chunks at a time; chunk counts that do and do not divide by four, a second query tile, short lists in between."""
+    chunks at a time: chunk counts that do and do not divide by four, also after a full round of four (there the running
+    rescale meets the slots without weight), a second query tile, lists of fewer chunks or one in between."""
     w = custom(18, torch.bfloat16, hq, hkv, D, [max(k, 1) + 50 for k in keep], [32, 45, 7][:len(keep)], keep, salient=0.05)
     dw = workload.DeviceWorkload(w)
-    assert hcsa.dllm_hcsa_attend_workspace(dw.batch, dw.max_k) > 0
+    assert hcsa.dllm_hcsa_attend_form_of(dw.batch, dw.max_k, dw.total_k)[:2] == (chunks, 1)
     check_attend(w, oracle_select(w), dw=dw)
 
 
@@ -901,11 +904,15 @@ def test_attend_merges_chunks_of_more_queries_than_one_turn(D):
     eight or sixteen rows), beside a sequence in one chunk and one that is attended densely."""
     w = custom(21, torch.bfloat16, 32, 8, D, [2300, 80, 600], [300 if D == 128 else 550, 33, 600], [2100, 40, 0],
                mode=np.array([0, 0, 1], np.uint8), salient=0.05)
-    check_attend(w, oracle_select(w))
+    dw = workload.DeviceWorkload(w)
+    assert hcsa.dllm_hcsa_attend_form_of(dw.batch, dw.max_k, dw.total_k)[0] > 1
+    check_attend(w, oracle_select(w), dw=dw)
 
 
 @pytest.mark.parametrize("hq,hkv,D,keep", [(32, 32, 128, [256]), (32, 8, 128, [1, 300, 0]), (32, 32, 128, [256, 33, 200, 31]),
-                                            (6, 2, 128, [65, 64, 0, 1]), (8, 4, 64, [500, 127]), (32, 32, 128, [994, 276, 600, 700])])
+                                            (6, 2, 128, [65, 64, 0, 1]), (8, 4, 64, [500, 127]), (32, 32, 128, [994, 276, 600, 700]),
+                                            (32, 32, 128, [500]), (8, 2, 64, [1023, 3, 640]), (4, 4, 128, [129, 410]),
+                                            (32, 8, 128, [2000, 400, 0])])
 def test_attend_lists_shared_out_by_head_dim(hq, hkv, D, keep):
     """Short lists and few of them: several workgroups per list, each with all K rows and its part of head_dim of V and
     of the output (two or four at head_dim 128, two at 64, one or two per compute unit); lists around the 32-row
@@ -914,5 +921,24 @@ def test_attend_lists_shared_out_by_head_dim(hq, hkv, D, keep):
     lens, qlens = [max(k, 1) + 40 for k in keep] + [70], [32, 45, 7, 32][:n] + [70]
     mode = np.array([0] * n + [1], np.uint8)
     w = custom(19, torch.bfloat16, hq, hkv, D, lens, qlens, keep + [0], mode=mode, salient=0.05)
-    check_attend(w, oracle_select(w))
+    dw = workload.DeviceWorkload(w)
+    chunks, parts, _ = hcsa.dllm_hcsa_attend_form_of(dw.batch, dw.max_k, dw.total_k)
+    assert chunks == 1 and parts > 1
+    check_attend(w, oracle_select(w), dw=dw)
     check_pack_and_packed_attend(custom(19, torch.bfloat16, hq, hkv, D, lens[:n], qlens[:n], keep, salient=0.05), f"parts {keep}")
+
+
+@pytest.mark.parametrize("hq,hkv,D,keep,qlens", [
+    # more sequences than a wave has lanes (each workgroup then reads its own entries)
+    (1, 1, 128, [40 + 7 * i % 90 for i in range(90)], [5 + i % 9 for i in range(90)]),
+    (3, 1, 64, [40 + 7 * i % 90 for i in range(70)], [5 + i % 9 for i in range(70)]),
+    (2, 1, 128, [40 + 7 * i % 90 for i in range(100)], [5 + i % 9 for i in range(100)]),
+    # blocks of several query tiles, which reuse the workgroup's tile space
+    (32, 8, 128, [300, 130], [64, 34]), (32, 8, 128, [300, 130], [200, 170]), (16, 4, 64, [300, 130], [64, 33]),
+    (16, 4, 64, [300, 130], [200, 161])])
+def test_attend_parts_of_large_batches_and_blocks(hq, hkv, D, keep, qlens):
+    w = custom(20, torch.bfloat16, hq, hkv, D, [k + 40 for k in keep], qlens, keep, salient=0.05)
+    dw = workload.DeviceWorkload(w)
+    chunks, parts, _ = hcsa.dllm_hcsa_attend_form_of(dw.batch, dw.max_k, dw.total_k)
+    assert chunks == 1 and parts > 1
+    check_attend(w, oracle_select(w), dw=dw)
