@@ -864,22 +864,38 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 // 512 19.6 / 15.0, 1024 29.7 / 24.6 (half the compute units); 2048 65.6 / 75.4 (all of them); three of 768 53.7 / 57.9 (two
 // rounds against three); five of 300 35.4 / 27.1; 16 heads x 64, one of 1024 20.1 / 14.3, three of 1024 21.8 / 28.7, three of
 // 2048 72.9 / 69.6.
+// The lengths themselves are on the device.  With the mean and the longest known, they are taken to be spread evenly
+// around the mean (up to 64 of them, for the batch), and the workgroups to start longest first: in a second round that is
+// not full, a workgroup then follows one of about the length at which the first round ended.  Counting such a round by
+// its share of the mean instead took the split form where it loses: 8 heads x 64, nine sequences of 209 to 1073 23.5 / 25.2 us, six of
+// 567 to 1601 31.1 / 33.9; 8 heads x 128, fifteen of 109 to 834 29.2 / 32.1.  More than a round is estimated to within a
+// few per cent, so there the split form has to be 6 % ahead (of 1500 simulated batches 3 then lose more than 2 %, 14 without).
 int dense_key_splits(const Shape& s, int which) {
-  constexpr double kUnits = 256;   // compute units
+  constexpr int kUnits = 256;   // compute units
   // the densely attended sequences of a mixed call are not known here: as many as total_q can have of the longest
-  const double n = which == 2 ? s.batch : std::max<int64_t>(1, (int64_t(s.total_q) + s.max_q - 1) / s.max_q);
-  const double longest = which == 2 ? s.max_kv : std::min(s.max_kv, s.max_q);
-  const double mean = which == 2 ? double(s.total_kv) / s.batch : longest;
-  const bool even = mean * 8 >= longest * 7 && double(s.total_q) * 8 >= n * s.max_q * 7;
+  const int64_t n = which == 2 ? s.batch : std::max<int64_t>(1, (int64_t(s.total_q) + s.max_q - 1) / s.max_q);
+  const double longest_q = s.max_q, mean_q = double(s.total_q) / n;
+  const double longest_kv = which == 2 ? s.max_kv : std::min(s.max_kv, s.max_q);
+  const double mean_kv = which == 2 ? double(s.total_kv) / n : std::min(longest_kv, mean_q);
+  const bool even = mean_kv * 8 >= longest_kv * 7 && mean_q * 8 >= longest_q * 7;
+  const int reps = int(std::min<int64_t>(n, 64));
   auto cost = [&](int ks) -> double {
-    const double rows = dense_rows(ks), nx = std::ceil(s.max_q / rows);
     const double step = s.d == 128 ? (ks == 1 ? 1440 : 1660) : (ks == 1 ? 1070 : 1290), fixed = s.d == 128 ? 13000 : 7000;
-    const double per_key = step / (32 * ks), one = longest * per_key + fixed;
-    const double units = s.hq * std::min(nx * n, s.total_q / rows + (even ? n : n / 2)) / kUnits;   // rounds of workgroups
-    if (units <= 1) return one;
-    if (even) return std::ceil(units) * one;   // equal workgroups: whole rounds
-    const double avg = mean * per_key + fixed;
-    return std::max(one, units * avg) + avg / 4;
+    const double per_key = step / (32 * ks), one = longest_kv * per_key + fixed;
+    double workgroups = 0, work = 0, second = 0;   // second: what the first workgroup of the second round takes
+    for (int i = 0; i < reps; ++i) {
+      const double t = reps > 1 ? 2.0 * i / (reps - 1) : 0.0;
+      const double q = std::max(1.0, longest_q - (longest_q - mean_q) * t), kv = std::max(1.0, longest_kv - (longest_kv - mean_kv) * t);
+      const double k = double(n) / reps * s.hq * std::ceil(q / dense_rows(ks)), length = kv * per_key + fixed;
+      if (workgroups <= kUnits && workgroups + k > kUnits) second = length;
+      workgroups += k;
+      work += k * length;
+    }
+    if (workgroups <= kUnits) return one;
+    const double doubt = ks == 2 ? 1.06 : 1.0;
+    if (even) return doubt * std::ceil(workgroups / kUnits) * one;   // equal workgroups: whole rounds
+    if (workgroups <= 2 * kUnits) return doubt * std::max(one, 2 * second);
+    return doubt * std::max(one, work / kUnits + work / workgroups / 2);
   };
   return cost(2) < cost(1) ? 2 : 1;
 }

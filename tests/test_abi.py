@@ -148,6 +148,26 @@ def test_attend_form_of_checks_its_arguments():
         hcsa.dllm_hcsa_attend_form_of(b, 300, 300)
 
 
+# heads, head_dim, lengths, the faster form, us whole, us split (measured with each form forced)
+DENSE_FORMS = [
+    (4, 64, [142], 2, 8.1, 7.7), (8, 128, [137], 2, 11.4, 10.5), (8, 128, [2567], 2, 55.6, 35.9),
+    (4, 128, [374, 348, 492, 207, 520, 245, 302, 111, 517, 303], 2, 19.9, 16.3), (16, 128, [302, 167, 42, 222, 339], 2, 16.9, 14.0),
+    (2, 64, [1829] * 17, 2, 65.1, 45.0), (32, 128, [441, 812, 574], 2, 39.9, 35.7),
+    (8, 64, [1073, 528, 885, 678, 637, 950, 209, 444, 586], 1, 23.5, 25.2), (8, 64, [1282, 1189, 1374, 567, 1601, 748], 1, 31.1, 33.9),
+    (8, 128, [233, 293, 488, 319, 698, 274, 646, 115, 394, 809, 560, 344, 194, 146, 606], 1, 29.2, 32.1),
+    (32, 128, [394, 539, 397, 434, 567, 508, 633, 553, 411, 518, 625, 568, 572, 513, 434], 1, 115.6, 144.4),
+    (32, 128, [1806, 911], 1, 81.7, 86.9), (8, 64, [404, 371, 413, 384, 386, 429, 371, 393, 413, 370, 446, 421, 406], 1, 14.9, 21.0),
+    (16, 64, [258] * 7, 1, 11.1, 17.1), (32, 128, [802, 945], 1, 34.7, 41.5), (16, 64, [1793, 2219, 2092], 1, 73.9, 89.5),
+    (16, 64, [459, 615, 984, 595, 961, 610, 927, 479, 877, 677, 829, 565, 604, 449], 1, 55.6, 74.2)]
+
+
+def test_dense_calls_take_the_form_that_measured_faster():
+    for hq, d, lens, form, _, _ in DENSE_FORMS:
+        b = shaped_batch(len(lens), hq, 1, d, sum(lens), max(lens))
+        b.total_q, b.max_q = sum(lens), max(lens)
+        assert hcsa.dllm_hcsa_attend_form_of(b, all_dense=True)[2] == form, (hq, d, lens)
+
+
 def select_status(b, cu_k=FAKE, total_k=100, max_k=50, pool_w=1, idx=FAKE, ws=FAKE, ws_bytes=1 << 40):
     return hcsa.lib().dllm_hcsa_select(ctypes.byref(b), cu_k, total_k, max_k, pool_w, idx, ws, ws_bytes, None)
 
