@@ -5,10 +5,12 @@
 // Pure data movement, bound by HBM: per kept (head, row) pair one K row and one V row are gathered
 // (16-byte non-temporal loads, a row's chunks in neighbouring lanes) and written out contiguously.
 // A workgroup takes a run of consecutive list positions of one (sequence, head), so its stores cover
-// one contiguous span; several rows per lane group are in flight before the first store.  The stores are
-// plain ones: the attention that follows reads the packed rows, and finds up to 256 MB of them in the
-// memory-side cache (16 sequences of 32 heads, 135 MB packed, then attended over: 81.9 us with non-temporal
-// stores, 73.7 us with plain ones).
+// one contiguous span; several rows per lane group are in flight before the first store.  The attention that
+// follows reads the packed rows, and finds up to 256 MB of them in the memory-side cache if the stores leave them there:
+// non-temporal ones do not, plain ones do but stay in the L2s until the end of the launch, so the stores are
+// written through at device scope (sc1).  us, non-temporal / plain / written through: packing 67 MB 26.6 / 26.6 / 23.5, 134 MB
+// 50.7 / 55.7 / 51.0, 537 MB 195 / 214 / 203; packing and attending 67 MB 50.2 / 42.1 / 38.8, 134 MB 80.2 / 81.1 /
+// 77.2, 537 MB 302 / 292 / 287, 135 MB in lists of very different length 82.5 / 73.7 / 70.2.
 #include "common.h"
 
 namespace dllm {
@@ -40,8 +42,12 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(
   const char* kbase = k + (int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head) * es + c * 16;
   const char* vbase = v + (int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head) * es + c * 16;
   const int64_t out_row = int64_t(CH) * 16;
-  char* kout = kp + (int64_t(h) * total_k + ko0) * out_row + c * 16;
-  char* vout = vp + (int64_t(h) * total_k + ko0) * out_row + c * 16;
+  // this workgroup's rows of the output, as buffers: what lies past their end is not stored
+  const int64_t out0 = (int64_t(h) * total_k + ko0 + t0) * out_row;
+  const int out_bytes = min(kb - t0, ROWS_PER_WG) * int(out_row);
+  constexpr int kRawBuffer = 0x00027000, kThrough = 16;   // 32-bit data format; sc1
+  const __amdgpu_buffer_rsrc_t kout = __builtin_amdgcn_make_buffer_rsrc(kp + out0, 0, out_bytes, kRawBuffer);
+  const __amdgpu_buffer_rsrc_t vout = __builtin_amdgcn_make_buffer_rsrc(vp + out0, 0, out_bytes, kRawBuffer);
 
   v4u kr[kPackInFlight], vr[kPackInFlight];
 #pragma unroll
@@ -53,11 +59,9 @@ __global__ __launch_bounds__(kPackThreads) void pack_kernel(
   }
 #pragma unroll
   for (int p = 0; p < kPackInFlight; ++p) {
-    const int t = t0 + p * ROWS + sub;
-    if (t < kb) {
-      *reinterpret_cast<v4u*>(kout + t * out_row) = kr[p];
-      *reinterpret_cast<v4u*>(vout + t * out_row) = vr[p];
-    }
+    const int at = (p * ROWS + sub) * int(out_row) + c * 16;
+    __builtin_amdgcn_raw_buffer_store_b128(kr[p], kout, at, 0, kThrough);
+    __builtin_amdgcn_raw_buffer_store_b128(vr[p], vout, at, 0, kThrough);
   }
 }
 

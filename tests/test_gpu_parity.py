@@ -592,6 +592,27 @@ def test_paper_defaults_full_size(c):
 
 # ------------------------------------------------------------------ packing (Section 4.5) and the packed Reuse step
 
+@pytest.mark.parametrize("dtype,D", [(torch.bfloat16, 128), (torch.bfloat16, 64), (torch.float32, 128)])
+def test_pack_writes_its_rows_and_nothing_else(dtype, D):
+    """List lengths around the 32, 64 and 128 rows of a workgroup; the buffers lie inside larger ones whose other bytes
+    must survive (the last rows of the last head are followed by them)."""
+    keep = [1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 0, 257]
+    w = custom(22, dtype, 2, 1, D, [k + 20 for k in keep], [4] * len(keep), keep)
+    dw = workload.DeviceWorkload(w)
+    idx = oracle_select(w)
+    rows = w.n_q_heads * dw.total_k
+    space = [torch.full((rows + 300, D), 7.0, dtype=dtype, device=dw.device) for _ in range(2)]
+    kp, vp = (x[100:100 + rows].view(w.n_q_heads, dw.total_k, D) for x in space)
+    hcsa.dllm_hcsa_pack(dw.batch, torch.from_numpy(idx).to(dw.device), dw.cu_k, dw.total_k, dw.max_k, kp, vp)
+    for x, src, got in zip(space, (w.k, w.v), (kp, vp)):
+        assert (x[:100] == 7.0).all() and (x[100 + rows:] == 7.0).all()
+        for b in range(len(keep)):
+            c0, c1 = int(w.cu_k[b]), int(w.cu_k[b + 1])
+            for h in range(w.n_q_heads):
+                want = src[int(w.cu_kv[b]) + torch.from_numpy(idx[h, c0:c1]).long(), 0]
+                assert torch.equal(got[h, c0:c1].cpu(), want)
+
+
 def check_pack_and_packed_attend(w, name):
     say(f"pack {name} dtype={w.dtype} B={w.batch} Hq={w.n_q_heads} Hkv={w.n_kv_heads} D={w.head_dim} "
         f"maxk={int(w.keep.max())}")
