@@ -193,7 +193,9 @@ dllm_status dllm_hcsa_select_static(const dllm_batch *batch,
  * 0 .. L_b-1 if seq_mode[b] == DLLM_SEQ_DENSE.  No mask, no positional term.  idx need not be
  * sorted and may repeat a row (it then counts twice).  A sequence with nothing to attend to
  * (k_b == 0 sparse, or L_b == 0 dense) gets zeros.  Scores, softmax state and accumulators are
- * fp32; bf16 inputs are multiplied on the matrix cores, fp32 inputs with fp32 arithmetic.
+ * fp32; bf16 inputs are multiplied on the matrix cores, fp32 inputs with fp32 arithmetic.  Before they are
+ * normalised, probabilities may reach 2^8 with bf16 inputs and 1 with fp32 inputs, and the sums over the rows of their
+ * products with V have to stay below 2^128.
  *
  * seq_mode may be NULL (all sparse).  cu_k may be NULL only if total_k == 0; every sequence not flagged
  * dense then counts as keeping nothing and gets zeros.  idx == NULL with

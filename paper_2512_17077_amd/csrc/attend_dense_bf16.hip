@@ -34,7 +34,7 @@
 //     kDenseHeadroom) behind one uniform branch per iteration.  When it is raised after iteration j, the
 //     row sums are rescaled at once; the output accumulators, which still have to take P(j) V(j) at the
 //     old scale during iteration j+1, are rescaled one iteration later.
-//   - The loop is unrolled over one turn of the rings (eight steps), so every LDS address is a register
+//   - The loop is unrolled over one turn of the rings (eight steps, four in the split form), so every LDS address is a register
 //     fixed before the loop plus an immediate offset.
 #include <algorithm>
 #include <cfloat>

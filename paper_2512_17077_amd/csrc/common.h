@@ -28,7 +28,11 @@ struct Shape {
 // 9.66 / 19.0 against 9.23 / 18.65 us, 21 MB 12.6 / 22.3 against 12.2 / 21.2, 42 MB 16.3 / 26.7 against 16.2 / 25.8, 34 MB
 // under grouped queries 16.9 / 29.4 against 16.7 / 28.0; but the stream itself loses from 100 MB on (34.1 against 35.1 us;
 // at 168 MB 38.4 against 41.8), the gather from 260 MB on (33.1 against 36.2 us on the kept rows of 264 MB of K, while 101 MB
-// gains 55.4 -> 53.5 us a step, 168 MB 59.0 -> 57.4).
+// gains 55.4 -> 53.5 us a step, 168 MB 59.0 -> 57.4).  The two other kernels that read K always take the hint: the
+// one-launch selection (hint / none: K of 17 MB 19.3 / 19.3 us, 67 MB 37.3 / 39.9, 134 MB 59.2 / 65.1; a step 41.3 / 40.9, 89.5 /
+// 90.6, 157.1 / 154.4) and the Reuse kernel that walks several lists (attention / step over K of 25 MB 12.8 / 29.1
+// against 13.0 / 28.2, 50 MB 14.0 / 34.3 against 14.2 / 33.3, 126 MB 22.7 / 55.6 against 21.3 / 54.0, 264 MB 33.4 / 85.7
+// against 36.5 / 89.0: up to 3 % of a step are left there below 128 MB).
 inline int64_t k_bytes(const Shape& s, int es) { return int64_t(s.total_kv) * s.hkv * s.d * es; }
 inline bool streams_once(const Shape& s, int es) { return k_bytes(s, es) > (int64_t(64) << 20); }
 inline bool gathers_once(const Shape& s, int es) { return k_bytes(s, es) > (int64_t(128) << 20); }
