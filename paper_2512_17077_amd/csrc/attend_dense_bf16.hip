@@ -55,6 +55,7 @@ constexpr int kDenseQB = 2;          // 32-query blocks per wave
 constexpr int dense_rows(int ks) { return kDenseWaves * kDenseQB * 32 / ks; }
 
 typedef __attribute__((ext_vector_type(16))) int i32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // The state a wave carries through the key loop, bound to the registers the step text of
 // attend_dense_step.inc names.
@@ -64,7 +65,7 @@ typedef __attribute__((ext_vector_type(16))) int i32x16;
 //   v[160:175], v[176:191]   pb_a, pb_b   packed probabilities of two consecutive steps, [qb][u][4]
 //   v[192 : 192 + 4*NT)      kop   K operands of the next score chain, [t][4]
 //   v[80:95]                 addr  LDS byte addresses: K operand [t], then V^T operand [rd][db] from +8
-//   a[.. + 16*2)             ls    row-sum blocks [qb][16] (only row 0 is used)
+//   a[.. + 4*2)              ls    row sums [qb][4] (only the first register is used)
 //   v72 .. v75               nmz[2] (= -m z per block), mx[2] (lane maxima of the newest scores)
 //   v[76:79], v[224:255]     scratch of a step (logits in flight, V^T operand buffers)
 // C++ code may read and write the v-register variables between steps like any others, and may write q;
@@ -94,16 +95,18 @@ struct DenseTileLoad {
       "=v"(x[16 * (k) + 8]), "=v"(x[16 * (k) + 9]), "=v"(x[16 * (k) + 10]), "=v"(x[16 * (k) + 11]),               \
       "=v"(x[16 * (k) + 12]), "=v"(x[16 * (k) + 13]), "=v"(x[16 * (k) + 14]), "=v"(x[16 * (k) + 15])
 
-// Row sums are taken on the matrix cores: one more accumulator block per query block (ls) takes P^T times
-// a matrix whose first row is ones (the operand `ones`: lanes 0 and 32 hold eight bf16 ones, the others
-// zeros), so row 0 of that block (register 0 of lanes 0..31) is the sum of the bf16 probabilities of the
-// lane's query -- the same values the P V product multiplies, added in fp32 like its terms.  The vector
-// form (unpack each packed pair with a shift and a mask, two adds) costs four vector instructions per pair
-// of scores, a third of the step's vector work; v_dot2c_f32_bf16 does it in one but runs on the matrix
-// pipe and holds back the MFMAs (+18 cycles per MFMA), and summing the unrounded values is off by up to
-// 2^-8 of a row that one key rules.  Measured: 2 % of the launch.
-#define DLLM_LS_OUT_128 "={a[192:207]}"(ls[0]), "={a[208:223]}"(ls[1])
-#define DLLM_LS_OUT_64 "={a[96:111]}"(ls[0]), "={a[112:127]}"(ls[1])
+// Row sums are taken on the matrix cores: the bf16 probabilities of the lane's query, the same values the P V
+// product multiplies, added in fp32 like its terms.  A v_mfma_f32_16x16x32_bf16 does it for a block of 32 queries
+// and 16 keys: read as its B operand, the registers of P^T hold query c in column c % 16, with keys in contraction
+// slots 0..7 and 16..23 if c < 16, in the other slots if not.  The A operand (`ones`) has bf16 ones in row 0 for the
+// first kind and in row 4 for the second, so the four accumulators (ls) hold the sum of query c in the first register of
+// lane c and zeros elsewhere.  (A 32x32x16 product with one row of ones takes twice the matrix time: 494 -> 481 us on
+// eight sequences of 2048, 32 heads x 128, and 28 a-registers more.)  The vector form (unpack each packed pair with a
+// shift and a mask, two adds) costs four vector instructions per pair of scores, a third of the step's vector work;
+// v_dot2c_f32_bf16 does it in one but runs on the matrix pipe and holds back the MFMAs (+18 cycles per MFMA), and summing
+// the unrounded values is off by up to 2^-8 of a row that one key rules.
+#define DLLM_LS_OUT_128 "={a[192:195]}"(ls[0]), "={a[196:199]}"(ls[1])
+#define DLLM_LS_OUT_64 "={a[96:99]}"(ls[0]), "={a[100:103]}"(ls[1])
 #define DLLM_LS_TIED(a, b) a(ls[0]), b(ls[1])
 
 // One step: AB reads the scores st_a and the probabilities pb_b and leaves the next scores in st_b and its own
@@ -140,7 +143,7 @@ template <>
 struct DenseState<128> {
   static constexpr int kAcc = 128;   // accumulator registers
   f32x16 acc[8], q[4], st_a[2], st_b[2], kop[2], pb_a, pb_b;
-  f32x16 ls[2];   // row sums (a-registers behind the queries, see above)
+  f32x4 ls[2];   // row sums (a-registers behind the queries, see above)
   v4u ones;
   float nmz[2], mx[2];   // v72, v73 (= -m z per block); v74, v75 (lane maxima of the newest scores)
   i32x16 addr;
@@ -181,8 +184,8 @@ struct DenseState<128> {
                  : "{v[192:207]}"(kop[0]), "{v[208:223]}"(kop[1]), DLLM_Q_IN);
   }
   __device__ __forceinline__ void row_sums(float& l0, float& l1) {
-    asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a192\n\tv_accvgpr_read_b32 %1, a208"
-                 : "=v"(l0), "=v"(l1) : "{a[192:207]}"(ls[0]), "{a[208:223]}"(ls[1]));
+    asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a192\n\tv_accvgpr_read_b32 %1, a196"
+                 : "=v"(l0), "=v"(l1) : "{a[192:195]}"(ls[0]), "{a[196:199]}"(ls[1]));
   }
   __device__ __forceinline__ void acc_clear() { asm volatile(DLLM_DENSE_ACC_INIT_128 : DLLM_ACC_OUT, DLLM_LS_OUT_128); }
   // acc[qb] *= al[qb]; waits out the matrix pipe first (results may be read only 12 wait states after the
@@ -217,7 +220,7 @@ template <>
 struct DenseState<64> {
   static constexpr int kAcc = 64;
   f32x16 acc[4], q[2], st_a[2], st_b[2], kop[1], pb_a, pb_b;
-  f32x16 ls[2];   // row sums (a-registers behind the queries, see above)
+  f32x4 ls[2];   // row sums (a-registers behind the queries, see above)
   v4u ones;
   float nmz[2], mx[2];   // v72, v73 (= -m z per block); v74, v75 (lane maxima of the newest scores)
   i32x16 addr;
@@ -250,8 +253,8 @@ struct DenseState<64> {
                  : "{v[192:207]}"(kop[0]), DLLM_Q_IN);
   }
   __device__ __forceinline__ void row_sums(float& l0, float& l1) {
-    asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a96\n\tv_accvgpr_read_b32 %1, a112"
-                 : "=v"(l0), "=v"(l1) : "{a[96:111]}"(ls[0]), "{a[112:127]}"(ls[1]));
+    asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a96\n\tv_accvgpr_read_b32 %1, a100"
+                 : "=v"(l0), "=v"(l1) : "{a[96:99]}"(ls[0]), "{a[100:103]}"(ls[1]));
   }
   __device__ __forceinline__ void acc_clear() { asm volatile(DLLM_DENSE_ACC_INIT_64 : DLLM_ACC_OUT, DLLM_LS_OUT_64); }
   __device__ __forceinline__ void acc_scale(float al0, float al1) {
@@ -569,7 +572,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     palpha[qb] = 1.0f;
   }
   {
-    const uint32_t one2 = (lane & 31) == 0 ? 0x3f803f80u : 0u;
+    const uint32_t one2 = (lane & 31) == (lane & 4 ? 20 : 0) ? 0x3f803f80u : 0u;   // rows 0 and 4, see DLLM_LS_OUT_128
     w.ones = v4u{one2, one2, one2, one2};
   }
   w.acc_clear();
@@ -777,7 +780,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   return;   // the counts sit where outputs would go
 #endif
   float lrow[NQB];
-  w.row_sums(lrow[0], lrow[1]);   // lanes 0..31: the query's sum; lanes 32..63: row 4 of the block, zero
+  w.row_sums(lrow[0], lrow[1]);   // lanes 0..31: the query's sum; lanes 32..63: zero
   // Writes query block qb: accumulators `a` ([db][16]) over the row sum l.  A lane holds four elements of one row at a
   // time, so the block goes through LDS (`stage`, the wave's own 32 rows) and out in whole rows.
   auto store_block = [&](int qb, const float* a, float l, char* stage) __attribute__((always_inline)) {

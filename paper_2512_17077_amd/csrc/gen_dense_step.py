@@ -15,7 +15,7 @@ Run `python3 gen_dense_step.py` in this folder after changing the schedule; the 
 One step (iteration j) at D = 128, NQB = 2 blocks of 32 queries per wave:
     slots  0..15   S^T(j+1) = K(j+1) Q^T         MFMA(t, qb), K operand t shared by the two blocks
     slots 16..31   O^T += V(j-1)^T P(j-1)^T      MFMA(u, db, qb), V^T operand (u, db) shared likewise
-    slots 32..35   l += ones P(j-1)^T             row sums of the same probabilities, MFMA(u, qb)
+    slots 32..35   l += ones P(j-1)^T             row sums of the same probabilities, 16x16x32 MFMA(u, qb), half as long
     all slots      P(j) = exp2(S(j) z - m z)      on the scores of the previous step: per pair of scores
                                                    2 fma, 2 exp, 1 cvt_pk (-> bf16 x 2)
     slots 20..31   row maxima of S(j+1)           16 max / max3
@@ -67,7 +67,9 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
     n_pv = 2 * NDB * 2                     # P V MFMAs
     n_ls = 4                               # row-sum MFMAs
     nslots = n_s + n_pv + n_ls
-    LS = QR + 4 * NT * 2                   # a: ls[qb][16] after the queries
+    LS = QR + 4 * NT * 2                   # a: ls[qb][4] after the queries
+    # matrix-pipe time before each slot, in halves of a 32x32x16 product (a row-sum product takes one half)
+    at = [2 * s if s <= n_s + n_pv else n_s + n_pv + s for s in range(nslots + 1)]
 
     # ---- MFMAs per slot
     mfma = []
@@ -84,11 +86,11 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
                 a = ACC + 16 * (NDB * qb + db)
                 mfma.append((f"v_mfma_f32_32x32x16_bf16 {ar(a, 16)}, {vr(VOP + 4 * (p % NBUF), 4)}, "
                              f"{vr(pold + 4 * (2 * qb + u), 4)}, {ar(a, 16)}", ("v", p) if qb == 0 else None))
-    # row sums: row 0 of ones * P^T, accumulated like the outputs (the a-register blocks after the queries)
+    # row sums: rows 0 and 4 of ones * P^T, accumulated like the outputs (four a-registers each, after the queries)
     for u in range(2):
         for qb in range(2):
-            a = LS + 16 * qb
-            mfma.append((f"v_mfma_f32_32x32x16_bf16 {ar(a, 16)}, %[ones], {vr(pold + 4 * (2 * qb + u), 4)}, {ar(a, 16)}", None))
+            a = LS + 4 * qb
+            mfma.append((f"v_mfma_f32_16x16x32_bf16 {ar(a, 4)}, %[ones], {vr(pold + 4 * (2 * qb + u), 4)}, {ar(a, 4)}", None))
 
     # ---- LDS reads per slot: (text, tag)
     ds = [[] for _ in range(nslots)]
@@ -144,8 +146,8 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             ops += cvt + add0 + add1
         cvt, add0, add1 = finish(len(pairs) - 1)
         ops += ["s_nop 0"] + cvt + add0 + add1      # the nop keeps the last exp's result from being read at once
-        for s in range(nslots):   # evenly: about three per MFMA at D = 128
-            valu[s] += ops[s * len(ops) // nslots:(s + 1) * len(ops) // nslots]
+        for s in range(nslots):   # evenly over the matrix pipe's time: about three per MFMA at D = 128
+            valu[s] += ops[at[s] * len(ops) // at[-1]:at[s + 1] * len(ops) // at[-1]]
         # row maxima of the new scores, well after the S chain
         mops = []
         for i in range(8):
@@ -259,7 +261,7 @@ def gen_score0(D):
 def gen_acc_init(D):
     regs = list(range(16 * 2 * (D // 32)))
     ls = 16 * 2 * (D // 32) + 4 * (D // 16) * 2
-    regs += list(range(ls, ls + 32))        # the row-sum blocks behind the queries
+    regs += list(range(ls, ls + 8))         # the row sums behind the queries
     return [f"v_accvgpr_write_b32 a{i}, 0" for i in regs]
 
 
@@ -273,10 +275,10 @@ def gen_acc_scale(D):
             lines += [f"v_accvgpr_read_b32 {vr(TMP + c)}, a{r}" for c, r in enumerate(regs)]
             lines += [f"v_mul_f32_e32 {vr(TMP + c)}, %[al{qb}], {vr(TMP + c)}" for c in range(4)]
             lines += [f"v_accvgpr_write_b32 a{r}, {vr(TMP + c)}" for c, r in enumerate(regs)]
-    ls = 2 * n + 4 * (D // 16) * 2   # the row sums: only row 0 of each block is ever non-zero
+    ls = 2 * n + 4 * (D // 16) * 2   # the row sums: only the first register of each four is ever non-zero
     for qb in range(2):
-        lines += [f"v_accvgpr_read_b32 {vr(TMP)}, a{ls + 16 * qb}", f"v_mul_f32_e32 {vr(TMP)}, %[al{qb}], {vr(TMP)}",
-                  f"v_accvgpr_write_b32 a{ls + 16 * qb}, {vr(TMP)}"]
+        lines += [f"v_accvgpr_read_b32 {vr(TMP)}, a{ls + 4 * qb}", f"v_mul_f32_e32 {vr(TMP)}, %[al{qb}], {vr(TMP)}",
+                  f"v_accvgpr_write_b32 a{ls + 4 * qb}, {vr(TMP)}"]
     lines += ["s_nop 7"]
     return lines
 
@@ -289,7 +291,7 @@ def gen_acc_read(k):
 def main():
     out = ["// Generated by gen_dense_step.py -- do not edit by hand.  One 32-key step of the dense Refresh kernel as",
            "// inline-assembly text over a fixed register map; see the generator for the schedule and the map.",
-           "// Named operands: %[ones] (four v-registers: the A operand whose first row is bf16 ones), %[zs] (softmax_scale * log2 e, scalar), %[koff] (byte offset of the K rows fetched",
+           "// Named operands: %[ones] (four v-registers: the A operand of the row sums), %[zs] (softmax_scale * log2 e, scalar), %[koff] (byte offset of the K rows fetched",
            "// for step j+2), %[voff0], %[voff1] (byte offsets of the V rows of step j-1, keys 0..15 and 16..31),",
            "// %[grow] (out, scalar pair: lanes whose newest scores outgrew the running maximum by more than %[lazy]);",
            "// in the _AB text (the first step of a tile) also %[kt], %[vt] (scalar pairs: first K / V row of the tile",
