@@ -20,7 +20,7 @@ BUILD_DIR = os.path.join(_HERE, "_build")
 LIB_PATH = os.path.join(_HERE, "libdllm_hcsa.so")
 
 SOURCES = ["api.hip", "checks.hip", "select_kernels.hip", "pack_kernels.hip", "attend_f32.hip",
-           "attend_sparse_bf16.hip", "attend_dense_bf16.hip"]
+           "attend_sparse_bf16.hip", "attend_dense_bf16.hip", "attend_dense_paired_bf16.hip"]
 # the same sources with the device-side precondition checks compiled in (a debugging aid, see include/dllm_hcsa.h)
 LIB_PATH_CHECKED = os.path.join(_HERE, "libdllm_hcsa_checked.so")
 CHECKED_FLAGS = ["-DDLLM_CHECK_PRECONDITIONS"]

@@ -1,6 +1,7 @@
 // Refresh-phase attention (Section 2.3, Eq. 3): dense bidirectional softmax attention, bf16 inputs,
 // fp32 softmax state and accumulators, on the gfx950 matrix cores.  This path is a dense
 // contraction (4*Lq*Lkv*D flop per head against O(L*D) bytes), so it is bound by MFMA throughput.
+// This file holds the kernel for head_dim D = 128; attend_dense_paired_bf16.hip the one for 64.
 //
 // Shape of the kernel
 //   - A workgroup is four waves, one per SIMD, and owns 256 query rows of one (sequence, head); a wave
@@ -42,7 +43,7 @@
 #include <type_traits>
 #include <utility>
 
-#include "attn_tile.h"
+#include "attend_dense.h"
 #include "attend_dense_step.inc"
 
 namespace dllm {
@@ -72,13 +73,11 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // the accumulators are only ever handed from one assembly block to the next (this compiler cannot take
 // single elements out of an a-register tuple that an assembly block has written), so clearing,
 // rescaling and reading them are assembly blocks too.
-template <int D>
-struct DenseState;
 
 // What the first step of a tile needs to request the tile two ahead: the tile's first K and V row
 // (wave-uniform), the byte offset of each of this lane's 16-byte chunks from there, and the LDS address
 // of this wave's slice of a load round.
-template <int NLD>
+constexpr int NLD = 4;   // 16-byte loads per lane, tile and tensor
 struct DenseTileLoad {
   const char *k, *v;
   uint32_t off[NLD];
@@ -105,15 +104,14 @@ struct DenseTileLoad {
 // shift and a mask, two adds) costs four vector instructions per pair of scores, a third of the step's vector work;
 // v_dot2c_f32_bf16 does it in one but runs on the matrix pipe and holds back the MFMAs (+18 cycles per MFMA), and summing
 // the unrounded values is off by up to 2^-8 of a row that one key rules.
-#define DLLM_LS_OUT_128 "={a[192:195]}"(ls[0]), "={a[196:199]}"(ls[1])
-#define DLLM_LS_OUT_64 "={a[96:99]}"(ls[0]), "={a[100:103]}"(ls[1])
+#define DLLM_LS_OUT "={a[192:195]}"(ls[0]), "={a[196:199]}"(ls[1])
 #define DLLM_LS_TIED(a, b) a(ls[0]), b(ls[1])
 
 // One step: AB reads the scores st_a and the probabilities pb_b and leaves the next scores in st_b and its own
 // probabilities in pb_a, BA the other way round.  Split: the texts in which every step requests a tile.
-#define DLLM_STEP_FUNCTION(D, NLD)                                                                                  \
+#define DLLM_STEP_FUNCTION(D)                                                                                       \
   template <bool AB, bool Split, int KOFF, int VOFF0, int VOFF1, int LK, int LV>                                    \
-  __device__ __forceinline__ void step(float zs, const DenseTileLoad<NLD>& tl, uint64_t& grow) {                    \
+  __device__ __forceinline__ void step(float zs, const DenseTileLoad& tl, uint64_t& grow) {                    \
     if constexpr (AB && Split)                                                                                      \
       asm volatile(DLLM_DENSE_STEP_##D##_AB_SPLIT                                                                   \
                    : DLLM_STEP_OUT("={v[128:143]}"(st_b[0]), "={v[144:159]}"(st_b[1]), "={v[160:175]}"(pb_a))        \
@@ -139,8 +137,7 @@ struct DenseTileLoad {
                    : "memory", DLLM_DENSE_SCRATCH);                                                                 \
   }
 
-template <>
-struct DenseState<128> {
+struct DenseState {
   static constexpr int kAcc = 128;   // accumulator registers
   f32x16 acc[8], q[4], st_a[2], st_b[2], kop[2], pb_a, pb_b;
   f32x4 ls[2];   // row sums (a-registers behind the queries, see above)
@@ -156,7 +153,7 @@ struct DenseState<128> {
       "{a[80:95]}"(acc[5]), "{a[96:111]}"(acc[6]), "{a[112:127]}"(acc[7])
 #define DLLM_Q_IN "{a[128:143]}"(q[0]), "{a[144:159]}"(q[1]), "{a[160:175]}"(q[2]), "{a[176:191]}"(q[3])
 #define DLLM_STEP_OUT(st0, st1, pb) DLLM_ACC_OUT, st0, st1, pb, "={v[192:207]}"(kop[0]), "={v[208:223]}"(kop[1]), \
-      DLLM_LS_OUT_128, "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
+      DLLM_LS_OUT, "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
 #define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "11"(kop[0]), "12"(kop[1]), DLLM_LS_TIED("13", "14"),          \
       [ones] "v"(ones), "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr),             \
       [zs] "s"(zs), [lazy] "s"(kLazyGrowthDense), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
@@ -164,7 +161,7 @@ struct DenseState<128> {
       [lo2] "v"(tl.off[2]), [lo3] "v"(tl.off[3]), [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
 #define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1]),                     \
       [vo2] "v"(tl.off_v[2]), [vo3] "v"(tl.off_v[3])
-  DLLM_STEP_FUNCTION(128, 4)
+  DLLM_STEP_FUNCTION(128)
 #undef DLLM_STEP_OUT
 #undef DLLM_STEP_IN
 #undef DLLM_STEP_LOADS
@@ -173,7 +170,7 @@ struct DenseState<128> {
   // offset added to the V^T operand addresses (it is not a compile-time constant here)
   __device__ __forceinline__ void tail(i32x16 ad) {
     asm volatile(DLLM_DENSE_TAIL_128
-                 : DLLM_ACC_OUT, DLLM_LS_OUT_128
+                 : DLLM_ACC_OUT, DLLM_LS_OUT
                  : DLLM_ACC_TIED, DLLM_LS_TIED("8", "9"), [ones] "v"(ones), "{v[160:175]}"(pb_a), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 256)
                  : "memory", DLLM_DENSE_SCRATCH);
   }
@@ -187,11 +184,11 @@ struct DenseState<128> {
     asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a192\n\tv_accvgpr_read_b32 %1, a196"
                  : "=v"(l0), "=v"(l1) : "{a[192:195]}"(ls[0]), "{a[196:199]}"(ls[1]));
   }
-  __device__ __forceinline__ void acc_clear() { asm volatile(DLLM_DENSE_ACC_INIT_128 : DLLM_ACC_OUT, DLLM_LS_OUT_128); }
+  __device__ __forceinline__ void acc_clear() { asm volatile(DLLM_DENSE_ACC_INIT_128 : DLLM_ACC_OUT, DLLM_LS_OUT); }
   // acc[qb] *= al[qb]; waits out the matrix pipe first (results may be read only 12 wait states after the
   // MFMA was issued, and nothing but software enforces it)
   __device__ __forceinline__ void acc_scale(float al0, float al1) {
-    asm volatile(DLLM_DENSE_ACC_SCALE_128 : DLLM_ACC_OUT, DLLM_LS_OUT_128 : DLLM_ACC_TIED, DLLM_LS_TIED("8", "9"), [al0] "v"(al0), [al1] "v"(al1) : DLLM_DENSE_SCRATCH);
+    asm volatile(DLLM_DENSE_ACC_SCALE_128 : DLLM_ACC_OUT, DLLM_LS_OUT : DLLM_ACC_TIED, DLLM_LS_TIED("8", "9"), [al0] "v"(al0), [al1] "v"(al1) : DLLM_DENSE_SCRATCH);
   }
   // all accumulators of block qb, head_dim block db, after the matrix pipe has drained
   __device__ __forceinline__ void acc_read(float (&x)[kAcc]) {
@@ -216,67 +213,6 @@ struct DenseState<128> {
   __device__ __forceinline__ void kop_set(int t, int c, float x) { kop[t / 4][4 * (t % 4) + c] = x; }
 };
 
-template <>
-struct DenseState<64> {
-  static constexpr int kAcc = 64;
-  f32x16 acc[4], q[2], st_a[2], st_b[2], kop[1], pb_a, pb_b;
-  f32x4 ls[2];   // row sums (a-registers behind the queries, see above)
-  v4u ones;
-  float nmz[2], mx[2];   // v72, v73 (= -m z per block); v74, v75 (lane maxima of the newest scores)
-  i32x16 addr;
-#define DLLM_ACC_OUT "={a[0:15]}"(acc[0]), "={a[16:31]}"(acc[1]), "={a[32:47]}"(acc[2]), "={a[48:63]}"(acc[3])
-#define DLLM_ACC_TIED "0"(acc[0]), "1"(acc[1]), "2"(acc[2]), "3"(acc[3])
-#define DLLM_ACC_IN "{a[0:15]}"(acc[0]), "{a[16:31]}"(acc[1]), "{a[32:47]}"(acc[2]), "{a[48:63]}"(acc[3])
-#define DLLM_Q_IN "{a[64:79]}"(q[0]), "{a[80:95]}"(q[1])
-#define DLLM_STEP_OUT(st0, st1, pb) DLLM_ACC_OUT, st0, st1, pb, "={v[192:207]}"(kop[0]), DLLM_LS_OUT_64,             \
-      "={v74}"(mx[0]), "={v75}"(mx[1]), [grow] "=s"(grow)
-#define DLLM_STEP_IN(st0, st1, pb) DLLM_ACC_TIED, "7"(kop[0]), DLLM_LS_TIED("8", "9"), [ones] "v"(ones),            \
-      "{v72}"(nmz[0]), "{v73}"(nmz[1]), DLLM_Q_IN, st0, st1, pb, "{v[80:95]}"(addr), [zs] "s"(zs),                  \
-      [lazy] "s"(kLazyGrowthDense), [koff] "n"(KOFF), [voff0] "n"(VOFF0), [voff1] "n"(VOFF1)
-#define DLLM_STEP_LOADS [kt] "s"(tl.k), [vt] "s"(tl.v), [lo0] "v"(tl.off[0]), [lo1] "v"(tl.off[1]),                \
-      [wl] "s"(tl.wave_lds), [lk] "n"(LK), [lv] "n"(LV)
-#define DLLM_STEP_LOADS_SPLIT DLLM_STEP_LOADS, [vo0] "v"(tl.off_v[0]), [vo1] "v"(tl.off_v[1])
-  DLLM_STEP_FUNCTION(64, 2)
-#undef DLLM_STEP_OUT
-#undef DLLM_STEP_IN
-#undef DLLM_STEP_LOADS
-#undef DLLM_STEP_LOADS_SPLIT
-  __device__ __forceinline__ void tail(i32x16 ad) {
-    asm volatile(DLLM_DENSE_TAIL_64
-                 : DLLM_ACC_OUT, DLLM_LS_OUT_64
-                 : DLLM_ACC_TIED, DLLM_LS_TIED("4", "5"), [ones] "v"(ones), "{v[160:175]}"(pb_a), "{v[80:95]}"(ad), [voff0] "n"(0), [voff1] "n"(16 * 128)
-                 : "memory", DLLM_DENSE_SCRATCH);
-  }
-  __device__ __forceinline__ void score0() {
-    asm volatile(DLLM_DENSE_SCORE0_64
-                 : "={v[96:111]}"(st_a[0]), "={v[112:127]}"(st_a[1])
-                 : "{v[192:207]}"(kop[0]), DLLM_Q_IN);
-  }
-  __device__ __forceinline__ void row_sums(float& l0, float& l1) {
-    asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a96\n\tv_accvgpr_read_b32 %1, a100"
-                 : "=v"(l0), "=v"(l1) : "{a[96:99]}"(ls[0]), "{a[100:103]}"(ls[1]));
-  }
-  __device__ __forceinline__ void acc_clear() { asm volatile(DLLM_DENSE_ACC_INIT_64 : DLLM_ACC_OUT, DLLM_LS_OUT_64); }
-  __device__ __forceinline__ void acc_scale(float al0, float al1) {
-    asm volatile(DLLM_DENSE_ACC_SCALE_64 : DLLM_ACC_OUT, DLLM_LS_OUT_64 : DLLM_ACC_TIED, DLLM_LS_TIED("4", "5"), [al0] "v"(al0), [al1] "v"(al1) : DLLM_DENSE_SCRATCH);
-  }
-  __device__ __forceinline__ void acc_read(float (&x)[kAcc]) {
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-    asm volatile(DLLM_DENSE_ACC_READ_0 : DLLM_R16(0, x) : DLLM_ACC_IN);
-    asm volatile(DLLM_DENSE_ACC_READ_1 : DLLM_R16(1, x) : DLLM_ACC_IN);
-    asm volatile(DLLM_DENSE_ACC_READ_2 : DLLM_R16(2, x) : DLLM_ACC_IN);
-    asm volatile(DLLM_DENSE_ACC_READ_3 : DLLM_R16(3, x) : DLLM_ACC_IN);
-  }
-#undef DLLM_ACC_OUT
-#undef DLLM_ACC_TIED
-#undef DLLM_ACC_IN
-#undef DLLM_Q_IN
-  __device__ __forceinline__ float q_get(int qb, int t, int c) const { return q[qb][4 * t + c]; }
-  __device__ __forceinline__ void q_set(int qb, int t, int c, float x) { q[qb][4 * t + c] = x; }
-  __device__ __forceinline__ float kop_get(int t, int c) const { return kop[0][4 * t + c]; }
-  __device__ __forceinline__ void kop_set(int t, int c, float x) { kop[0][4 * t + c] = x; }
-};
-
 // f(integral_constant<int, 0>), f(integral_constant<int, 1>), ... in order
 template <typename F, int... C>
 __device__ __forceinline__ void for_each_round(F& f, std::integer_sequence<int, C...>) {
@@ -285,19 +221,19 @@ __device__ __forceinline__ void for_each_round(F& f, std::integer_sequence<int, 
 
 // which: 1 = only sequences flagged dense in seq_mode; 2 = every sequence
 // KS: wave groups that share the keys (1 or 2; see launch_attend_dense_bf16 for which calls take which)
-template <int D, int KS>
+template <int KS>
 __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv, const uint8_t* __restrict__ seq_mode,
     int which, uint16_t* __restrict__ o, Shape s DLLM_CHECK_PARAM) {
   DLLM_CHECK_EXIT();
   constexpr int NQB = kDenseQB;
+  constexpr int D = 128;
   constexpr int CH = D / 8;
   constexpr int ROWB = 2 * D;
   constexpr int TILEB = kDenseK * ROWB;
   constexpr int VBASE = kDenseRing * TILEB;      // V ring follows the K ring
   constexpr int NTHREADS = kDenseWaves * 64;
-  constexpr int NLD = kDenseK * CH / NTHREADS;   // 16-byte loads per lane, tile and tensor
   constexpr int NT = D / 16;
   constexpr int NDB = D / 32;
   constexpr int SPT = 2 / KS;                    // steps a wave takes per tile
@@ -307,110 +243,19 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   // a ring turn that starts with fewer steps than this left (or the step after it) reaches the last tile
   constexpr int NEAR_END = KS == 1 ? 2 * ROUND : 2 * ROUND + 2;
   constexpr int kDenseRows = dense_rows(KS);
-  static_assert(NLD >= 1 && kDenseK * CH % NTHREADS == 0, "tile does not split evenly over the threads");
+  static_assert(NLD * NTHREADS == kDenseK * CH, "the loads of a tile");
   static_assert(kDenseRing * TILEB <= 65536, "ring offsets must fit the 16-bit LDS offset field");
 
   // K ring, V ring, and 64 rows more: the queries pass through LDS too (see below), one slot per wave that has its own
   __shared__ __attribute__((aligned(16))) char smem[(2 * kDenseRing + 1) * TILEB];
 
-  // Which query tile of which (sequence, head) this workgroup takes.
-  //
-  // Batches of up to 64 sequences are launched as a one-dimensional grid with just enough workgroups for the
-  // query tiles the batch can have (the host bounds their number from total_q), and every workgroup finds
-  // its tile itself: lane i looks at sequence i, a prefix sum over the tiles of the sequences that are
-  // attended densely places the workgroup.  A mixed batch then starts no workgroups for its sparse
-  // sequences, and a ragged one none for the query tiles short sequences do not have (an empty workgroup
-  // holds a whole compute unit until it has found out that it is empty).  Larger batches use the
-  // three-dimensional grid (query tile, head, sequence) with an early exit.
-  //
-  // Workgroups are handed to the eight XCDs round-robin by launch order, and each XCD has its own L2.
-  // The numbering is such that the workgroups that stream the same K/V -- the query tiles of the query
-  // heads that share one KV head of one sequence -- land on one XCD (launch ids equal modulo 8) and
-  // share its L2, while consecutive (sequence, KV head) pairs go to different XCDs.
-  int qtile, h, b, q0, nq, kv0, L;
-  if (gridDim.y == 1 && gridDim.z == 1) {
-    const int lane0 = threadIdx.x & 63;
-    int my_q0 = 0, my_nq = 0, my_kv0 = 0, my_L = 0, my_tiles = 0;
-    if (lane0 < s.batch) {
-      my_q0 = cu_q[lane0];
-      my_nq = cu_q[lane0 + 1] - my_q0;
-      my_kv0 = cu_kv[lane0];
-      my_L = cu_kv[lane0 + 1] - my_kv0;
-      const bool dense = which == 2 || (seq_mode != nullptr && seq_mode[lane0] == DLLM_SEQ_DENSE);
-      my_tiles = dense ? (my_nq + kDenseRows - 1) / kDenseRows : 0;
-    }
-    // Longest sequences first: a workgroup lasts as long as its sequence has keys, and with the long ones at the
-    // end of the launch most compute units wait for a few (seven sequences of 537 to 2076 keys, 16 heads x 64:
-    // 82.9 us in batch order, 81.2 us longest first; 83.1 and 79.2 on another card).  Lane i goes on with the sequence of rank i among the densely
-    // attended ones; equal lengths need no ranking.
-    const uint64_t with_tiles = __builtin_amdgcn_ballot_w64(my_tiles != 0);
-    const int first_L = with_tiles != 0 ? __builtin_amdgcn_readlane(my_L, __builtin_ctzll(with_tiles)) : 0;
-    if (__builtin_amdgcn_ballot_w64(my_tiles != 0 && my_L != first_L) != 0) {
-      const int key = my_tiles != 0 ? my_L : -1;
-      int rank = lane0 < s.batch ? 0 : lane0;   // lanes past the batch stay where they are
-      for (int i = 0; i < s.batch; ++i) {
-        const int other = __builtin_amdgcn_readlane(key, i);
-        if (lane0 < s.batch) rank += other > key || (other == key && i < lane0) ? 1 : 0;
-      }
-      my_q0 = __builtin_amdgcn_ds_permute(rank * 4, my_q0);
-      my_nq = __builtin_amdgcn_ds_permute(rank * 4, my_nq);
-      my_kv0 = __builtin_amdgcn_ds_permute(rank * 4, my_kv0);
-      my_L = __builtin_amdgcn_ds_permute(rank * 4, my_L);
-      my_tiles = __builtin_amdgcn_ds_permute(rank * 4, my_tiles);
-    }
-    const int incl = int(wave_inclusive_sum(uint32_t(my_tiles)));
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    const int n = blockIdx.x;
-    int place;   // position of the tile in (sequence, tile) order, times what follows
-    uint64_t m;
-    if ((s.hkv & 7) == 0) {
-      // XCD x = n % 8 takes KV heads x, x + 8, ...; within the XCD: sequence, KV head, query head of its group, tile
-      const int per_seq = s.group * (s.hkv >> 3);
-      place = n >> 3;
-      if (place >= total * per_seq) return;
-      m = __builtin_amdgcn_ballot_w64(incl * per_seq > place);
-      b = __builtin_ctzll(m);
-      const int tb = __builtin_amdgcn_readlane(my_tiles, b);
-      const int rem = place - (__builtin_amdgcn_readlane(incl, b) - tb) * per_seq;
-      const int per_head_group = tb * s.group;
-      const int kvh = (rem / per_head_group) * 8 + (n & 7), r = rem % per_head_group;
-      qtile = r % tb;
-      h = kvh * s.group + r / tb;
-    } else {
-      place = n / s.hq;
-      h = n % s.hq;
-      if (place >= total) return;
-      m = __builtin_amdgcn_ballot_w64(incl > place);
-      b = __builtin_ctzll(m);
-      qtile = place - (__builtin_amdgcn_readlane(incl, b) - __builtin_amdgcn_readlane(my_tiles, b));
-    }
-    q0 = __builtin_amdgcn_readlane(my_q0, b);
-    nq = __builtin_amdgcn_readlane(my_nq, b);
-    kv0 = __builtin_amdgcn_readlane(my_kv0, b);
-    L = __builtin_amdgcn_readlane(my_L, b);
-  } else {
-    const int nx = gridDim.x, units = s.hkv * gridDim.z;
-    const int n = blockIdx.x + nx * (blockIdx.y + gridDim.y * blockIdx.z);
-    qtile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    if ((units & 7) == 0) {
-      const int per_unit = s.group * nx;
-      const int j = n >> 3;   // position in this XCD's own launch sequence
-      const int r = j % per_unit, unit = (j / per_unit) * 8 + (n & 7);
-      qtile = r % nx;
-      h = (unit % s.hkv) * s.group + r / nx;
-      b = unit / s.hkv;
-    }
-    if (which == 1 && !(seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE)) return;
-    q0 = cu_q[b];
-    nq = cu_q[b + 1] - q0;
-    kv0 = cu_kv[b];
-    L = cu_kv[b + 1] - kv0;
-  }
-  const int qbase = qtile * kDenseRows;
-  if (qbase >= nq) return;
+  DensePlace at;
+  if (!place_dense<kDenseRows>(s, cu_q, cu_kv, seq_mode, which, at)) return;
+  const int h = at.h, q0 = at.q0, nq = at.nq, kv0 = at.kv0, L = at.L;
+  const int qbase = at.qtile * kDenseRows;
   const int g = h / s.group;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int col = lane & 31, hf = lane >> 5;
+  const int hf = lane >> 5;
   // the query blocks this wave takes, and which half of every tile's keys (0 when all waves take both)
   const int qwave = KS == 1 ? wave : wave & 1;
   const int part = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave >> 1);
@@ -447,10 +292,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #endif
 
   if (L == 0) {   // nothing to attend to: zeros
-    for (int e = tid; e < kDenseRows * D; e += NTHREADS) {
-      const int r = qbase + e / D;
-      if (r < nq) o[(int64_t(q0 + r) * s.hq + h) * D + e % D] = 0;
-    }
+    zero_dense_rows<D>(qbase, kDenseRows, at, s.hq, o);
     return;
   }
 
@@ -458,7 +300,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   const char* vbase = reinterpret_cast<const char*>(v + int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head);
   const int64_t pitch = s.kv_tok * 2;
 
-  DenseState<D> w;
+  DenseState w;
   // LDS addresses, fixed for the whole pass; ring slot, 32-key half and 16-key quarter are immediates
   {
     KAddr<D> kaddr;
@@ -572,7 +414,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     palpha[qb] = 1.0f;
   }
   {
-    const uint32_t one2 = (lane & 31) == (lane & 4 ? 20 : 0) ? 0x3f803f80u : 0u;   // rows 0 and 4, see DLLM_LS_OUT_128
+    const uint32_t one2 = (lane & 31) == (lane & 4 ? 20 : 0) ? 0x3f803f80u : 0u;   // rows 0 and 4, see DLLM_LS_OUT
     w.ones = v4u{one2, one2, one2, one2};
   }
   w.acc_clear();
@@ -610,7 +452,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   // the last tile the last one is requested again, into a ring slot nobody reads any more.
   const int64_t tile_bytes = int64_t(kDenseK) * pitch;
   const bool last_whole = ntiles * kDenseK == L;
-  DenseTileLoad<NLD> tl;
+  DenseTileLoad tl;
   tl.wave_lds = wave_lds;
   int64_t advance_k, advance_v;   // what the pointers move by after a tile's first step; 0 once they reached the last tile
   auto aim_loads = [&](int tile) __attribute__((always_inline)) {   // for the requests of `tile`'s first step
@@ -765,7 +607,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #ifdef DLLM_DENSE_STAMPS
   const uint64_t t_loop1 = __builtin_readcyclecounter();
 #endif
-  float accv[DenseState<D>::kAcc];   // [qb][db][16]
+  float accv[DenseState::kAcc];   // [qb][db][16]
   w.acc_read(accv);
 #ifdef DLLM_DENSE_STAMPS
   if (tid == 0) {
@@ -781,98 +623,42 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #endif
   float lrow[NQB];
   w.row_sums(lrow[0], lrow[1]);   // lanes 0..31: the query's sum; lanes 32..63: zero
-  // Writes query block qb: accumulators `a` ([db][16]) over the row sum l.  A lane holds four elements of one row at a
-  // time, so the block goes through LDS (`stage`, the wave's own 32 rows) and out in whole rows.
-  auto store_block = [&](int qb, const float* a, float l, char* stage) __attribute__((always_inline)) {
-    const float inv = 1.0f / l;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        v2u w2;
-        const float* x = a + 16 * db + 4 * i4;
-        w2.x = cvt_pk_bf16(x[0] * inv, x[1] * inv);
-        w2.y = cvt_pk_bf16(x[2] * inv, x[3] * inv);
-        *reinterpret_cast<v2u*>(stage + tile_off<D>(col, 4 * db + i4) + 8 * hf) = w2;
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int i = 0; i < 32 * CH / 64; ++i) {
-      const int f = i * 64 + lane, r = f / CH, c = f % CH;
-      const int qi = qbase + (qwave * NQB + qb) * 32 + r;
-      if (qi < nq)
-        *reinterpret_cast<v4u*>(o + (int64_t(q0 + qi) * s.hq + h) * D + c * 8) =
-            *reinterpret_cast<const v4u*>(stage + tile_off<D>(r, c));
-    }
-  };
   wait_tile_loads();   // the requests past the last tile still write to the rings, which are now space for the outputs
   __syncthreads();
   if constexpr (KS == 1) {
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) store_block(qb, accv + 16 * NDB * qb, sum_across_halves(lrow[qb]), smem + (NQB * wave + qb) * 32 * ROWB);
+    for (int qb = 0; qb < NQB; ++qb) 
+      store_dense_block<D>(accv + 16 * NDB * qb, sum_across_halves(lrow[qb]), smem + (NQB * wave + qb) * 32 * ROWB,
+                           qbase + (qwave * NQB + qb) * 32, at, s.hq, o);
   } else {
-    // Two waves hold (m, l, O) of the same queries over different keys: each finishes the block with its own number
-    // (`part`) and hands the other one over through LDS.
     static_assert(NQB == 2 && kDenseWaves == 4, "two wave pairs, two blocks each");
-    constexpr int kBlock = NDB * 4 * 64;   // float4s of one block
-    float4* mrg = reinterpret_cast<float4*>(smem);                              // [wave][db][i4][lane]
-    float* ml = reinterpret_cast<float*>(smem + kDenseWaves * kBlock * 16);     // [wave][m: 32 | l: 32]
-    static_assert(kDenseWaves * kBlock * 16 + kDenseWaves * 64 * 4 <= 2 * kDenseRing * TILEB, "merge space");
-    auto hand_over = [&](auto qc) __attribute__((always_inline)) {
-      constexpr int QB = decltype(qc)::value;
-#pragma unroll
-      for (int n = 0; n < NDB * 4; ++n) {
-        const float* x = accv + 16 * NDB * QB + 4 * n;
-        mrg[wave * kBlock + n * 64 + lane] = make_float4(x[0], x[1], x[2], x[3]);
-      }
-      const float l = sum_across_halves(lrow[QB]);
-      if (hf == 0) {
-        ml[wave * 64 + col] = no_keys ? -INFINITY : -w.nmz[QB];
-        ml[wave * 64 + 32 + col] = l;
-      }
-    };
-    auto finish = [&](auto qc) __attribute__((always_inline)) {
-      constexpr int QB = decltype(qc)::value;
-      const int other = wave ^ 2;
-      const float m_mine = no_keys ? -INFINITY : -w.nmz[QB], m_other = ml[other * 64 + col];
-      const float m = fmaxf(m_mine, m_other);   // one of the two has seen a key
-      const float f_mine = __builtin_amdgcn_exp2f(m_mine - m), f_other = __builtin_amdgcn_exp2f(m_other - m);
-      float x[16 * NDB];
-#pragma unroll
-      for (int n = 0; n < NDB * 4; ++n) {
-        const float4 y = mrg[other * kBlock + n * 64 + lane];
-        const float* a = accv + 16 * NDB * QB + 4 * n;
-        x[4 * n + 0] = a[0] * f_mine + y.x * f_other;
-        x[4 * n + 1] = a[1] * f_mine + y.y * f_other;
-        x[4 * n + 2] = a[2] * f_mine + y.z * f_other;
-        x[4 * n + 3] = a[3] * f_mine + y.w * f_other;
-      }
-      // (the space the other wave's block came through is this wave's alone now)
-      store_block(QB, x, sum_across_halves(lrow[QB]) * f_mine + ml[other * 64 + 32 + col] * f_other,
-                  smem + other * kBlock * 16);
-    };
-    if (part == 0) hand_over(DLLM_IC(1)); else hand_over(DLLM_IC(0));
-    __syncthreads();
-    if (part == 0) finish(DLLM_IC(0)); else finish(DLLM_IC(1));
+    static_assert(dense_merge_bytes<D>() <= 2 * kDenseRing * TILEB, "merge space");
+    const float m[2] = {no_keys ? -INFINITY : -w.nmz[0], no_keys ? -INFINITY : -w.nmz[1]};
+    merge_dense_halves<D>(accv, lrow, m, part, smem, qbase + qwave * NQB * 32, at, s.hq, o);
   }
 }
 
 // Whether a call splits every tile's keys between two wave pairs (2) or not (1).  The split form makes twice the
 // workgroups, each half as long, for a call that would leave compute units idle; it costs a sixth more per score (every
-// step requests a tile) and the same start and end per workgroup.  In shader cycles, from the clock at the marks of
-// both forms: 1440 per step and 13000 besides at head_dim 128 (split: 1660), 1070 and 7000 at head_dim 64 (split: 1290); one
-// workgroup runs per compute unit at a time.  Measured (us, whole / split): 32 heads x 128, one sequence of 256 14.6 / 11.3,
-// 512 19.6 / 15.0, 1024 29.7 / 24.6 (half the compute units); 2048 65.6 / 75.4 (all of them); three of 768 53.7 / 57.9 (two
-// rounds against three); five of 300 35.4 / 27.1; 16 heads x 64, one of 1024 20.1 / 14.3, three of 1024 21.8 / 28.7, three of
-// 2048 72.9 / 69.6.
+// step requests a tile) and the same start and end per workgroup.  Measured (us, whole / split): 32 heads x 128, one
+// sequence of 256 14.6 / 11.3, 512 19.6 / 15.0, 1024 29.7 / 24.6 (half the compute units); 2048 65.6 / 75.4 (all of them);
+// three of 768 53.7 / 57.9 (two rounds against three); five of 300 35.4 / 27.1.
+// head_dim 128, in shader cycles from the clock at the marks of both forms: 1440 per step and 13000 besides (split:
+// 1660); one workgroup runs per compute unit at a time.
+// head_dim 64 (two workgroups per compute unit), in ns, fitted to 101 batches measured in both forms (4 to 32 heads, one to 40
+// sequences of 64 to 6000): a step takes 449 (split: 485) on a compute unit that the workgroup has for itself and 500 (525)
+// of a shared one, where a workgroup costs 1000 (1500) besides; 3000 before the first step.  Ragged batches of up to 512
+// workgroups keep the whole form unless the split one is estimated 1.3 times as fast: there the estimate knows least
+// (8 heads, nine of 209 to 1073 22.5 / 19.3, six of 567 to 1601 29.8 / 28.3, thirteen of 370 to 446 13.8 / 14.1; with one
+// wave per SIMD, as this kernel used to be, 21 to 23.5 / 25.2, 31.1 / 33.9, 14.9 / 21.0).  Over those batches the choice is 0.7 % above
+// the better form in the mean (the whole form always: 11.6 %, the split one: 2.8 %).  16 heads: nine of 416 17.5 /
+// 20.1, three of 600 15.3 / 11.6, four of 2048 70.0 / 74.6, two of 4400 190 / 176.
 // The lengths themselves are on the device.  With the mean and the longest known, they are taken to be spread evenly
-// around the mean (up to 64 of them, for the batch), and the workgroups to start longest first: in a second round that is
-// not full, a workgroup then follows one of about the length at which the first round ended.  Counting such a round by
-// its share of the mean instead took the split form where it loses: 8 heads x 64, nine sequences of 209 to 1073 23.5 / 25.2 us, six of
-// 567 to 1601 31.1 / 33.9; 8 heads x 128, fifteen of 109 to 834 29.2 / 32.1.  More than a round is estimated to within a
-// few per cent, so there the split form has to be 6 % ahead (of 1500 simulated batches 3 then lose more than 2 %, 14 without).
+// around the mean (up to 64 of them, for the batch), and the workgroups to start longest first: at head_dim 128, in a second
+// round that is not full, a workgroup then follows one of about the length at which the first round ended.  Counting such
+// a round by its share of the mean instead took the split form where it loses (8 heads x 128, fifteen of 109 to 834 29.2 /
+// 32.1).  More than a round is estimated to within a few per cent, so there the split form has to be 6 % ahead (of 1500
+// simulated batches 3 then lose more than 2 %, 14 without).
 int dense_key_splits(const Shape& s, int which) {
   constexpr int kUnits = 256;   // compute units
   // the densely attended sequences of a mixed call are not known here: as many as total_q can have of the longest
@@ -882,8 +668,10 @@ int dense_key_splits(const Shape& s, int which) {
   const double mean_kv = which == 2 ? double(s.total_kv) / n : std::min(longest_kv, mean_q);
   const bool even = mean_kv * 8 >= longest_kv * 7 && mean_q * 8 >= longest_q * 7;
   const int reps = int(std::min<int64_t>(n, 64));
+  const bool shared = s.d == 64;   // two workgroups per compute unit
   auto cost = [&](int ks) -> double {
-    const double step = s.d == 128 ? (ks == 1 ? 1440 : 1660) : (ks == 1 ? 1070 : 1290), fixed = s.d == 128 ? 13000 : 7000;
+    const double step = shared ? (ks == 1 ? 500 : 525) : (ks == 1 ? 1440 : 1660);
+    const double fixed = shared ? (ks == 1 ? 1000 : 1500) : 13000, start = shared ? 3000 : 0;
     const double per_key = step / (32 * ks), one = longest_kv * per_key + fixed;
     double workgroups = 0, work = 0, second = 0;   // second: what the first workgroup of the second round takes
     for (int i = 0; i < reps; ++i) {
@@ -893,6 +681,13 @@ int dense_key_splits(const Shape& s, int which) {
       if (workgroups <= kUnits && workgroups + k > kUnits) second = length;
       workgroups += k;
       work += k * length;
+    }
+    if (shared) {
+      const double alone = longest_kv * (ks == 1 ? 449 : 485) / (32 * ks) + 1000;
+      if (workgroups <= kUnits) return start + alone;
+      if (even) return start + std::ceil(workgroups / kUnits) * one;
+      if (workgroups <= 2 * kUnits) return (ks == 2 ? 1.3 : 1.0) * (start + std::max(alone, work / kUnits));
+      return start + std::max(one, work / kUnits + work / workgroups / 2);
     }
     if (workgroups <= kUnits) return one;
     const double doubt = ks == 2 ? 1.06 : 1.0;
@@ -922,8 +717,8 @@ hipError_t launch_attend_dense_bf16(const Shape& s, const void* q, const void* k
                                               static_cast<uint16_t*>(o), s DLLM_CHECK_PASS);
     return hipGetLastError();
   };
-  if (ks == 2) return s.d == 128 ? launch(attend_dense_bf16_kernel<128, 2>) : launch(attend_dense_bf16_kernel<64, 2>);
-  return s.d == 128 ? launch(attend_dense_bf16_kernel<128, 1>) : launch(attend_dense_bf16_kernel<64, 1>);
+  if (s.d == 64) return launch_attend_dense_paired(s, ks, grid, q, k, v, cu_q, cu_kv, seq_mode, which, o, st);
+  return ks == 2 ? launch(attend_dense_bf16_kernel<2>) : launch(attend_dense_bf16_kernel<1>);
 }
 
 }  // namespace dllm

@@ -84,6 +84,9 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
 hipError_t launch_attend_dense_bf16(const Shape& s, const void* q, const void* k, const void* v,
                                     const int32_t* cu_q, const int32_t* cu_kv, const uint8_t* seq_mode, int which,
                                     void* o, hipStream_t st);
+hipError_t launch_attend_dense_paired(const Shape& s, int ks, dim3 grid, const void* q, const void* k, const void* v,
+                                      const int32_t* cu_q, const int32_t* cu_kv, const uint8_t* seq_mode, int which,
+                                      void* o, hipStream_t st);
 
 // ---- optional device-side precondition checks (checks.hip; built with -DDLLM_CHECK_PRECONDITIONS)
 // In that build every entry point first runs validators over the offset arrays and the index lists, which

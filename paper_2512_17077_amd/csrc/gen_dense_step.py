@@ -240,20 +240,123 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
     return lines
 
 
+# ---- the form with two waves per SIMD (head_dim 64): half the registers, so probabilities take the place of the scores
+# they come from, and K and V^T operands take turns in four a-register buffers
+P2 = dict(NMZ=48, MX=50, TMP=52, ADDR=56, ST_A=64, ST_B=96, OPND=104)
+
+
+def gen_paired_step(cur, nxt, with_loads, split=False):
+    """One step of the form that runs two waves per SIMD (head_dim 64; split as in gen_step): in iteration j
+        slots  0..7    S^T(j+1) = K(j+1) Q^T         beside them P(j), keys 0..15 of the step
+        slots  8..13   O^T += V(j)^T P(j)^T, row sums  of keys 0..15; beside them P(j), keys 16..31
+        slots 14..19   the same of keys 16..31        beside them the row maxima of S(j+1)
+    K operands of step j+2 are fetched once the buffers' V^T operands are used up, and the other way round."""
+    D, NT, NDB = 64, 4, 2
+    QR, LS = 64, 96
+    r = P2
+    opnd = [ar(r["OPND"] + 4 * i, 4) for i in range(4)]
+    prob = [[vr(cur + 16 * qb + 8 * u, 4) for u in range(2)] for qb in range(2)]
+    mfma, need, reads = [], [], []   # per slot: text, operand it waits for, LDS reads issued behind it
+    for t in range(NT):
+        for qb in range(2):
+            st = vr(nxt + 16 * qb, 16)
+            mfma.append(f"v_mfma_f32_32x32x16_bf16 {st}, {opnd[t]}, {ar(QR + 4 * (NT * qb + t), 4)}, {'0' if t == 0 else st}")
+            need.append(("k", t) if qb == 0 else None)
+            u, db = divmod(t, NDB)
+            reads.append([] if qb == 0 else
+                         [(f"ds_read_b64_tr_b16 {ar(r['OPND'] + 4 * t + 2 * rd, 2)}, {vr(r['ADDR'] + 4 + NDB * rd + db)} "
+                           f"offset:%[voff{u}]", ("v", t)) for rd in range(2)])
+    for u in range(2):
+        for db in range(NDB):
+            for qb in range(2):
+                a, n = ar(16 * (NDB * qb + db), 16), NDB * u + db
+                mfma.append(f"v_mfma_f32_32x32x16_bf16 {a}, {opnd[n]}, {prob[qb][u]}, {a}")
+                need.append(("v", n) if qb == 0 else None)
+                reads.append([] if qb == 0 else [(f"ds_read_b128 {opnd[n]}, {vr(r['ADDR'] + n)} offset:%[koff]", ("k", n))])
+        for qb in range(2):
+            a = ar(LS + 4 * qb, 4)
+            mfma.append(f"v_mfma_f32_16x16x32_bf16 {a}, %[ones], {prob[qb][u]}, {a}")
+            need.append(None)
+            reads.append([])
+
+    # vector work: the pairs of scores, keys 0..15 of both query blocks first
+    ops, done = [], {}
+    pairs = [(qb, u, jj) for u in range(2) for qb in range(2) for jj in range(4)]
+
+    def convert(i):
+        qb, u, jj = pairs[i]
+        t0 = r["TMP"] + 2 * (i % 2)
+        ops.append(f"v_cvt_pk_bf16_f32 {vr(cur + 16 * qb + 8 * u + jj)}, {vr(t0)}, {vr(t0 + 1)}")
+        done[i] = len(ops)
+
+    for i, (qb, u, jj) in enumerate(pairs):
+        t0 = r["TMP"] + 2 * (i % 2)
+        s0 = cur + 16 * qb + 8 * u + 2 * jj
+        ops += [f"v_fma_f32 {vr(t0 + c)}, {vr(s0 + c)}, %[zs], {vr(r['NMZ'] + qb)}" for c in range(2)]
+        ops += [f"v_exp_f32_e32 {vr(t0 + c)}, {vr(t0 + c)}" for c in range(2)]
+        if i > 0:
+            convert(i - 1)
+    ops.append("s_nop 0")   # the last exp's result is not read at once
+    convert(15)
+    tops = []
+    for i in range(8):
+        for qb in range(2):
+            s0, m = nxt + 16 * qb + 2 * i, vr(r["MX"] + qb)
+            tops.append(f"v_max_f32_e32 {m}, {vr(s0)}, {vr(s0 + 1)}" if i == 0 else f"v_max3_f32 {m}, {m}, {vr(s0)}, {vr(s0 + 1)}")
+    # a product reads a converted probability no sooner than two instructions later
+    cut = done[7] + 2
+    phases = [(range(0, 8), ops[:cut]), (range(8, 14), ops[cut:] + tops[:2]), (range(14, 20), tops[2:])]
+    valu = [[] for _ in mfma]
+    for slots, work in phases:
+        for n, s in enumerate(slots):
+            valu[s] = work[n * len(work) // len(slots):(n + 1) * len(work) // len(slots)]
+
+    order = [tag for rd in reads for _, tag in rd]
+    lines, issued = [], []
+    seq = [("%[kt]", "%[lk]", "lo", i) for i in range(2)] + [("%[vt]", "%[lv]", "vo" if split else "lo", i) for i in range(2)]
+    for s, text in enumerate(mfma):
+        if need[s] is not None:
+            if need[s][0] == "k":   # fetched in the previous step
+                n = len(order) - 1 - max(i for i, t in enumerate(order) if t == need[s]) + len(issued)
+            else:
+                n = len(issued) - 1 - max(i for i, t in enumerate(issued) if t == need[s])
+            lines.append(f"s_waitcnt lgkmcnt({min(n, 15)})")
+        lines.append(text)
+        if with_loads and s == 1:
+            # Tile boundary: the next tile has landed in every wave (the one after it stays in flight), and every wave
+            # is done with the previous tile, whose ring slots the loads below refill.  (split: K rows of the step after
+            # next have landed; what stays in flight are the V rows requested with them and the previous step's loads.)
+            lines += [f"s_waitcnt vmcnt({6 if split else 4})", "s_barrier"]
+        load = seq[(s - 2) // 2] if with_loads and s in (2, 4, 6, 8) else None
+        if load:
+            lines.append(f"s_add_u32 m0, %[wl], {load[1]}+{load[3] * 256 * 16}")
+        for text, tag in reads[s]:
+            lines.append(text)
+            issued.append(tag)
+        lines += valu[s][:1]
+        if load:
+            lines.append(f"global_load_lds_dwordx4 %[{load[2]}{load[3]}], {load[0]}")
+        lines += valu[s][1:]
+    t, m, z = r["TMP"], r["MX"], r["NMZ"]
+    lines += [f"v_fma_f32 {vr(t)}, {vr(m)}, %[zs], {vr(z)}", f"v_fma_f32 {vr(t + 1)}, {vr(m + 1)}, %[zs], {vr(z + 1)}",
+              f"v_max_f32_e32 {vr(t)}, {vr(t)}, {vr(t + 1)}", f"v_cmp_gt_f32_e64 %[grow], {vr(t)}, %[lazy]"]
+    return lines
+
+
 def as_macro(name, lines):
     body = " \\\n".join(f'  "{l}\\n\\t"' for l in lines)
     return f"#define {name} \\\n{body}\n"
 
 
-def gen_score0(D):
+def gen_score0(D, st=ST_A, kop=lambda t: vr(KOP + 4 * t, 4)):
     """S^T(0) into st_a from the K operands in kop, then enough wait states for any reader"""
     NT, NDB = D // 16, D // 32
     QR = 16 * 2 * NDB
     lines = []
     for t in range(NT):
         for qb in range(2):
-            c = "0" if t == 0 else vr(ST_A + 16 * qb, 16)
-            lines.append(f"v_mfma_f32_32x32x16_bf16 {vr(ST_A + 16 * qb, 16)}, {vr(KOP + 4 * t, 4)}, "
+            c = "0" if t == 0 else vr(st + 16 * qb, 16)
+            lines.append(f"v_mfma_f32_32x32x16_bf16 {vr(st + 16 * qb, 16)}, {kop(t)}, "
                          f"{ar(QR + 4 * (NT * qb + t), 4)}, {c}")
     return lines + ["s_nop 15", "s_nop 15"]
 
@@ -265,7 +368,7 @@ def gen_acc_init(D):
     return [f"v_accvgpr_write_b32 a{i}, 0" for i in regs]
 
 
-def gen_acc_scale(D):
+def gen_acc_scale(D, TMP=TMP):
     """acc[qb] *= %[al<qb>] for both blocks, well after the last MFMA and before the next one."""
     n = 16 * (D // 32)
     lines = ["s_nop 15", "s_nop 15"]
@@ -300,7 +403,7 @@ def main():
            "// the steps of the form that splits a tile's keys between two wave pairs: both request tiles, the V rows at",
            "// offsets %[vo0..] of their own.",
            ""]
-    for D in (128, 64):
+    for D in (128,):
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_AB", gen_step(D, ST_A, ST_B, PB_A, PB_B, with_loads=True)))
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_BA", gen_step(D, ST_B, ST_A, PB_B, PB_A)))
         out.append(as_macro(f"DLLM_DENSE_STEP_{D}_AB_SPLIT", gen_step(D, ST_A, ST_B, PB_A, PB_B, with_loads=True, split=True)))
@@ -309,6 +412,14 @@ def main():
         out.append(as_macro(f"DLLM_DENSE_SCORE0_{D}", gen_score0(D)))
         out.append(as_macro(f"DLLM_DENSE_ACC_INIT_{D}", gen_acc_init(D)))
         out.append(as_macro(f"DLLM_DENSE_ACC_SCALE_{D}", gen_acc_scale(D)))
+    out.append(as_macro("DLLM_DENSE_ACC_INIT_64", gen_acc_init(64)))
+    st_a, st_b = P2["ST_A"], P2["ST_B"]
+    out.append(as_macro("DLLM_DENSE_PAIRED_STEP_AB", gen_paired_step(st_a, st_b, True)))
+    out.append(as_macro("DLLM_DENSE_PAIRED_STEP_BA", gen_paired_step(st_b, st_a, False)))
+    out.append(as_macro("DLLM_DENSE_PAIRED_STEP_AB_SPLIT", gen_paired_step(st_a, st_b, True, True)))
+    out.append(as_macro("DLLM_DENSE_PAIRED_STEP_BA_SPLIT", gen_paired_step(st_b, st_a, True, True)))
+    out.append(as_macro("DLLM_DENSE_PAIRED_SCORE0", ["s_nop 1"] + gen_score0(64, st_a, lambda t: ar(P2["OPND"] + 4 * t, 4))))
+    out.append(as_macro("DLLM_DENSE_PAIRED_ACC_SCALE", gen_acc_scale(64, P2["TMP"])))
     for k in range(8):
         out.append(as_macro(f"DLLM_DENSE_ACC_READ_{k}", gen_acc_read(k)))
     outdir = os.path.dirname(os.path.abspath(__file__))

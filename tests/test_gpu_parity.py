@@ -390,6 +390,26 @@ def test_dense_keys_and_queries_around_tile_edges(Hq, Hkv, D):
         check_attend(w, np.zeros((Hq, 0), np.int32), name=f"dense L={L}")
 
 
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("Hq,Hkv", [(2, 1), (48, 8)])
+def test_dense_head_dim_64_around_the_turns_of_its_rings(Hq, Hkv, rising):
+    """The head_dim 64 kernel requests its tiles three and four ahead and takes its fast path until 18 steps (10 in the split
+    form) before the end: key counts around those marks and around whole turns, with logits that grow along the
+    sequence (the running maximum is raised again and again, the tile pointers are set anew each time) and without."""
+    for part, lens in enumerate(([543, 575, 577, 609, 639], [641, 703, 833, 1023, 1025])):
+        w = custom(90 + part, torch.bfloat16, Hq, Hkv, 64, lens, [256, 130, 31, 257, 64], [0] * 5, mode=np.ones(5, np.uint8), salient=0.05)
+        if rising:
+            for b in range(5):
+                lo, hi = int(w.cu_kv[b]), int(w.cu_kv[b + 1])
+                w.k[lo:hi] = (w.k[lo:hi].float() * (1.0 + 7.0 * torch.linspace(0.0, 1.0, hi - lo)[:, None, None])).to(torch.bfloat16)
+        dw = workload.DeviceWorkload(w)
+        assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == (2 if Hq == 2 else 1)
+        dw.o.fill_(float("nan"))
+        dw.dense_refresh()
+        ref = oracle_attend(w, np.zeros((Hq, 0), np.int32))
+        assert np.abs(dw.o.float().cpu().numpy() - ref).max() <= 2e-2   # P and O rounded to bf16, see test_dense_large_logits
+
+
 def test_dense_large_logits():
     """Half of the K rows scaled by 4: base-2 logits reach +-25 and a few keys carry each query.  The
     dense kernel keeps Q as given and scales the fp32 scores (scaling Q and rounding it to bf16 again
