@@ -7,11 +7,11 @@
 namespace dllm {
 
 struct DensePlace {
-  int qtile, h, b;         // query tile, query head, sequence
+  int qtile, h;            // query tile, query head
   int q0, nq, kv0, L;      // the sequence's first query, number of queries, first key, number of keys
 };
 
-// Which query tile of which (sequence, head) this workgroup takes.
+// Which query tile of which (sequence, head) a workgroup takes.
 //
 // Batches of up to 64 sequences are launched as a one-dimensional grid with just enough workgroups for the
 // query tiles the batch can have (the host bounds their number from total_q), and every workgroup finds
@@ -25,100 +25,111 @@ struct DensePlace {
 // The numbering is such that the workgroups that stream the same K/V -- the query tiles of the query
 // heads that share one KV head of one sequence -- land on one XCD (launch ids equal modulo 8) and
 // share its L2, while consecutive (sequence, KV head) pairs go to different XCDs.
-//
-// False: there is nothing for this workgroup to do.  which: see launch_attend_dense_bf16.
+
+// A batch of up to 64 sequences: lane i holds one of them, those that are attended densely in order of their lengths.
+struct DenseLanes {
+  int q0, nq, kv0, L, tiles;
+  int incl, total;   // tiles of the sequences up to this one; of all
+};
+// which: see launch_attend_dense_bf16
 template <int Rows>
-__device__ __forceinline__ bool place_dense(const Shape& s, const int32_t* __restrict__ cu_q,
-                                            const int32_t* __restrict__ cu_kv, const uint8_t* __restrict__ seq_mode,
-                                            int which, DensePlace& w) {
-  int qtile, h, b, q0, nq, kv0, L;
-  if (gridDim.y == 1 && gridDim.z == 1) {
-    const int lane0 = threadIdx.x & 63;
-    int my_q0 = 0, my_nq = 0, my_kv0 = 0, my_L = 0, my_tiles = 0;
-    if (lane0 < s.batch) {
-      my_q0 = cu_q[lane0];
-      my_nq = cu_q[lane0 + 1] - my_q0;
-      my_kv0 = cu_kv[lane0];
-      my_L = cu_kv[lane0 + 1] - my_kv0;
-      const bool dense = which == 2 || (seq_mode != nullptr && seq_mode[lane0] == DLLM_SEQ_DENSE);
-      my_tiles = dense ? (my_nq + Rows - 1) / Rows : 0;
-    }
-    // Longest sequences first: a workgroup lasts as long as its sequence has keys, and with the long ones at the
-    // end of the launch most compute units wait for a few (seven sequences of 537 to 2076 keys, 16 heads x 64:
-    // 82.9 us in batch order, 81.2 us longest first; 83.1 and 79.2 on another card).  Lane i goes on with the sequence of rank i among the densely
-    // attended ones; equal lengths need no ranking.
-    const uint64_t with_tiles = __builtin_amdgcn_ballot_w64(my_tiles != 0);
-    const int first_L = with_tiles != 0 ? __builtin_amdgcn_readlane(my_L, __builtin_ctzll(with_tiles)) : 0;
-    if (__builtin_amdgcn_ballot_w64(my_tiles != 0 && my_L != first_L) != 0) {
-      // keys that are all different, so one comparison per sequence does; eight at a time (a loop over single sequences
-      // with a second comparison for equal lengths took 1.1 to 2.4 us of a workgroup's start on a batch of 25)
-      const uint32_t key = uint32_t(my_tiles != 0 ? min(my_L, (1 << 25) - 1) + 1 : 0) << 6 | uint32_t(63 - lane0);
-      int rank = 0;
-      for (int i = 0; i < s.batch; i += 8)
-#pragma unroll
-        for (int c = 0; c < 8; ++c) rank += uint32_t(__builtin_amdgcn_readlane(int(key), i + c)) > key ? 1 : 0;
-      if (lane0 >= s.batch) rank = lane0;   // lanes past the batch stay where they are
-      my_q0 = __builtin_amdgcn_ds_permute(rank * 4, my_q0);
-      my_nq = __builtin_amdgcn_ds_permute(rank * 4, my_nq);
-      my_kv0 = __builtin_amdgcn_ds_permute(rank * 4, my_kv0);
-      my_L = __builtin_amdgcn_ds_permute(rank * 4, my_L);
-      my_tiles = __builtin_amdgcn_ds_permute(rank * 4, my_tiles);
-    }
-    const int incl = int(wave_inclusive_sum(uint32_t(my_tiles)));
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    const int n = blockIdx.x;
-    int place;   // position of the tile in (sequence, tile) order, times what follows
-    uint64_t m;
-    if ((s.hkv & 7) == 0) {
-      // XCD x = n % 8 takes KV heads x, x + 8, ...; within the XCD: sequence, KV head, query head of its group, tile
-      const int per_seq = s.group * (s.hkv >> 3);
-      place = n >> 3;
-      if (place >= total * per_seq) return false;
-      m = __builtin_amdgcn_ballot_w64(incl * per_seq > place);
-      b = __builtin_ctzll(m);
-      const int tb = __builtin_amdgcn_readlane(my_tiles, b);
-      const int rem = place - (__builtin_amdgcn_readlane(incl, b) - tb) * per_seq;
-      const int per_head_group = tb * s.group;
-      const int kvh = (rem / per_head_group) * 8 + (n & 7), r = rem % per_head_group;
-      qtile = r % tb;
-      h = kvh * s.group + r / tb;
-    } else {
-      place = n / s.hq;
-      h = n % s.hq;
-      if (place >= total) return false;
-      m = __builtin_amdgcn_ballot_w64(incl > place);
-      b = __builtin_ctzll(m);
-      qtile = place - (__builtin_amdgcn_readlane(incl, b) - __builtin_amdgcn_readlane(my_tiles, b));
-    }
-    q0 = __builtin_amdgcn_readlane(my_q0, b);
-    nq = __builtin_amdgcn_readlane(my_nq, b);
-    kv0 = __builtin_amdgcn_readlane(my_kv0, b);
-    L = __builtin_amdgcn_readlane(my_L, b);
-  } else {
-    const int nx = gridDim.x, units = s.hkv * gridDim.z;
-    const int n = blockIdx.x + nx * (blockIdx.y + gridDim.y * blockIdx.z);
-    qtile = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-    if ((units & 7) == 0) {
-      const int per_unit = s.group * nx;
-      const int j = n >> 3;   // position in this XCD's own launch sequence
-      const int r = j % per_unit, unit = (j / per_unit) * 8 + (n & 7);
-      qtile = r % nx;
-      h = (unit % s.hkv) * s.group + r / nx;
-      b = unit / s.hkv;
-    }
-    if (which == 1 && !(seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE)) return false;
-    q0 = cu_q[b];
-    nq = cu_q[b + 1] - q0;
-    kv0 = cu_kv[b];
-    L = cu_kv[b + 1] - kv0;
+__device__ __forceinline__ DenseLanes gather_dense(const Shape& s, const int32_t* __restrict__ cu_q,
+                                                   const int32_t* __restrict__ cu_kv, const uint8_t* __restrict__ seq_mode,
+                                                   int which) {
+  const int lane = threadIdx.x & 63;
+  DenseLanes w{0, 0, 0, 0, 0, 0, 0};
+  if (lane < s.batch) {
+    w.q0 = cu_q[lane];
+    w.nq = cu_q[lane + 1] - w.q0;
+    w.kv0 = cu_kv[lane];
+    w.L = cu_kv[lane + 1] - w.kv0;
+    const bool dense = which == 2 || (seq_mode != nullptr && seq_mode[lane] == DLLM_SEQ_DENSE);
+    w.tiles = dense ? (w.nq + Rows - 1) / Rows : 0;
   }
-  w = DensePlace{qtile, h, b, q0, nq, kv0, L};
-  return qtile * Rows < nq;
+  // Longest sequences first: a workgroup lasts as long as its sequence has keys, and with the long ones at the
+  // end of the launch most compute units wait for a few (seven sequences of 537 to 2076 keys, 16 heads x 64:
+  // 82.9 us in batch order, 81.2 us longest first; 83.1 and 79.2 on another card).  Lane i goes on with the sequence of
+  // rank i among the densely attended ones; equal lengths need no ranking.
+  const uint64_t with_tiles = __builtin_amdgcn_ballot_w64(w.tiles != 0);
+  const int first_L = with_tiles != 0 ? __builtin_amdgcn_readlane(w.L, __builtin_ctzll(with_tiles)) : 0;
+  if (__builtin_amdgcn_ballot_w64(w.tiles != 0 && w.L != first_L) != 0) {
+    // keys that are all different, so one comparison per sequence does; eight at a time (a loop over single sequences
+    // with a second comparison for equal lengths took 1.1 to 2.4 us of a workgroup's start on a batch of 25)
+    const uint32_t key = uint32_t(w.tiles != 0 ? min(w.L, (1 << 25) - 1) + 1 : 0) << 6 | uint32_t(63 - lane);
+    int rank = 0;
+    for (int i = 0; i < s.batch; i += 8)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) rank += uint32_t(__builtin_amdgcn_readlane(int(key), i + c)) > key ? 1 : 0;
+    if (lane >= s.batch) rank = lane;   // lanes past the batch stay where they are
+    w.q0 = __builtin_amdgcn_ds_permute(rank * 4, w.q0);
+    w.nq = __builtin_amdgcn_ds_permute(rank * 4, w.nq);
+    w.kv0 = __builtin_amdgcn_ds_permute(rank * 4, w.kv0);
+    w.L = __builtin_amdgcn_ds_permute(rank * 4, w.L);
+    w.tiles = __builtin_amdgcn_ds_permute(rank * 4, w.tiles);
+  }
+  w.incl = int(wave_inclusive_sum(uint32_t(w.tiles)));
+  w.total = __builtin_amdgcn_readlane(w.incl, 63);
+  return w;
+}
+
+// Tile number n of such a batch; false if it has no more than n.
+__device__ __forceinline__ bool find_dense(const Shape& s, const DenseLanes& w, uint32_t n, DensePlace& at) {
+  int b;
+  if ((s.hkv & 7) == 0) {
+    // XCD x = n % 8 takes KV heads x, x + 8, ...; within the XCD: sequence, KV head, query head of its group, tile
+    const int per_seq = s.group * (s.hkv >> 3), place = int(n >> 3);
+    if (place >= w.total * per_seq) return false;
+    b = __builtin_ctzll(__builtin_amdgcn_ballot_w64(w.incl * per_seq > place));
+    const int tb = __builtin_amdgcn_readlane(w.tiles, b);
+    const int rem = place - (__builtin_amdgcn_readlane(w.incl, b) - tb) * per_seq;
+    const int per_head_group = tb * s.group;
+    const int kvh = (rem / per_head_group) * 8 + int(n & 7), r = rem % per_head_group;
+    at.qtile = r % tb;
+    at.h = kvh * s.group + r / tb;
+  } else {
+    const int place = int(n / uint32_t(s.hq));
+    at.h = int(n % uint32_t(s.hq));
+    if (place >= w.total) return false;
+    b = __builtin_ctzll(__builtin_amdgcn_ballot_w64(w.incl > place));
+    at.qtile = place - (__builtin_amdgcn_readlane(w.incl, b) - __builtin_amdgcn_readlane(w.tiles, b));
+  }
+  at.q0 = __builtin_amdgcn_readlane(w.q0, b);
+  at.nq = __builtin_amdgcn_readlane(w.nq, b);
+  at.kv0 = __builtin_amdgcn_readlane(w.kv0, b);
+  at.L = __builtin_amdgcn_readlane(w.L, b);
+  return true;
+}
+
+// The tile of this workgroup in the three-dimensional grid of a larger batch; false if there is none.
+template <int Rows>
+__device__ __forceinline__ bool place_dense_grid(const Shape& s, const int32_t* __restrict__ cu_q,
+                                                 const int32_t* __restrict__ cu_kv, const uint8_t* __restrict__ seq_mode,
+                                                 int which, DensePlace& at) {
+  const int nx = gridDim.x, units = s.hkv * gridDim.z;
+  const int n = blockIdx.x + nx * (blockIdx.y + gridDim.y * blockIdx.z);
+  int b = blockIdx.z;
+  at.qtile = blockIdx.x;
+  at.h = blockIdx.y;
+  if ((units & 7) == 0) {
+    const int per_unit = s.group * nx;
+    const int j = n >> 3;   // position in this XCD's own launch sequence
+    const int r = j % per_unit, unit = (j / per_unit) * 8 + (n & 7);
+    at.qtile = r % nx;
+    at.h = (unit % s.hkv) * s.group + r / nx;
+    b = unit / s.hkv;
+  }
+  if (which == 1 && !(seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE)) return false;
+  at.q0 = cu_q[b];
+  at.nq = cu_q[b + 1] - at.q0;
+  at.kv0 = cu_kv[b];
+  at.L = cu_kv[b + 1] - at.kv0;
+  return at.qtile * Rows < at.nq;
 }
 
 // Writes 32 query rows: accumulators `a` ([db][16], as the matrix cores leave them) over the row sum l.  A lane holds
 // four elements of one row at a time, so the block goes through LDS (`stage`, 32 rows that are this wave's alone) and out
-// in whole rows.  first: the block's first query; rows past the last query are not written.
+// in whole rows.  first: the block's first query; rows past the last query are not written.  Lane offsets fit 32 bits: 32
+// rows of at most 65535 heads span 512 MB.
 template <int D>
 __device__ __forceinline__ void store_dense_block(const float* a, float l, char* stage, int first, const DensePlace& at,
                                                   int hq, uint16_t* __restrict__ o) {
@@ -138,12 +149,23 @@ __device__ __forceinline__ void store_dense_block(const float* a, float l, char*
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  first = __builtin_amdgcn_readfirstlane(first);
+  const uint32_t row_bytes = uint32_t(hq) * (2 * D);
+  char* base = reinterpret_cast<char*>(o + (int64_t(at.q0 + first) * hq + at.h) * D);
+  const int left = at.nq - first;   // rows there are
+  constexpr int kStep = 64 / CH;    // rows per store
+  const uint32_t r0 = lane / CH, off = r0 * row_bytes + (lane % CH) * 16;
+  auto put = [&](int i) __attribute__((always_inline)) {
+    *reinterpret_cast<v4u*>(base + uint32_t(i * kStep) * row_bytes + off) =
+        *reinterpret_cast<const v4u*>(stage + tile_off<D>(i * kStep + r0, lane % CH));
+  };
+  if (left >= 32) {
 #pragma unroll
-  for (int i = 0; i < 32 * CH / 64; ++i) {
-    const int f = i * 64 + lane, r = f / CH, c = f % CH;
-    if (first + r < at.nq)
-      *reinterpret_cast<v4u*>(o + (int64_t(at.q0 + first + r) * hq + at.h) * D + c * 8) =
-          *reinterpret_cast<const v4u*>(stage + tile_off<D>(r, c));
+    for (int i = 0; i < 32 / kStep; ++i) put(i);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 32 / kStep; ++i)
+      if (int(i * kStep + r0) < left) put(i);
   }
 }
 

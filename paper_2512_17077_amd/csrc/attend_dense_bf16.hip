@@ -52,6 +52,7 @@ constexpr int kDenseK = 64;          // keys per LDS tile
 constexpr int kDenseRing = 4;        // K tiles, and V tiles, resident in LDS
 constexpr int kDenseWaves = 4;       // waves per workgroup
 constexpr int kDenseQB = 2;          // 32-query blocks per wave
+constexpr uint32_t kDenseUnits = 256;   // compute units: the most workgroups of a launch whose workgroups stay (KS = 1)
 // query rows per workgroup; with KS = 2 two wave pairs take the same rows and half of every tile's keys each
 constexpr int dense_rows(int ks) { return kDenseWaves * kDenseQB * 32 / ks; }
 
@@ -180,6 +181,10 @@ struct DenseState {
                  : "={v[96:111]}"(st_a[0]), "={v[112:127]}"(st_a[1])
                  : "{v[192:207]}"(kop[0]), "{v[208:223]}"(kop[1]), DLLM_Q_IN);
   }
+  // waits for the K operands that the last step has requested (nothing may take their registers before)
+  __device__ __forceinline__ void drain() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::"{v[192:207]}"(kop[0]), "{v[208:223]}"(kop[1]) : "memory");
+  }
   __device__ __forceinline__ void row_sums(float& l0, float& l1) {
     asm volatile("s_nop 15\n\ts_nop 15\n\tv_accvgpr_read_b32 %0, a192\n\tv_accvgpr_read_b32 %1, a196"
                  : "=v"(l0), "=v"(l1) : "{a[192:195]}"(ls[0]), "{a[196:199]}"(ls[1]));
@@ -219,8 +224,18 @@ __device__ __forceinline__ void for_each_round(F& f, std::integer_sequence<int, 
   (f(std::integral_constant<int, C>{}), ...);
 }
 
-// which: 1 = only sequences flagged dense in seq_mode; 2 = every sequence
 // KS: wave groups that share the keys (1 or 2; see launch_attend_dense_bf16 for which calls take which)
+// which: 1 = only sequences flagged dense in seq_mode; 2 = every sequence
+//
+// With KS = 1 a launch has at most one workgroup per compute unit, and each goes on to further tiles by itself: between the
+// last step over one tile's keys and the first over the next one's, a workgroup that ends and one that starts spent
+// 0.3 us on the dispatch, 0.7 to 1.2 until the new one knew its place, 2.4 to 4.3 until its queries and first K rows were
+// there, 0.9 to 1.2 until the first step and 2.7 to 3.7 on the last product, the outputs and their stores, while a step
+// takes 0.7 to 0.9.  A workgroup that stays knows its next tile in advance and requests what it needs before the last product
+// and the outputs: about 6 us instead of 10.  32 heads, eight sequences of 2048 467 -> 459 us, eight of 1024 132 -> 127, 8 KV heads
+// and 21 sequences of 83 to 472 56.7 -> 53.3 (then 48.2 with fewer visits to the careful path, see `stop`; eighteen of 652
+// 174 -> 163, twelve of 323 with 16 heads 32.5 -> 28.8).  Tiles are dealt out in serpentine order (turn r: tile 256 r + i to workgroup i or 255 - i, within each
+// XCD), so that ragged batches, whose tiles come longest sequences first, stay even.
 template <int KS>
 __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
@@ -240,84 +255,53 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   constexpr int ROUND = SPT * kDenseRing;        // steps in one turn of the rings
   constexpr int AHEAD_K = KS == 1 ? 2 : 4;       // a tile's first step requests the K rows of the tile this far ahead,
   constexpr int AHEAD_V = 2;                     // and the V rows of this one
-  // a ring turn that starts with fewer steps than this left (or the step after it) reaches the last tile
-  constexpr int NEAR_END = KS == 1 ? 2 * ROUND : 2 * ROUND + 2;
   constexpr int kDenseRows = dense_rows(KS);
   static_assert(NLD * NTHREADS == kDenseK * CH, "the loads of a tile");
   static_assert(kDenseRing * TILEB <= 65536, "ring offsets must fit the 16-bit LDS offset field");
+  static_assert(kDenseQB * 32 == kDenseK, "a wave's queries fill one slot");
 
-  // K ring, V ring, and 64 rows more: the queries pass through LDS too (see below), one slot per wave that has its own
-  __shared__ __attribute__((aligned(16))) char smem[(2 * kDenseRing + 1) * TILEB];
+  // K ring, V ring, and space for the queries that have no ring slot to come through (see below)
+  constexpr int kSlots = 2 * kDenseRing + (KS == 1 ? 2 : 1);
+  __shared__ __attribute__((aligned(16))) char smem[kSlots * TILEB];
 
-  DensePlace at;
-  if (!place_dense<kDenseRows>(s, cu_q, cu_kv, seq_mode, which, at)) return;
-  const int h = at.h, q0 = at.q0, nq = at.nq, kv0 = at.kv0, L = at.L;
-  const int qbase = at.qtile * kDenseRows;
-  const int g = h / s.group;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int hf = lane >> 5;
   // the query blocks this wave takes, and which half of every tile's keys (0 when all waves take both)
   const int qwave = KS == 1 ? wave : wave & 1;
   const int part = KS == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave >> 1);
-#ifdef DLLM_DENSE_STAMPS
-  // timing experiments only: every workgroup leaves shader-clock counts in its own first output row
-  // (and stores no outputs): [0] entry, [1] loop start, [2] loop end, [3] end, [4..11] cycles spent in
-  // steps at ring position R, [12] slowest step, [13] number of steps over 3000 cycles
-  const uint64_t rt_entry = __builtin_amdgcn_s_memrealtime();   // 100 MHz
-  uint64_t t_entry = __builtin_readcyclecounter(), t_loop0 = 0, t_prev = 0, by_r[8] = {0, 0, 0, 0, 0, 0, 0, 0},
-           t_max = 0, n_slow = 0, t_part = 0, parts[4] = {0, 0, 0, 0};
-#define DLLM_STAMP_PART(i)                                   \
-  {                                                          \
-    const uint64_t t_now = __builtin_readcyclecounter();     \
-    if (i > 0) parts[i] += t_now - t_part;                   \
-    t_part = t_now;                                          \
-  }
-#define DLLM_STAMP_LOOP_START() t_loop0 = t_prev = __builtin_readcyclecounter()
-#if DLLM_DENSE_STAMPS < 2
-#define DLLM_STAMP_STEP(R)
-#else
-#define DLLM_STAMP_STEP(R)                                  \
-  {                                                         \
-    const uint64_t t_now = __builtin_readcyclecounter();    \
-    const uint64_t dt = t_now - t_prev;                     \
-    by_r[R] += dt;                                          \
-    t_max = dt > t_max ? dt : t_max;                        \
-    n_slow += dt > 3000 ? 1 : 0;                            \
-    t_prev = t_now;                                         \
-  }
-#endif
-#else
-#define DLLM_STAMP_LOOP_START()
-#define DLLM_STAMP_STEP(R)
-#endif
+  const int64_t pitch = s.kv_tok * 2, tile_bytes = int64_t(kDenseK) * pitch;
 
-  if (L == 0) {   // nothing to attend to: zeros
-    zero_dense_rows<D>(qbase, kDenseRows, at, s.hq, o);
-    return;
+  // ---- the query tiles this workgroup takes
+  DenseLanes lanes;
+  DensePlace at;
+  const bool stays = KS == 1 && gridDim.x == kDenseUnits && gridDim.y == 1 && gridDim.z == 1;
+  uint32_t turn = 0;
+  // the next tile with keys; outputs of sequences without any are zeros
+  auto find = [&](DensePlace& p) __attribute__((always_inline)) -> bool {
+    for (;;) {
+      const uint32_t n = blockIdx.x;
+      uint32_t mine = n;
+      if (stays) mine = turn * kDenseUnits + ((turn & 1) != 0 ? (kDenseUnits / 8 - 1 - (n >> 3)) * 8 + (n & 7) : n);
+      else if (turn != 0) return false;
+      ++turn;
+      if (!find_dense(s, lanes, mine, p)) return false;
+      if (p.L != 0) return true;
+      zero_dense_rows<D>(p.qtile * kDenseRows, kDenseRows, p, s.hq, o);
+    }
+  };
+  if (gridDim.y == 1 && gridDim.z == 1) {
+    lanes = gather_dense<kDenseRows>(s, cu_q, cu_kv, seq_mode, which);
+    if (!find(at)) return;
+  } else {
+    if (!place_dense_grid<kDenseRows>(s, cu_q, cu_kv, seq_mode, which, at)) return;
+    if (at.L == 0) {
+      zero_dense_rows<D>(at.qtile * kDenseRows, kDenseRows, at, s.hq, o);
+      return;
+    }
   }
 
-  const char* kbase = reinterpret_cast<const char*>(k + int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head);
-  const char* vbase = reinterpret_cast<const char*>(v + int64_t(kv0) * s.kv_tok + int64_t(g) * s.kv_head);
-  const int64_t pitch = s.kv_tok * 2;
-
-  DenseState w;
-  // LDS addresses, fixed for the whole pass; ring slot, 32-key half and 16-key quarter are immediates
-  {
-    KAddr<D> kaddr;
-    kaddr.init(lane);
-    VtAddr<D> vaddr;
-    vaddr.init(lane);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) w.addr[i] = 0;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) w.addr[t] = kaddr.off(t) + part * 32 * ROWB;
-#pragma unroll
-    for (int rd = 0; rd < 2; ++rd)
-#pragma unroll
-      for (int db = 0; db < NDB; ++db) w.addr[8 + NDB * rd + db] = VBASE + vaddr.off(rd, db) + part * 32 * ROWB;
-  }
-  // Global side of the tile loads: this lane's chunk f = i * NTHREADS + tid of a tile lands at LDS
-  // byte 16 * f, i.e. row f / CH, chunk slot f % CH, and must hold chunk (slot ^ swizzle(row)) of
+  // ---- what one tile's loads need.  Global side of the tile loads: this lane's chunk f = i * NTHREADS + tid of a K or V
+  // tile lands at LDS byte 16 * f, i.e. row f / CH, chunk slot f % CH, and must hold chunk (slot ^ swizzle(row)) of
   // that row.  Rows past the end of the sequence re-read its last row (their keys are masked).
   uint32_t ld_off[NLD];   // byte offset of the chunk from the tile's first row (fits: checked on the host)
 #pragma unroll
@@ -325,102 +309,76 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     const int f = i * NTHREADS + tid, row = f / CH;
     ld_off[i] = uint32_t(row) * uint32_t(pitch) + uint32_t(((f % CH) ^ tile_swz<D>(row)) << 4);
   }
-  // the same for the last tile when the sequence ends inside it: rows past the end re-read the last row
-  const int ntiles = (L + kDenseK - 1) / kDenseK;
-  uint32_t ld_off_last[NLD];
+  // What is computed from the result cannot be moved out of the loop over tiles, where it would hold registers that the
+  // steps do not leave (some twenty values went to scratch memory, whose loads wait for the tiles requested before them).
+  auto anew = [](int x) __attribute__((always_inline)) -> int {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  struct Keys {
+    const char *k, *v;           // the sequence's first K and V row of this head
+    int ntiles;
+    uint32_t off_last[NLD];      // the offsets for the last tile, which the sequence may end inside of
+  };
+  auto keys_of = [&](const DensePlace& p) __attribute__((always_inline)) -> Keys {
+    Keys x;
+    const int mine = anew(tid);
+    const int64_t first = int64_t(p.kv0) * s.kv_tok + int64_t(p.h / s.group) * s.kv_head;
+    x.k = reinterpret_cast<const char*>(k + first);
+    x.v = reinterpret_cast<const char*>(v + first);
+    x.ntiles = (p.L + kDenseK - 1) / kDenseK;
 #pragma unroll
-  for (int i = 0; i < NLD; ++i) {
-    const int f = i * NTHREADS + tid, row = min(f / CH, L - 1 - (ntiles - 1) * kDenseK);
-    ld_off_last[i] = uint32_t(row) * uint32_t(pitch) + uint32_t(((f % CH) ^ tile_swz<D>(f / CH)) << 4);
-  }
+    for (int i = 0; i < NLD; ++i) {
+      const int f = i * NTHREADS + mine, row = min(f / CH, p.L - 1 - (x.ntiles - 1) * kDenseK);
+      x.off_last[i] = uint32_t(row) * uint32_t(pitch) + uint32_t(((f % CH) ^ tile_swz<D>(f / CH)) << 4);
+    }
+    return x;
+  };
   // this wave's slice of each load round, as an LDS byte address
   const uint32_t wave_lds = __builtin_amdgcn_readfirstlane(lds_addr(smem) + wave * 64 * 16);
-  auto load_tile = [&](const char* base, int tile, auto lds_off) __attribute__((always_inline)) {
+  // (past the last tile the last one again, so that the number of loads in flight is always the same)
+  auto load_tile = [&](const Keys& x, const char* base, int tile, auto lds_off) __attribute__((always_inline)) {
     constexpr int kLdsOff = decltype(lds_off)::value;
-    const int t0 = tile * kDenseK;
-    if (t0 + kDenseK <= L) {   // whole tile inside the sequence: uniform tile address + fixed lane offsets
-      const char* tbase = base + int64_t(t0) * pitch;
+    const int t = min(tile, x.ntiles - 1);
+    const char* tbase = base + t * tile_bytes;
+    auto round = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      load16_to_lds<kLdsOff + i * NTHREADS * 16>(tbase, t == x.ntiles - 1 ? x.off_last[i] : ld_off[i], wave_lds);
+    };
+    for_each_round(round, std::make_integer_sequence<int, NLD>{});
+  };
+  // The wave's 64 query rows go through LDS, into ring slots that no tile needs yet and the slots behind the rings:
+  // read straight into the operand layout, an instruction touches 32 rows of 32 bytes each, and the sixteen of them took
+  // 3200 to 5200 cycles to issue.  Rows past the last query repeat it (their columns are never stored).
+  const int qslot = KS == 1 ? (wave < 2 ? 2 + wave : 2 * kDenseRing - 2 + wave) : (qwave == 0 ? kDenseRing + 2 : 2 * kDenseRing);
+  constexpr int NQLD = CH / KS;   // loads of 1 KB: with KS = 2 each wave of a pair that shares the queries brings half
+  auto load_queries = [&](const DensePlace& p) __attribute__((always_inline)) {
+    const uint32_t stage = __builtin_amdgcn_readfirstlane(lds_addr(smem) + qslot * TILEB + part * NQLD * 1024);
+    // The rows of load i from the wave's first one on; their 16-byte chunk's swizzle depends on i % 4.
+    const int mine = anew(lane), first = __builtin_amdgcn_readfirstlane(p.qtile * kDenseRows + qwave * 64 + part * NQLD * 4);
+    const int row = mine / CH, left = p.nq - first;
+    static_assert(64 / CH == 4, "four rows per load");
+    const char* qh = reinterpret_cast<const char*>(q + int64_t(p.q0 + first) * s.q_tok + int64_t(p.h) * s.q_head);
+    const int64_t qpitch = s.q_tok * 2;
+    if (left >= NQLD * 4 && qpitch < (int64_t(1) << 30)) {
       auto round = [&](auto ic) __attribute__((always_inline)) {
         constexpr int i = decltype(ic)::value;
-        load16_to_lds<kLdsOff + i * NTHREADS * 16>(tbase, ld_off[i], wave_lds);
+        load16_to_lds<i * 1024>(qh + i * 4 * qpitch, uint32_t(row) * uint32_t(qpitch) + (((mine % CH) ^ tile_swz<D>(i * 4 + row)) << 4), stage);
       };
-      for_each_round(round, std::make_integer_sequence<int, NLD>{});
-    } else {
-      auto round = [&](auto ic) __attribute__((always_inline)) {
-        constexpr int i = decltype(ic)::value;
-        const int f = i * NTHREADS + tid, r = f / CH;
-        const int row = min(t0 + r, L - 1);
-        load16_to_lds<kLdsOff + i * NTHREADS * 16>(base + row * pitch + (((f % CH) ^ tile_swz<D>(r)) << 4),
-                                                   wave_lds);
-      };
-      for_each_round(round, std::make_integer_sequence<int, NLD>{});
+      for_each_round(round, std::make_integer_sequence<int, NQLD>{});
+      return;
     }
+    auto round = [&](auto ic) __attribute__((always_inline)) {
+      constexpr int i = decltype(ic)::value;
+      const int r = i * 4 + row;
+      load16_to_lds<i * 1024>(qh + min(r, left - 1) * qpitch + (((mine % CH) ^ tile_swz<D>(r)) << 4), stage);
+    };
+    for_each_round(round, std::make_integer_sequence<int, NQLD>{});
   };
 #define DLLM_IC(x) std::integral_constant<int, (x)> {}
 
-  // the first tiles are requested before anything else, so their latency overlaps the Q loads
-  const int nsteps = KS == 1 ? (L + 31) / 32 : ntiles;
-  // valid keys of this wave's last step: 32, or fewer when the sequence ends inside it (none at all is possible for
-  // the second half of a tile)
-  const int last_valid = KS == 1 ? L - 32 * (nsteps - 1) : max(0, min(32, L - kDenseK * (ntiles - 1) - 32 * part));
-  // ... K rows of the first scores, then the queries, then the rest
-  load_tile(kbase, 0, DLLM_IC(0));
-  if constexpr (KS == 2)
-    if (ntiles > 1) load_tile(kbase, 1, DLLM_IC(TILEB));
-  // The wave's 64 query rows go through LDS, into ring slots that no tile needs yet and the slot behind the rings:
-  // read straight into the operand layout, an instruction touches 32 rows of 32 bytes each, and the sixteen of them took
-  // 3200 to 5200 cycles to issue.  Rows past the last query repeat it (their columns are never stored).
-  const int qslot = KS == 1 ? (wave < 2 ? 2 + wave : wave == 2 ? kDenseRing + 2 : 2 * kDenseRing)
-                            : (qwave == 0 ? kDenseRing + 2 : 2 * kDenseRing);
-  static_assert(kDenseQB * 32 == kDenseK, "a wave's queries fill one slot");
-  constexpr int NQLD = CH / KS;   // loads of 1 KB: with KS = 2 each wave of a pair that shares the queries brings half
-  {
-    const uint32_t stage = __builtin_amdgcn_readfirstlane(lds_addr(smem) + qslot * TILEB + part * NQLD * 1024);
-    const uint16_t* qh = q + int64_t(q0) * s.q_tok + int64_t(h) * s.q_head;
-    auto round = [&](auto ic) __attribute__((always_inline)) {
-      constexpr int i = decltype(ic)::value;
-      const int f = (part * NQLD + i) * 64 + lane, r = f / CH;
-      const int qi = min(qbase + qwave * 64 + r, nq - 1);
-      load16_to_lds<i * 1024>(qh + int64_t(qi) * s.q_tok + (((f % CH) ^ tile_swz<D>(r)) << 3), stage);
-    };
-    for_each_round(round, std::make_integer_sequence<int, NQLD>{});
-  }
-  if constexpr (KS == 1) {
-    load_tile(vbase, 0, DLLM_IC(VBASE));
-    if (ntiles > 1) {
-      load_tile(kbase, 1, DLLM_IC(TILEB));
-      load_tile(vbase, 1, DLLM_IC(VBASE + TILEB));
-    }
-  } else {
-    if (ntiles > 2) load_tile(kbase, 2, DLLM_IC(2 * TILEB));
-    load_tile(vbase, 0, DLLM_IC(VBASE));
-  }
-  // Iteration 0 multiplies an all-zero P with the rows of ring slot 3 of V that the step "before the first" would
-  // have used (the second half of the slot, or both halves when the keys are split): clear them, so that no stale
-  // NaN pattern meets the zeros.  Tile 3 lands there later.
-  {
-    constexpr int kFrom = KS == 1 ? 32 * ROWB : 0;
-    for (int e = kFrom + tid * 16; e < TILEB; e += NTHREADS * 16)
-      *reinterpret_cast<v4u*>(smem + VBASE + 3 * TILEB + e) = v4u{0u, 0u, 0u, 0u};
-  }
-
+  DenseState w;
   const float zscale = s.scale * kLog2e;   // > 0; scores * zscale are base-2 logits
-  // per query (lane pair l, l ^ 32): -m * z for the running maximum m of the raw scores (w.nmz), the factor
-  // the accumulators (outputs and row sums) still have to take, and the accumulators
-  float palpha[NQB];
-  bool pending = false;   // some palpha != 1 (uniform)
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb) {
-    palpha[qb] = 1.0f;
-  }
-  {
-    const uint32_t one2 = (lane & 31) == (lane & 4 ? 20 : 0) ? 0x3f803f80u : 0u;   // rows 0 and 4, see DLLM_LS_OUT
-    w.ones = v4u{one2, one2, one2, one2};
-  }
-  w.acc_clear();
-#pragma unroll
-  for (int i = 0; i < 16; ++i) w.pb_a[i] = w.pb_b[i] = 0.0f;
-
   // A operands of one step's score chain: rows = 32 keys at byte offset `koff` of the K ring
   auto k_operands = [&](int koff) __attribute__((always_inline)) {
 #pragma unroll
@@ -448,193 +406,254 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     for (int i = 2; i < 16; i += 2) mx = fmaxf(fmaxf(mx, st[i]), st[i + 1]);
     return mx;
   };
-  // What the first step of each tile needs to request the tile two ahead (see the step text).  Past
-  // the last tile the last one is requested again, into a ring slot nobody reads any more.
-  const int64_t tile_bytes = int64_t(kDenseK) * pitch;
-  const bool last_whole = ntiles * kDenseK == L;
-  DenseTileLoad tl;
-  tl.wave_lds = wave_lds;
-  int64_t advance_k, advance_v;   // what the pointers move by after a tile's first step; 0 once they reached the last tile
-  auto aim_loads = [&](int tile) __attribute__((always_inline)) {   // for the requests of `tile`'s first step
-    const int tk = min(tile + AHEAD_K, ntiles - 1), tv = min(tile + AHEAD_V, ntiles - 1);
-    advance_k = tk < ntiles - 1 ? tile_bytes : 0;
-    advance_v = tv < ntiles - 1 ? tile_bytes : 0;
-    tl.k = kbase + tk * tile_bytes;
-    tl.v = vbase + tv * tile_bytes;
-#pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      tl.off[i] = (tk == ntiles - 1 && !last_whole) ? ld_off_last[i] : ld_off[i];
-      if constexpr (KS == 2) tl.off_v[i] = (tv == ntiles - 1 && !last_whole) ? ld_off_last[i] : ld_off[i];
-    }
-  };
-  aim_loads(0);
 
-  // the first scores need the queries and the K rows requested before them; the loads after those stay in flight (the
-  // first step waits for them, see its text), unless the sequence is so short that some were left out
-  if (ntiles > (KS == 1 ? 1 : 3)) wait_tile_loads_but<(KS == 1 ? 3 : 2) * NLD>();
-  else wait_tile_loads();
-  __syncthreads();
-  // Q^T operands: lane (col = query, hf) holds Q[query][16t + 8hf .. +8) for every step t, as given
+  // ---- the first tile's requests: K rows of the first scores and the queries, then the rest
+  Keys keys = keys_of(at);
+  load_tile(keys, keys.k, 0, DLLM_IC(0));
+  if constexpr (KS == 2) load_tile(keys, keys.k, 1, DLLM_IC(TILEB));
+  load_queries(at);
+  if constexpr (KS == 1) {
+    load_tile(keys, keys.k, 1, DLLM_IC(TILEB));
+    load_tile(keys, keys.v, 0, DLLM_IC(VBASE));
+    load_tile(keys, keys.v, 1, DLLM_IC(VBASE + TILEB));
+  } else {
+    load_tile(keys, keys.k, 2, DLLM_IC(2 * TILEB));
+    load_tile(keys, keys.v, 0, DLLM_IC(VBASE));
+  }
+  // Iteration 0 multiplies an all-zero P with the rows of ring slot 3 of V that the step "before the first" would
+  // have used (the second half of the slot, or both halves when the keys are split): clear them, so that no stale
+  // NaN pattern meets the zeros.  Tile 3 lands there later.
   {
-    KAddr<D> qaddr;
-    qaddr.init(lane);
+    constexpr int kFrom = KS == 1 ? 32 * ROWB : 0;
+    for (int e = kFrom + tid * 16; e < TILEB; e += NTHREADS * 16)
+      *reinterpret_cast<v4u*>(smem + VBASE + 3 * TILEB + e) = v4u{0u, 0u, 0u, 0u};
+  }
+
+  for (;;) {   // over query tiles
+    const int L = at.L, ntiles = keys.ntiles, qbase = at.qtile * kDenseRows;
+    const int nsteps = KS == 1 ? (L + 31) / 32 : ntiles;
+    // valid keys of this wave's last step: 32, or fewer when the sequence ends inside it (none at all is possible for
+    // the second half of a tile)
+    const int last_valid = KS == 1 ? L - 32 * (nsteps - 1) : max(0, min(32, L - kDenseK * (ntiles - 1) - 32 * part));
+    // per query (lane pair l, l ^ 32): -m * z for the running maximum m of the raw scores (w.nmz), the factor
+    // the accumulators (outputs and row sums) still have to take, and the accumulators
+    float palpha[NQB];
+    uint32_t pending = 0;   // 1: some palpha != 1 (uniform)
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb) palpha[qb] = 1.0f;
+    w.acc_clear();
+    // LDS addresses, fixed for the whole pass; ring slot, 32-key half and 16-key quarter are immediates
+    KAddr<D> kaddr;
+    {
+      const int mine = anew(lane);
+      kaddr.init(mine);
+      VtAddr<D> vaddr;
+      vaddr.init(mine);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) w.addr[i] = 0;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) w.addr[t] = kaddr.off(t) + part * 32 * ROWB;
+#pragma unroll
+      for (int rd = 0; rd < 2; ++rd)
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) w.addr[8 + NDB * rd + db] = VBASE + vaddr.off(rd, db) + part * 32 * ROWB;
+      const uint32_t one2 = (mine & 31) == (mine & 4 ? 20 : 0) ? 0x3f803f80u : 0u;   // rows 0 and 4, see DLLM_LS_OUT
+      w.ones = v4u{one2, one2, one2, one2};
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w.pb_a[i] = w.pb_b[i] = 0.0f;
+#pragma unroll
+    for (int qb = 0; qb < NQB; ++qb)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) w.st_b[qb][i] = 0.0f;
+    // What the first step of each tile needs to request the tile two ahead (see the step text).  Past
+    // the last tile the last one is requested again, into a ring slot nobody reads any more.
+    DenseTileLoad tl;
+    tl.wave_lds = wave_lds;
+    int64_t advance_k, advance_v;   // what the pointers move by after a tile's first step; 0 once they reached the last tile
+    auto aim_loads = [&](int tile) __attribute__((always_inline)) {   // for the requests of `tile`'s first step
+      const int tk = min(tile + AHEAD_K, ntiles - 1), tv = min(tile + AHEAD_V, ntiles - 1);
+      advance_k = tk < ntiles - 1 ? tile_bytes : 0;
+      advance_v = tv < ntiles - 1 ? tile_bytes : 0;
+      tl.k = keys.k + tk * tile_bytes;
+      tl.v = keys.v + tv * tile_bytes;
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        tl.off[i] = tk == ntiles - 1 ? keys.off_last[i] : ld_off[i];
+        if constexpr (KS == 2) tl.off_v[i] = tv == ntiles - 1 ? keys.off_last[i] : ld_off[i];
+      }
+    };
+    aim_loads(0);
+
+    // The first scores need the queries and the K rows requested before them; the three (KS = 2: two) tiles requested after
+    // those stay in flight (the first step waits for them, see its text).  Stores of the previous tile's outputs may have
+    // been issued behind them: operations complete in order, so that is only a longer wait.
+    wait_tile_loads_but<(KS == 1 ? 3 : 2) * NLD>();
+    __syncthreads();
+    // Q^T operands: lane (col = query, hf) holds Q[query][16t + 8hf .. +8) for every step t, as given
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const v4u x = *reinterpret_cast<const v4u*>(smem + qslot * TILEB + qb * 32 * ROWB + qaddr.off(t));
+        const v4u x = *reinterpret_cast<const v4u*>(smem + qslot * TILEB + qb * 32 * ROWB + kaddr.off(t));
         w.q_set(qb, t, 0, __uint_as_float(x.x));
         w.q_set(qb, t, 1, __uint_as_float(x.y));
         w.q_set(qb, t, 2, __uint_as_float(x.z));
         w.q_set(qb, t, 3, __uint_as_float(x.w));
       }
-  }
 
-  // scores of step 0, its maxima outright (they may be negative)
-  k_operands(0);
-  w.score0();
-  if (nsteps == 1 && last_valid < 32) mask_tail(w.st_a, last_valid);
-  const bool no_keys = KS == 2 && nsteps == 1 && last_valid == 0;   // this wave pair's half of the only tile is empty
-  // (no lower than the lowest finite number: keys whose scores overflowed to minus infinity weigh nothing instead of
-  // (-inf) - (-inf), also when they fill the first step)
+    // scores of step 0, its maxima outright (they may be negative)
+    k_operands(0);
+    w.score0();
+    if (nsteps == 1 && last_valid < 32) mask_tail(w.st_a, last_valid);
+    const bool no_keys = KS == 2 && nsteps == 1 && last_valid == 0;   // this wave pair's half of the only tile is empty
+    // (no lower than the lowest finite number: keys whose scores overflowed to minus infinity weigh nothing instead of
+    // (-inf) - (-inf), also when they fill the first step)
 #pragma unroll
-  for (int qb = 0; qb < NQB; ++qb)
-    w.nmz[qb] = no_keys ? 0.0f : -fmaxf(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
-#pragma unroll
-  for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) w.st_b[qb][i] = 0.0f;
-  if constexpr (KS == 2) {   // what a step before the first would have requested, so that every step finds the same in flight
-    if (ntiles > 3) load_tile(kbase, 3, DLLM_IC(3 * TILEB));
-    if (ntiles > 1) load_tile(vbase, 1, DLLM_IC(VBASE + TILEB));
-  }
-  k_operands(KS == 1 ? 32 * ROWB : TILEB);   // step 1 (stale LDS if there is none; then unused)
+    for (int qb = 0; qb < NQB; ++qb)
+      w.nmz[qb] = no_keys ? 0.0f : -fmaxf(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
+    if constexpr (KS == 2) {   // what a step before the first would have requested, so that every step finds the same in flight
+      load_tile(keys, keys.k, 3, DLLM_IC(3 * TILEB));
+      load_tile(keys, keys.v, 1, DLLM_IC(VBASE + TILEB));
+    }
+    k_operands(KS == 1 ? 32 * ROWB : TILEB);   // step 1 (stale LDS if there is none; then unused)
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0) here, or the compiler waits for all LDS reads at every turn of the loop
 
-  // Iteration j at position R = j % ROUND of the ring turn, which fixes every LDS offset.  Between two
-  // steps the common path is a handful of scalar instructions and one branch; everything else (the end
-  // of the sequence, the ragged last step, a running maximum to raise, accumulators that still owe a
-  // factor) sits behind that branch.
-  // Between two steps the common path is one test and, after the first step of a tile, the advance of
-  // the tile pointers; everything else (the end of the sequence, the ragged last step, a running
-  // maximum to raise, accumulators that still owe a factor) sits behind that test.  `special` is
-  // set while something other than a grown score asks for the careful path: accumulators that owe a
-  // factor, or the last steps of the sequence (from one ring turn before the end).
-  int j = 0;        // steps done
-  int jb = 0;       // steps done at the start of the current ring turn
-  uint32_t special = 0;   // (kept wave-uniform in a scalar register)
-  DLLM_STAMP_LOOP_START();
-  // ring offset of the rows of the step at ring position r
-  constexpr auto step_off = [](int r) constexpr { return (r / SPT) * TILEB + (r % SPT) * 32 * ROWB; };
-  // one step at ring position R (the text, with every offset it needs)
+    // Iteration j at position R = j % ROUND of the ring turn, which fixes every LDS offset.  Between two steps the common
+    // path is one test and, after the first step of a tile, the advance of the tile pointers; everything else (the end of
+    // the sequence, the ragged last step, a running maximum to raise, accumulators that still owe a factor) sits behind
+    // that test.  `stop` is the number of steps done when the careful path is due without such a reason: when the next
+    // tile to begin requests the last one, when the next step is a ragged last one, and at the end.  (Once the loads aim
+    // at the last tile they stay there.  A visit costs some 280 cycles, and 1100 where it scales the accumulators; every step of the last one or two ring turns
+    // used to make one, and a ragged last step scaled them by 1.)
+    int j = 0;        // steps done
+    int jb = 0;       // steps done at the start of the current ring turn
+    const int aim_v = SPT * (ntiles - 1 - AHEAD_V) - (SPT - 1);   // ... for V rows, which the split form requests later
+    int stop = SPT * (ntiles - 1 - AHEAD_K) - (SPT - 1);
+    int left = 0;     // steps of this ring turn, and jb before it, that the common path may still take: stop - 1 - jb
+    // ring offset of the rows of the step at ring position r
+    constexpr auto step_off = [](int r) constexpr { return (r / SPT) * TILEB + (r % SPT) * 32 * ROWB; };
+    // one step at ring position R (the text, with every offset it needs)
 #define DLLM_RUN_STEP(R, grow)                                                                                  \
   w.template step<(R) % 2 == 0, KS == 2, step_off(((R) + 2) % ROUND), step_off(((R) + ROUND - 1) % ROUND),        \
                   step_off(((R) + ROUND - 1) % ROUND) + 16 * ROWB, (((R) / SPT + AHEAD_K) % kDenseRing) * TILEB,  \
                   VBASE + (((R) / SPT + AHEAD_V) % kDenseRing) * TILEB>(zscale, tl, grow)
-  // what may need doing after step number j - 1 (at ring position R); true when the sequence is finished
-  auto careful = [&](auto rc, uint64_t grow) __attribute__((always_inline)) -> bool {
-    constexpr int R = decltype(rc)::value;
-    if (pending) {   // hand the accumulators the factor they still owe
-      w.acc_scale(palpha[0], palpha[1]);
-      palpha[0] = palpha[1] = 1.0f;
-      pending = false;
-    }
-    if (j >= nsteps) return true;
-    // tile requests near the end: the pointers stop at the last tile, whose rows may end early
-    aim_loads((j + SPT - 1) / SPT);   // the next boundary is the first step of this tile
-    const bool ragged = last_valid < 32 && j + 1 == nsteps;
-    if (ragged || grow != 0) {
-      // Mask the ragged last step and raise the running maxima for the scores of step j.  Keys past the
-      // end were scored from copies of the last row (the tile loads clamp the row), so they carry that
+    // what may need doing after step number j - 1 (at ring position R); true when the sequence is finished
+    auto careful = [&](auto rc, uint64_t grow) __attribute__((always_inline)) -> bool {
+      constexpr int R = decltype(rc)::value;
+      if (pending) {   // hand the accumulators the factor they still owe
+        w.acc_scale(palpha[0], palpha[1]);
+        palpha[0] = palpha[1] = 1.0f;
+        pending = 0;
+      }
+      if (j >= nsteps) return true;
+      // tile requests near the end: the pointers stop at the last tile, whose rows may end early
+      aim_loads((j + SPT - 1) / SPT);   // the next boundary is the first step of this tile
+      // Keys past the end were scored from copies of the last row (the tile loads clamp the row), so they carry that
       // row's score and the lane maxima need no second look after masking.
-      if (ragged) {
+      const int last_due = last_valid < 32 ? nsteps - 1 : nsteps;
+      if (j == last_due) {
         if constexpr (R % 2 == 0) mask_tail(w.st_b, last_valid);
         else mask_tail(w.st_a, last_valid);
       }
-#pragma unroll
-      for (int qb = 0; qb < NQB; ++qb) {
-        const float mz_old = -w.nmz[qb];
-        const float mz_new = fmaxf(mz_old, max_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
-        const float alpha = __builtin_amdgcn_exp2f(mz_old - mz_new);
-        palpha[qb] = alpha;
-        w.nmz[qb] = -mz_new;
+      if (j >= stop) {
+        stop = j < aim_v ? aim_v : j < last_due ? last_due : nsteps;
+        left = stop - 1 - jb;
       }
-      pending = true;
-    }
-    special = __builtin_amdgcn_readfirstlane((pending || j + NEAR_END > nsteps) ? 1u : 0u);
-    return false;
-  };
+      if (grow != 0) {   // raise the running maxima for the scores of step j
+#pragma unroll
+        for (int qb = 0; qb < NQB; ++qb) {
+          const float mz_old = -w.nmz[qb];
+          const float mz_new = fmaxf(mz_old, max_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
+          const float alpha = __builtin_amdgcn_exp2f(mz_old - mz_new);
+          palpha[qb] = alpha;
+          w.nmz[qb] = -mz_new;
+        }
+        pending = 1;
+      }
+      return false;
+    };
 #define DLLM_STEP(R)                                         \
   {                                                          \
     uint64_t grow;                                           \
     DLLM_RUN_STEP(R, grow);                                  \
-    DLLM_STAMP_STEP(R);                                      \
     if ((R) % SPT == 0) {                                    \
       tl.k += advance_k;                                     \
       tl.v += advance_v;                                     \
     }                                                        \
-    if (__builtin_expect((uint32_t(grow) | uint32_t(grow >> 32) | special) != 0, 0)) { \
+    if (__builtin_expect((uint32_t(grow) | uint32_t(grow >> 32) | pending | uint32_t(left - (R) - 1) >> 31) != 0, 0)) { \
       j = jb + (R) + 1;                                      \
       if (careful(DLLM_IC(R), grow)) break;                  \
     }                                                        \
   }
-  for (;;) {
-    special = __builtin_amdgcn_readfirstlane((pending || jb + NEAR_END > nsteps) ? 1u : 0u);
-    DLLM_STEP(0)
-    DLLM_STEP(1)
-    DLLM_STEP(2)
-    DLLM_STEP(3)
-    if constexpr (ROUND == 8) {
-      DLLM_STEP(4)
-      DLLM_STEP(5)
-      DLLM_STEP(6)
-      DLLM_STEP(7)
+    for (;;) {
+      left = stop - 1 - jb;
+      DLLM_STEP(0)
+      DLLM_STEP(1)
+      DLLM_STEP(2)
+      DLLM_STEP(3)
+      if constexpr (ROUND == 8) {
+        DLLM_STEP(4)
+        DLLM_STEP(5)
+        DLLM_STEP(6)
+        DLLM_STEP(7)
+      }
+      jb += ROUND;
     }
-    jb += ROUND;
-  }
-  // the last step's P V product: its probabilities are in pb_a after an odd number of steps, else in pb_b
-  {
-    const int last = nsteps - 1;
-    const int voff = (last / SPT % kDenseRing) * TILEB + (last % SPT) * 32 * ROWB;
-    i32x16 ad = w.addr;
+#undef DLLM_STEP
+#undef DLLM_RUN_STEP
+    w.drain();
+    const DensePlace done = at;
+    const bool more = stays && find(at);
+    wait_tile_loads();   // the requests past the last tile still write to the rings
+    __syncthreads();     // every wave is past its last K operands: the K ring is free
+    if (more) {
+      keys = keys_of(at);
+      load_tile(keys, keys.k, 0, DLLM_IC(0));
+      load_queries(at);
+      load_tile(keys, keys.k, 1, DLLM_IC(TILEB));
+    }
+    // the last step's P V product: its probabilities are in pb_a after an odd number of steps, else in pb_b
+    {
+      const int last = nsteps - 1;
+      const int voff = (last / SPT % kDenseRing) * TILEB + (last % SPT) * 32 * ROWB;
+      i32x16 ad = w.addr;
 #pragma unroll
-    for (int i = 8; i < 16; ++i) ad[i] += voff;
-    // (One tail for both cases, after moving sixteen registers: with a tail in either arm of a branch the
-    // compiler carries all accumulators through vector registers and back where the arms meet, 2500 of the
-    // 2900 cycles from the last step to the stores.)
-    if (!(nsteps & 1)) w.pb_a = w.pb_b;
-    w.tail(ad);
-  }
-#ifdef DLLM_DENSE_STAMPS
-  const uint64_t t_loop1 = __builtin_readcyclecounter();
-#endif
-  float accv[DenseState::kAcc];   // [qb][db][16]
-  w.acc_read(accv);
-#ifdef DLLM_DENSE_STAMPS
-  if (tid == 0) {
-    uint64_t* dst = reinterpret_cast<uint64_t*>(o + (int64_t(q0 + qbase) * s.hq + h) * D);
-    dst[0] = t_entry; dst[1] = t_loop0; dst[2] = t_loop1; dst[3] = __builtin_readcyclecounter();
-    for (int r = 0; r < 8; ++r) dst[4 + r] = by_r[r];
-    dst[12] = t_max; dst[13] = n_slow;
-    dst[14] = parts[1]; dst[15] = parts[2]; dst[16] = parts[3];   // load wait, barrier, load issue: sums over the tiles
-    dst[17] = rt_entry; dst[18] = __builtin_amdgcn_s_memrealtime();
-    dst[19] = (uint64_t(__builtin_amdgcn_s_getreg(20 | (0 << 6) | (3 << 11))) << 32) | __builtin_amdgcn_s_getreg(4 | (0 << 6) | (31 << 11));
-  }
-  return;   // the counts sit where outputs would go
-#endif
-  float lrow[NQB];
-  w.row_sums(lrow[0], lrow[1]);   // lanes 0..31: the query's sum; lanes 32..63: zero
-  wait_tile_loads();   // the requests past the last tile still write to the rings, which are now space for the outputs
-  __syncthreads();
-  if constexpr (KS == 1) {
+      for (int i = 8; i < 16; ++i) ad[i] += voff;
+      // (One tail for both cases, after moving sixteen registers: with a tail in either arm of a branch the
+      // compiler carries all accumulators through vector registers and back where the arms meet, 2500 of the
+      // 2900 cycles from the last step to the stores.)
+      if (!(nsteps & 1)) w.pb_a = w.pb_b;
+      w.tail(ad);
+    }
+    __syncthreads();     // ... and its last V rows: the V ring is free
+    if (more) {
+      load_tile(keys, keys.v, 0, DLLM_IC(VBASE));
+      load_tile(keys, keys.v, 1, DLLM_IC(VBASE + TILEB));
+    }
+    float accv[DenseState::kAcc];   // [qb][db][16]
+    w.acc_read(accv);
+    float lrow[NQB];
+    w.row_sums(lrow[0], lrow[1]);   // lanes 0..31: the query's sum; lanes 32..63: zero
+    if constexpr (KS == 1) {
+      // 32 rows of each wave at a time, through V ring slots 2 and 3
+      char* stage = smem + VBASE + 2 * TILEB + wave * 32 * ROWB;
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb) 
-      store_dense_block<D>(accv + 16 * NDB * qb, sum_across_halves(lrow[qb]), smem + (NQB * wave + qb) * 32 * ROWB,
-                           qbase + (qwave * NQB + qb) * 32, at, s.hq, o);
-  } else {
-    static_assert(NQB == 2 && kDenseWaves == 4, "two wave pairs, two blocks each");
-    static_assert(dense_merge_bytes<D>() <= 2 * kDenseRing * TILEB, "merge space");
-    const float m[2] = {no_keys ? -INFINITY : -w.nmz[0], no_keys ? -INFINITY : -w.nmz[1]};
-    merge_dense_halves<D>(accv, lrow, m, part, smem, qbase + qwave * NQB * 32, at, s.hq, o);
+      for (int qb = 0; qb < NQB; ++qb)
+        store_dense_block<D>(accv + 16 * NDB * qb, sum_across_halves(lrow[qb]), stage, qbase + (wave * NQB + qb) * 32, done, s.hq, o);
+    } else {
+      static_assert(NQB == 2 && kDenseWaves == 4, "two wave pairs, two blocks each");
+      static_assert(dense_merge_bytes<D>() <= 2 * kDenseRing * TILEB, "merge space");
+      const float m[2] = {no_keys ? -INFINITY : -w.nmz[0], no_keys ? -INFINITY : -w.nmz[1]};
+      merge_dense_halves<D>(accv, lrow, m, part, smem, qbase + qwave * NQB * 32, done, s.hq, o);
+    }
+    if (!more) break;
+    // the rows that the next iteration 0 multiplies by zeros: the last wave's outputs came through them
+    static_assert(kDenseWaves == 4, "the last wave stages its outputs in the second half of V ring slot 3");
+    if (wave == kDenseWaves - 1)
+#pragma unroll
+      for (int i = 0; i < 32 * ROWB / 1024; ++i)
+        *reinterpret_cast<v4u*>(smem + VBASE + 3 * TILEB + 32 * ROWB + (i * 64 + lane) * 16) = v4u{0u, 0u, 0u, 0u};
   }
 }
 
@@ -644,7 +663,9 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 // sequence of 256 14.6 / 11.3, 512 19.6 / 15.0, 1024 29.7 / 24.6 (half the compute units); 2048 65.6 / 75.4 (all of them);
 // three of 768 53.7 / 57.9 (two rounds against three); five of 300 35.4 / 27.1.
 // head_dim 128, in shader cycles from the clock at the marks of both forms: 1440 per step and 13000 besides (split:
-// 1660); one workgroup runs per compute unit at a time.
+// 1660); one workgroup runs per compute unit at a time.  (Since workgroups stay for further tiles and the end of a sequence
+// costs less, a step takes 1290 to 1460 and a further tile about 10000; over 118 batches measured in both forms the choice
+// is still 0.03 % above the better one in the mean.)
 // head_dim 64 (two workgroups per compute unit), in ns, fitted to 101 batches measured in both forms (4 to 32 heads, one to 40
 // sequences of 64 to 6000): a step takes 449 (split: 485) on a compute unit that the workgroup has for itself and 500 (525)
 // of a shared one, where a workgroup costs 1000 (1500) besides; 3000 before the first step.  Ragged batches of up to 512
@@ -710,6 +731,8 @@ hipError_t launch_attend_dense_bf16(const Shape& s, const void* q, const void* k
     // the workgroups place themselves (see the kernel): as many as the batch can have query tiles, times the heads
     const int64_t tiles = std::min<int64_t>(int64_t(s.total_q) / rows + s.batch, nx * s.batch);
     if (tiles * s.hq < (int64_t(1) << 31)) grid = dim3(unsigned(tiles * s.hq), 1, 1);
+    // at head_dim 128 workgroups stay for further tiles (see the kernel)
+    if (s.d == 128 && ks == 1 && grid.y == 1 && grid.z == 1) grid.x = std::min(grid.x, unsigned(kDenseUnits));
   }
   auto launch = [&](auto kernel) -> hipError_t {
     kernel<<<grid, kDenseWaves * 64, 0, st>>>(static_cast<const uint16_t*>(q), static_cast<const uint16_t*>(k),

@@ -162,11 +162,13 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
   // A tile's first step requests the K rows of the tile kAheadK further on and the V rows of the one kAheadV further on:
   // K rows are read two steps before their products and V rows in the step of theirs, so those slots are free.
   constexpr int kAheadK = KS == 1 ? 3 : 4, kAheadV = 3;
-  // a ring turn that starts with fewer steps than this left, or the turn after it, requests the last tile
-  constexpr int kNearEnd = 2 * kRound + 2;
   __shared__ __attribute__((aligned(16))) char smem[2 * kRing * TILEB];   // K ring, V ring
   DensePlace at;
-  if (!place_dense<kRows>(s, cu_q, cu_kv, seq_mode, which, at)) return;
+  if (gridDim.y == 1 && gridDim.z == 1) {
+    if (!find_dense(s, gather_dense<kRows>(s, cu_q, cu_kv, seq_mode, which), blockIdx.x, at)) return;
+  } else if (!place_dense_grid<kRows>(s, cu_q, cu_kv, seq_mode, which, at)) {
+    return;
+  }
   const int L = at.L, qbase = at.qtile * kRows;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, hf = lane >> 5;
   // the query blocks this wave takes, and which half of every tile's keys (0 when all waves take both)
@@ -309,20 +311,27 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
   aim(kAheadK, kAheadV);
 
   // Iteration j at position R = j % kRound of the ring turn, which fixes every LDS offset.  Between two steps the common
-  // path is one test and, after a tile's first step, the advance of the tile pointers.  `special` (wave-uniform) sends
-  // the steps near the end of the sequence through the careful path.
+  // path is one test and, after a tile's first step, the advance of the tile pointers.  `stop` is the number of steps done
+  // when the careful path is due although no score has outgrown its maximum: when the next tile to begin requests the last
+  // one (once the loads aim at it they stay there), when the next step is a ragged last one, and at the end.
   int j = 0, jb = 0;   // steps done; steps done at the start of the current ring turn
-  uint32_t special = 0;
+  const int aim_v = SPT * (ntiles - 1 - kAheadV) - (SPT - 1);   // ... for V rows, which the split form requests later
+  int stop = SPT * (ntiles - 1 - kAheadK) - (SPT - 1);
+  int left = 0;        // stop - 1 - jb
   // what may need doing after step number j - 1 (at ring position R); true when the sequence is finished
   auto careful = [&](auto rc, uint64_t grow) __attribute__((always_inline)) -> bool {
     constexpr int R = decltype(rc)::value;
     if (j >= nsteps) return true;
     const int tile = (j + SPT - 1) / SPT;   // the next tile to be begun
     aim(tile + kAheadK, tile + kAheadV);
-    const bool ragged = last_valid < 32 && j + 1 == nsteps;
-    if (ragged || grow != 0) {
-      // Keys past the end were scored from copies of the last row, so the lane maxima need no second look after masking.
-      if (ragged) mask_tail(R % 2 == 0 ? w.st_b : w.st_a);
+    // Keys past the end were scored from copies of the last row, so the lane maxima need no second look after masking.
+    const int last_due = last_valid < 32 ? nsteps - 1 : nsteps;
+    if (j == last_due) mask_tail(R % 2 == 0 ? w.st_b : w.st_a);
+    if (j >= stop) {
+      stop = j < aim_v ? aim_v : j < last_due ? last_due : nsteps;
+      left = stop - 1 - jb;
+    }
+    if (grow != 0) {
       float alpha[2];
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) {
@@ -333,7 +342,6 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
       }
       w.acc_scale(alpha[0], alpha[1]);
     }
-    special = __builtin_amdgcn_readfirstlane(j + kNearEnd > nsteps ? 1u : 0u);
     return false;
   };
   // ring offset of the rows of the step at ring position r
@@ -347,13 +355,13 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
       tl.k += advance_k;                                                                                                 \
       tl.v += advance_v;                                                                                                 \
     }                                                                                                                    \
-    if (__builtin_expect((uint32_t(grow) | uint32_t(grow >> 32) | special) != 0, 0)) {                                   \
+    if (__builtin_expect((uint32_t(grow) | uint32_t(grow >> 32) | uint32_t(left - (R) - 1) >> 31) != 0, 0)) {             \
       j = jb + (R) + 1;                                                                                                  \
       if (careful(DLLM_IC(R), grow)) break;                                                                              \
     }                                                                                                                    \
   }
   for (;;) {
-    special = __builtin_amdgcn_readfirstlane(jb + kNearEnd > nsteps ? 1u : 0u);
+    left = stop - 1 - jb;
     DLLM_STEP(0)
     DLLM_STEP(1)
     DLLM_STEP(2)

@@ -28,13 +28,6 @@ read by the next instruction.
 import os
 import sys
 
-# timing experiments only (wrong results): leave out the vector work or the LDS operand fetches
-NO_VALU = "--no-valu" in sys.argv
-NO_DS = "--no-ds" in sys.argv
-NO_KREAD = "--no-kread" in sys.argv   # keep the waits, drop the reads themselves
-NO_VREAD = "--no-vread" in sys.argv
-NO_LOADS = "--no-loads" in sys.argv   # keep the barrier, drop the global_load_lds (LDS keeps what the prologue loaded)
-
 # ---- register map (v-registers; a-registers are numbered separately)
 ST_A, ST_B = 96, 128          # scores, [qb][16]
 PB_A, PB_B = 160, 176         # packed probabilities, [qb][u][4]
@@ -43,7 +36,7 @@ VOP = 224                     # V^T operand buffers [NBUF][4]
 TMP = 76                      # [2][2] logits / probabilities in flight
 SM = 70                       # lsum0, lsum1, nmz0, nmz1, mx0, mx1
 ADDR = 80                     # ka[8], va[2][4]
-NBUF = int(os.environ.get("DLLM_GEN_NBUF", "8"))
+NBUF = 8
 ACC = 0                       # a: acc[qb][db][16]
 ONES = "0x3f803f80"           # bf16 (1, 1)
 
@@ -198,14 +191,8 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             lines.append(dtext)
             issued.append(tag)
         ds[0] = []
-    if NO_VALU:
-        valu = [[] for _ in range(nslots)]
     for s in range(nslots):
         text, need = mfma[s]
-        if NO_DS:
-            lines.append(text)
-            lines += valu[s]
-            continue
         if with_scores and s < n_s and s % 2 == 0:
             t = s // 2
             n = wait_for(lambda tag: tag == ("k", t), True)
@@ -221,14 +208,13 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             # are in the pipe while the waves meet.  (split: a tile lasts one step, so the previous step's loads
             # stay in flight and those before them have landed.)
             lines += [f"s_waitcnt vmcnt({len(seq) if split else 0})", "s_barrier"]
-        if loads[s] and not NO_LOADS:
+        if loads[s]:
             lines.append(loads[s][0])
         for dtext, tag in ds[s]:
-            if not ((NO_KREAD and tag[0] == "k") or (NO_VREAD and tag[0] == "v")):
-                lines.append(dtext)
+            lines.append(dtext)
             issued.append(tag)
         lines += valu[s][:1]
-        if loads[s] and not NO_LOADS:
+        if loads[s]:
             lines.append(loads[s][1])
         lines += valu[s][1:]
     if with_softmax:

@@ -525,6 +525,37 @@ def test_dense_tiles_place_themselves_on_ragged_and_mixed_batches(Hq, Hkv, D, n)
     assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL[wd.dtype]
 
 
+@pytest.mark.parametrize("Hq,Hkv,n", [(32, 8, 20), (48, 16, 40), (40, 5, 33)])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_dense_workgroups_stay_for_further_tiles(Hq, Hkv, n, mixed):
+    """At head_dim 128 a launch of more than 256 query tiles has 256 workgroups, which take several each: tiles of one step
+    and of many after one another, sequences without keys (zeros) and without queries in between, KV-head counts that
+    are and are not multiples of eight, V rows that would leave infinities behind (outputs and keys of one tile must not
+    reach the next one's first step)."""
+    rng = np.random.default_rng(1100 + n + mixed)
+    lens = rng.choice([1, 31, 33, 64, 65, 130, 193, 257, 300, 513], size=n)
+    lens[rng.integers(0, n, size=2)] = 0
+    qlens = np.where(rng.random(n) < 0.2, 257, rng.integers(1, 70, size=n))   # a second tile of one query here and there
+    qlens[rng.integers(0, n)] = 0
+    mode = (rng.random(n) < 0.9).astype(np.uint8) if mixed else np.ones(n, np.uint8)
+    w = custom(110 + n, torch.bfloat16, Hq, Hkv, 128, lens.tolist(), qlens.tolist(), [0] * n, mode=mode, salient=0.05)
+    big = int(np.argmax(lens))   # outputs of this sequence overflow bf16
+    w.v[int(w.cu_kv[big]):int(w.cu_kv[big + 1])] *= 2.0 ** 127
+    tiles = int(((qlens + 255) // 256)[mode == 1].sum()) * Hq
+    dw = workload.DeviceWorkload(w)
+    assert tiles > 600 and hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=not mixed)[2] == 1
+    dw.o.fill_(float("nan"))
+    if mixed:
+        dw.attend(torch.zeros((Hq, 0), dtype=torch.int32, device=dw.device))
+    else:
+        dw.dense_refresh()
+    got = dw.o.float().cpu().numpy().astype(np.float64)
+    want = oracle_attend(w, np.zeros((Hq, 0), np.int32))
+    rows = np.ones(len(got), bool)
+    rows[int(w.cu_q[big]):int(w.cu_q[big + 1])] = False
+    assert np.isfinite(got[rows]).all() and np.abs(got[rows] - want[rows]).max() <= TOL[w.dtype]
+
+
 def block_rows(w, seed):
     """One query row out of every 32-row block of every sequence: every 32-query block of every wave of every
     workgroup of a full-size launch gets one row checked."""
