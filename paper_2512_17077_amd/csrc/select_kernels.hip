@@ -14,6 +14,7 @@
 // lane owns a whole row, each wave stages 64 rows through LDS: 16-byte chunks are loaded so that a
 // row's chunks sit in neighbouring lanes, written to LDS with an XOR swizzle, and read back one row
 // per lane without bank conflicts.
+#include <algorithm>
 #include <atomic>
 #include <type_traits>
 #include <utility>
@@ -604,7 +605,7 @@ __global__ __launch_bounds__(T) void topk_reg_kernel(
 // ------------------------------------------------------------------ scores and top-k in one workgroup
 // One workgroup per (sequence, KV head) walks the head's whole K column once, keeps the keys of its
 // GT query heads in registers (one key per lane, tile and head) and ranks them there: the scores never
-// travel to HBM and back and the lists need no second launch.  Lists of up to kFusedWords * 64
+// travel to HBM and back and the lists need no second launch.  Lists of up to W * NT * 64
 // positions; the arithmetic, the tie rule and the output order are those of the kernels above.
 //
 // Ranking is a radix select over digits of 10, 11 and 11 bits.  The first histogram is counted while
@@ -615,21 +616,24 @@ __global__ __launch_bounds__(T) void topk_reg_kernel(
 // kept positions (see there).
 // With a pooling window the keys are max-pooled in the registers once the column is in (see there); the
 // first histogram is then counted afterwards, in the open.
-constexpr int kFusedWords = 128;   // 64-row tiles per list at most (8192 positions): W waves of kFusedWords / W tiles
-// Eight waves of 16 tiles for every group size.  (Four waves of 32 tiles for one or two query heads per
-// KV head, so that two workgroups share a compute unit and one's start-up and ranking run under the
-// other's streaming, measured 2-10 % slower on every batch tried.)
-template <int GT> constexpr int fused_waves() { return 8; }
+constexpr int kFusedWaves = 8;
+constexpr int kFusedTiles = 16;       // 64-row tiles per wave at most: lists of up to 8192 positions
+constexpr int kFusedTilesShort = 2;   // ... in the instance for short lists, up to 1024 (see launch_fused)
+// Eight waves for every group size.  (Four waves of 32 tiles for one or two query heads per KV head, so that two
+// workgroups share a compute unit and one's start-up and ranking run under the other's streaming, measured 2-10 %
+// slower on every batch tried.)
 template <int N> struct KeyVec { typedef __attribute__((ext_vector_type(N))) uint32_t type; };
 constexpr int kBinsA = 1024, kBinsB = 2048;   // digits: key >> 22, (key >> 11) & 2047, key & 2047
 
-template <int ES, int D, int GT>
+template <int ES, int D, int GT, int NT>
 struct FusedLds {   // byte offsets inside the workgroup's dynamic LDS
-  static constexpr int W = fused_waves<GT>();
+  static constexpr int W = kFusedWaves, kFusedWords = W * NT;
   static constexpr size_t stage = size_t(W) * 64 * D * ES;            // the waves' tiles while streaming
   static constexpr size_t hist_bc = size_t(GT) * 2 * kBinsB * 4;                // afterwards: second and third histograms
-  static constexpr size_t kept = size_t(GT) * kFusedWords * 64 * 4;                 // at the end: the kept positions [GT][8192]
-  static constexpr size_t region0 = stage > hist_bc ? (stage > kept ? stage : kept) : (hist_bc > kept ? hist_bc : kept);
+  static constexpr size_t edges = size_t(GT) * W * 128 * 4;                     // ... and behind them the waves' edge tiles (pooling)
+  static constexpr size_t kept = size_t(GT) * kFusedWords * 64 * 4;             // at the end: the kept positions [GT][kFusedWords * 64]
+  static constexpr size_t most(size_t a, size_t b) { return a > b ? a : b; }
+  static constexpr size_t region0 = most(stage, most(hist_bc + edges, kept));
   static constexpr size_t off_a = region0;                                      // first histogram [GT][kBinsA]
   static constexpr size_t off_counts = off_a + size_t(GT) * kBinsA * 4;         // two bitmaps [GT][waves * tiles] of 64 bits, [2][waves] totals
   static constexpr size_t off_res = off_counts + size_t(GT) * kFusedWords * 16 + 2 * 8 * 4;   // [GT][4]
@@ -668,16 +672,16 @@ __device__ __forceinline__ uint3 pick_bin(const uint32_t* hrow, uint32_t kth, in
 // to pick up the previous compare's.
 __device__ __forceinline__ void set_lane(uint32_t& v, uint32_t x, int u) { v = int(threadIdx.x & 63) == u ? x : v; }
 
-template <int ES, int D, int GT>
-__global__ __launch_bounds__(fused_waves<GT>() * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void select_fused_kernel(
+template <int ES, int D, int GT, int NT>
+__global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void select_fused_kernel(
     const char* __restrict__ k, const char* __restrict__ q, const int32_t* __restrict__ cu_q,
     const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ cu_k, int32_t total_k, int32_t forced_tail,
     int32_t pool_w, int32_t ranked, int32_t* __restrict__ idx_out, Shape s DLLM_CHECK_PARAM) {
   DLLM_CHECK_EXIT();
-  constexpr int ROWB = D * ES, CH = ROWB / 16, EPC = 16 / ES, W = fused_waves<GT>(), NT = kFusedWords / W, T = W * 64;
+  constexpr int ROWB = D * ES, CH = ROWB / 16, EPC = 16 / ES, W = kFusedWaves, T = W * 64;
   static_assert(NT <= 32, "a wave's tile masks are collected one per lane, its keys in one register vector per head");
   static_assert(GT <= W, "one wave scans one head's histogram");
-  using Lds = FusedLds<ES, D, GT>;
+  using Lds = FusedLds<ES, D, GT, NT>;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   v4u* mine_all = reinterpret_cast<v4u*>(lds);
   uint32_t* hist_b = reinterpret_cast<uint32_t*>(lds);            // [GT][kBinsB], once streaming is over
@@ -841,7 +845,6 @@ __global__ __launch_bounds__(fused_waves<GT>() * 64) __attribute__((amdgpu_waves
     // built one position at a time: the keys moved on by one more lane per step, to either side, and
     // the running maximum.  Positions past the candidates hold key 0 and get it back at the end.
     uint32_t* edge = reinterpret_cast<uint32_t*>(lds + Lds::hist_bc);   // [GT][W][first | last][64]
-    static_assert(Lds::hist_bc + size_t(GT) * W * 128 * 4 <= Lds::region0, "the waves' edge tiles fit beside the histograms");
     const int last_u = max(ntiles - 1, 0);
     edge[((0 * W + wave) * 2 + 0) * 64 + lane] = k0[0];
     edge[((0 * W + wave) * 2 + 1) * 64 + lane] = k0[last_u];
@@ -974,8 +977,8 @@ __global__ __launch_bounds__(fused_waves<GT>() * 64) __attribute__((amdgpu_waves
   // lists go out in whole lines.  Keys equal to the threshold have a bitmap of their own, used only
   // when not all of them are kept (scores that tie exactly): a word then keeps its first few equal
   // keys, as many as the rule "lower position first" leaves for it.
-  static_assert(GT * kFusedWords <= T && W <= 8, "one thread per tile of each head; the waves' totals fit wave_tot");
-  constexpr int kWords = kFusedWords;   // tiles, and so bitmap words, per head
+  constexpr int kWords = W * NT;   // tiles, and so bitmap words, per head
+  static_assert(GT * 128 <= T && kWords <= 128 && W <= 8, "two waves per head, one thread per tile; the waves' totals fit wave_tot");
   uint64_t* bitmap = reinterpret_cast<uint64_t*>(lds + Lds::off_counts);   // [GT][kWords] keys above the threshold
   uint64_t* bitmap_eq = bitmap + GT * kWords;                              // [GT][kWords] keys equal to it
   uint32_t* wave_tot = reinterpret_cast<uint32_t*>(bitmap_eq + GT * kWords);   // [2][W]
@@ -1098,7 +1101,7 @@ static bool fused_can(const Shape& s, dllm_dtype dt, int32_t pool_w, int32_t hea
   if (head_sum) return false;
   if (s.group != 1 && s.group != 2 && s.group != 4) return false;
   if (s.d * (dt == DLLM_BF16 ? 2 : 4) > 256) return false;
-  return s.max_kv <= kFusedWords * 64;
+  return s.max_kv <= kFusedWaves * kFusedTiles * 64;
 }
 // ... and where it pays (measured on batches of equal lists, 1 to 4 query heads per KV head, lists of
 // 2048 to 8192): each (sequence, KV head) pair is one workgroup that takes most of a compute unit's
@@ -1121,11 +1124,27 @@ static int compute_units() {
   cached.store(n);
   return n;
 }
-static bool fused_pays(const Shape& s) {
-  // a call this small is launch latency and nothing else: one launch instead of two (7.9 against 9.4 us on
-  // one sequence of 256 positions with four heads; at 1024 positions and 32 heads two launches win again)
-  if (int64_t(s.total_kv) * s.hkv <= 4096) return true;
+// Lists of up to 1024 take the instance that ranks two tiles per wave instead of sixteen, and calls of one round of them are
+// mostly launches and latencies.  Then both forms are estimated, in us, from these measurements (32 queries; unpooled / window 3,
+// one launch against two): 4 heads of 256 floats x 64 5.9 / 7.4 against 7.9 / 8.2; 32 heads x 128 bf16, one sequence of
+// 100 6.1 / 7.5 against 8.5 / 8.9, of 256 6.5 / 8.0 against 8.5 / 8.9, of 512 7.4 / 9.1 against 8.6 / 9.1, of 1024 9.7 / 11.4 against
+// 8.8 / 9.4, eight of 512 9.3 / 10.7 against 12.5 / 12.9, eight of 1000 13.8 / 15.5 against 19.6 / 20.2; 16 heads over 4 KV heads
+// x 128, one of 300 10.9 / 13.6 against 10.2 / 10.7, of 689 14.6 / 17.8 against 10.4 / 11.0, four of 250 9.7 / 12.5 against 10.3 /
+// 10.6; 8 over 4 x 64, one of 300 7.2 / 8.7 against 8.0 / 8.4, of 900 8.4 / 10.4 against 8.3 / 9.0.  With sixteen tiles per
+// wave the one launch took 0.5 to 0.9 us longer, 2 to 3 with four query heads per KV head and 2 to 7 more with the window.
+static bool fused_pays_short(const Shape& s, dllm_dtype dt, int32_t pool_w) {
+  const double row = s.d * (dt == DLLM_BF16 ? 2 : 4), mb = double(s.total_kv) * s.hkv * row * 1e-6, pooled = pool_w > 1;
+  const int nt = (s.max_kv + 63) / 64, per_wave = (nt + kFusedWaves - 1) / kFusedWaves;
+  const int per_simd = nt > kFusedWaves / 2 * per_wave ? 2 * per_wave : per_wave;   // tiles the busiest SIMD scores
+  double one = 5.4 + 0.0033 * s.max_kv * row / 256 + per_simd * s.group * s.d / 600.0;   // a unit's stream, its multiply-adds
+  one += 0.55 * std::max(0.0, s.group * row / 256 - 1.0) + 0.3 * (s.group - 1);   // the block's queries, the other heads
+  one += pooled * (1.1 + 0.4 * s.group) + 0.07 * std::max(0.0, mb - 10.0);
+  const double two = (s.d == 128 ? 8.6 : 8.1) + (s.group * s.d > 256 ? 1.6 : 0.0) + 0.4 * pooled + 0.17 * std::max(0.0, mb - 10.0);
+  return one < two;
+}
+static bool fused_pays(const Shape& s, dllm_dtype dt, int32_t pool_w) {
   const int64_t pairs = int64_t(s.batch) * s.hkv, cus = compute_units();
+  if (pairs <= cus && s.max_kv <= kFusedWaves * kFusedTilesShort * 64) return fused_pays_short(s, dt, pool_w);
   const int64_t rounds = (pairs + cus - 1) / cus;
   const bool full = rounds == 1 ? 4 * pairs >= 3 * cus : 5 * pairs >= 4 * rounds * cus;
   const bool even = 4 * int64_t(s.total_kv) >= 3 * int64_t(s.batch) * s.max_kv;
@@ -1137,24 +1156,30 @@ static hipError_t launch_fused(const Shape& s, const void* k, const void* q, con
                                const int32_t* cu_kv, const int32_t* cu_k, int32_t total_k, int32_t forced_tail,
                                int32_t pool_w, int32_t* idx_out, hipStream_t st) {
   const char *kp = static_cast<const char*>(k), *qp = static_cast<const char*>(q);
-  auto launch = [&](auto kernel, size_t lds, int waves) -> hipError_t {
+  auto launch = [&](auto kernel, size_t lds) -> hipError_t {
     const hipError_t ea = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                               hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (ea != hipSuccess) return ea;
     const int32_t ranked = s.batch <= 64 && int64_t(s.batch) * s.hkv > compute_units() ? 1 : 0;
-    kernel<<<dim3(s.batch * s.hkv), dim3(waves * 64), lds, st>>>(kp, qp, cu_q, cu_kv, cu_k, total_k, forced_tail,
-                                                                      pool_w, ranked, idx_out, s DLLM_CHECK_PASS);
+    kernel<<<dim3(s.batch * s.hkv), dim3(kFusedWaves * 64), lds, st>>>(kp, qp, cu_q, cu_kv, cu_k, total_k, forced_tail,
+                                                                       pool_w, ranked, idx_out, s DLLM_CHECK_PASS);
     return hipGetLastError();
   };
-  if (s.group == 4) return launch(select_fused_kernel<ES, D, 4>, FusedLds<ES, D, 4>::bytes, fused_waves<4>());
-  if (s.group == 2) return launch(select_fused_kernel<ES, D, 2>, FusedLds<ES, D, 2>::bytes, fused_waves<2>());
-  return launch(select_fused_kernel<ES, D, 1>, FusedLds<ES, D, 1>::bytes, fused_waves<1>());
+  auto pick = [&](auto tiles) -> hipError_t {
+    constexpr int NT = decltype(tiles)::value;
+    if (s.group == 4) return launch(select_fused_kernel<ES, D, 4, NT>, FusedLds<ES, D, 4, NT>::bytes);
+    if (s.group == 2) return launch(select_fused_kernel<ES, D, 2, NT>, FusedLds<ES, D, 2, NT>::bytes);
+    return launch(select_fused_kernel<ES, D, 1, NT>, FusedLds<ES, D, 1, NT>::bytes);
+  };
+  // A wave ranks all the tiles its registers hold, also those the list does not have.
+  if (s.max_kv <= kFusedWaves * kFusedTilesShort * 64) return pick(std::integral_constant<int, kFusedTilesShort>{});
+  return pick(std::integral_constant<int, kFusedTiles>{});
 }
 
 int32_t select_form_of(const Shape& s, dllm_dtype dt, int32_t pool_w, int32_t head_sum) {
   const int32_t form = g_select_form.load();
   const bool one = form != DLLM_SELECT_FORM_TWO_LAUNCHES && fused_can(s, dt, pool_w, head_sum) &&
-                   (form == DLLM_SELECT_FORM_ONE_LAUNCH || fused_pays(s));
+                   (form == DLLM_SELECT_FORM_ONE_LAUNCH || fused_pays(s, dt, pool_w));
   return one ? DLLM_SELECT_FORM_ONE_LAUNCH : DLLM_SELECT_FORM_TWO_LAUNCHES;
 }
 

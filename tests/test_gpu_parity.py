@@ -87,6 +87,20 @@ def test_select_small_configs(c):
     check_select(synth.config(c))
 
 
+@pytest.mark.parametrize("pool_w,forced_tail", [(1, 0), (3, 0), (63, 16)])
+@pytest.mark.parametrize("dtype,Hq,Hkv,D", [(torch.bfloat16, 4, 4, 128), (torch.bfloat16, 8, 4, 64), (torch.bfloat16, 8, 2, 128),
+                                            (torch.float32, 4, 4, 64)])
+def test_select_lists_around_the_short_instance_of_one_launch(pool_w, forced_tail, dtype, Hq, Hkv, D):
+    """One-launch selection ranks two tiles of 64 positions per wave while the longest list has at most 1024, sixteen beyond:
+    lengths around tiles, around one and two tiles in each of the eight waves and around that line, with exact ties."""
+    for part, lens in enumerate(([64, 65, 449, 511, 512, 513], [63, 960, 961, 1023, 1024], [1025, 100, 1024])):
+        keep = [max(forced_tail, 1, n // 3) for n in lens]
+        w = custom(120 + part, dtype, Hq, Hkv, D, lens, [32, 5, 17, 32, 33, 64][:len(lens)], keep, salient=0.05)
+        lo = int(w.cu_kv[1])
+        w.k[lo:lo + 60] = w.k[lo]   # equal scores inside and across the threshold
+        check_select_ex(w, pool_w, forced_tail, False, f"part {part}")
+
+
 def test_select_config3_full():
     check_select(synth.config(3))
 
