@@ -53,14 +53,7 @@ __device__ __forceinline__ DenseLanes gather_dense(const Shape& s, const int32_t
   const uint64_t with_tiles = __builtin_amdgcn_ballot_w64(w.tiles != 0);
   const int first_L = with_tiles != 0 ? __builtin_amdgcn_readlane(w.L, __builtin_ctzll(with_tiles)) : 0;
   if (__builtin_amdgcn_ballot_w64(w.tiles != 0 && w.L != first_L) != 0) {
-    // keys that are all different, so one comparison per sequence does; eight at a time (a loop over single sequences
-    // with a second comparison for equal lengths took 1.1 to 2.4 us of a workgroup's start on a batch of 25)
-    const uint32_t key = uint32_t(w.tiles != 0 ? min(w.L, (1 << 25) - 1) + 1 : 0) << 6 | uint32_t(63 - lane);
-    int rank = 0;
-    for (int i = 0; i < s.batch; i += 8)
-#pragma unroll
-      for (int c = 0; c < 8; ++c) rank += uint32_t(__builtin_amdgcn_readlane(int(key), i + c)) > key ? 1 : 0;
-    if (lane >= s.batch) rank = lane;   // lanes past the batch stay where they are
+    const int rank = rank_longest_first(w.tiles != 0 ? w.L : -1, s.batch);   // lanes past the batch stay where they are
     w.q0 = __builtin_amdgcn_ds_permute(rank * 4, w.q0);
     w.nq = __builtin_amdgcn_ds_permute(rank * 4, w.nq);
     w.kv0 = __builtin_amdgcn_ds_permute(rank * 4, w.kv0);

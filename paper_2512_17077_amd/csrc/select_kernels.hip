@@ -699,12 +699,7 @@ __global__ __launch_bounds__(kFusedWaves * 64) __attribute__((amdgpu_waves_per_e
   if (ranked) {
     const int ln = threadIdx.x & 63, i = min(ln, s.batch - 1);
     const int a0 = cu_k[i], a1 = cu_k[i + 1], b0 = cu_kv[i], b1 = cu_kv[i + 1], c0 = cu_q[i], c1 = cu_q[i + 1];
-    const int mine = ln < s.batch ? (a1 == a0 ? -1 : b1 - b0) : -2;   // (a sequence that is not scored has no length)
-    int rank = 0;
-    for (int j = 0; j < s.batch; ++j) {
-      const int other = __builtin_amdgcn_readlane(mine, j);
-      rank += (other > mine) || (other == mine && j < ln);
-    }
+    const int rank = rank_longest_first(a1 == a0 ? -1 : b1 - b0, s.batch);   // (a sequence that is not scored has no length)
     const uint64_t hit = __ballot(ln < s.batch && rank == b);   // exactly one lane: the ranks are a permutation
     b = hit ? __builtin_ctzll(hit) : 0;
     ck0 = __builtin_amdgcn_readlane(a0, b); ck1 = __builtin_amdgcn_readlane(a1, b);
