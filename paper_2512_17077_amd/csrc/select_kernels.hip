@@ -4,7 +4,7 @@
 //   score_kernel        qsum[h,:] = sum of the sequence's block queries (fp32, ascending rows), then
 //                       one pass over K: s[h,j] = fma chain over d of qsum[h,d] * K[j, h/G, d]
 //   head_sum_kernel     (head-summed selection only, Section 2.4 Eq. 5) the pooled scores summed over heads
-//   topk_reg_kernel     per (sequence, head), lists of up to 4096 candidates: pooled keys in registers,
+//   topk_reg_kernel     per (sequence, head), lists of up to 4096 candidates (8192 while all workgroups run at once): pooled keys in registers,
 //                       radix select of the k-th largest, ordered compaction (ties to the lower
 //                       position, output ascending)
 //   topk_kernel         the same for longer lists, with the keys in LDS
@@ -224,28 +224,57 @@ __global__ __launch_bounds__(kScoreWaves * 64, (ES * D <= 256 ? 2 : 1)) void sco
 // summed[kv0 + j] = sum over query heads, ascending and starting from +0, of the pooled score of
 // candidate j (the window clipped to the candidates): one thread per position, so the shared
 // selection ranks one pre-summed row per sequence instead of walking every head inside the top-k.
+// Few workgroups and a chain of loads per head are what bounds it, so the scores of sixteen heads are requested together,
+// every position once: with a window they pass through LDS (with loads in the order of the sum, one per window
+// position, selection of one sequence of 4161 positions with 32 heads and windows of 1 / 3 / 5 took 30.4 / 35.2 / 46.3 us,
+// now 19.9 / 22.8 / 24.9, of which 3 to 5 are the list written by whole lines, see topk_reg_kernel).
+constexpr int kSumHeads = 16;
+template <bool Pooled>
 __global__ __launch_bounds__(256) void head_sum_kernel(const float* __restrict__ scores,
                                                        const int32_t* __restrict__ cu_kv,
                                                        const int32_t* __restrict__ cu_k, int32_t total_kv,
                                                        int32_t pool_w, int32_t forced_tail, int32_t n_heads,
                                                        float* __restrict__ summed DLLM_CHECK_PARAM) {
   DLLM_CHECK_EXIT();
-  const int b = blockIdx.y;
+  __shared__ float tile[Pooled ? kSumHeads : 1][256 + 64];   // positions j0 - half .. j0 + 255 + half
+  const int b = blockIdx.y, tid = threadIdx.x;
   if (cu_k[b + 1] == cu_k[b]) return;
   const int kv0 = cu_kv[b];
   const int L = cu_kv[b + 1] - kv0 - forced_tail;   // candidates
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= L) return;
-  const int half = pool_w >> 1;
-  const int lo = max(0, j - half), hi = min(L - 1, j + half);
+  const int j0 = blockIdx.x * 256, half = Pooled ? pool_w >> 1 : 0;
+  if (j0 >= L) return;
+  // A position past either end repeats the first or last candidate, which the clipped window holds anyway.
+  const int p = max(0, min(j0 - half + tid, L - 1)), p2 = max(0, min(j0 - half + 256 + tid, L - 1));
   float acc = 0.0f;
-  for (int hh = 0; hh < n_heads; ++hh) {
-    const float* __restrict__ src = scores + int64_t(hh) * total_kv + kv0;
-    float val = src[lo];
-    for (int t = lo + 1; t <= hi; ++t) val = fmaxf(val, src[t]);
-    acc = acc + val;
+  for (int h0 = 0; h0 < n_heads; h0 += kSumHeads) {
+    const int n = min(kSumHeads, n_heads - h0);
+    float x[kSumHeads], y[kSumHeads];
+#pragma unroll
+    for (int u = 0; u < kSumHeads; ++u) x[u] = scores[int64_t(h0 + min(u, n - 1)) * total_kv + kv0 + p];
+    if constexpr (!Pooled) {
+#pragma unroll
+      for (int u = 0; u < kSumHeads; ++u)
+        if (u < n) acc = acc + x[u];
+    } else {
+      if (tid < 2 * half) {
+#pragma unroll
+        for (int u = 0; u < kSumHeads; ++u) y[u] = scores[int64_t(h0 + min(u, n - 1)) * total_kv + kv0 + p2];
+      }
+      __syncthreads();   // the previous heads have been read
+#pragma unroll
+      for (int u = 0; u < kSumHeads; ++u) {
+        tile[u][tid] = x[u];
+        if (tid < 2 * half) tile[u][256 + tid] = y[u];
+      }
+      __syncthreads();
+      for (int u = 0; u < n; ++u) {
+        float val = tile[u][tid];
+        for (int t = 1; t <= 2 * half; ++t) val = fmaxf(val, tile[u][tid + t]);
+        acc = acc + val;
+      }
+    }
   }
-  summed[kv0 + j] = acc;
+  if (j0 + tid < L) summed[kv0 + j0 + tid] = acc;
 }
 
 // ------------------------------------------------------------------ top-k
@@ -451,16 +480,16 @@ __global__ __launch_bounds__(kTopkThreads) void topk_kernel(
 // those counts itself.  Positions past the end of the list hold key 0, the smallest: they are not counted
 // in the first pass, and wherever later passes count them (in digit 0) they stand below every real key
 // and, among equal keys, behind every real position, so they change neither the threshold nor the list.
-template <int R, int T>
+template <int R, int T, bool HeadSum>
 __global__ __launch_bounds__(T) void topk_reg_kernel(
     const float* __restrict__ scores, const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ cu_k,
-    int32_t total_kv, int32_t total_k, int32_t pool_w, int32_t forced_tail, int32_t head_sum, int32_t n_heads,
+    int32_t total_kv, int32_t total_k, int32_t pool_w, int32_t forced_tail, int32_t n_heads,
     int32_t* __restrict__ idx_out DLLM_CHECK_PARAM) {
   DLLM_CHECK_EXIT();
   constexpr int kCopies = 16, kWaves = T / 64;
   constexpr int E = R * kWaves / 64;   // (round, wave) counts per lane in the final scan
   static_assert(T >= 256 && R * kWaves % 64 == 0 && (E == 1 || E == 2), "one or two counts per lane");
-  extern __shared__ uint32_t dyn[];   // pooled selection only: the raw scores of the list
+  extern __shared__ uint32_t dyn[];   // pooled selection: the raw scores of the list; head-summed selection: the kept positions
   __shared__ __align__(16) uint32_t hist0[256 * kCopies];   // first pass, bank-separated copies (see topk_kernel)
   __shared__ __align__(16) uint32_t hist[4][256];           // [0]: the folded first pass
   __shared__ uint32_t counts[R * kWaves];
@@ -473,12 +502,12 @@ __global__ __launch_bounds__(T) void topk_reg_kernel(
   const int L = cu_kv[b + 1] - kv0 - forced_tail;
   const int kb = kb_all - forced_tail;
   if (kb < 0 || L < kb) return;   // broken precondition (see topk_kernel): write nothing
-  const int h_first = head_sum ? 0 : h, h_last = head_sum ? n_heads : h + 1;
+  const int h_first = HeadSum ? 0 : h, h_last = HeadSum ? n_heads : h + 1;
   for (int t = tid; t < forced_tail; t += T)
     for (int hh = h_first; hh < h_last; ++hh) idx_out[int64_t(hh) * total_k + o0 + kb + t] = L + t;
   if (kb <= 0) return;
 
-  const float* __restrict__ src = scores + int64_t(head_sum ? 0 : h) * total_kv + kv0;
+  const float* __restrict__ src = scores + int64_t(HeadSum ? 0 : h) * total_kv + kv0;
   for (int t = tid; t < 256 * kCopies; t += T) hist0[t] = 0;
   for (int t = tid; t < 3 * 256; t += T) (&hist[1][0])[t] = 0;
 
@@ -596,8 +625,15 @@ __global__ __launch_bounds__(T) void topk_reg_kernel(
       keep = gt || (eq && eq_before < need_eq);
     }
     if (keep) {
-      out[slot] = tid + u * T;
-      for (int hh = h_first + 1; hh < h_last; ++hh) out[int64_t(hh - h_first) * total_k + slot] = tid + u * T;
+      if constexpr (HeadSum) dyn[slot] = uint32_t(tid + u * T);
+      else out[slot] = tid + u * T;
+    }
+  }
+  if constexpr (HeadSum) {   // the one list goes out to all heads in whole lines, a head per wave at a time
+    __syncthreads();
+    for (int i = lane; i < kb; i += 64) {
+      const int pos = int32_t(dyn[i]);
+      for (int hh = wave; hh < n_heads; hh += kWaves) out[int64_t(hh) * total_k + i] = pos;
     }
   }
 }
@@ -1201,22 +1237,33 @@ hipError_t launch_select(const Shape& s, dllm_dtype dt, const void* q, const voi
   const float* ranked = scores;
   if (head_sum) {   // sum (pooled) scores over the heads first; the top-k then ranks one plain row per sequence
     float* summed = reinterpret_cast<float*>(static_cast<char*>(ws) + p.off_summed);
-    head_sum_kernel<<<dim3((s.max_kv + 255) / 256, s.batch), 256, 0, st>>>(scores, cu_kv, cu_k, s.total_kv, pool_w,
-                                                                           forced_tail, s.hq, summed DLLM_CHECK_PASS);
+    auto sum = [&](auto kernel) {
+      kernel<<<dim3((s.max_kv + 255) / 256, s.batch), 256, 0, st>>>(scores, cu_kv, cu_k, s.total_kv, pool_w, forced_tail, s.hq,
+                                                                    summed DLLM_CHECK_PASS);
+    };
+    if (pool_w == 1) sum(head_sum_kernel<false>);
+    else sum(head_sum_kernel<true>);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     ranked = summed;
     pool_w = 1;
   }
   const dim3 grid(head_sum ? 1 : s.hq, s.batch);
   const int32_t lpad = (s.max_kv + 63) & ~63;
-  if (s.max_kv <= 8 * kTopkThreads) {
-    // Keys in registers.  (Sixteen keys per thread for lists of up to 8192 measured slower than the
-    // kernel below on the mixed workload, 20.5 against 18.1 us, although each workgroup took less time:
-    // they did not all run at once.  Thirty-two per thread in four waves took 25 us.)
-    topk_reg_kernel<8, kTopkThreads><<<grid, kTopkThreads, pool_w == 1 ? 0 : size_t(lpad) * 4, st>>>(
-        ranked, cu_kv, cu_k, s.total_kv, total_k, pool_w, forced_tail, head_sum, s.hq, idx_out DLLM_CHECK_PASS);
+  auto ranked_in_registers = [&](auto kernel) {
+    kernel<<<grid, kTopkThreads, pool_w == 1 && !head_sum ? 0 : size_t(lpad) * 4, st>>>(
+        ranked, cu_kv, cu_k, s.total_kv, total_k, pool_w, forced_tail, s.hq, idx_out DLLM_CHECK_PASS);
     return hipGetLastError();
-  }
+  };
+  if (s.max_kv <= 8 * kTopkThreads) 
+    return head_sum ? ranked_in_registers(topk_reg_kernel<8, kTopkThreads, true>)
+                    : ranked_in_registers(topk_reg_kernel<8, kTopkThreads, false>);
+  // Sixteen keys per thread for lists of up to 8192, against the kernel below (selection in two launches, us, unpooled / window
+  // 3): 16 lists of 4736 13.0 / 14.8 against 15.0 / 17.5, 32 of 8000 14.4 / 17.3 against 18.0 / 22.6, 128 of 6500 25.1 / 27.6 against
+  // 27.7 / 31.5, 640 of 6000 66.1 / 70.1 against 67.2 / 80.6.  (At 768 lists of 8192 it lost, 20.5 against 18.1 us of the launch:
+  // not all of its workgroups run at once.  Thirty-two keys per thread in four waves took 25 us.)
+  if (s.max_kv <= 16 * kTopkThreads && int64_t(grid.x) * grid.y <= 704) 
+    return head_sum ? ranked_in_registers(topk_reg_kernel<16, kTopkThreads, true>)
+                    : ranked_in_registers(topk_reg_kernel<16, kTopkThreads, false>);
   const size_t lds = size_t(lpad) * 4 * (pool_w == 1 ? 1 : 2);
   if (lds > 64 * 1024) {   // beyond the default dynamic-LDS limit: raise it for this kernel on this device
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(topk_kernel),

@@ -101,6 +101,27 @@ def test_select_lists_around_the_short_instance_of_one_launch(pool_w, forced_tai
         check_select_ex(w, pool_w, forced_tail, False, f"part {part}")
 
 
+@pytest.mark.parametrize("pool_w,forced_tail", [(1, 0), (3, 32), (63, 0)])
+@pytest.mark.parametrize("dtype,Hq,Hkv", [(torch.bfloat16, 20, 5), (torch.bfloat16, 16, 16), (torch.float32, 3, 3)])
+def test_select_head_sum_around_its_blocks(pool_w, forced_tail, dtype, Hq, Hkv):
+    """The head sum takes sixteen heads and 256 positions at a time, with the window's neighbours from beside them: head
+    counts below, at and above sixteen, candidate counts around the blocks."""
+    lens = [n + forced_tail for n in (1, 2, 31, 255, 256, 257, 513)]
+    w = custom(140, dtype, Hq, Hkv, 64, lens, [32] * 7, [forced_tail + max(1, (n - forced_tail) // 4) for n in lens], salient=0.05)
+    check_select_ex(w, pool_w, forced_tail, True, "head sum")
+
+
+@pytest.mark.parametrize("pool_w,forced_tail,head_sum", [(1, 0, False), (5, 32, False), (1, 0, True), (3, 16, True)])
+def test_select_lists_of_4097_to_8192(pool_w, forced_tail, head_sum):
+    """Lists that rank sixteen keys per thread, beside shorter ones, with exact ties across the threshold."""
+    lens = [4097, 8192, 8191, 700, 4096]
+    w = custom(141, torch.bfloat16, 6, 2, 64, lens, [32] * 5, [n // 3 for n in lens], salient=0.05)
+    for b in range(5):
+        lo = int(w.cu_kv[b])
+        w.k[lo + 100:lo + 600] = w.k[lo + 100]
+    check_select_ex(w, pool_w, forced_tail, head_sum, "4097 to 8192")
+
+
 def test_select_config3_full():
     check_select(synth.config(3))
 
