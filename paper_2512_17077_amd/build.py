@@ -30,6 +30,12 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-I", INCLUDE, "-I", CSRC]
 
+# The first 16 scalar registers of kernel arguments arrive with the launch instead of being loaded: 0.1 to 0.4 us per call of
+# selection, Reuse and fp32 attention (layer step 14.97 -> 14.76 us, mixed fp32 step 29.6 -> 29.2, batched selection 51.8 -> 51.5).
+# Not the dense kernels, whose start waits for the batch's offsets anyway (one layer 22.04 / 22.12 us, others the same).
+PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
+PRELOAD_SOURCES = {"select_kernels.hip", "attend_f32.hip", "attend_sparse_bf16.hip", "pack_kernels.hip"}
+
 
 def _hipcc() -> str:
     for cand in (shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
@@ -41,7 +47,8 @@ def _hipcc() -> str:
 def _compile(src: str, extra=(), subdir: str = "") -> str:
     os.makedirs(os.path.join(BUILD_DIR, subdir), exist_ok=True)
     obj = os.path.join(BUILD_DIR, subdir, os.path.splitext(src)[0] + ".o")
-    cmd = [_hipcc(), *HIPCC_FLAGS, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
+    preload = PRELOAD_FLAGS if src in PRELOAD_SOURCES else []
+    cmd = [_hipcc(), *HIPCC_FLAGS, *preload, *extra, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)
