@@ -211,7 +211,10 @@ __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* 
 // VS: workgroups per list, each of which takes all of the K rows and 1 / VS of head_dim of the V rows and of the
 // output (see plan_attend); they are VS consecutive values of blockIdx.z, so with a multiple of eight heads
 // they run on one XCD and share its L2.
-template <int D, bool Once, int VS>
+// QG: a sequence's blocks of 32 queries are shared out to several workgroups (blockIdx.z then counts, from the fastest,
+// parts of head_dim, sequences and groups of blocks), instead of being taken one after the other, which gathers the rows anew
+// for each.
+template <int D, bool Once, int VS, bool QG>
 __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ idx,
@@ -249,7 +252,13 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   }
   const int chunk = blockIdx.x, h = blockIdx.y;
   const int vpart = VS == 1 ? 0 : int(blockIdx.z) % VS;
-  const SeqInfo si = sequence_of_slot(cu_q, cu_kv, cu_k, s.batch, int(blockIdx.z) / VS, lane, ranked != 0);
+  int slot = int(blockIdx.z) / VS, qt0 = 0, qstep = 1;
+  if constexpr (QG) {
+    qt0 = slot / s.batch;
+    slot -= qt0 * s.batch;
+    qstep = int(gridDim.z) / (VS * s.batch);
+  }
+  const SeqInfo si = sequence_of_slot(cu_q, cu_kv, cu_k, s.batch, slot, lane, ranked != 0);
   const int b = si.b;
   if (seq_mode != nullptr && seq_mode[b] == DLLM_SEQ_DENSE) return;
   const int ko0 = si.ko0, kb = si.kb;
@@ -259,11 +268,12 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   const int c1 = min(kb, c0 + cg.rows);
   const int nch_b = cg.n;
   const int q0 = si.q0, nq = si.nq;
+  if (QG && qt0 * 32 >= nq) return;
   const int kv0 = si.kv0;
   const int g = h / s.group;
 
   if (kb == 0) {  // nothing kept: defined as zeros
-    if (vpart == 0)
+    if (vpart == 0 && qt0 == 0)
       for (int e = threadIdx.x; e < nq * D; e += W * 64)
         o[(int64_t(q0 + e / D) * s.hq + h) * D + e % D] = 0;
     return;
@@ -294,7 +304,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
     return x;
   };
 
-  for (int qt = 0; qt * 32 < nq; ++qt) {
+  for (int qt = qt0; qt * 32 < nq; qt += qstep) {
     float m_used = -INFINITY, lsum = 0.0f;
     f32x16 acc[NDB];
 #pragma unroll
@@ -457,7 +467,7 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
         }
       }
     }
-    if ((qt + 1) * 32 < nq) __syncthreads();   // merge space becomes tile space again
+    if ((qt + qstep) * 32 < nq) __syncthreads();   // merge space becomes tile space again
   }
 }
 
@@ -829,7 +839,14 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
       else launch(attend_sparse_multi_bf16_kernel<64, false>);
     }
   } else {
-    dim3 grid(p.n_chunks, s.hq, s.batch * p.v_split);
+    // Blocks of more than 32 queries go to workgroups of their own while all are resident at once (two per compute unit).  Not
+    // in mixed calls, where max_q may be that of a densely attended sequence.  Bound by the gathers of each block, one after
+    // the other, before: one sequence, 32 heads x 128, 1289 kept rows, block of 128: 55.4 -> 22.3 us; 210 rows, block of 64:
+    // 9.3 -> 6.3; two of 1162 rows, 16 heads over 4, block of 256: 107.8 -> 46.3.
+    const int64_t units = n_items * p.v_split;
+    const int blocks = int((int64_t(s.max_q) + 31) / 32);
+    const int groups = seq_mode == nullptr && units > 0 ? int(std::max<int64_t>(1, std::min<int64_t>(blocks, 512 / units))) : 1;
+    dim3 grid(p.n_chunks, s.hq, s.batch * p.v_split * groups);
     // the start order only matters when the workgroups cannot all be resident at once (two per compute unit), or
     // when the parts of lists of unequal length share compute units: long ones then get short ones beside them
     const int ranked = n_items > 512 || (p.v_split > 1 && n_items * p.v_split > n_cu) ? 1 : 0;
@@ -837,16 +854,22 @@ hipError_t launch_attend_sparse_bf16(const Shape& s, const AttendPlan& p, const 
       kernel<<<grid, kWaves * 64, 0, st>>>(qh, kh, vh, cu_q, cu_kv, idx, cu_k, total_k, seq_mode, oh, po, pm, pl,
                                            p.chunk_rows, ranked, s DLLM_CHECK_PASS);
     };
-    auto launch_split = [&](auto vs) {
+    auto launch_split = [&](auto vs, auto once) {
       constexpr int VS = decltype(vs)::value;
-      if (s.d == 128) launch(attend_sparse_bf16_kernel<128, false, VS>);
-      else if constexpr (VS <= 2) launch(attend_sparse_bf16_kernel<64, false, VS>);
+      constexpr bool Once = decltype(once)::value;
+      if (groups > 1) {
+        if (s.d == 128) launch(attend_sparse_bf16_kernel<128, Once, VS, true>);
+        else if constexpr (VS <= 2) launch(attend_sparse_bf16_kernel<64, Once, VS, true>);
+      } else {
+        if (s.d == 128) launch(attend_sparse_bf16_kernel<128, Once, VS, false>);
+        else if constexpr (VS <= 2) launch(attend_sparse_bf16_kernel<64, Once, VS, false>);
+      }
     };
-    if (p.v_split == 4) launch_split(std::integral_constant<int, 4>{});
-    else if (p.v_split == 2) launch_split(std::integral_constant<int, 2>{});
-    else if (!gathers_once(s, 2)) launch_split(std::integral_constant<int, 1>{});
-    else if (s.d == 128) launch(attend_sparse_bf16_kernel<128, true, 1>);
-    else launch(attend_sparse_bf16_kernel<64, true, 1>);
+    constexpr std::false_type stay{};
+    if (p.v_split == 4) launch_split(std::integral_constant<int, 4>{}, stay);
+    else if (p.v_split == 2) launch_split(std::integral_constant<int, 2>{}, stay);
+    else if (!gathers_once(s, 2)) launch_split(std::integral_constant<int, 1>{}, stay);
+    else launch_split(std::integral_constant<int, 1>{}, std::true_type{});
   }
   e = hipGetLastError();
   if (e != hipSuccess || p.n_chunks <= 1) return e;

@@ -1049,3 +1049,16 @@ def test_attend_parts_of_large_batches_and_blocks(hq, hkv, D, keep, qlens):
     chunks, parts, _ = hcsa.dllm_hcsa_attend_form_of(dw.batch, dw.max_k, dw.total_k)
     assert chunks == 1 and parts > 1
     check_attend(w, oracle_select(w), dw=dw)
+
+
+@pytest.mark.parametrize("hq,hkv,D,keep,qlens", [
+    (32, 32, 128, [200], [33]), (32, 8, 128, [300, 40, 0], [64, 1, 97]), (8, 2, 64, [130, 0, 77], [100, 70, 32]),
+    (32, 32, 128, [1200], [129]), (8, 8, 64, [1200, 33], [64, 290]),        # in chunks that are merged
+    (2, 1, 128, [90, 35], [1100, 31]),                                       # more blocks than groups of them
+    (16, 4, 128, [64, 129] * 16, [33, 65] * 16), (32, 8, 128, [64, 129] * 16, [33, 65] * 16)])   # two groups; one
+def test_attend_blocks_of_queries_over_workgroups(hq, hkv, D, keep, qlens):
+    """Blocks of 32 queries have workgroups of their own while those are resident at once: sequences of fewer blocks than the
+    longest, more blocks than groups, lists in chunks, nothing kept, packed and gathered."""
+    w = custom(22, torch.bfloat16, hq, hkv, D, [k + 40 for k in keep], qlens, keep, salient=0.05)
+    check_pack_and_packed_attend(w, f"blocks {qlens[:3]}")
+    check_attend(w, oracle_select(w))
