@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Turns rocprofv3 byte-counter runs of bench.py into profiles/hbm_traffic.json and profiles/hbm_traffic_pmc.md.
 
-The runs (on the GPU machine, from /tmp with TMPDIR=/tmp; one call and one counter per run, so that every
+The runs (from /tmp with TMPDIR=/tmp; one call and one counter per run, so that every
 dispatch after the copy probe belongs to the call that is named):
 
     for CALL in select_reuse attend_reuse ...; do for C in FETCH_SIZE WRITE_SIZE; do
