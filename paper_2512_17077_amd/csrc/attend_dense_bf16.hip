@@ -560,7 +560,11 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
         stop = j < aim_v ? aim_v : j < last_due ? last_due : nsteps;
         left = stop - 1 - jb;
       }
-      if (grow != 0) {   // raise the running maxima for the scores of step j
+      // Raise the running maxima for the scores of step j; before a ragged last step (last_due is nsteps otherwise, which j
+      // is not here) always, since a key that sets its query's maximum has a probability that bf16 holds exactly.  Leaving
+      // that out saved 0.9 us a call (eight heads, three sequences of 78 9.7 -> 8.8, 32 heads, 38 of 155 63.8 -> 59.9), but put
+      // ragged batches further from 64 bits (six of 300 to 1500, 32 heads over 8 2.3206 -> 2.3259e-3).
+      if (grow != 0 || j == last_due) {
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
           const float mz_old = -w.nmz[qb];

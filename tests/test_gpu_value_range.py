@@ -100,3 +100,37 @@ def test_keys_whose_score_overflows_to_minus_infinity(dtype, hq, hkv, D, first, 
     got, ref = masked_outputs(dtype, hq, hkv, D, 200, first, last)
     assert torch.isfinite(got).all()
     assert (got - ref).abs().max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("hq,hkv,D,form", [(2, 1, 128, 2), (2, 1, 64, 2), (16, 8, 128, 1), (16, 8, 64, 1)])
+def test_a_ragged_last_step_raises_the_maximum(hq, hkv, D, form):
+    """Two keys carry each sequence: one in the first 32, the largest in the ragged last step, with values that nearly cancel.
+    Both set their query's running maximum, so both probabilities are powers of two and what is left of the output is exact
+    but for its own rounding and fp32: logits up to 32 are rounded to 2^-20 twice on either side, which leaves 2^-18 of values up
+    to 2.  A probability rounded to bf16 leaves up to 2^-9 of them."""
+    n, extra = 20, [1, 7, 16, 31]
+    lens = [64 * (1 + b // 4) + extra[b % 4] for b in range(n)]
+    qlens = [40] * n if form == 2 else [256] * n
+    w = synth.make_workload("last", synth.SEED_BASE + 2300, torch.bfloat16, hq, hkv, D, lens, qlens, [0] * n,
+                            seq_mode=np.ones(n, np.uint8))
+    rng = np.random.default_rng(5)
+    w.q.fill_(0.0)
+    w.q[:, :, 0] = 1.0
+    w.k.fill_(0.0)
+    w.k[:, :, 0] = -60.0 / (w.softmax_scale * math.log2(math.e))
+    w.v.fill_(0.0)
+    ref = torch.empty(w.q.shape, dtype=torch.float64)
+    for b in range(n):
+        lo, hi, unit = int(w.cu_kv[b]), int(w.cu_kv[b + 1]), 1.0 / (w.softmax_scale * math.log2(math.e))
+        first, last = lo + int(rng.integers(0, 32)), hi - 1 - int(rng.integers(0, extra[b % 4]))
+        below = float(rng.uniform(0.05, 0.95))
+        w.k[last, :, 0], w.k[first, :, 0] = 3.0 * unit, (3.0 - below) * unit
+        ratio = torch.exp2((w.k[first, :, 0].double() - w.k[last, :, 0].double()) / unit)
+        w.v[last], w.v[first] = 1.0, (-1.0 / ratio[:, None]).to(w.v.dtype).expand(-1, D)
+        each = (1.0 + ratio * w.v[first, :, 0].double()) / (1.0 + ratio)
+        ref[int(w.cu_q[b]):int(w.cu_q[b + 1])] = each.repeat_interleave(hq // hkv)[None, :, None]
+    dw = workload.DeviceWorkload(w)
+    assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == form
+    dw.dense_refresh()
+    err = (dw.o.double().cpu() - ref).abs()
+    assert (err <= 2.0 ** -8 * ref.abs() + 2.0 ** -16).all(), float(err.max())
