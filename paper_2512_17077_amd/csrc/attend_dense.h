@@ -6,6 +6,13 @@
 
 namespace dllm {
 
+// The larger of the two, or not a number if one of them is not (v_max_f32 would drop it).
+__device__ __forceinline__ float maximum(float a, float b) { return __builtin_elementwise_maximum(a, b); }
+__device__ __forceinline__ float maximum_across_halves(float x) {
+  const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 struct DensePlace {
   int qtile, h;            // query tile, query head
   int q0, nq, kv0, L;      // the sequence's first query, number of queries, first key, number of keys

@@ -101,7 +101,11 @@ struct DenseTileLoad {
 // slots 0..7 and 16..23 if c < 16, in the other slots if not.  The A operand (`ones`) has bf16 ones in row 0 for the
 // first kind and in row 4 for the second, so the four accumulators (ls) hold the sum of query c in the first register of
 // lane c and zeros elsewhere.  (A 32x32x16 product with one row of ones takes twice the matrix time: 494 -> 481 us on
-// eight sequences of 2048, 32 heads x 128, and 28 a-registers more.)  The vector form (unpack each packed pair with a
+// eight sequences of 2048, 32 heads x 128, and 28 a-registers more.)  Two queries share a column, so a probability that is no
+// number would reach its neighbour's sum as 0 * NaN; there is none, because they come out of the exponential clamped to
+// 0 .. 1 (NaN to 0), at the price of its longer encoding (0.4 %; sixteen lanes' own sums by 4x4x4 products, which keep
+// columns apart too, cost 0.7 to 1.9 %).  A query that has scored plus infinity or NaN still ends as NaN: its maximum is
+// that, so its accumulators are multiplied by it or all its probabilities are 0.  The vector form (unpack each packed pair with a
 // shift and a mask, two adds) costs four vector instructions per pair of scores, a third of the step's vector work;
 // v_dot2c_f32_bf16 does it in one but runs on the matrix pipe and holds back the MFMAs (+18 cycles per MFMA), and summing
 // the unrounded values is off by up to 2^-8 of a row that one key rules.
@@ -401,9 +405,9 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
   };
   // largest score of a step per lane (a query's scores sit in the lane pair l, l ^ 32)
   auto lane_max = [&](const f32x16& st) __attribute__((always_inline)) -> float {
-    float mx = fmaxf(st[0], st[1]);
+    float mx = maximum(st[0], st[1]);
 #pragma unroll
-    for (int i = 2; i < 16; i += 2) mx = fmaxf(fmaxf(mx, st[i]), st[i + 1]);
+    for (int i = 2; i < 16; i += 2) mx = maximum(maximum(mx, st[i]), st[i + 1]);
     return mx;
   };
 
@@ -511,7 +515,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     // (-inf) - (-inf), also when they fill the first step)
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb)
-      w.nmz[qb] = no_keys ? 0.0f : -fmaxf(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
+      w.nmz[qb] = no_keys ? 0.0f : -maximum(maximum_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
     if constexpr (KS == 2) {   // what a step before the first would have requested, so that every step finds the same in flight
       load_tile(keys, keys.k, 3, DLLM_IC(3 * TILEB));
       load_tile(keys, keys.v, 1, DLLM_IC(VBASE + TILEB));
@@ -568,7 +572,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
           const float mz_old = -w.nmz[qb];
-          const float mz_new = fmaxf(mz_old, max_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
+          const float mz_new = maximum(mz_old, maximum_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
           const float alpha = __builtin_amdgcn_exp2f(mz_old - mz_new);
           palpha[qb] = alpha;
           w.nmz[qb] = -mz_new;

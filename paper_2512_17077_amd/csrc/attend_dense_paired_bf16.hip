@@ -271,9 +271,9 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
         if (8 * (i / 4) + 4 * hf + (i % 4) >= last_valid) st[qb][i] = -INFINITY;
   };
   auto lane_max = [&](const f32x16& st) __attribute__((always_inline)) -> float {
-    float mx = fmaxf(st[0], st[1]);
+    float mx = maximum(st[0], st[1]);
 #pragma unroll
-    for (int i = 2; i < 16; i += 2) mx = fmaxf(fmaxf(mx, st[i]), st[i + 1]);
+    for (int i = 2; i < 16; i += 2) mx = maximum(maximum(mx, st[i]), st[i + 1]);
     return mx;
   };
 
@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
   // (-inf) - (-inf), also when they fill the first step)
 #pragma unroll
   for (int qb = 0; qb < 2; ++qb)
-    w.nmz[qb] = no_keys ? 0.0f : -fmaxf(max_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
+    w.nmz[qb] = no_keys ? 0.0f : -maximum(maximum_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
 #pragma unroll
   for (int i = 0; i < 16; ++i) w.st_b[0][i] = w.st_b[1][i] = 0.0f;
   w.k_operands<KS == 1 ? 32 * ROWB : TILEB>();   // step 1 (copies of the last row if there is none; then unused)
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) {
         const float mz_old = -w.nmz[qb];
-        const float mz_new = fmaxf(mz_old, max_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
+        const float mz_new = maximum(mz_old, maximum_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
         alpha[qb] = __builtin_amdgcn_exp2f(mz_old - mz_new);
         w.nmz[qb] = -mz_new;
       }

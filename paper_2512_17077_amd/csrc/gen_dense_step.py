@@ -21,6 +21,8 @@ One step (iteration j) at D = 128, NQB = 2 blocks of 32 queries per wave:
     slots 20..31   row maxima of S(j+1)           16 max / max3
     LDS            16 transposing reads (V^T operands, four slots ahead of their MFMAs),
                    8 ds_read_b128 (K operands of step j+2, after the S chain has consumed the old ones)
+Probabilities are clamped to 0 .. 1, which changes none that a query with finite scores has (its running maximum is raised
+first), and maxima are taken with NaN kept (v_maximum3_f32), so that such a query asks for the raise that makes it NaN.
 Matrix results are read by vector instructions no sooner than four MFMAs after they were issued (the
 hardware does not interlock that; 12 wait states are required), and a transcendental's result is not
 read by the next instruction.
@@ -135,7 +137,7 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             cvt, add0, add1 = finish(i - 1) if i > 0 else ([], [], [])
             ops += [f"v_fma_f32 {vr(t0)}, {vr(s0)}, %[zs], {vr(SM + 2 + qb)}",
                     f"v_fma_f32 {vr(t0 + 1)}, {vr(s0 + 1)}, %[zs], {vr(SM + 2 + qb)}"]
-            ops += [f"v_exp_f32_e32 {vr(t0)}, {vr(t0)}", f"v_exp_f32_e32 {vr(t0 + 1)}, {vr(t0 + 1)}"]
+            ops += [f"v_exp_f32_e64 {vr(t0 + c)}, {vr(t0 + c)} clamp" for c in range(2)]
             ops += cvt + add0 + add1
         cvt, add0, add1 = finish(len(pairs) - 1)
         ops += ["s_nop 0"] + cvt + add0 + add1      # the nop keeps the last exp's result from being read at once
@@ -147,8 +149,7 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             for qb in range(2):
                 s0 = nxt + 16 * qb + 2 * i
                 m = vr(SM + 4 + qb)
-                mops.append(f"v_max_f32_e32 {m}, {vr(s0)}, {vr(s0 + 1)}" if i == 0 else
-                            f"v_max3_f32 {m}, {m}, {vr(s0)}, {vr(s0 + 1)}")
+                mops.append(f"v_maximum3_f32 {m}, {vr(s0) if i == 0 else m}, {vr(s0)}, {vr(s0 + 1)}")
         start = n_s + 4
         span = nslots - start
         for i, op in enumerate(mops):
@@ -221,8 +222,8 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
         # does any new score exceed its running maximum by more than the lazy step?  (lanes as a mask)
         lines += [f"v_fma_f32 {vr(TMP)}, {vr(SM + 4)}, %[zs], {vr(SM + 2)}",
                   f"v_fma_f32 {vr(TMP + 1)}, {vr(SM + 5)}, %[zs], {vr(SM + 3)}",
-                  f"v_max_f32_e32 {vr(TMP)}, {vr(TMP)}, {vr(TMP + 1)}",
-                  f"v_cmp_gt_f32_e64 %[grow], {vr(TMP)}, %[lazy]"]
+                  f"v_maximum3_f32 {vr(TMP)}, {vr(TMP)}, {vr(TMP)}, {vr(TMP + 1)}",
+                  f"v_cmp_nle_f32_e64 %[grow], {vr(TMP)}, %[lazy]"]
     return lines
 
 
@@ -279,7 +280,7 @@ def gen_paired_step(cur, nxt, with_loads, split=False):
         t0 = r["TMP"] + 2 * (i % 2)
         s0 = cur + 16 * qb + 8 * u + 2 * jj
         ops += [f"v_fma_f32 {vr(t0 + c)}, {vr(s0 + c)}, %[zs], {vr(r['NMZ'] + qb)}" for c in range(2)]
-        ops += [f"v_exp_f32_e32 {vr(t0 + c)}, {vr(t0 + c)}" for c in range(2)]
+        ops += [f"v_exp_f32_e64 {vr(t0 + c)}, {vr(t0 + c)} clamp" for c in range(2)]
         if i > 0:
             convert(i - 1)
     ops.append("s_nop 0")   # the last exp's result is not read at once
@@ -288,7 +289,7 @@ def gen_paired_step(cur, nxt, with_loads, split=False):
     for i in range(8):
         for qb in range(2):
             s0, m = nxt + 16 * qb + 2 * i, vr(r["MX"] + qb)
-            tops.append(f"v_max_f32_e32 {m}, {vr(s0)}, {vr(s0 + 1)}" if i == 0 else f"v_max3_f32 {m}, {m}, {vr(s0)}, {vr(s0 + 1)}")
+            tops.append(f"v_maximum3_f32 {m}, {vr(s0) if i == 0 else m}, {vr(s0)}, {vr(s0 + 1)}")
     # a product reads a converted probability no sooner than two instructions later
     cut = done[7] + 2
     phases = [(range(0, 8), ops[:cut]), (range(8, 14), ops[cut:] + tops[:2]), (range(14, 20), tops[2:])]
@@ -325,7 +326,7 @@ def gen_paired_step(cur, nxt, with_loads, split=False):
         lines += valu[s][1:]
     t, m, z = r["TMP"], r["MX"], r["NMZ"]
     lines += [f"v_fma_f32 {vr(t)}, {vr(m)}, %[zs], {vr(z)}", f"v_fma_f32 {vr(t + 1)}, {vr(m + 1)}, %[zs], {vr(z + 1)}",
-              f"v_max_f32_e32 {vr(t)}, {vr(t)}, {vr(t + 1)}", f"v_cmp_gt_f32_e64 %[grow], {vr(t)}, %[lazy]"]
+              f"v_maximum3_f32 {vr(t)}, {vr(t)}, {vr(t)}, {vr(t + 1)}", f"v_cmp_nle_f32_e64 %[grow], {vr(t)}, %[lazy]"]
     return lines
 
 

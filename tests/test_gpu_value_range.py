@@ -134,3 +134,48 @@ def test_a_ragged_last_step_raises_the_maximum(hq, hkv, D, form):
     dw.dense_refresh()
     err = (dw.o.double().cpu() - ref).abs()
     assert (err <= 2.0 ** -8 * ref.abs() + 2.0 ** -16).all(), float(err.max())
+
+
+@pytest.mark.parametrize("first,last", [(0, 1), (40, 41), (199, 200), (64, 128)])
+@pytest.mark.parametrize("nan", [False, True])
+@pytest.mark.parametrize("hq,hkv,n,D,form", [(4, 2, 1, 128, 2), (4, 2, 1, 64, 2), (16, 8, 20, 128, 1), (16, 8, 20, 64, 1)])
+def test_scores_that_overflow_spoil_their_own_query_only(hq, hkv, n, D, form, first, last, nan):
+    """Keys that score plus infinity for a few queries (or queries that hold NaN: their outputs are no numbers) and minus infinity
+    for all others, which must come out as if those keys were not there: queries share matrix products, but none may see
+    another's values."""
+    L, nq, bad = 200, 70 if form == 2 else 256, [3, 17, 36, 52, 69]
+    w = synth.make_workload("contained", synth.SEED_BASE + 2200, torch.bfloat16, hq, hkv, D, [L] * n, [nq] * n, [0] * n,
+                            seq_mode=np.ones(n, np.uint8))
+    w.q.copy_((2.0 ** 64 * (1.0 + w.q.float().abs())).to(w.q.dtype))
+    w.k.copy_((2.0 ** -64 * w.k.float()).to(w.k.dtype))
+    for b in range(n):
+        w.q[[b * nq + i for i in bad]] *= float("nan") if nan else -1.0
+        w.k[b * L + first:b * L + last] = -2.0 ** 70
+    rest = [i for i in range(L) if not first <= i < last]
+    good = [i for i in range(nq) if i not in bad]
+    q = w.q.double().view(n, nq, hq, D).transpose(1, 2)
+    k, v = (x.double().view(n, L, hkv, D)[:, rest].repeat_interleave(hq // hkv, 2).transpose(1, 2) for x in (w.k, w.v))
+    ref = torch.matmul(torch.softmax(torch.matmul(q, k.transpose(2, 3).contiguous()) * w.softmax_scale, -1), v)
+    dw = workload.DeviceWorkload(w)
+    assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == form
+    dw.dense_refresh()
+    got = dw.o.double().cpu().view(n, nq, hq, D).transpose(1, 2)
+    assert torch.isnan(got[:, :, bad]).all()
+    assert torch.isfinite(got[:, :, good]).all()
+    assert (got - ref)[:, :, good].abs().max() <= TOL[torch.bfloat16]
+
+
+@pytest.mark.parametrize("pos", [0, 40, 64, 130, 199])
+@pytest.mark.parametrize("hq,hkv,n,D,form", [(4, 2, 1, 128, 2), (4, 2, 1, 64, 2), (16, 8, 20, 128, 1), (16, 8, 20, 64, 1)])
+def test_a_key_that_is_no_number_shows(hq, hkv, n, D, form, pos):
+    """One NaN in a key: all outputs of its KV head's query heads are NaN, whichever step meets it; no others are."""
+    L, nq = 200, 70 if form == 2 else 256
+    w = synth.make_workload("nan", synth.SEED_BASE + 2201, torch.bfloat16, hq, hkv, D, [L] * n, [nq] * n, [0] * n,
+                            seq_mode=np.ones(n, np.uint8))
+    w.k[[b * L + pos for b in range(n)], 1, 5] = float("nan")
+    dw = workload.DeviceWorkload(w)
+    assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == form
+    dw.dense_refresh()
+    group = hq // hkv
+    assert torch.isnan(dw.o[:, group:2 * group]).all()
+    assert torch.isfinite(dw.o[:, :group]).all() and torch.isfinite(dw.o[:, 2 * group:]).all()
