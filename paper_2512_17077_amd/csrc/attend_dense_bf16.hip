@@ -680,8 +680,12 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 // workgroups keep the whole form unless the split one is estimated 1.3 times as fast: there the estimate knows least
 // (8 heads, nine of 209 to 1073 22.5 / 19.3, six of 567 to 1601 29.8 / 28.3, thirteen of 370 to 446 13.8 / 14.1; with one
 // wave per SIMD, as this kernel used to be, 21 to 23.5 / 25.2, 31.1 / 33.9, 14.9 / 21.0).  Over those batches the choice is 0.7 % above
-// the better form in the mean (the whole form always: 11.6 %, the split one: 2.8 %).  16 heads: nine of 416 17.5 /
-// 20.1, three of 600 15.3 / 11.6, four of 2048 70.0 / 74.6, two of 4400 190 / 176.
+// the better form in the mean (the whole form always: 11.6 %, the split one: 2.8 %).  16 heads: nine of 416 18.5 /
+// 20.9, three of 600 15.3 / 11.6, four of 2048 70.0 / 74.6, two of 4400 190 / 176.  Even batches need
+// the split form 3 % ahead and ragged ones beyond 512 workgroups 5 %: the two estimates came that near each other where the
+// whole form is 3 to 13 % faster (8 heads, nineteen of 459 21.8 / 22.9; 32 heads, ten of 1183 to 1494 172 / 188, twenty of
+// 580 to 628 88.7 / 96.0; 16 heads, seven of 537 to 2076 65.4 / 67.8, of 448 to 1804 65.5 / 68.3, of 422 to 2925 68.2 / 72.7, of 783 to 2873 99.9 / 106.8);
+// not where most sequences fill no more than a split workgroup (32 heads, 25 of 70 to 133 19.3 / 17.6).
 // The lengths themselves are on the device.  With the mean and the longest known, they are taken to be spread evenly
 // around the mean (up to 64 of them, for the batch), and the workgroups to start longest first: at head_dim 128, in a second
 // round that is not full, a workgroup then follows one of about the length at which the first round ended.  Counting such
@@ -714,9 +718,9 @@ int dense_key_splits(const Shape& s, int which) {
     if (shared) {
       const double alone = longest_kv * (ks == 1 ? 449 : 485) / (32 * ks) + 1000;
       if (workgroups <= kUnits) return start + alone;
-      if (even) return start + std::ceil(workgroups / kUnits) * one;
+      if (even) return (ks == 2 ? 1.03 : 1.0) * (start + std::ceil(workgroups / kUnits) * one);
       if (workgroups <= 2 * kUnits) return (ks == 2 ? 1.3 : 1.0) * (start + std::max(alone, work / kUnits));
-      return start + std::max(one, work / kUnits + work / workgroups / 2);
+      return (ks == 2 && mean_q > dense_rows(2) ? 1.05 : 1.0) * (start + std::max(one, work / kUnits + work / workgroups / 2));
     }
     if (workgroups <= kUnits) return one;
     const double doubt = ks == 2 ? 1.06 : 1.0;

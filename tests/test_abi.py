@@ -359,3 +359,16 @@ def test_generated_dense_step_text_is_current(tmp_path):
     subprocess.run([sys.executable, os.path.join(csrc, "gen_dense_step.py"), f"--out={tmp_path}"], check=True,
                    capture_output=True)
     assert open(tmp_path / "attend_dense_step.inc").read() == open(os.path.join(csrc, "attend_dense_step.inc")).read()
+
+
+@pytest.mark.parametrize("heads,batch,longest,total,form", [
+    (16, 7, 2076, 8616, 1), (16, 7, 1804, 9029, 1), (16, 7, 2925, 8678, 1), (16, 7, 2873, 11594, 1),   # ragged, beyond 512 workgroups
+    (32, 25, 133, 2705, 2),                                                                             # short ones
+    (16, 7, 1200, 8400, 2), (16, 3, 600, 1800, 2), (16, 4, 2048, 8192, 1), (16, 9, 416, 3744, 1), (8, 19, 459, 8721, 1), (32, 20, 628, 12080, 1)])   # even ones
+def test_dense_calls_at_head_dim_64_take_the_form_that_measured_faster(heads, batch, longest, total, form):
+    b = good_batch()
+    b.batch, b.n_q_heads, b.n_kv_heads, b.head_dim = batch, heads, 4, 64
+    b.q_stride_tok, b.q_stride_head, b.kv_stride_tok, b.kv_stride_head = heads * 64, 64, 4 * 64, 64
+    b.total_q = b.total_kv = total
+    b.max_q = b.max_kv = longest
+    assert hcsa.dllm_hcsa_attend_form_of(b, all_dense=True)[2] == form
