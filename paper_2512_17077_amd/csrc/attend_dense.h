@@ -126,6 +126,14 @@ __device__ __forceinline__ bool place_dense_grid(const Shape& s, const int32_t* 
   return at.qtile * Rows < at.nq;
 }
 
+// LDS accesses of this wave before this point come before those behind it, whichever lanes make them (a lane's own
+// addresses may be provably different ones).  No instruction: LDS serves a wave in order.
+__device__ __forceinline__ void order_wave_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Writes 32 query rows: accumulators `a` ([db][16], as the matrix cores leave them) over the row sum l.  A lane holds
 // four elements of one row at a time, so the block goes through LDS (`stage`, 32 rows that are this wave's alone) and out
 // in whole rows.  first: the block's first query; rows past the last query are not written.  Lane offsets fit 32 bits: 32
@@ -136,6 +144,7 @@ __device__ __forceinline__ void store_dense_block(const float* a, float l, char*
   constexpr int CH = D / 8;
   const int lane = threadIdx.x & 63, col = lane & 31, hf = lane >> 5;
   const float inv = 1.0f / l;
+  order_wave_lds();   // the rows may be read from until here: by the block before, or as the other wave's block
 #pragma unroll
   for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -146,9 +155,7 @@ __device__ __forceinline__ void store_dense_block(const float* a, float l, char*
       w2.y = cvt_pk_bf16(x[2] * inv, x[3] * inv);
       *reinterpret_cast<v2u*>(stage + tile_off<D>(col, 4 * db + i4) + 8 * hf) = w2;
     }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  order_wave_lds();
   first = __builtin_amdgcn_readfirstlane(first);
   const uint32_t row_bytes = uint32_t(hq) * (2 * D);
   char* base = reinterpret_cast<char*>(o + (int64_t(at.q0 + first) * hq + at.h) * D);

@@ -658,6 +658,7 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     if (!more) break;
     // the rows that the next iteration 0 multiplies by zeros: the last wave's outputs came through them
     static_assert(kDenseWaves == 4, "the last wave stages its outputs in the second half of V ring slot 3");
+    order_wave_lds();
     if (wave == kDenseWaves - 1)
 #pragma unroll
       for (int i = 0; i < 32 * ROWB / 1024; ++i)
