@@ -278,10 +278,7 @@ __global__ __launch_bounds__(256) void head_sum_kernel(const float* __restrict__
 }
 
 // ------------------------------------------------------------------ top-k
-#ifndef DLLM_TOPK_THREADS
-#define DLLM_TOPK_THREADS 512
-#endif
-constexpr int kTopkThreads = DLLM_TOPK_THREADS;
+constexpr int kTopkThreads = 512;
 
 __device__ __forceinline__ uint32_t order_key(float f) {
   // monotone map fp32 -> uint32 (larger float, larger key); +0 and -0 were already merged
