@@ -144,8 +144,9 @@ dllm_status dllm_hcsa_select_ex(const dllm_batch *batch,
  * several) and the batch is fairly even (total_kv >= 3/4 * batch * max_kv), where it measures 5 to
  * 30 % faster.  Calls of at most one pair per compute unit and lists of up to 1024 positions, where launches
  * and latencies count most, take the form that an estimate of both times calls the faster (it depends on the
- * pooling window too).  This call overrides that choice for the whole process (all threads, all later calls); it exists for measurement and for tests that must reach both forms.  Returns the previous setting,
- * or -1 (and changes nothing) for a value that is none of the three.
+ * pooling window too).  This call overrides that choice for the whole process (all threads, all later calls);
+ * it exists for measurement and for tests that must reach both forms.  Returns the previous setting, or -1
+ * (and changes nothing) for a value that is none of the three.
  */
 #define DLLM_SELECT_FORM_AUTO 0
 #define DLLM_SELECT_FORM_TWO_LAUNCHES 1

@@ -372,3 +372,20 @@ def test_dense_calls_at_head_dim_64_take_the_form_that_measured_faster(heads, ba
     b.total_q = b.total_kv = total
     b.max_q = b.max_kv = longest
     assert hcsa.dllm_hcsa_attend_form_of(b, all_dense=True)[2] == form
+
+
+ONE, TWO = hcsa.DLLM_SELECT_FORM_ONE_LAUNCH, hcsa.DLLM_SELECT_FORM_TWO_LAUNCHES
+
+
+@pytest.mark.parametrize("dtype,hq,hkv,d,batch,longest,total,pool_w,form", [
+    (hcsa.DLLM_BF16, 8, 4, 64, 21, 203, 4263, 63, TWO), (hcsa.DLLM_BF16, 8, 8, 128, 6, 163, 816, 63, TWO),
+    (hcsa.DLLM_BF16, 16, 16, 64, 1, 701, 701, 31, TWO), (hcsa.DLLM_BF16, 8, 4, 64, 1, 100, 100, 9, TWO),
+    (hcsa.DLLM_F32, 4, 4, 64, 17, 137, 2329, 63, TWO), (hcsa.DLLM_F32, 4, 4, 64, 1, 500, 500, 15, TWO),
+    (hcsa.DLLM_BF16, 16, 16, 64, 1, 500, 500, 3, ONE), (hcsa.DLLM_BF16, 32, 32, 128, 8, 1000, 8000, 9, ONE),
+    (hcsa.DLLM_BF16, 32, 32, 128, 8, 500, 4000, 15, ONE), (hcsa.DLLM_F32, 4, 4, 64, 1, 100, 100, 15, ONE)])
+def test_short_selection_takes_the_form_that_measured_faster_for_its_window(dtype, hq, hkv, d, batch, longest, total, pool_w, form):
+    b = good_batch()
+    b.dtype, b.batch, b.n_q_heads, b.n_kv_heads, b.head_dim = dtype, batch, hq, hkv, d
+    b.q_stride_tok, b.q_stride_head, b.kv_stride_tok, b.kv_stride_head = hq * d, d, hkv * d, d
+    b.total_q, b.max_q, b.total_kv, b.max_kv = 32 * batch, 32, total, longest
+    assert hcsa.dllm_hcsa_select_form_of(b, pool_w) == form
