@@ -20,6 +20,7 @@
 #include <utility>
 
 #include "common.h"
+#include "score_rules.h"
 
 namespace dllm {
 
@@ -1087,16 +1088,9 @@ SelectPlan plan_select(const Shape& s) {
 template <int ES, int D>
 static hipError_t launch_score(const Shape& s, const void* k, const void* q, const int32_t* cu_q,
                                const int32_t* cu_kv, const int32_t* cu_k, float* scores, hipStream_t st) {
-  // Tiles per wave: one while all workgroups are resident at once (their LDS decides), two beyond, four in large calls that
-  // score a tile for four or more query heads (8192 positions x 24 sequences: two cost 10 % there, four cost one-head calls
-  // 3 %).  Selection in two launches, us, one tile / two: 32 heads x 128, four sequences of 551 to 1988 17.1 / 15.2, one of 8000
-  // 22.7 / 21.1, eight of 1500 25.4 / 24.3, seven of 627 to 1310 18.8 / 19.9; all resident: one of 1024 8.4 / 9.8, two of 1500 12.3 /
-  // 12.5; 32 heads over 8, six of 5000 25.2 / 23.5, forty of 1851 to 3424 65.4 / 62.5 (four 69.0), forty of 2414 to 4403 85.6 / 81.6 (83.4); 16
-  // heads x 64 (twice as many fit), sixteen of 1232 to 1637 15.9 / 14.9, nine of 686 10.9 / 11.0.  (Dealing a sequence's tiles out
-  // evenly over its workgroups' waves instead of in blocks cost 1 to 4 %.)
-  const int64_t wg_tiles = int64_t(s.total_kv) * s.hkv / kScoreRowsPerBlock;
-  const int64_t resident = 256 * (int64_t(160) * 1024 / (kScoreWaves * 64 * D * ES + 4096));
-  const int tpw = s.group >= 4 && wg_tiles >= 5 * 1024 ? 4 : wg_tiles > resident ? 2 : 1;
+  // (Dealing a sequence's tiles out evenly over its workgroups' waves instead of in blocks cost 1 to 4 %.)
+  static_assert(kScoreRowsPerBlock == 256, "dllm_rule_score_tiles counts in workgroups of four tiles");
+  const int tpw = dllm_rule_score_tiles(s.batch, s.total_kv, s.max_kv, s.hkv, s.group, D * ES);
   const int rows_per_block = kScoreRowsPerBlock * tpw;
   dim3 grid(s.hkv, (s.max_kv + rows_per_block - 1) / rows_per_block, s.batch);
   dim3 block(kScoreWaves * 64);

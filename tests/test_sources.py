@@ -5,7 +5,8 @@ import re
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_17077_amd", "csrc")
 
 # preprocessor names the sources may test: the checked build and one size
-KNOWN = {"DLLM_CHECK_PRECONDITIONS", "DLLM_PACK_INFLIGHT", "DLLM_PRECONDITION_RULES_H", "__HIPCC__"}
+KNOWN = {"DLLM_CHECK_PRECONDITIONS", "DLLM_PACK_INFLIGHT", "DLLM_PRECONDITION_RULES_H", "DLLM_SCORE_RULES_H",
+         "__HIPCC__"}
 
 
 def test_no_undocumented_switches():
