@@ -527,6 +527,7 @@ __global__ __launch_bounds__(T) void topk_reg_kernel(
       if (j < L) {
         const int lo = max(0, j - half), hi = min(L - 1, j + half);
         float val = raw[lo];
+#pragma unroll 2   // one LDS latency for two positions
         for (int t = lo + 1; t <= hi; ++t) val = fmaxf(val, raw[t]);
         x[u] = val;
       }
@@ -1158,20 +1159,21 @@ static int compute_units() {
 // 10.6; 8 over 4 x 64, one of 300 7.2 / 8.7 against 8.0 / 8.4, of 900 8.4 / 10.4 against 8.3 / 9.0.  With sixteen tiles per
 // wave the one launch took 0.5 to 0.9 us longer, 2 to 3 with four query heads per KV head and 2 to 7 more with the window.
 // Wider windows cost the one launch more: it moves its keys on by a lane per position and side, the top-k reads LDS
-// (windows 3 / 15 / 63, one launch against two, 32 heads x 128, one of 256 8.2 / 9.8 / 14.9 against 8.9 / 9.5 / 11.7, of 1000 11.4 / 13.5 /
-// 18.8 against 9.6 / 10.6 / 15.1; 8 over 4 x 64, eight of 256 8.7 / 11.3 / 19.2 against 8.5 / 8.9 / 11.2; 8 over 2 x 64 11.5 / 15.6 / 29.9
-// against 9.0 / 9.6 / 11.8).  The block's queries cost both forms alike (1 / 32 / 256, 32 heads x 128, one of 256 6.3 / 6.8 / 9.4 against
-// 8.2 / 8.4 / 11.2) and are not priced.  Over 1327 calls measured in both forms the choice is 0.18 % above the better one in the mean, 14 % at most.
+// (windows 3 / 15 / 63, one launch against two, 32 heads x 128, one of 256 8.2 / 9.8 / 15.1 against 8.9 / 9.2 / 10.1, of 1000 11.5 / 13.7 /
+// 18.8 against 9.6 / 10.1 / 12.3; 8 over 4 x 64, eight of 256 8.7 / 11.3 / 19.4 against 8.6 / 8.6 / 9.5; 8 over 2 x 64 11.5 / 15.7 / 30.2
+// against 9.1 / 9.2 / 10.1).  The block's queries cost both forms alike (1 / 32 / 256, 32 heads x 128, one of 256 6.3 / 6.8 / 9.5 against
+// 8.3 / 8.5 / 11.2) and are not priced.  Over 2361 calls measured in both forms the choice is 0.18 % above the better one in
+// the mean, 18 % at most (four query heads per KV head and blocks of 256 queries, where one launch would win).
 static bool fused_pays_short(const Shape& s, dllm_dtype dt, int32_t pool_w) {
   const double row = s.d * (dt == DLLM_BF16 ? 2 : 4), mb = double(s.total_kv) * s.hkv * row * 1e-6, pooled = pool_w > 1;
   const double wider = std::max(0, pool_w / 2 - 1);   // positions on either side beyond the first
   const int nt = (s.max_kv + 63) / 64, per_wave = (nt + kFusedWaves - 1) / kFusedWaves;
   const int per_simd = nt > kFusedWaves / 2 * per_wave ? 2 * per_wave : per_wave;   // tiles the busiest SIMD scores
-  double one = 5.8 + 0.003 * s.max_kv * row / 256 + per_simd * s.group * s.d / 400.0;   // a unit's stream, its multiply-adds
-  one += 0.55 * std::max(0.0, s.group * row / 256 - 1.0) + 0.2 * (s.group - 1);   // the block's queries, the other heads
-  one += pooled * (1.1 + 0.37 * s.group) + wider * (0.08 + 0.127 * s.group) + 0.07 * std::max(0.0, mb - 10.0);
+  double one = 5.8 + 0.003 * s.max_kv * row / 256 + per_simd * s.group * s.d / 420.0;   // a unit's stream, its multiply-adds
+  one += 0.33 * std::max(0.0, s.group * row / 256 - 1.0) + 0.24 * (s.group - 1);   // the block's queries, the other heads
+  one += pooled * (1.1 + 0.39 * s.group) + wider * (0.065 + 0.12 * s.group) + 0.07 * std::max(0.0, mb - 10.0);
   double two = (s.d == 128 ? 8.6 : 8.1) + (s.group * s.d > 256 ? 1.6 : 0.0) + 0.17 * std::max(0.0, mb - 10.0);
-  two += 0.4 * pooled + 0.09 * wider * ((s.max_kv + kTopkThreads - 1) / kTopkThreads);
+  two += 0.4 * pooled + 0.06 * wider * ((s.max_kv + kTopkThreads - 1) / kTopkThreads);
   return one < two;
 }
 static bool fused_pays(const Shape& s, dllm_dtype dt, int32_t pool_w) {
