@@ -428,9 +428,10 @@ def test_dense_keys_and_queries_around_tile_edges(Hq, Hkv, D):
 @pytest.mark.parametrize("rising", [False, True])
 @pytest.mark.parametrize("Hq,Hkv", [(2, 1), (48, 8)])
 def test_dense_head_dim_64_around_the_turns_of_its_rings(Hq, Hkv, rising):
-    """The head_dim 64 kernel requests its tiles three and four ahead and takes its fast path until 18 steps (10 in the split
-    form) before the end: key counts around those marks and around whole turns, with logits that grow along the
-    sequence (the running maximum is raised again and again, the tile pointers are set anew each time) and without."""
+    """The head_dim 64 kernel requests its tiles three and four ahead, into rings that turn every eight steps (four in the
+    split form), and leaves its fast path when it aims at the last tile, nine steps (five) before the end: key counts
+    around whole turns, with logits that grow along the sequence (the running maximum is raised on the way, the tile
+    pointers are set anew each time) and without."""
     for part, lens in enumerate(([543, 575, 577, 609, 639], [641, 703, 833, 1023, 1025])):
         w = custom(90 + part, torch.bfloat16, Hq, Hkv, 64, lens, [256, 130, 31, 257, 64], [0] * 5, mode=np.ones(5, np.uint8), salient=0.05)
         if rising:
@@ -443,6 +444,37 @@ def test_dense_head_dim_64_around_the_turns_of_its_rings(Hq, Hkv, rising):
         dw.dense_refresh()
         ref = oracle_attend(w, np.zeros((Hq, 0), np.int32))
         assert np.abs(dw.o.float().cpu().numpy() - ref).max() <= 2e-2   # P and O rounded to bf16, see test_dense_large_logits
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,form", [(2, 1, 64, 2), (48, 8, 64, 1), (2, 1, 128, 2), (48, 8, 128, 1)])
+def test_dense_raised_maxima_near_the_last_tiles(Hq, Hkv, D, form):
+    """Three to seven tiles of keys, where the fast path ends at its first step or soon after, with logits that grow to some
+    hundred: the running maximum is raised several times, beside the tile requests that stop at the last tile, the ragged
+    last step and the end.  48 heads make 288 query tiles: at head_dim 128 a workgroup goes through this for two of them."""
+    for part, lens in enumerate(([191, 193, 255, 257, 319], [321, 383, 385, 447, 65])):
+        w = custom(150 + part, torch.bfloat16, Hq, Hkv, D, lens, [256, 250, 231, 257, 256], [0] * 5, mode=np.ones(5, np.uint8))
+        for b in range(5):
+            lo, hi = int(w.cu_kv[b]), int(w.cu_kv[b + 1])
+            w.k[lo:hi] = (w.k[lo:hi].float() * (1.0 + 31.0 * torch.linspace(0.0, 1.0, hi - lo)[:, None, None])).to(torch.bfloat16)
+        dw = workload.DeviceWorkload(w)
+        assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == form
+        dw.o.fill_(float("nan"))
+        dw.dense_refresh()
+        ref = oracle_attend(w, np.zeros((Hq, 0), np.int32))
+        assert np.abs(dw.o.float().cpu().numpy() - ref).max() <= 2e-2   # as above
+
+
+@pytest.mark.parametrize("n", [64, 65])
+@pytest.mark.parametrize("Hq,Hkv,D", [(8, 2, 128), (8, 8, 64), (5, 5, 128)])
+def test_dense_batches_around_64_sequences(Hq, Hkv, D, n):
+    """Up to 64 sequences the workgroups place themselves (and stay, at head_dim 128), beyond they have a place in the grid:
+    ragged lengths, several query tiles, sequences without keys or queries."""
+    rng = np.random.default_rng(160 + n)
+    lens = rng.choice([0, 1, 31, 64, 65, 130, 193, 300], size=n)
+    qlens = rng.choice([0, 1, 40, 129, 257, 300], size=n)
+    lens[0], qlens[0] = 300, 300
+    w = custom(160 + n, torch.bfloat16, Hq, Hkv, D, lens.tolist(), qlens.tolist(), [0] * n, mode=np.ones(n, np.uint8), salient=0.05)
+    check_attend(w, np.zeros((Hq, 0), np.int32), name=f"{n} dense sequences")
 
 
 def test_dense_large_logits():
