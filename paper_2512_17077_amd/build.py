@@ -30,9 +30,9 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
                "-I", INCLUDE, "-I", CSRC]
 
-# The first 16 scalar registers of kernel arguments arrive with the launch instead of being loaded: 0.1 to 0.4 us per call of
-# selection, Reuse and fp32 attention (layer step 14.97 -> 14.76 us, mixed fp32 step 29.6 -> 29.2, batched selection 51.8 -> 51.5).
-# Not the dense kernels, whose start waits for the batch's offsets anyway (one layer 22.04 / 22.12 us, others the same).
+# The first 16 scalar registers of kernel arguments arrive with the launch instead of being loaded: 0.1 us per call of
+# selection in the median of 500 short calls, 0.4 on the mixed fp32 step (29.6 -> 29.2); longer ones gain no more than two runs
+# differ by.  Not the dense kernels, whose start waits for the batch's offsets anyway (one layer 22.04 / 22.12 us).
 PRELOAD_FLAGS = ["-mllvm", "-amdgpu-kernarg-preload-count=16"]
 PRELOAD_SOURCES = {"select_kernels.hip", "attend_f32.hip", "attend_sparse_bf16.hip", "pack_kernels.hip"}
 

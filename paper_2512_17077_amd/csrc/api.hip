@@ -176,9 +176,10 @@ namespace dllm {
 // 32 heads x 128, attend calls back to back, us whole or in the best chunks / two parts / four parts: one sequence of
 // 256 kept rows 7.3 / 6.4 / 5.8, 512 9.5 / 9.2 / 8.1, 1024 11.4 / 14.2 / 12.3, 2048 14.4 / 23.8 / 20.8; two of 1024 14.2 / 14.3 /
 // 12.5; four of 256 8.6 / 7.5 / 7.9, of 1024 17.3 / 15.1 / 17.9, of 276 to 994 14.8 / 14.6 / 13.6; eight of 1024 28.7 / 31.8 / 43.0.
-// The rows are priced once, though they are gathered once per 32 queries: with larger blocks the rule takes too few
-// chunks (one sequence of 1024 kept rows, 32 heads: blocks of 64 and 128 queries 22.2 and 41.8 us in four parts, where 2048
-// kept rows in chunks take 23.7 and 41.6).
+// The rows are priced once, though they are gathered once per 32 queries, side by side where the chip has room
+// (launch_attend_sparse_bf16) and in turn otherwise, and a part's are counted as if none ran beside it: with larger blocks
+// the rule takes too few chunks (one sequence, 32 heads, blocks of 64 / 128 / 256 queries: 1024 kept rows in four parts 13.6 /
+// 18.4 / 32.2 us, 2048 in four chunks 15.7 / 20.7, in four parts 56.6).
 // total_k: rows kept per head over the batch, or -1 for the workspace query, which does not know it and plans for the
 // most chunks any total can ask for (a larger total only ever makes fewer chunks the better choice).
 AttendPlan plan_attend(const Shape& s, dllm_dtype dt, int32_t max_k, int64_t total_k) {

@@ -31,10 +31,10 @@
 //     logits around 20): scores leave the matrix core raw, and one fused multiply-add per score,
 //     s * z - m * z with z = softmax_scale * log2(e), makes them base-2 logits relative to the running
 //     maximum m.
-//   - m is set 2^24 above the maximum and raised lazily (only when a score exceeds it by more than 2^8, see
-//     kDenseHeadroom) behind one uniform branch per iteration.  When it is raised after iteration j, the
-//     row sums are rescaled at once; the output accumulators, which still have to take P(j) V(j) at the
-//     old scale during iteration j+1, are rescaled one iteration later.
+//   - m is set 2^24 above the maximum and raised lazily (when a score exceeds it, see kDenseHeadroom, and before a
+//     ragged last step) behind one uniform branch per iteration.  When it is raised after iteration j, the accumulators,
+//     row sums among them, still have to take P(j) V(j) and the sums of P(j) at the old scale during iteration j+1 and are
+//     rescaled one iteration later.
 //   - The loop is unrolled over one turn of the rings (eight steps, four in the split form), so every LDS address is a register
 //     fixed before the loop plus an immediate offset.
 #include <algorithm>
@@ -67,7 +67,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 //   v[160:175], v[176:191]   pb_a, pb_b   packed probabilities of two consecutive steps, [qb][u][4]
 //   v[192 : 192 + 4*NT)      kop   K operands of the next score chain, [t][4]
 //   v[80:95]                 addr  LDS byte addresses: K operand [t], then V^T operand [rd][db] from +8
-//   a[.. + 4*2)              ls    row sums [qb][4] (only the first register is used)
+//   a[.. + 4*2)              ls    row sums [qb][4] (only the first register is used, see DLLM_LS_OUT)
 //   v72 .. v75               nmz[2] (= -m z per block), mx[2] (lane maxima of the newest scores)
 //   v[76:79], v[224:255]     scratch of a step (logits in flight, V^T operand buffers)
 // C++ code may read and write the v-register variables between steps like any others, and may write q;
@@ -216,9 +216,7 @@ struct DenseState {
 #undef DLLM_ACC_IN
 #undef DLLM_Q_IN
   // element access (indices are compile-time constants after unrolling)
-  __device__ __forceinline__ float q_get(int qb, int t, int c) const { return q[2 * qb + t / 4][4 * (t % 4) + c]; }
   __device__ __forceinline__ void q_set(int qb, int t, int c, float x) { q[2 * qb + t / 4][4 * (t % 4) + c] = x; }
-  __device__ __forceinline__ float kop_get(int t, int c) const { return kop[t / 4][4 * (t % 4) + c]; }
   __device__ __forceinline__ void kop_set(int t, int c, float x) { kop[t / 4][4 * (t % 4) + c] = x; }
 };
 

@@ -15,8 +15,9 @@
 //     ids one tile further ahead, so every load has a product's time (512 NQ cycles at D = 64) to arrive.
 // Bound: matrix time where the keys are many, the chain launch -> offsets -> ids -> rows, about 5 us, where they are few.
 // 8 heads x 64, a sequence of 700 tokens beside three Reuse blocks over up to 630 kept rows: 1.08 GFLOP, 6.9 us at the full
-// rate, 9.4 us because 200 workgroups leave 56 compute units out; measured 22 us in one launch.  The 12 us between
-// are not accounted for (the operand loads of eight waves per row from the L2 are the first suspect).  One wave per
+// rate, 9.4 us because 200 workgroups leave 56 compute units out; measured 22 us in one launch: by clock marks 0.8 us
+// until a workgroup knows its place, 1.6 to 3.3 until its queries and first keys are there, 13.6 in the loop (six tiles a
+// wave, whose products, softmax and row sums follow one another), 1.2 in the merge, launch and drain around them.  One wave per
 // query row with vector arithmetic took 630 us in two launches; one sequence with 4 heads and 64 kept rows takes 5.5 us
 // instead of 14.6.
 #include <algorithm>

@@ -36,11 +36,10 @@ PB_A, PB_B = 160, 176         # packed probabilities, [qb][u][4]
 KOP = 192                     # K operands [t][4]
 VOP = 224                     # V^T operand buffers [NBUF][4]
 TMP = 76                      # [2][2] logits / probabilities in flight
-SM = 70                       # lsum0, lsum1, nmz0, nmz1, mx0, mx1
+SM = 70                       # two unused, nmz0, nmz1, mx0, mx1
 ADDR = 80                     # ka[8], va[2][4]
 NBUF = 8
 ACC = 0                       # a: acc[qb][db][16]
-ONES = "0x3f803f80"           # bf16 (1, 1)
 
 
 def vr(base, n=1):
@@ -129,18 +128,16 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             qb, u, jj = pairs[i]
             t0 = TMP + 2 * (i % 2)
             w = pnew + 4 * (2 * qb + u) + jj
-            return [f"v_cvt_pk_bf16_f32 {vr(w)}, {vr(t0)}, {vr(t0 + 1)}"], [], []
+            return [f"v_cvt_pk_bf16_f32 {vr(w)}, {vr(t0)}, {vr(t0 + 1)}"]
 
         for i, (qb, u, jj) in enumerate(pairs):
             t0 = TMP + 2 * (i % 2)
             s0 = cur + 16 * qb + 8 * u + 2 * jj
-            cvt, add0, add1 = finish(i - 1) if i > 0 else ([], [], [])
             ops += [f"v_fma_f32 {vr(t0)}, {vr(s0)}, %[zs], {vr(SM + 2 + qb)}",
                     f"v_fma_f32 {vr(t0 + 1)}, {vr(s0 + 1)}, %[zs], {vr(SM + 2 + qb)}"]
             ops += [f"v_exp_f32_e64 {vr(t0 + c)}, {vr(t0 + c)} clamp" for c in range(2)]
-            ops += cvt + add0 + add1
-        cvt, add0, add1 = finish(len(pairs) - 1)
-        ops += ["s_nop 0"] + cvt + add0 + add1      # the nop keeps the last exp's result from being read at once
+            ops += finish(i - 1) if i > 0 else []
+        ops += ["s_nop 0"] + finish(len(pairs) - 1)   # the nop keeps the last exp's result from being read at once
         for s in range(nslots):   # evenly over the matrix pipe's time: about three per MFMA at D = 128
             valu[s] += ops[at[s] * len(ops) // at[-1]:at[s + 1] * len(ops) // at[-1]]
         # row maxima of the new scores, well after the S chain

@@ -1257,14 +1257,14 @@ hipError_t launch_select(const Shape& s, dllm_dtype dt, const void* q, const voi
         ranked, cu_kv, cu_k, s.total_kv, total_k, pool_w, forced_tail, s.hq, idx_out DLLM_CHECK_PASS);
     return hipGetLastError();
   };
-  if (s.max_kv <= 8 * kTopkThreads) 
+  if (s.max_kv <= 8 * kTopkThreads)
     return head_sum ? ranked_in_registers(topk_reg_kernel<8, kTopkThreads, true>)
                     : ranked_in_registers(topk_reg_kernel<8, kTopkThreads, false>);
   // Sixteen keys per thread for lists of up to 8192, against the kernel below (selection in two launches, us, unpooled / window
   // 3): 16 lists of 4736 13.0 / 14.8 against 15.0 / 17.5, 32 of 8000 14.4 / 17.3 against 18.0 / 22.6, 128 of 6500 25.1 / 27.6 against
   // 27.7 / 31.5, 640 of 6000 66.1 / 70.1 against 67.2 / 80.6.  (At 768 lists of 8192 it lost, 20.5 against 18.1 us of the launch:
   // not all of its workgroups run at once.  Thirty-two keys per thread in four waves took 25 us.)
-  if (s.max_kv <= 16 * kTopkThreads && int64_t(grid.x) * grid.y <= 704) 
+  if (s.max_kv <= 16 * kTopkThreads && int64_t(grid.x) * grid.y <= 704)
     return head_sum ? ranked_in_registers(topk_reg_kernel<16, kTopkThreads, true>)
                     : ranked_in_registers(topk_reg_kernel<16, kTopkThreads, false>);
   const size_t lds = size_t(lpad) * 4 * (pool_w == 1 ? 1 : 2);
