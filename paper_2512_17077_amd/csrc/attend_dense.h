@@ -13,6 +13,17 @@ __device__ __forceinline__ float maximum_across_halves(float x) {
   return maximum(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// What a step may not see.  Queries share the row-sum products, whose columns hold two of them told apart by zeros, so a
+// probability that is infinite or NaN would reach another query's sum as 0 * NaN.  A query whose scores are infinite or NaN, or
+// so large (2^31 and beyond) that the rounding of its maximum leaves them far above it, is lost: its scores of the
+// step are taken out, and its accumulators, which are its own, are multiplied by NaN.
+// mx: the query's largest score of a step, mz: the base-2 logit that stands for its running maximum
+__device__ __forceinline__ bool is_lost(float mx, float zscale, float mz) { return !(fmaf(mx, zscale, -mz) <= 64.0f); }
+__device__ __forceinline__ void drop_scores(f32x16& st, bool lost) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) st[i] = lost ? -INFINITY : st[i];
+}
+
 struct DensePlace {
   int qtile, h;            // query tile, query head
   int q0, nq, kv0, L;      // the sequence's first query, number of queries, first key, number of keys

@@ -31,8 +31,8 @@
 //     logits around 20): scores leave the matrix core raw, and one fused multiply-add per score,
 //     s * z - m * z with z = softmax_scale * log2(e), makes them base-2 logits relative to the running
 //     maximum m.
-//   - m is set 2^24 above the maximum and raised lazily (when a score exceeds it, see kDenseHeadroom, and before a
-//     ragged last step) behind one uniform branch per iteration.  When it is raised after iteration j, the accumulators,
+//   - m is set 2^24 above the maximum and raised lazily (when a score exceeds it by more than 2^8, see kDenseHeadroom, and
+//     before a ragged last step) behind one uniform branch per iteration.  When it is raised after iteration j, the accumulators,
 //     row sums among them, still have to take P(j) V(j) and the sums of P(j) at the old scale during iteration j+1 and are
 //     rescaled one iteration later.
 //   - The loop is unrolled over one turn of the rings (eight steps, four in the split form), so every LDS address is a register
@@ -101,11 +101,9 @@ struct DenseTileLoad {
 // slots 0..7 and 16..23 if c < 16, in the other slots if not.  The A operand (`ones`) has bf16 ones in row 0 for the
 // first kind and in row 4 for the second, so the four accumulators (ls) hold the sum of query c in the first register of
 // lane c and zeros elsewhere.  (A 32x32x16 product with one row of ones takes twice the matrix time: 494 -> 481 us on
-// eight sequences of 2048, 32 heads x 128, and 28 a-registers more.)  Two queries share a column, so a probability that is no
-// number would reach its neighbour's sum as 0 * NaN; there is none, because they come out of the exponential clamped to
-// 0 .. 1 (NaN to 0), at the price of its longer encoding (0.4 %; sixteen lanes' own sums by 4x4x4 products, which keep
-// columns apart too, cost 0.7 to 1.9 %).  A query that has scored plus infinity or NaN still ends as NaN: its maximum is
-// that, so its accumulators are multiplied by it or all its probabilities are 0.  The vector form (unpack each packed pair with a
+// eight sequences of 2048, 32 heads x 128, and 28 a-registers more.)  Two queries share a column, so no probability may be
+// infinite or NaN, see is_lost (4x4x4 products, in which every lane has a column, cost 0.7 to 1.9 % of the calls'
+// time).  The vector form (unpack each packed pair with a
 // shift and a mask, two adds) costs four vector instructions per pair of scores, a third of the step's vector work;
 // v_dot2c_f32_bf16 does it in one but runs on the matrix pipe and holds back the MFMAs (+18 cycles per MFMA), and summing
 // the unrounded values is off by up to 2^-8 of a row that one key rules.
@@ -512,8 +510,16 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
     // (no lower than the lowest finite number: keys whose scores overflowed to minus infinity weigh nothing instead of
     // (-inf) - (-inf), also when they fill the first step)
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-      w.nmz[qb] = no_keys ? 0.0f : -maximum(maximum_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
+    for (int qb = 0; qb < NQB; ++qb) {
+      const float mx = maximum_across_halves(lane_max(w.st_a[qb])), mz = maximum(mx * zscale + kDenseHeadroom, -FLT_MAX);
+      const bool lost = is_lost(mx, zscale, mz);
+      if (__builtin_expect(__builtin_amdgcn_ballot_w64(lost) != 0, 0)) {
+        drop_scores(w.st_a[qb], lost);
+        if (lost) palpha[qb] = NAN;
+        pending = 1;
+      }
+      w.nmz[qb] = no_keys ? 0.0f : lost ? FLT_MAX : -mz;
+    }
     if constexpr (KS == 2) {   // what a step before the first would have requested, so that every step finds the same in flight
       load_tile(keys, keys.k, 3, DLLM_IC(3 * TILEB));
       load_tile(keys, keys.v, 1, DLLM_IC(VBASE + TILEB));
@@ -569,11 +575,14 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
       if (grow != 0 || j == last_due) {
 #pragma unroll
         for (int qb = 0; qb < NQB; ++qb) {
-          const float mz_old = -w.nmz[qb];
-          const float mz_new = maximum(mz_old, maximum_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
+          const float mz_old = -w.nmz[qb], mx = maximum_across_halves(w.mx[qb]);
+          const float mz_new = maximum(mz_old, mx * zscale + kDenseHeadroom);
+          const bool lost = is_lost(mx, zscale, mz_new);
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(lost) != 0, 0))
+            drop_scores(R % 2 == 0 ? w.st_b[qb] : w.st_a[qb], lost);
           const float alpha = __builtin_amdgcn_exp2f(mz_old - mz_new);
-          palpha[qb] = alpha;
-          w.nmz[qb] = -mz_new;
+          palpha[qb] = lost ? NAN : alpha;
+          if (!lost) w.nmz[qb] = -mz_new;
         }
         pending = 1;
       }

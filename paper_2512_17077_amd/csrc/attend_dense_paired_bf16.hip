@@ -302,9 +302,18 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
   if (nsteps == 1 && last_valid < 32) mask_tail(w.st_a);
   // (no lower than the lowest finite number: keys whose scores overflowed to minus infinity weigh nothing instead of
   // (-inf) - (-inf), also when they fill the first step)
+  bool lost[2];   // see is_lost
 #pragma unroll
-  for (int qb = 0; qb < 2; ++qb)
-    w.nmz[qb] = no_keys ? 0.0f : -maximum(maximum_across_halves(lane_max(w.st_a[qb])) * zscale + kDenseHeadroom, -FLT_MAX);
+  for (int qb = 0; qb < 2; ++qb) {
+    const float mx = maximum_across_halves(lane_max(w.st_a[qb])), mz = maximum(mx * zscale + kDenseHeadroom, -FLT_MAX);
+    lost[qb] = is_lost(mx, zscale, mz);
+    w.nmz[qb] = no_keys ? 0.0f : lost[qb] ? FLT_MAX : -mz;
+  }
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(lost[0] || lost[1]) != 0, 0)) {
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) drop_scores(w.st_a[qb], lost[qb]);
+    w.acc_scale(lost[0] ? NAN : 1.0f, lost[1] ? NAN : 1.0f);
+  }
 #pragma unroll
   for (int i = 0; i < 16; ++i) w.st_b[0][i] = w.st_b[1][i] = 0.0f;
   w.k_operands<KS == 1 ? 32 * ROWB : TILEB>();   // step 1 (copies of the last row if there is none; then unused)
@@ -337,10 +346,13 @@ __global__ __launch_bounds__(kThreads, 2) void attend_dense_paired_bf16_kernel(
       float alpha[2];
 #pragma unroll
       for (int qb = 0; qb < 2; ++qb) {
-        const float mz_old = -w.nmz[qb];
-        const float mz_new = maximum(mz_old, maximum_across_halves(w.mx[qb]) * zscale + kDenseHeadroom);
-        alpha[qb] = __builtin_amdgcn_exp2f(mz_old - mz_new);
-        w.nmz[qb] = -mz_new;
+        const float mz_old = -w.nmz[qb], mx = maximum_across_halves(w.mx[qb]);
+        const float mz_new = maximum(mz_old, mx * zscale + kDenseHeadroom);
+        const bool over = is_lost(mx, zscale, mz_new);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(over) != 0, 0))
+          drop_scores(R % 2 == 0 ? w.st_b[qb] : w.st_a[qb], over);
+        alpha[qb] = over ? NAN : __builtin_amdgcn_exp2f(mz_old - mz_new);
+        if (!over) w.nmz[qb] = -mz_new;
       }
       w.acc_scale(alpha[0], alpha[1]);
     }

@@ -38,11 +38,10 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazyGrowth = 2.0f;
 // Dense sequences have many, and heads with salient keys raise m often with a small lag: the mixed burst (8 sequences of
 // 2048 in its dense part, 32 heads) takes 628 us with a lag of 2^8 and 508 with 2^32, for 3 % of the error.  So that the
-// larger lag does not cost range at the top, m is set kDenseHeadroom above the maximum and raised when a score exceeds it:
-// probabilities run from 2^-24 to 1, which the step text relies on (it clamps them to 0 .. 1, so that not even a query
-// whose scores overflow puts infinities or NaN into the products it shares with others).  At the bottom 2^-24 |V| has
-// to be representable: the matrix cores keep denormals.
-constexpr float kLazyGrowthDense = 0.0f;
+// larger lag does not cost range at the top, m is set kDenseHeadroom above the maximum: probabilities run from 2^-24 to
+// 2^8, and sums overflow only where they would with a lag of 2^8 (|V| of about 2^104).  At the bottom 2^-24 |V| has to
+// be representable: the matrix cores keep denormals.
+constexpr float kLazyGrowthDense = 8.0f;
 constexpr float kDenseHeadroom = 24.0f;
 
 // XOR applied to the chunk index of `row`; depends on row & 15 only

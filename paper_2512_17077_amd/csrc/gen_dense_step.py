@@ -21,8 +21,8 @@ One step (iteration j) at D = 128, NQB = 2 blocks of 32 queries per wave:
     slots 20..31   row maxima of S(j+1)           16 max / max3
     LDS            16 transposing reads (V^T operands, four slots ahead of their MFMAs),
                    8 ds_read_b128 (K operands of step j+2, after the S chain has consumed the old ones)
-Probabilities are clamped to 0 .. 1, which changes none that a query with finite scores has (its running maximum is raised
-first), and maxima are taken with NaN kept (v_maximum3_f32), so that such a query asks for the raise that makes it NaN.
+Maxima are taken with NaN kept (v_maximum3_f32), and a maximum that is no number asks for the raise too: scores that are
+infinite or NaN never reach the exponentials (see drop_scores).
 Matrix results are read by vector instructions no sooner than four MFMAs after they were issued (the
 hardware does not interlock that; 12 wait states are required), and a transcendental's result is not
 read by the next instruction.
@@ -135,7 +135,7 @@ def gen_step(D, cur, nxt, pnew, pold, with_scores=True, with_softmax=True, with_
             s0 = cur + 16 * qb + 8 * u + 2 * jj
             ops += [f"v_fma_f32 {vr(t0)}, {vr(s0)}, %[zs], {vr(SM + 2 + qb)}",
                     f"v_fma_f32 {vr(t0 + 1)}, {vr(s0 + 1)}, %[zs], {vr(SM + 2 + qb)}"]
-            ops += [f"v_exp_f32_e64 {vr(t0 + c)}, {vr(t0 + c)} clamp" for c in range(2)]
+            ops += [f"v_exp_f32_e32 {vr(t0 + c)}, {vr(t0 + c)}" for c in range(2)]
             ops += finish(i - 1) if i > 0 else []
         ops += ["s_nop 0"] + finish(len(pairs) - 1)   # the nop keeps the last exp's result from being read at once
         for s in range(nslots):   # evenly over the matrix pipe's time: about three per MFMA at D = 128
@@ -277,7 +277,7 @@ def gen_paired_step(cur, nxt, with_loads, split=False):
         t0 = r["TMP"] + 2 * (i % 2)
         s0 = cur + 16 * qb + 8 * u + 2 * jj
         ops += [f"v_fma_f32 {vr(t0 + c)}, {vr(s0 + c)}, %[zs], {vr(r['NMZ'] + qb)}" for c in range(2)]
-        ops += [f"v_exp_f32_e64 {vr(t0 + c)}, {vr(t0 + c)} clamp" for c in range(2)]
+        ops += [f"v_exp_f32_e32 {vr(t0 + c)}, {vr(t0 + c)}" for c in range(2)]
         if i > 0:
             convert(i - 1)
     ops.append("s_nop 0")   # the last exp's result is not read at once

@@ -137,19 +137,19 @@ def test_a_ragged_last_step_raises_the_maximum(hq, hkv, D, form):
 
 
 @pytest.mark.parametrize("first,last", [(0, 1), (40, 41), (199, 200), (64, 128)])
-@pytest.mark.parametrize("nan", [False, True])
+@pytest.mark.parametrize("bad_value", [-1.0, -2.0 ** -74, float("nan")])
 @pytest.mark.parametrize("hq,hkv,n,D,form", [(4, 2, 1, 128, 2), (4, 2, 1, 64, 2), (16, 8, 20, 128, 1), (16, 8, 20, 64, 1)])
-def test_scores_that_overflow_spoil_their_own_query_only(hq, hkv, n, D, form, first, last, nan):
-    """Keys that score plus infinity for a few queries (or queries that hold NaN: their outputs are no numbers) and minus infinity
-    for all others, which must come out as if those keys were not there: queries share matrix products, but none may see
-    another's values."""
+def test_scores_that_overflow_spoil_their_own_query_only(hq, hkv, n, D, form, first, last, bad_value):
+    """Keys that score plus infinity for a few queries (or 2^66, far beyond what logits can tell apart; or queries that hold
+    NaN) and minus infinity for all others, which must come out as if those keys were not there: queries share matrix
+    products, but none may see another's values.  The few are NaN where they scored infinity or hold NaN."""
     L, nq, bad = 200, 70 if form == 2 else 256, [3, 17, 36, 52, 69]
     w = synth.make_workload("contained", synth.SEED_BASE + 2200, torch.bfloat16, hq, hkv, D, [L] * n, [nq] * n, [0] * n,
                             seq_mode=np.ones(n, np.uint8))
     w.q.copy_((2.0 ** 64 * (1.0 + w.q.float().abs())).to(w.q.dtype))
     w.k.copy_((2.0 ** -64 * w.k.float()).to(w.k.dtype))
     for b in range(n):
-        w.q[[b * nq + i for i in bad]] *= float("nan") if nan else -1.0
+        w.q[[b * nq + i for i in bad]] *= bad_value
         w.k[b * L + first:b * L + last] = -2.0 ** 70
     rest = [i for i in range(L) if not first <= i < last]
     good = [i for i in range(nq) if i not in bad]
@@ -160,7 +160,7 @@ def test_scores_that_overflow_spoil_their_own_query_only(hq, hkv, n, D, form, fi
     assert hcsa.dllm_hcsa_attend_form_of(dw.batch, all_dense=True)[2] == form
     dw.dense_refresh()
     got = dw.o.double().cpu().view(n, nq, hq, D).transpose(1, 2)
-    assert torch.isnan(got[:, :, bad]).all()
+    assert bad_value == -2.0 ** -74 or torch.isnan(got[:, :, bad]).all()
     assert torch.isfinite(got[:, :, good]).all()
     assert (got - ref)[:, :, good].abs().max() <= TOL[torch.bfloat16]
 
