@@ -680,8 +680,8 @@ __global__ __launch_bounds__(kDenseWaves * 64, 1) void attend_dense_bf16_kernel(
 // three of 768 53.7 / 57.9 (two rounds against three); five of 300 35.4 / 27.1.
 // head_dim 128, in shader cycles from the clock at the marks of both forms: 1440 per step and 13000 besides (split:
 // 1660); one workgroup runs per compute unit at a time.  (Since workgroups stay for further tiles and the end of a sequence
-// costs less, a step takes 1290 to 1460 and a further tile about 10000; over 118 batches measured in both forms the choice
-// is still 0.03 % above the better one in the mean.)
+// costs less, a step takes 1290 to 1460 and a further tile about 10000; over 80 batches measured in both forms since the
+// choice is 0.2 % above the better one in the mean, 5 % at most.)
 // head_dim 64 (two workgroups per compute unit), in ns, fitted to 101 batches measured in both forms (4 to 32 heads, one to 40
 // sequences of 64 to 6000): a step takes 449 (split: 485) on a compute unit that the workgroup has for itself and 500 (525)
 // of a shared one, where a workgroup costs 1000 (1500) besides; 3000 before the first step.  Ragged batches of up to 512
