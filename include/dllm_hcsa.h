@@ -42,7 +42,8 @@
  *              non-decreasing, starting at 0 and ending at total_*, max_* really bounding the
  *              per-sequence values, 0 <= k_b <= L_b, and idx entries inside [0, L_b).  A library built
  *              with -DDLLM_CHECK_PRECONDITIONS checks all of these on the device before anything
- *              depends on them (see dllm_hcsa_precondition_errors).  NaN inputs are unsupported.
+ *              depends on them (see dllm_hcsa_precondition_errors).  NaN inputs are unsupported.  In attention a
+ *              query whose scores are NaN or overflow to plus infinity gets NaN; no other query's output changes.
  */
 #ifndef DLLM_HCSA_H
 #define DLLM_HCSA_H

@@ -21,6 +21,7 @@
 // units and lists of unequal length, runs one eight-wave workgroup per compute unit that walks a
 // length-balanced share of the lists back to back.
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "attn_tile.h"
@@ -168,7 +169,7 @@ __device__ __forceinline__ void sparse_tile_math(const char* ktile, const char* 
   tmax = max_across_halves(tmax) * zscale;   // zscale >= 0
   if (__builtin_amdgcn_ballot_w64(tmax > m_used + kLazyGrowth) != 0) {
     const float m_new = fmaxf(m_used, tmax);
-    const float alpha = __builtin_amdgcn_exp2f(m_used - m_new);   // first tile: exp2(-inf) = 0
+    const float alpha = __builtin_amdgcn_exp2f(m_used - m_new);   // first tile: exp2 of the lowest number, 0
     m_used = m_new;
     lsum *= alpha;
 #pragma unroll
@@ -305,7 +306,8 @@ __global__ __launch_bounds__(kWaves * 64, 2) void attend_sparse_bf16_kernel(
   };
 
   for (int qt = qt0; qt * 32 < nq; qt += qstep) {
-    float m_used = -INFINITY, lsum = 0.0f;
+    // (not minus infinity: a first tile whose scores all are, because they overflowed, weighs nothing instead of NaN)
+    float m_used = -FLT_MAX, lsum = 0.0f;
     f32x16 acc[NDB];
 #pragma unroll
     for (int db = 0; db < NDB; ++db)
@@ -640,7 +642,7 @@ __global__ __launch_bounds__(kWavesMulti * 64, 1) void attend_sparse_multi_bf16_
         if (wave < nxt.ntiles) fetch(kra, vra, nxt, bf ^ 1, wave);
       }
     };
-    float m_used = -INFINITY, lsum = 0.0f;
+    float m_used = -FLT_MAX, lsum = 0.0f;
     f32x16 acc[NDB];
 #pragma unroll
     for (int db = 0; db < NDB; ++db)

@@ -179,3 +179,27 @@ def test_a_key_that_is_no_number_shows(hq, hkv, n, D, form, pos):
     group = hq // hkv
     assert torch.isnan(dw.o[:, group:2 * group]).all()
     assert torch.isfinite(dw.o[:, :group]).all() and torch.isfinite(dw.o[:, 2 * group:]).all()
+
+
+@pytest.mark.parametrize("first,last", [(0, 1), (40, 41), (199, 200), (64, 128)])
+@pytest.mark.parametrize("dtype,D,dense", [(torch.bfloat16, 128, False), (torch.bfloat16, 64, False), (torch.float32, 64, False),
+                                           (torch.float32, 128, True)])
+def test_overflow_stays_with_its_query_in_kept_lists_and_fp32(dtype, D, dense, first, last):
+    """The same over kept lists (of all positions) and in fp32."""
+    L, nq, hq, hkv, bad = 200, 40, 4, 2, [3, 17, 36]
+    w = synth.make_workload("contained", synth.SEED_BASE + 2202, dtype, hq, hkv, D, [L], [nq], [0 if dense else L],
+                            seq_mode=np.full(1, 1 if dense else 0, np.uint8))
+    w.q.copy_((2.0 ** 64 * (1.0 + w.q.float().abs())).to(dtype))
+    w.k.copy_((2.0 ** -64 * w.k.float()).to(dtype))
+    w.q[bad] *= -1.0
+    w.k[first:last] = -2.0 ** 70
+    rest = [i for i in range(L) if not first <= i < last]
+    good = [i for i in range(nq) if i not in bad]
+    q = w.q.double().transpose(0, 1)
+    k, v = (x.double()[rest].repeat_interleave(hq // hkv, 1).transpose(0, 1) for x in (w.k, w.v))
+    ref = torch.matmul(torch.softmax(torch.matmul(q, k.transpose(1, 2).contiguous()) * w.softmax_scale, -1), v).transpose(0, 1)
+    dw = workload.DeviceWorkload(w)
+    dw.attend(torch.arange(0 if dense else L, dtype=torch.int32).repeat(hq, 1).to(dw.device))
+    got = dw.o.double().cpu()
+    assert torch.isnan(got[bad]).all() and torch.isfinite(got[good]).all()
+    assert (got - ref)[good].abs().max() <= TOL[dtype]
